@@ -380,3 +380,179 @@ def tolerance(case):
     if case["kind"] == "generate":
         return {"rel": 1e-4, "differ": 0.01}
     return {"rel": 2e-3, "differ": 0.01}
+
+
+# ------------------------------------------------------------------------------------------------ 64-bit values
+class _Exact:
+    """One model of a state in plain torch, 64 bits throughout: prefix caches as given, block keys and values kept."""
+
+    def __init__(self, s, role, prefix=True):
+        self.dm, self.pf, self.d = s.models[role], s.prefixes[role], s.models[role].desc
+        self.lens = [int(v) for v in s.lens] if prefix else [0] * len(s.lens)
+        self.g = self.d.n_q_heads // self.d.n_kv_heads
+        self.block = {}                                    # (layer, beam) -> keys, values [n, T, Hkv, hd] of the block
+
+    def pages(self, b, tokens):
+        return self.pf.page_table[b, :-(-tokens // PAGE)].long()
+
+    def prefix(self, l, b):
+        """Cached keys and values of a beam, [tokens, Hkv, hd]."""
+        d, P = self.d, self.lens[b]
+        k, v = self.pf.kv_pool[l][:, self.pages(b, P)].double()
+        k = k.view(-1, d.n_kv_heads, PAGE, d.head_dim).transpose(1, 2).reshape(-1, d.n_kv_heads, d.head_dim)
+        v = v.view(-1, d.n_kv_heads, d.head_dim, PAGE).permute(0, 3, 1, 2).reshape(-1, d.n_kv_heads, d.head_dim)
+        return k[:P], v[:P]
+
+    def norm(self, x):
+        return x * torch.rsqrt((x * x).mean(-1, keepdim=True) + self.d.rms_eps)
+
+    def rope(self, x, pos):
+        half = self.d.head_dim // 2
+        theta = self.d.rope_base ** (-torch.arange(half, dtype=torch.float64, device=DEVICE) / half)
+        a = pos.double()[:, None] * theta
+        c, s = a.cos()[:, None, :], a.sin()[:, None, :]
+        x1, x2 = x[..., :half], x[..., half:]
+        return torch.cat([x1 * c - x2 * s, x2 * c + x1 * s], -1)
+
+    def attend(self, l, b, q, t0):
+        """q [n, T, Hq, hd] at block positions t0.. of one beam; its block keys and values are in place."""
+        n, T, _, hd = q.shape
+        pk, pv = self.prefix(l, b)
+        bk, bv = self.block[l, b]
+        out, scale = torch.empty_like(q), hd ** -0.5
+        causal = torch.ones(T, t0 + T, dtype=torch.bool, device=DEVICE).tril(t0).repeat_interleave(self.g, 0)
+        for h in range(self.d.n_kv_heads):
+            heads = slice(h * self.g, (h + 1) * self.g)
+            for i0 in range(0, n, 4):                      # a few candidates at a time bound the scores' size
+                qs = q[i0:i0 + 4, :, heads].reshape(-1, T * self.g, hd) * scale
+                sp = qs.reshape(-1, hd) @ pk[:, h].t()
+                sb = torch.stack([x @ y[:, h].t() for x, y in zip(qs, bk[i0:i0 + 4])])
+                sb = sb.masked_fill(~causal, -math.inf).reshape(-1, t0 + T)
+                w = torch.softmax(torch.cat([sp, sb], 1), 1)
+                P = sp.shape[1]
+                o = (w[:, :P] @ pv[:, h]).view(len(qs), -1, hd)
+                wb = w[:, P:].reshape(len(qs), -1, t0 + T)
+                o = o + torch.stack([x @ y[:, h] for x, y in zip(wb, bv[i0:i0 + 4])])
+                out[i0:i0 + 4, :, heads] = o.view(len(qs), T, self.g, hd)
+        return out
+
+    def forward(self, tokens, t0=0):
+        """tokens [B, n, T] at block positions t0.. -> residual stream after the last layer, [B, n, T, d]."""
+        d = self.d
+        Bn, n, T = tokens.shape
+        hq, hkv, hd = d.n_q_heads, d.n_kv_heads, d.head_dim
+        x = self.dm.embed[tokens.reshape(-1).long()].double()
+        pos = torch.arange(t0, t0 + T, device=DEVICE).repeat(n)
+        for l, w in enumerate(self.dm.layers):
+            y = (self.norm(x) @ w["wqkv"].double().t()).view(Bn, n * T, hq + 2 * hkv, hd)
+            o = []
+            for b in range(Bn):
+                qk = self.rope(y[b, :, :hq + hkv], pos + self.lens[b])
+                new = [v.reshape(n, T, hkv, hd) for v in (qk[:, hq:], y[b, :, hq + hkv:])]
+                if t0:
+                    new = [torch.cat([a, c], 1) for a, c in zip(self.block[l, b], new)]
+                self.block[l, b] = new
+                o.append(self.attend(l, b, qk[:, :hq].reshape(n, T, hq, hd), t0))
+            x = x + torch.stack(o).view(Bn * n * T, hq * hd) @ w["wo"].double().t()
+            gate, up = (self.norm(x) @ w["wgu"].double().t()).view(len(x), -1, 2, B.GATE_UP_GROUP).unbind(2)
+            act = (torch.nn.functional.silu(gate) * up).reshape(len(x), -1)
+            x = x + act @ w["wd"].double().t()
+        return x.view(Bn, n, T, -1)
+
+    def logits(self, h):
+        return self.norm(h) @ self.dm.head.double().t()
+
+    def start(self, n):
+        return self.pf.h_last.double()[:, None, :].expand(-1, n, -1)
+
+    def score(self, cand):
+        """Block and token log-likelihoods, or the rewards and no second value; and the last state of every block."""
+        x = self.forward(cand)
+        if self.d.head == "prm":
+            return torch.sigmoid(self.logits(x[:, :, -1])[..., 0]), None, x[:, :, -1]
+        h = torch.cat([self.start(cand.shape[1])[:, :, None], x[:, :, :-1]], 2).reshape(-1, self.d.d_model)
+        tok = torch.empty(len(h), dtype=torch.float64, device=DEVICE)
+        for r in range(0, len(h), 2048):
+            z = self.logits(h[r:r + 2048])
+            at = cand.reshape(-1)[r:r + 2048, None].long()
+            tok[r:r + 2048] = z.gather(1, at)[:, 0] - z.logsumexp(1)
+        tok = tok.view(cand.shape)
+        return tok.sum(-1), tok, x[:, :, -1]
+
+    def generate(self, u, limit):
+        Bn, n, L = u.shape
+        h, cand, tok = self.start(n), torch.empty((Bn, n, L), dtype=torch.int64, device=DEVICE), torch.empty_like(u)
+        for t in range(L):
+            p = torch.log_softmax(self.logits(h.reshape(Bn * n, -1))[:, :limit], 1)
+            cdf = p.exp().cumsum(1)
+            pick = (cdf > u[:, :, t].reshape(-1, 1) * cdf[:, -1:]).to(torch.uint8).argmax(1, keepdim=True)
+            cand[:, :, t], tok[:, :, t] = pick.view(Bn, n), p.gather(1, pick).view(Bn, n)
+            h = self.forward(cand[:, :, t:t + 1], t)[:, :, 0]
+        return cand, tok.sum(-1), tok, h
+
+    def store(self, pool, l, b, k, v, at):
+        """Keys and values [T, Hkv, hd] into a 64-bit copy of the pool, from token `at` of the beam on."""
+        d = self.d
+        p = torch.arange(at, at + len(k), device=DEVICE)
+        page, slot = self.pf.page_table[b].long()[p // PAGE], p % PAGE
+        pool[l, 0].view(-1, d.n_kv_heads, PAGE, d.head_dim)[page, :, slot] = k
+        pool[l, 1].view(-1, d.n_kv_heads, d.head_dim, PAGE)[page, :, :, slot] = v
+
+
+def _exact_select(lt, ld, r, betas, u):
+    lt, ld, r = lt.double(), ld.double(), r.double()
+    idx = torch.empty(u.shape, dtype=torch.int64, device=DEVICE)
+    for j, beta in enumerate(betas):
+        cdf = torch.softmax((lt - ld) + beta * r, 1).cumsum(1)
+        idx[:, j] = (cdf > u[:, j:j + 1] * cdf[:, -1:]).to(torch.uint8).argmax(1)
+    return idx, r.max(1).values
+
+
+def exact(case, seed):
+    w, d = work(case), W.get_config(case["models"]).models()[case["role"] or "target"]
+    steps = case["L"] if case["kind"] in ("generate", "iteration") else 1
+    if w["flops"] > 2e14 or steps * case["B"] * d.n_layers * d.n_kv_heads * -(-case["n"] // 4) > 60000:
+        return None                                        # over about 20 seconds in 64 bits
+    s = prepare(case, seed)
+    try:
+        return _exact(s, case)
+    finally:
+        torch.cuda.synchronize()
+
+
+def _exact(s, case):
+    kind = case["kind"]
+    if kind == "select":
+        return _exact_select(s.lt, s.ld, s.r, s.betas, s.u)
+    if kind == "prefill":
+        e = _Exact(s, case["role"], prefix=False)
+        pool, last, o = torch.zeros_like(e.pf.kv_pool, dtype=torch.float64), [], 0
+        for b, P in enumerate(int(v) for v in s.lens):
+            one = _Exact.__new__(_Exact)
+            one.__dict__.update(e.__dict__, block={}, lens=[0])
+            last.append(one.forward(s.tokens[o:o + P].view(1, 1, P))[0, 0, -1])
+            for l in range(e.d.n_layers):
+                e.store(pool, l, b, one.block[l, 0][0][0], one.block[l, 0][1][0], 0)
+            o += P
+        return pool, torch.stack(last)
+    if kind == "generate":
+        cand, out, tok, _ = _Exact(s, case["role"]).generate(s.u_tok, s.limit)
+        return cand, out, tok
+    models = {r: _Exact(s, r) for r in ROLES}
+    if kind == "step":
+        got = {r: models[r].score(s.cand) for r in ROLES}
+        out = {r: got[r][0] for r in ROLES}
+        idx, top = _exact_select(out["target"], out["draft"], out["prm"], s.betas, s.u)
+        return out, {r: got[r][1] for r in ROLES if r != "prm"}, idx, top
+    out, last = {}, {}
+    cand, out["draft"], _, last["draft"] = models["draft"].generate(s.u_tok, s.limit)
+    for r in ("target", "prm"):
+        out[r], _, last[r] = models[r].score(cand)
+    idx, top = _exact_select(out["target"], out["draft"], out["prm"], s.betas[:1], s.u)
+    beams, pick = torch.arange(len(s.lens), device=DEVICE), idx[:, 0]
+    pools = {r: models[r].pf.kv_pool.double() for r in ROLES}
+    for r, e in models.items():
+        for (l, b), (k, v) in e.block.items():
+            e.store(pools[r], l, b, k[pick[b]], v[pick[b]], e.lens[b])
+    lens = {r: s.lens0 + case["L"] for r in ROLES}
+    return (cand, {r: out[r] for r in ROLES}, idx, s.flags, top, pools, {r: last[r][beams, pick] for r in ROLES}, lens)
