@@ -10,7 +10,7 @@
 // constants. LDS rows are 128 bytes (64 bf16); the 16-byte chunk c of row r is stored at
 // chunk position c ^ ((r >> 1) & 7) so that the 32 rows a fragment read touches spread over all
 // banks. Workgroup ids are dealt round-robin to the 8 XCDs by the hardware; the id -> tile map
-// below keeps all M-tiles of one N-tile on one XCD, so a weight tile is fetched from HBM once
+// below keeps the M-tiles of one N-tile on one XCD, so a weight tile is fetched from HBM once
 // and re-used out of that XCD's L2 by workgroups that walk through K in step.
 //
 // Epilogues: plain float store; residual add into the float stream; SwiGLU (gate/up columns
@@ -33,14 +33,13 @@ struct GemmArgs {
   const bf16_t* W;
   int M, N, K;
   int m_tiles, n_tiles;
-  int m_blocks;          // ceil(m_tiles / 8)
   float* C;              // ME_STORE / ME_RESIDUAL: [M, N]
   bf16_t* act;           // ME_SWIGLU: [M, N/2]
   const int32_t* tok;    // ME_LMHEAD: target token per row
   float* part_max;       // ME_LMHEAD: [M, n_tiles]
   float* part_sum;
   float* zt;             // ME_LMHEAD: [M]
-  int ksplit;            // ME_STORE only: gridDim.y slices of K, slice s writes its partial product to C + s*M*N
+  int ksplit;            // ME_STORE only: slices of K, slice s writes its partial product to C + s*M*N
   // ME_QKV_ROPE: the product is the QKV projection [M, (Hq + 2 Hkv) * hd]; the epilogue rotates the q and k heads
   // (pairs (i, i + hd/2), angles from the table cs[M][hd] = cos | sin) and writes bf16 q [M][Hq][hd], block keys
   // kblk[cand*Lk + t][Hkv][hd] and block values transposed per candidate vT[cand][Hkv][hd][Lp], where row m is
@@ -101,15 +100,24 @@ __global__ void __launch_bounds__(128 * NWN) gemm_mfma_kernel(GemmArgs a) {
   // its rows inside the lane instead of across lanes.
   extern __shared__ __attribute__((aligned(1024))) char smem[];
 
-  // id -> (m_tile, n_tile): ids congruent mod 8 share an XCD. An XCD owns the N-tiles n = 8j + xcd; the 32
-  // workgroups that run on it at one time form a block of 8 M-tiles x 4 of its N-tiles, so that every A panel
-  // is fetched into that XCD's L2 once per 4 users and every W tile once per 8 users.
-  const int id = blockIdx.x;
-  const int xcd = id & 7, seq = id >> 3;
-  const int blk = seq >> 5, within = seq & 31;
-  const int m_tile = (blk % a.m_blocks) * 8 + (within & 7);
-  const int n_tile = ((blk / a.m_blocks) * 4 + (within >> 3)) * 8 + xcd;
-  if (n_tile >= a.n_tiles || m_tile >= a.m_tiles) return;
+  // id -> (K slice, m_tile, n_tile): ids congruent mod 8 share an XCD, and every XCD takes an equal, contiguous run of
+  // the tile list. The list goes through bands of 4 N-tiles, in a band through blocks of 8 M-tiles, so that the 32
+  // workgroups that run on an XCD at one time are 8 M-tiles x 4 N-tiles: every A panel is fetched into that XCD's L2
+  // once per 4 users and every W tile once per 8 users. The list has no gaps: a grid padded to whole blocks leaves the
+  // shader engines of an XCD unevenly loaded (with 70 tiles of one M-tile all of them met on one engine of four and ran
+  // in two rounds: 48 us instead of 26 at 64 x 17920 x 1536).
+  const int tiles = a.m_tiles * a.n_tiles, total = tiles * a.ksplit, per_xcd = (total + 7) >> 3;
+  int idx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (idx >= total) return;
+  const int kslice = idx / tiles;
+  idx -= kslice * tiles;
+  const int band = idx / (4 * a.m_tiles);
+  idx -= band * 4 * a.m_tiles;
+  const int bw = a.n_tiles - 4 * band < 4 ? a.n_tiles - 4 * band : 4;
+  const int mb = idx / (8 * bw);
+  idx -= mb * 8 * bw;
+  const int mh = a.m_tiles - 8 * mb < 8 ? a.m_tiles - 8 * mb : 8;
+  const int n_tile = 4 * band + idx / mh, m_tile = 8 * mb + idx % mh;
   const int m0 = m_tile * BM, n0 = n_tile * BN;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -125,8 +133,8 @@ __global__ void __launch_bounds__(128 * NWN) gemm_mfma_kernel(GemmArgs a) {
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   // K-tiles [kt0, kt0 + KT) of this workgroup's K slice
-  const int kt0 = (int)((long)blockIdx.y * (a.K / 64) / a.ksplit);
-  const int KT = (int)((long)(blockIdx.y + 1) * (a.K / 64) / a.ksplit) - kt0;
+  const int kt0 = (int)((long)kslice * (a.K / 64) / a.ksplit);
+  const int KT = (int)((long)(kslice + 1) * (a.K / 64) / a.ksplit) - kt0;
   // LDS ring of five slots; a slot holds one operand tile (A: BM x 64, W: 256 x 64). K-tile t uses slot 2t for
   // W and slot 2t+1 for A (mod 5), so besides the two slots being multiplied three are in flight: the weights,
   // which stream from HBM, are requested about two K-tiles ahead, the activations about one.
@@ -236,7 +244,7 @@ __global__ void __launch_bounds__(128 * NWN) gemm_mfma_kernel(GemmArgs a) {
 
   // accumulator element r of a lane: row lrow, column 8*(r/4) + 4*lhalf + r%4 of the 32x32 tile
   if (EPI == ME_STORE || EPI == ME_RESIDUAL) {
-    float* __restrict__ Cs = a.C + (size_t)blockIdx.y * a.M * a.N;
+    float* __restrict__ Cs = a.C + (size_t)kslice * a.M * a.N;
     const bool vec = (a.N & 3) == 0 && ((uintptr_t)a.C & 15) == 0;   // 16-byte pieces stay aligned and inside a row
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -416,9 +424,8 @@ static void launch_variant(const GemmArgs& a, hipStream_t s) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     configured = true;
   }
-  int per_xcd = (a.n_tiles + 7) / 8;                 // N-tiles owned by one XCD
-  int blocks = a.m_blocks * ((per_xcd + 3) / 4);     // 8 x 4 blocks per XCD
-  gemm_mfma_kernel<BM, EPI, NWN, HD128><<<dim3(blocks * 32 * 8, a.ksplit), 128 * NWN, smem, s>>>(a);
+  const int per_xcd = (a.m_tiles * a.n_tiles * a.ksplit + 7) / 8;
+  gemm_mfma_kernel<BM, EPI, NWN, HD128><<<8 * per_xcd, 128 * NWN, smem, s>>>(a);
 }
 
 int mfma_lmhead_tiles(int V) { return (V + 255) / 256; }
@@ -458,7 +465,6 @@ bool launch_gemm_mfma_qkv_rope(const bf16_t* A, const bf16_t* W, const float* cs
   a.n_tiles = (N + 255) / 256;
   bool small = ((M + 255) / 256) * a.n_tiles <= 128 || M <= 128;
   a.m_tiles = small ? (M + 127) / 128 : (M + 255) / 256;
-  a.m_blocks = (a.m_tiles + 7) / 8;
   if (md.hd == 128) { if (small) launch_variant<128, ME_QKV_ROPE, 4, true>(a, s); else launch_variant<256, ME_QKV_ROPE, 4, true>(a, s); }
   else { if (small) launch_variant<128, ME_QKV_ROPE, 4, false>(a, s); else launch_variant<256, ME_QKV_ROPE, 4, false>(a, s); }
   return true;
@@ -481,7 +487,6 @@ bool launch_gemm_mfma(int epi, const bf16_t* A, const bf16_t* W, int M, int N, i
   // 128-row tiles when twice as many workgroups still fit the 256 CUs in one round
   bool small = bm ? bm == 128 : ((M + 255) / 256) * a.n_tiles <= 128 || M <= 128;
   a.m_tiles = small ? (M + 127) / 128 : (M + 255) / 256;
-  a.m_blocks = (a.m_tiles + 7) / 8;
 #define DISPATCH(E)                                                       \
   if (small) launch_variant<128, E, 4>(a, s);                             \
   else launch_variant<256, E, 4>(a, s);
