@@ -100,24 +100,33 @@ __global__ void __launch_bounds__(128 * NWN) gemm_mfma_kernel(GemmArgs a) {
   // its rows inside the lane instead of across lanes.
   extern __shared__ __attribute__((aligned(1024))) char smem[];
 
-  // id -> (K slice, m_tile, n_tile): ids congruent mod 8 share an XCD, and every XCD takes an equal, contiguous run of
-  // the tile list. The list goes through bands of 4 N-tiles, in a band through blocks of 8 M-tiles, so that the 32
-  // workgroups that run on an XCD at one time are 8 M-tiles x 4 N-tiles: every A panel is fetched into that XCD's L2
-  // once per 4 users and every W tile once per 8 users. The list has no gaps: a grid padded to whole blocks leaves the
+  // id -> (K slice, m_tile, n_tile): ids congruent mod 8 share an XCD. The tile list goes through bands of 32 N-tiles,
+  // in a band through blocks of 8 M-tiles, in a block through sub-bands of 4 N-tiles, so that 32 consecutive entries are
+  // 8 M-tiles x 4 N-tiles: an XCD that runs them at one time fetches every A panel into its L2 once per 4 users and
+  // every W tile once per 8 users. Every 256 entries the XCDs take 32 each: they then work on the same 8 A panels at the
+  // same time (with one contiguous eighth of the list each they drift apart in M: 16384 x 37888 x 3584 then takes 5 %
+  // longer). What is left, and all of a short list, is cut into eight equal runs. The list has no gaps: a grid padded to whole blocks leaves the
   // shader engines of an XCD unevenly loaded (with 70 tiles of one M-tile all of them met on one engine of four and ran
   // in two rounds: 48 us instead of 26 at 64 x 17920 x 1536).
-  const int tiles = a.m_tiles * a.n_tiles, total = tiles * a.ksplit, per_xcd = (total + 7) >> 3;
-  int idx = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if (idx >= total) return;
+  const int tiles = a.m_tiles * a.n_tiles, total = tiles * a.ksplit;
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, dealt = total >> 8;
+  int idx;
+  if (slot < 32 * dealt) {
+    idx = (slot >> 5) * 256 + xcd * 32 + (slot & 31);
+  } else {
+    const int rest = total - 256 * dealt, run = (rest + 7) >> 3, at = xcd * run + slot - 32 * dealt;
+    if (at >= rest) return;                              // slot - 32 * dealt < run by the size of the grid
+    idx = 256 * dealt + at;
+  }
   const int kslice = idx / tiles;
   idx -= kslice * tiles;
-  const int band = idx / (4 * a.m_tiles);
-  idx -= band * 4 * a.m_tiles;
-  const int bw = a.n_tiles - 4 * band < 4 ? a.n_tiles - 4 * band : 4;
+  const int band = idx / (32 * a.m_tiles);
+  idx -= band * 32 * a.m_tiles;
+  const int bw = a.n_tiles - 32 * band < 32 ? a.n_tiles - 32 * band : 32;
   const int mb = idx / (8 * bw);
   idx -= mb * 8 * bw;
   const int mh = a.m_tiles - 8 * mb < 8 ? a.m_tiles - 8 * mb : 8;
-  const int n_tile = 4 * band + idx / mh, m_tile = 8 * mb + idx % mh;
+  const int m_tile = 8 * mb + idx % mh, n_tile = 32 * band + idx / mh;
   const int m0 = m_tile * BM, n0 = n_tile * BN;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -411,7 +420,7 @@ static void launch_variant(const GemmArgs& a, hipStream_t s) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     configured = true;
   }
-  const int per_xcd = (a.m_tiles * a.n_tiles * a.ksplit + 7) / 8;
+  const int total = a.m_tiles * a.n_tiles * a.ksplit, per_xcd = 32 * (total / 256) + (total % 256 + 7) / 8;
   gemm_mfma_kernel<BM, EPI, NWN, HD128><<<8 * per_xcd, 128 * NWN, smem, s>>>(a);
 }
 
