@@ -1,7 +1,7 @@
 // bf16 MFMA GEMM for gfx950: C[M,N] = A[M,K] * W[N,K]^T, float accumulation, K % 64 == 0.
 //
-// Block tile BM x 256 x 64 (BM = 256 or 128), 512 threads = 8 wavefronts laid out 2 (M) x 4 (N);
-// every wavefront owns a (BM/2) x 64 patch as (BM/64) x 2 accumulators of
+// Block tile 256 x 256 x 64 (smaller ones for smaller products, see the ring further down), 512 threads = 8 wavefronts
+// laid out 2 (M) x 4 (N); every wavefront owns a 128 x 64 patch as 4 x 2 accumulators of
 // v_mfma_f32_32x32x16_bf16. Operand tiles go global -> LDS directly (16 bytes per lane,
 // no register staging) into a ring of five 32 KiB slots: two being multiplied, three in flight.
 // Wavefronts issue in order and the vector-memory queue is short, so the eight loads a wavefront
@@ -84,16 +84,19 @@ __device__ __forceinline__ float half_wave_sum(float v) {
 }
 
 // HD128 (ME_QKV_ROPE only): head_dim 128 instead of 64.
-template <int BM, int EPI, int NWN, bool HD128 = false>
-__global__ void __launch_bounds__(128 * NWN) gemm_mfma_kernel(GemmArgs a) {
-  constexpr int BN = 256;
+// K-tiles in the ring of the small tiles: as many as 160 KiB of LDS hold, at most six
+constexpr int ring_stages(int bm, int bn) { return 160 * 1024 / ((bm + bn) * 128) > 6 ? 6 : 160 * 1024 / ((bm + bn) * 128); }
+
+template <int BM, int BN, int NWM, int EPI, bool HD128 = false>
+__global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
+  constexpr int NWN = BN / 64;
   // Rotary pairs are columns (i, i + hd/2) of a head. With head_dim 64 a wavefront's 64 columns are one head and
   // its two accumulator columns the two halves. With head_dim 128 a head spans two wavefronts, so the W tile is
   // loaded with rows 32..63 and 64..95 of every 128 exchanged: wavefront (head, wq) then holds columns
   // wq*32 .. +31 of the first half in accumulator column 0 and the same columns of the second half in column 1.
   constexpr bool SWAP = EPI == ME_QKV_ROPE && HD128;
-  constexpr int NW = 2 * NWN;                         // wavefronts: 2 along M x NWN along N
-  constexpr int WM = BM / 2, TM = WM / 32, WN = BN / NWN, TN = WN / 32;
+  constexpr int NW = NWM * NWN;                       // wavefronts: NWM along M x NWN along N
+  constexpr int WM = BM / NWM, TM = WM / 32, WN = BN / NWN, TN = WN / 32;
   // All epilogues multiply W-fragment x A-fragment, i.e. the transposed 32x32 product: a lane then holds runs of
   // four consecutive COLUMNS of one row of C. The storing epilogues write them as one 16-byte (8-byte bf16) piece
   // (four times fewer store instructions than with single elements of four rows), and the vocabulary head reduces
@@ -144,6 +147,27 @@ __global__ void __launch_bounds__(128 * NWN) gemm_mfma_kernel(GemmArgs a) {
   // K-tiles [kt0, kt0 + KT) of this workgroup's K slice
   const int kt0 = (int)((long)kslice * (a.K / 64) / a.ksplit);
   const int KT = (int)((long)(kslice + 1) * (a.K / 64) / a.ksplit) - kt0;
+  auto mma = [&](const bf16x8 (&af)[TM], const bf16x8 (&bfr)[TN]) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+  };
+  constexpr int LA = BM / (8 * NW), LB = BN / (8 * NW);   // direct-to-LDS loads per thread per operand tile
+  constexpr int NLD = LA + LB;
+  auto share_size = [](int sh) { int c = 0; for (int j = 0; j < NLD; ++j) c += (j * 4 / NLD == sh); return c; };
+  constexpr int S0 = share_size(0), S1 = share_size(1), S2 = share_size(2), S3 = share_size(3);
+#define SGB __builtin_amdgcn_sched_group_barrier
+#define PIPE_GROUP_ORDER(NLOADS)                                                                                   \
+  SGB(0x008, 2, 0);                                                                                                \
+  SGB(0x100, TM + TN, 0);                                                                                          \
+  if (NLOADS == 1) { SGB(0x008, 3, 0); SGB(0x010, 1, 0); SGB(0x008, TM * TN - 5, 0); }                             \
+  else if (NLOADS == 2) { SGB(0x008, 1, 0); SGB(0x010, 1, 0); SGB(0x008, 3, 0); SGB(0x010, 1, 0); SGB(0x008, TM * TN - 6, 0); } \
+  else SGB(0x008, TM * TN - 2, 0);                                                                                 \
+  __builtin_amdgcn_sched_barrier(0)
+
+  if constexpr (BM == 256) {
   // LDS ring of five slots; a slot holds one operand tile (A: BM x 64, W: 256 x 64). K-tile t uses slot 2t for
   // W and slot 2t+1 for A (mod 5), so besides the two slots being multiplied three are in flight: the weights,
   // which stream from HBM, are requested about two K-tiles ahead, the activations about one.
@@ -159,14 +183,6 @@ __global__ void __launch_bounds__(128 * NWN) gemm_mfma_kernel(GemmArgs a) {
 #pragma unroll
     for (int j = 0; j < TN; ++j) bfr[j] = lds_frag(Bs, wn * WN + j * 32 + lrow, ks * 2 + lhalf);
   };
-  auto mma = [&](const bf16x8 (&af)[TM], const bf16x8 (&bfr)[TN]) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
-  };
-  constexpr int LA = BM / (8 * NW), LB = BN / (8 * NW);   // direct-to-LDS loads per thread per operand tile
   auto issue_w = [&](int t) {                           // prologue only: t < 5 is its own phase
     const int src = t < KT ? t : KT - 1;
 #pragma unroll
@@ -177,9 +193,6 @@ __global__ void __launch_bounds__(128 * NWN) gemm_mfma_kernel(GemmArgs a) {
 #pragma unroll
     for (int i = 0; i < LA; ++i) load_span_async<NW>(a.A, m0, a.M, a.K, (kt0 + src) * 64, aslot(t), i, wave);
   };
-  constexpr int NLD = LA + LB;
-  auto share_size = [](int sh) { int c = 0; for (int j = 0; j < NLD; ++j) c += (j * 4 / NLD == sh); return c; };
-  constexpr int S0 = share_size(0), S1 = share_size(1), S2 = share_size(2), S3 = share_size(3);
   static_assert(LB == 4 && (S0 == 2) && S1 <= 2 && S2 <= 2 && S3 <= 2, "the waits below are written for these counts");
   // share SH of the loads of A-tile ta (phase pa) and W-tile tw (phase pw)
   auto issue_share = [&](int ta, int pa, int tw, int pw, auto share) {
@@ -192,15 +205,6 @@ __global__ void __launch_bounds__(128 * NWN) gemm_mfma_kernel(GemmArgs a) {
       else load_span_async<NW, SWAP>(a.W, n0, a.N, a.K, (kt0 + sw) * 64, wslot(pw), j - LA, wave);
     }
   };
-#define SGB __builtin_amdgcn_sched_group_barrier
-#define PIPE_GROUP_ORDER(NLOADS)                                                                                   \
-  SGB(0x008, 2, 0);                                                                                                \
-  SGB(0x100, TM + TN, 0);                                                                                          \
-  if (NLOADS == 1) { SGB(0x008, 3, 0); SGB(0x010, 1, 0); SGB(0x008, TM * TN - 5, 0); }                             \
-  else if (NLOADS == 2) { SGB(0x008, 1, 0); SGB(0x010, 1, 0); SGB(0x008, 3, 0); SGB(0x010, 1, 0); SGB(0x008, TM * TN - 6, 0); } \
-  else SGB(0x008, TM * TN - 2, 0);                                                                                 \
-  __builtin_amdgcn_sched_barrier(0)
-
   issue_w(0); issue_a(0); issue_w(1);
   issue_share(1, 1, 2, 2, std::integral_constant<int, 0>{});
   asm volatile("s_waitcnt vmcnt(6)\n\ts_barrier" ::: "memory");
@@ -234,6 +238,81 @@ __global__ void __launch_bounds__(128 * NWN) gemm_mfma_kernel(GemmArgs a) {
     step(std::integral_constant<int, 3>{}, kt); if (++kt >= KT) break;
     step(std::integral_constant<int, 4>{}, kt); if (++kt >= KT) break;
   }
+  } else {
+    // Small tiles (few rows, or few tiles for 256 CUs): the k-step is bound by the latency of the operand loads, not
+    // by the matrix pipe, so the ring holds S whole K-tiles and S-1 of them are in flight, activations as far ahead
+    // as weights. (With the five-slot ring above the activations are requested one K-tile ahead only: 1.1 - 1.75 us a
+    // k-step at 128 rows x 256 columns, most of it waiting.)
+    constexpr int S = ring_stages(BM, BN), STG = (BM + BN) * 128;
+    auto read_frags = [&](const char* st, int ks, bf16x8 (&af)[TM], bf16x8 (&bfr)[TN]) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) af[i] = lds_frag(st, wm * WM + i * 32 + lrow, ks * 2 + lhalf);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bfr[j] = lds_frag(st + BM * 128, wn * WN + j * 32 + lrow, ks * 2 + lhalf);
+    };
+    auto issue_share = [&](int t, char* st, auto share) {   // share SH of 4 of the loads of K-tile t (4: all of them)
+      constexpr int SH = decltype(share)::value;
+#pragma unroll
+      for (int j = 0; j < NLD; ++j) {
+        if (SH < 4 && j * 4 / NLD != SH) continue;
+        if (j < LA) load_span_async<NW>(a.A, m0, a.M, a.K, (kt0 + t) * 64, st, j, wave);
+        else load_span_async<NW, SWAP>(a.W, n0, a.N, a.K, (kt0 + t) * 64, st + BM * 128, j - LA, wave);
+      }
+    };
+    // own loads of all but the newest `ahead` K-tiles have landed and own fragment reads are done, then everybody's
+    auto wait_ahead = [&](int ahead) {
+      static_assert(S <= 6 && 4 * NLD < 63, "the counts below");
+      if (ahead >= 4) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(4 * NLD) : "memory");
+      else if (ahead == 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(3 * NLD) : "memory");
+      else if (ahead == 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NLD) : "memory");
+      else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NLD) : "memory");
+      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
+#define RING_GROUP_ORDER(NLOADS)                                                                     \
+  SGB(0x100, TM + TN, 0);                                                                            \
+  SGB(0x008, 1, 0);                                                                                  \
+  if (NLOADS) { SGB(0x010, NLOADS, 0); }                                                             \
+  SGB(0x008, TM * TN - 1, 0);                                                                        \
+  __builtin_amdgcn_sched_barrier(0)
+#define ALL_LOADS std::integral_constant<int, 4>{}
+#pragma unroll
+    for (int t = 0; t < S - 1; ++t)
+      if (t < KT) issue_share(t, smem + t * STG, ALL_LOADS);
+#undef ALL_LOADS
+    wait_ahead(KT - 1 < S - 2 ? KT - 1 : S - 2);
+    bf16x8 a0[TM], b0[TN], a1[TM], b1[TN];
+    const char* cur = smem;                              // slot of K-tile kt; the tile S-1 further on goes to the slot
+    char* free_slot = smem + (S - 1) * STG;              // that K-tile kt-1 was read from before the last barrier
+    read_frags(cur, 0, a0, b0);
+    auto step = [&](int kt, auto load) {
+      constexpr bool LOAD = decltype(load)::value;
+      const char* nxt = cur + STG == smem + S * STG ? smem : cur + STG;
+      if (LOAD) issue_share(kt + S - 1, free_slot, std::integral_constant<int, 0>{});
+      read_frags(cur, 1, a1, b1);
+      if (LOAD) issue_share(kt + S - 1, free_slot, std::integral_constant<int, 1>{});
+      mma(a0, b0);
+      RING_GROUP_ORDER((LOAD ? S0 + S1 : 0));
+      read_frags(cur, 2, a0, b0);
+      if (LOAD) issue_share(kt + S - 1, free_slot, std::integral_constant<int, 2>{});
+      mma(a1, b1);
+      RING_GROUP_ORDER((LOAD ? S2 : 0));
+      read_frags(cur, 3, a1, b1);
+      if (LOAD) issue_share(kt + S - 1, free_slot, std::integral_constant<int, 3>{});
+      mma(a0, b0);
+      RING_GROUP_ORDER((LOAD ? S3 : 0));
+      if (LOAD) wait_ahead(S - 2);
+      else wait_ahead(KT - 2 - kt);
+      if (LOAD || kt + 1 < KT) read_frags(nxt, 0, a0, b0);
+      mma(a1, b1);
+      RING_GROUP_ORDER(0);
+      free_slot = (char*)cur;
+      cur = nxt;
+    };
+    int kt = 0;
+    for (; kt + S - 1 < KT; ++kt) step(kt, std::true_type{});
+    for (; kt < KT; ++kt) step(kt, std::false_type{});
+  }
+#undef RING_GROUP_ORDER
 #undef PIPE_GROUP_ORDER
 #undef SGB
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -300,7 +379,7 @@ __global__ void __launch_bounds__(128 * NWN) gemm_mfma_kernel(GemmArgs a) {
     if (inside) emit(std::false_type{});
     else emit(std::true_type{});
   } else if (EPI == ME_QKV_ROPE) {
-    static_assert(EPI != ME_QKV_ROPE || (TN == 2 && NWN == 4), "one rotary half per accumulator column");
+    static_assert(EPI != ME_QKV_ROPE || TN == 2, "one rotary half per accumulator column");
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
     constexpr int HDIM = HD128 ? 128 : 64, HALF = HDIM / 2;
     const int head = HD128 ? (n0 >> 7) + (wn >> 1) : (n0 >> 6) + wn;
@@ -411,36 +490,59 @@ __global__ void __launch_bounds__(128 * NWN) gemm_mfma_kernel(GemmArgs a) {
   }
 }
 
-template <int BM, int EPI, int NWN, bool HD128 = false>
+template <int BM, int BN, int NWM, int EPI, bool HD128 = false>
 static void launch_variant(const GemmArgs& a, hipStream_t s) {
-  constexpr int smem = 5 * 256 * 128;
+  constexpr int smem = BM == 256 ? 5 * 256 * 128 : ring_stages(BM, BN) * (BM + BN) * 128;
   static bool configured = false;
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<BM, EPI, NWN, HD128>,
+    (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<BM, BN, NWM, EPI, HD128>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     configured = true;
   }
   const int total = a.m_tiles * a.n_tiles * a.ksplit, per_xcd = 32 * (total / 256) + (total % 256 + 7) / 8;
-  gemm_mfma_kernel<BM, EPI, NWN, HD128><<<8 * per_xcd, 128 * NWN, smem, s>>>(a);
+  gemm_mfma_kernel<BM, BN, NWM, EPI, HD128><<<8 * per_xcd, NWM * BN, smem, s>>>(a);
 }
 
 int mfma_lmhead_tiles(int V) { return (V + 255) / 256; }
 
-// Tile height and K-split for an M x N x K product whose consumer can sum partial products. Times in
-// microseconds from measurements on the 256-CU part: one 64-deep k-step of a resident workgroup costs c(BM),
-// workgroups run in rounds of 256, a launch has a fixed cost, and every extra partial costs one more
-// M x N float write here plus one read in the consumer.
-void mfma_gemm_plan(int M, int N, int K, int max_split, int* bm_out, int* split_out) {
-  const int KT = K / 64, n_tiles = (N + 255) / 256;
+// The tile shapes, and what one 64-deep k-step of a workgroup costs (us) when a few CUs are busy and when all 256 are.
+// The two wide ones are for products that fill the chip, where operand traffic counts (2048 x 37888 x 3584: 457, 539,
+// 670, 834 us in this order); the narrow ones put four to eight times as many workgroups on a short product and have
+// more of its loads in flight (256 x 2048 x 1536: 33.7, 21.4, 15.2, 11.8 us).
+struct TileShape { int bm, bn; double lat, full; };
+static const TileShape kTiles[MFMA_TILES] = {{256, 256, 1.15, 1.7}, {128, 256, 0.68, 1.04}, {128, 128, 0.46, 0.65}, {64, 128, 0.33, 0.41}};
+
+template <int EPI, bool HD128 = false>
+static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
+  a.m_tiles = (a.M + kTiles[tile].bm - 1) / kTiles[tile].bm;
+  a.n_tiles = (a.N + kTiles[tile].bn - 1) / kTiles[tile].bn;
+  if (tile == 0) launch_variant<256, 256, 2, EPI, HD128>(a, s);
+  else if (tile == 1) launch_variant<128, 256, 2, EPI, HD128>(a, s);
+  else if constexpr (EPI != ME_LMHEAD) {
+    // four wavefronts along M: two per SIMD cover each other's LDS reads (69 -> 64 us at 256 x 1536 x 8960)
+    if (tile == 2) launch_variant<128, 128, 4, EPI, HD128>(a, s);
+    else launch_variant<64, 128, 2, EPI, HD128>(a, s);
+  }
+}
+
+// Tile shape and K-split for an M x N x K product whose consumer can sum up to max_split partial products: the pair
+// with the least estimated time. Workgroups run in rounds of 256; a round that leaves CUs idle has k-steps between the
+// two costs of its tile; a launch costs about 4 us beside that, and every extra partial one more M x N float write here
+// and one more read in the consumer. The estimate is within 10 % of the measured times for 64..2048 rows of the
+// projections with K = 1024..18944, except that it misses up to 20 % of the narrow tiles' cost when they run in many
+// rounds, where the wide ones are ahead anyway.
+void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* tile_out, int* split_out) {
+  const int KT = K / 64;
   double best = 1e30;
-  *bm_out = 256; *split_out = 1;
-  for (int bm = M <= 128 ? 128 : 256; bm >= 128; bm >>= 1) {
-    long tiles = (long)((M + bm - 1) / bm) * n_tiles;
-    double c = bm == 256 ? 1.55 : 1.08;
-    for (int sp = 1; sp <= max_split && sp <= 8 && sp * 4 <= KT + 3; ++sp) {
-      long rounds = (tiles * sp + 255) / 256;
-      double t = (double)rounds * ((KT + sp - 1) / sp) * c + 8.0 + (2 * sp - 2) * (double)M * N * 4.0 / 4e6;
-      if (t < best - 1e-9) { best = t; *bm_out = bm; *split_out = sp; }
+  *tile_out = 0; *split_out = 1;
+  for (int tile = 0; tile < (wide_only ? 2 : MFMA_TILES); ++tile) {
+    const TileShape& ts = kTiles[tile];
+    const long tiles = (long)((M + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn);
+    for (int sp = 1; sp <= max_split && sp <= 8 && (sp == 1 || sp * 4 <= KT + 3); ++sp) {
+      const long whole = tiles * sp / 256, rest = tiles * sp % 256;
+      const double step = whole * ts.full + (rest ? ts.lat + (ts.full - ts.lat) * rest / 256.0 : 0.0);
+      const double t = 4.0 + step * ((KT + sp - 1) / sp) + (2 * sp - 2) * (double)M * N * 4.0 / 4e6;
+      if (t < best - 1e-9) { best = t; *tile_out = tile; *split_out = sp; }
     }
   }
 }
@@ -450,7 +552,7 @@ void mfma_gemm_plan(int M, int N, int K, int max_split, int* bm_out, int* split_
 // position g.t0 + m % g.L of candidate m / g.L. Returns false when the shape is not taken (head_dim other than
 // 64/128, K % 64 != 0, misaligned buffers); the caller then runs the projection and the rotary kernel separately.
 bool launch_gemm_mfma_qkv_rope(const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q, bf16_t* kblk, bf16_t* vT,
-                               const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s) {
+                               const BatchGeom& g, const ModelDims& md, int Lp, int tile, hipStream_t s) {
   const int M = g.M, N = (md.Hq + 2 * md.Hkv) * md.hd, K = md.d;
   if (K % 64 != 0 || M <= 0 || (md.hd != 64 && md.hd != 128)) return false;
   if (((uintptr_t)cs & 15) || ((uintptr_t)q & 7) || ((uintptr_t)kblk & 7)) return false;
@@ -458,41 +560,34 @@ bool launch_gemm_mfma_qkv_rope(const bf16_t* A, const bf16_t* W, const float* cs
   a.A = A; a.W = W; a.M = M; a.N = N; a.K = K; a.ksplit = 1;
   a.cs = cs; a.q = q; a.kblk = kblk; a.vT = vT;
   a.Hq = md.Hq; a.Hkv = md.Hkv; a.hd = md.hd; a.Lrows = g.L; a.t0 = g.t0; a.Lk = g.Lk; a.Lp = Lp;
-  a.n_tiles = (N + 255) / 256;
-  bool small = ((M + 255) / 256) * a.n_tiles <= 128 || M <= 128;
-  a.m_tiles = small ? (M + 127) / 128 : (M + 255) / 256;
-  if (md.hd == 128) { if (small) launch_variant<128, ME_QKV_ROPE, 4, true>(a, s); else launch_variant<256, ME_QKV_ROPE, 4, true>(a, s); }
-  else { if (small) launch_variant<128, ME_QKV_ROPE, 4, false>(a, s); else launch_variant<256, ME_QKV_ROPE, 4, false>(a, s); }
+  int split = 1;
+  if (tile < 0) mfma_gemm_plan(M, N, K, 1, false, &tile, &split);
+  if (md.hd == 128) launch_tile<ME_QKV_ROPE, true>(a, tile, s);
+  else launch_tile<ME_QKV_ROPE, false>(a, tile, s);
   return true;
 }
 
 // Returns false when the shape is not one this kernel takes (the caller then uses the SIMT kernel).
 // ksplit > 1 (ME_STORE only): C is [ksplit][M][N] and receives the partial products of the K slices.
-// bm: tile height 128 or 256, 0 = chosen here.
+// tile: index of the tile shape as mfma_gemm_plan gives it, negative = chosen here.
 bool launch_gemm_mfma(int epi, const bf16_t* A, const bf16_t* W, int M, int N, int K, float* C, bf16_t* act,
-                      const int32_t* tok, float* part_max, float* part_sum, float* zt, int ksplit, int bm,
+                      const int32_t* tok, float* part_max, float* part_sum, float* zt, int ksplit, int tile,
                       hipStream_t s) {
   if (K % 64 != 0 || M <= 0 || N <= 0) return false;
   if (epi == ME_SWIGLU && (N % 64 != 0 || ((uintptr_t)act & 7))) return false;
   if (ksplit < 1 || (ksplit > 1 && (epi != ME_STORE || ksplit > K / 64))) return false;
-  if (bm != 0 && bm != 128 && bm != 256) return false;
+  if (tile >= (epi == ME_LMHEAD ? 2 : MFMA_TILES)) return false;
   GemmArgs a = {};
   a.A = A; a.W = W; a.M = M; a.N = N; a.K = K; a.C = C; a.act = act; a.tok = tok;
   a.part_max = part_max; a.part_sum = part_sum; a.zt = zt; a.ksplit = ksplit;
-  a.n_tiles = (N + 255) / 256;
-  // 128-row tiles when twice as many workgroups still fit the 256 CUs in one round
-  bool small = bm ? bm == 128 : ((M + 255) / 256) * a.n_tiles <= 128 || M <= 128;
-  a.m_tiles = small ? (M + 127) / 128 : (M + 255) / 256;
-#define DISPATCH(E)                                                       \
-  if (small) launch_variant<128, E, 4>(a, s);                             \
-  else launch_variant<256, E, 4>(a, s);
+  int split = 1;
+  if (tile < 0) mfma_gemm_plan(M, N, K, 1, epi == ME_LMHEAD, &tile, &split);
   switch (epi) {
-    case ME_STORE: DISPATCH(ME_STORE); break;
-    case ME_RESIDUAL: DISPATCH(ME_RESIDUAL); break;
-    case ME_SWIGLU: DISPATCH(ME_SWIGLU); break;
-    case ME_LMHEAD: DISPATCH(ME_LMHEAD); break;
+    case ME_STORE: launch_tile<ME_STORE>(a, tile, s); break;
+    case ME_RESIDUAL: launch_tile<ME_RESIDUAL>(a, tile, s); break;
+    case ME_SWIGLU: launch_tile<ME_SWIGLU>(a, tile, s); break;
+    case ME_LMHEAD: launch_tile<ME_LMHEAD>(a, tile, s); break;
     default: return false;
   }
-#undef DISPATCH
   return true;
 }

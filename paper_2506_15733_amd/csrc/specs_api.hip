@@ -332,7 +332,7 @@ static void gemm(const T* A, const T* W, float* C, int M, int N, int K, GemmEpil
 template <>
 void gemm<bf16_t>(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, GemmEpilogue epi, hipStream_t s) {
   int e = epi == EPI_RESIDUAL_ADD ? MFMA_RESIDUAL : MFMA_STORE;
-  if (launch_gemm_mfma(e, A, W, M, N, K, C, nullptr, nullptr, nullptr, nullptr, nullptr, 1, 0, s)) {
+  if (launch_gemm_mfma(e, A, W, M, N, K, C, nullptr, nullptr, nullptr, nullptr, nullptr, 1, -1, s)) {
     count_path(SPECS_PATH_GEMM_MFMA);
   } else {
     count_path(SPECS_PATH_GEMM_PLAIN);
@@ -358,10 +358,10 @@ int gemm_residual_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* x, floa
   }
   // Also with one slice the product goes to `part` and the normalisation kernel, which reads x anyway, adds it:
   // the GEMM's epilogue then only writes, instead of waiting for a read of x before every store.
-  int bm = 0, split = 1;
-  if (K % 64 == 0 && max_split > 1) mfma_gemm_plan(M, N, K, max_split, &bm, &split);
+  int tile = -1, split = 1;
+  if (K % 64 == 0 && max_split > 1) mfma_gemm_plan(M, N, K, max_split, false, &tile, &split);
   if (max_split >= 1 &&
-      launch_gemm_mfma(MFMA_STORE, A, W, M, N, K, part, nullptr, nullptr, nullptr, nullptr, nullptr, split, bm, s)) {
+      launch_gemm_mfma(MFMA_STORE, A, W, M, N, K, part, nullptr, nullptr, nullptr, nullptr, nullptr, split, tile, s)) {
     count_path(SPECS_PATH_GEMM_MFMA);
     return split;
   }
@@ -394,7 +394,7 @@ static bool qkv_rope_fused(const T*, const T*, const float*, T*, T*, T*, const B
 template <>
 bool qkv_rope_fused<bf16_t>(const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q, bf16_t* kb, bf16_t* vT,
                             const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s) {
-  if (!launch_gemm_mfma_qkv_rope(A, W, cs, q, kb, vT, g, md, Lp, s)) return false;
+  if (!launch_gemm_mfma_qkv_rope(A, W, cs, q, kb, vT, g, md, Lp, -1, s)) return false;
   count_path(SPECS_PATH_GEMM_MFMA);
   return true;
 }
@@ -409,7 +409,7 @@ static void gate_up(const T* A, const T* Wgu, float* gu, T* act, int M, int F, i
 template <>
 void gate_up<bf16_t>(const bf16_t* A, const bf16_t* Wgu, float* gu, bf16_t* act, int M, int F, int K, hipStream_t s) {
   if (M <= 32 && launch_gemm_skinny(MFMA_SWIGLU, A, Wgu, M, 2 * F, K, nullptr, act, 1, s)) { count_path(SPECS_PATH_GEMM_SKINNY); return; }
-  if (launch_gemm_mfma(MFMA_SWIGLU, A, Wgu, M, 2 * F, K, nullptr, act, nullptr, nullptr, nullptr, nullptr, 1, 0, s)) {
+  if (launch_gemm_mfma(MFMA_SWIGLU, A, Wgu, M, 2 * F, K, nullptr, act, nullptr, nullptr, nullptr, nullptr, 1, -1, s)) {
     count_path(SPECS_PATH_GEMM_MFMA);
     return;
   }
@@ -430,7 +430,7 @@ static int lmhead_partials(const T* A, const T* W, const int32_t* tok, float* pm
 template <>
 int lmhead_partials<bf16_t>(const bf16_t* A, const bf16_t* W, const int32_t* tok, float* pm, float* ps, float* zt, int M,
                             int V, int K, hipStream_t s) {
-  if (launch_gemm_mfma(MFMA_LMHEAD, A, W, M, V, K, nullptr, nullptr, tok, pm, ps, zt, 1, 0, s)) {
+  if (launch_gemm_mfma(MFMA_LMHEAD, A, W, M, V, K, nullptr, nullptr, tok, pm, ps, zt, 1, -1, s)) {
     count_path(SPECS_PATH_GEMM_MFMA);
     return mfma_lmhead_tiles(V);
   }
@@ -808,8 +808,8 @@ extern "C" int specs_op_linear(specs_ctx* ctx, int32_t dtype, const void* A, con
     // same K-split decision as inside the scoring pass, as far as the workspace has room for the partial products
     size_t per = (size_t)M * N * sizeof(float);
     size_t room = ctx->workspace_bytes > 256 ? (ctx->workspace_bytes - 256) / per : 0;
-    int bm = 0, split = 1;
-    if (K % 64 == 0 && room > 1) mfma_gemm_plan(M, N, K, room > 8 ? 8 : (int)room, &bm, &split);
+    int tile = -1, split = 1;
+    if (K % 64 == 0 && room > 1) mfma_gemm_plan(M, N, K, room > 8 ? 8 : (int)room, false, &tile, &split);
     float* part = (float*)(ctx->workspace + 256);
     int sk = M <= 32 && room >= 1 ? skinny_gemm_split(N, K, room > 8 ? 8 : (int)room) : 0;
     if (sk && launch_gemm_skinny(MFMA_STORE, (const bf16_t*)A, (const bf16_t*)W, M, N, K, part, nullptr, sk,
@@ -817,7 +817,7 @@ extern "C" int specs_op_linear(specs_ctx* ctx, int32_t dtype, const void* A, con
       launch_add_partials_rmsnorm<bf16_t>(C, part, sk, accumulate ? 0 : 1, nullptr, nullptr, M, N, 0.f, ctx->stream);
       ctx->last_model = nullptr;
     } else if (split > 1 && launch_gemm_mfma(MFMA_STORE, (const bf16_t*)A, (const bf16_t*)W, M, N, K, part, nullptr, nullptr,
-                                      nullptr, nullptr, nullptr, split, bm, ctx->stream)) {
+                                      nullptr, nullptr, nullptr, split, tile, ctx->stream)) {
       launch_add_partials_rmsnorm<bf16_t>(C, part, split, accumulate ? 0 : 1, nullptr, nullptr, M, N, 0.f, ctx->stream);
       ctx->last_model = nullptr;                         // the workspace no longer holds a scored block
     } else {

@@ -61,6 +61,21 @@ def test_linear_bf16(ctx, M, N, K):
     close(out.cpu().numpy().astype(np.float64), want + c0, 2e-5)
 
 
+# one workgroup tile shape per line: ragged in rows and columns, fewer K-tiles than the ring holds, as many, more
+@pytest.mark.parametrize("M,N,K", [(65, 136, 64), (63, 129, 384), (70, 300, 192), (129, 520, 448),        # 64 x 128
+                                   (321, 8200, 320), (700, 4616, 384), (321, 8200, 64),                   # 128 x 128
+                                   (555, 37888, 192), (300, 17920, 128), (600, 9000, 256),                # 128 x 256
+                                   (1100, 33000, 128), (2060, 9000, 64)])                                 # 256 x 256
+def test_linear_tile_shapes(ctx, M, N, K):
+    from paper_2506_15733_amd import binding as B
+    a, ta = draw(f"a{M}.{K}", (M, K))
+    w, tw = draw(f"w{N}.{K}", (N, K), 0.02)
+    out = torch.zeros((M, N), dtype=torch.float32, device=DEV)
+    B.specs_op_linear(ctx, ta, tw, out, accumulate=False)
+    torch.cuda.synchronize()
+    close(out.cpu().numpy().astype(np.float64), oracle.linear(a, w), 2e-5)   # the bound of test_linear_bf16
+
+
 def test_linear_f32(ctx):
     from paper_2506_15733_amd import binding as B
     a, ta = draw("fa", (70, 100), 1.0, "f32")
