@@ -1,222 +1,288 @@
 // Attention for launches that cover one in-block position t of every candidate (token-by-token generation).
-// The prefix keys, shared by the n candidates of a beam, are handled by the MFMA kernel in its split mode, which
-// stacks the n*g query rows of a (beam, kv head) and leaves per-split partial results (O un-normalised, running
-// maximum m in the log2 domain, weight sum l). This file merges them with the candidate's own block keys
-// 0..t (at most a block length of them): one wavefront per (candidate, query head).
+// The prefix keys, shared by the n candidates of a beam, are handled by the MFMA kernel in its single-position mode,
+// which stacks the n*g query rows of a (beam, kv head) and leaves partial results per run of key tiles (O
+// un-normalised, running maximum m in the log2 domain, weight sum l). This file merges them with the candidate's own
+// block keys 0..t (at most a block length of them).
 #include "common.h"
 
 bool launch_attention_mfma_decode_prefix(const bf16_t* q, const bf16_t* poolK, const bf16_t* poolV, const BatchGeom& g,
-                                         const ModelDims& md, int max_ctx, float* part, size_t part_floats,
-                                         int* q_tiles_out, int* n_splits_out, hipStream_t s);
+                                         const ModelDims& md, const int32_t* lens_host, float* part, size_t part_floats,
+                                         int* run_tiles_out, int* n_splits_out, hipStream_t s);
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// Lp % 8 == 0 (block values are stored transposed and padded to Lp columns). The kernel is a chain of short
-// dependent phases, so every loop over memory is unrolled into batches of independent 16-byte loads.
+struct MergeArgs {
+  const bf16_t* q;      // [C][Hq][HD]
+  const bf16_t* kb;     // [C*Lk][Hkv][HD]
+  const bf16_t* vbT;    // [C][Hkv][HD][Lp]
+  const float* part_o;  // [beam*Hkv + kvh][split][n*g][HD]
+  const float* part_m;
+  const float* part_l;
+  bf16_t* out;          // [C][Hq*HD]
+  const int32_t* lens;
+  int b0, len_override;
+  int n, Hq, Hkv, Lk, Lp, t, run_tiles, n_splits, osum_off;
+  float scale_log2e;
+};
+
+// One workgroup of four wavefronts per (candidate, kv head, 16 of its query heads): the g query heads share the block
+// keys and values, which are therefore read once, in whole cache lines, and multiplied by MFMA (heads are the 16
+// columns). The kernel is a chain of short dependent phases on a few KB, bound by latency, so whatever does not depend
+// on computed values (statistics and the first partial outputs of the runs, values) is requested before the scores.
+// (One wavefront per (candidate, query head), each lane with a key row of its own, touched 64 cache lines with every
+// load: 25.9 us at 256 candidates x 12 heads with 8 runs each; this form 9.2 us with up to 19 runs. At 16 x 12, where the
+// prefix kernel wants 32 runs instead of 16, it takes 9.5 us as the other did with 16, and the prefix 8.5 instead of 10.7.)
 template <int HD>
-__global__ void __launch_bounds__(64) attention_decode_merge_kernel(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ kb, const bf16_t* __restrict__ vbT,
-    const float* __restrict__ part_o, const float* __restrict__ part_m, const float* __restrict__ part_l,
-    bf16_t* __restrict__ out, int n, int Hq, int Hkv, int Lk, int Lp, int t, int q_tiles, int n_splits,
-    float scale_log2e) {
-  constexpr int hd = HD;
-  extern __shared__ float sm[];                 // [hd] query, [Lp] block scores then weights, [n_splits] split weights
-  float* qs = sm;
-  float* sc = sm + hd;
-  float* wsplit = sc + Lp;
-  const int c = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-  const int g = Hq / Hkv, kvh = h / g, j = h - kvh * g;
-  const int b = c / n, i = c - b * n;
-  const int r = i * g + j, qt = r >> 7, rin = r & 127;
-  const size_t prow0 = (((size_t)b * Hkv + kvh) * q_tiles + qt) * n_splits * 128 + rin;   // + split*128
+__global__ void __launch_bounds__(256) attention_decode_merge_kernel(MergeArgs a) {
+  constexpr int KS = HD / 32;                   // MFMA K-steps of the scores
+  constexpr int ND = HD / 64;                   // 16-dim tiles of the output per wavefront
+  constexpr int NPG = 4, NPS = DECODE_MAX_RUNS / 4;   // partial outputs requested up front: 64-lane groups of 16-byte
+                                                // columns, runs per wavefront
+  constexpr int NVP = 4;                        // 32-key value steps requested up front
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int Lq = (a.Lp + 31) & ~31;             // keys of the weights, whole MFMA K-steps
+  const int PS = Lq + 8;                        // row stride of the bf16 weights: 16-byte reads of 16 rows spread over the banks
+  const int HS = a.Hq / a.Hkv < 16 ? a.Hq / a.Hkv : 16;            // head rows of the arrays
+  float* sc = (float*)smem;                     // [HS][SS] scores
+  bf16_t* pw = (bf16_t*)(sc + HS * (Lq + 4));   // [HS][PS] weights
+  float* wm = (float*)(pw + HS * PS);           // [HS][n_splits] maxima, then weights, of the runs
+  float* wl = wm + HS * a.n_splits;             // [HS][n_splits] weight sums
+  float* inv = wl + HS * a.n_splits;            // [HS]
+  float* osum = (float*)(smem + a.osum_off);    // [4][HS][HD] the wavefronts' sums of partial outputs
+  const int SS = Lq + 1;
 
-  const bf16_t* qr = q + ((size_t)c * Hq + h) * hd;
-  for (int d = lane; d < hd; d += 64) qs[d] = (float)qr[d];
-  for (int jk = lane; jk < Lp; jk += 64) sc[jk] = 0.f;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int col = lane & 15, quad = lane >> 4;
+  const int c = blockIdx.x, kvh = blockIdx.y, j0 = blockIdx.z * 16;
+  const int g = a.Hq / a.Hkv, gh = g - j0 < 16 ? g - j0 : 16;      // query heads of this workgroup
+  const int b = c / a.n, i = c - b * a.n, t = a.t;
+  const int P = a.len_override >= 0 ? a.len_override : a.lens[a.b0 + b];
+  const int ns = min((((P + 63) >> 6) + a.run_tiles - 1) / a.run_tiles, a.n_splits);   // runs of this beam
+  const size_t rows = (size_t)a.n * g;
+  const size_t prow0 = ((size_t)b * a.Hkv + kvh) * a.n_splits * rows + (size_t)i * g + j0;   // + split*rows + head
+  const int hc = col < gh ? col : gh - 1;       // columns beyond the heads repeat the last one and are not stored
+
+  bf16x8 qf[KS];
+  const bf16_t* qr = a.q + ((size_t)c * a.Hq + (size_t)kvh * g + j0 + hc) * HD + 8 * quad;
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8*)(qr + 32 * ks);
+  const int nkt = (t + 16) >> 4;                // 16-key tiles that hold a visible key
+  const bf16_t* kbase = a.kb + ((size_t)c * a.Lk * a.Hkv + kvh) * HD + 8 * quad;
+  bf16x8 kf[KS];
+  auto load_keys = [&](int kt) {
+    const int key = 16 * kt + col;
+    const bf16_t* kr = kbase + (size_t)(key <= t ? key : t) * a.Hkv * HD;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) kf[ks] = *(const bf16x8*)(kr + 32 * ks);
+  };
+  if (wave < nkt) load_keys(wave);
+  for (int e = tid; e < gh * ns; e += 256) {
+    const int s = e / gh, h = e - s * gh;
+    wm[h * a.n_splits + s] = a.part_m[prow0 + s * rows + h];
+    wl[h * a.n_splits + s] = a.part_l[prow0 + s * rows + h];
+  }
+  // partial outputs: wavefront w takes the runs w, w + 4, .., its lanes 16-byte columns of the heads' rows
+  const int ncol = gh * (HD / 4);
+  float4 po[NPG][NPS];
+  auto load_parts = [&](int g0) {
+#pragma unroll
+    for (int u = 0; u < NPG; ++u) {
+      if ((g0 + u) * 64 >= ncol) break;
+      const int idx = (g0 + u) * 64 + lane;
+      const float4* pb = (const float4*)(a.part_o + prow0 * HD) + (idx < ncol ? idx : ncol - 1);
+#pragma unroll
+      for (int k = 0; k < NPS; ++k)
+        if (wave + 4 * k < ns) po[u][k] = pb[(size_t)(wave + 4 * k) * rows * (HD / 4)];
+    }
+  };
+  load_parts(0);
+  const int nvs = (t + 32) >> 5;                // 32-key steps that hold a visible key
+  const bf16_t* vbase = a.vbT + (((size_t)c * a.Hkv + kvh) * HD + 16 * wave + col) * a.Lp;
+  // values of keys 32 st + 8 quad .. + 7; keys beyond t hold whatever an earlier call left there and become 0
+  auto load_vals = [&](int u, int st) {
+    const int key = 32 * st + 8 * quad;
+    bf16x8 v = *(const bf16x8*)(vbase + (size_t)64 * u * a.Lp + (key < a.Lp ? key : 0));
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = key + e <= t ? v[e] : (__bf16)0.f;
+    return v;
+  };
+  bf16x8 vv[ND][NVP];
+#pragma unroll
+  for (int u = 0; u < ND; ++u)
+#pragma unroll
+    for (int st = 0; st < NVP; ++st) vv[u][st] = load_vals(u, st < nvs ? st : 0);
+
+  // scores of the block keys: lane holds keys 16 kt + 4 quad + e of head col
+  for (int kt = wave; kt < nkt; kt += 4) {
+    floatx4 s4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) s4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qf[ks], s4, 0, 0, 0);
+    if (kt + 4 < nkt) load_keys(kt + 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (col < gh) sc[col * SS + 16 * kt + 4 * quad + e] = s4[e] * a.scale_log2e;
+  }
   __syncthreads();
-  // the candidate's own keys 0..t
+  // softmax statistics, heads dealt to the wavefronts
+  for (int h = wave; h < gh; h += 4) {
+    float mx = -INFINITY;
+    for (int k = lane; k <= t; k += 64) mx = fmaxf(mx, sc[h * SS + k]);
+    for (int s = lane; s < ns; s += 64) mx = fmaxf(mx, wm[h * a.n_splits + s]);
+    mx = ceilf(wave_max(mx));                   // finite (key t itself is always visible); an integer, so that
+                                                // the bf16 rounding of the weights does not depend on the reference
+    float l = 0.f;
+    for (int k = lane; k < Lq; k += 64) {
+      const float p = k <= t ? __builtin_amdgcn_exp2f(sc[h * SS + k] - mx) : 0.f;
+      l += p;
+      pw[h * PS + k] = (bf16_t)p;               // the weight that multiplies V is a bf16 operand
+    }
+    for (int s = lane; s < ns; s += 64) {
+      const float w = __builtin_amdgcn_exp2f(wm[h * a.n_splits + s] - mx);
+      l += w * wl[h * a.n_splits + s];
+      wm[h * a.n_splits + s] = w;
+    }
+    l = wave_sum(l);
+    if (lane == 0) inv[h] = 1.0f / l;
+  }
+  __syncthreads();
+  for (int g0 = 0; g0 * 64 < ncol; g0 += NPG) {
+    if (g0) load_parts(g0);
+#pragma unroll
+    for (int u = 0; u < NPG; ++u) {
+      const int idx = (g0 + u) * 64 + lane;
+      if (idx >= ncol) break;
+      const float* wr = wm + idx / (HD / 4) * a.n_splits + wave;
+      float4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int k = 0; k < NPS; ++k)
+        if (wave + 4 * k < ns) {
+          const float w = wr[4 * k];
+          o.x = fmaf(w, po[u][k].x, o.x);
+          o.y = fmaf(w, po[u][k].y, o.y);
+          o.z = fmaf(w, po[u][k].z, o.z);
+          o.w = fmaf(w, po[u][k].w, o.w);
+        }
+      ((float4*)osum)[wave * HS * (HD / 4) + idx] = o;
+    }
+  }
+  __syncthreads();
+  const float winv = inv[hc];
+#pragma unroll
+  for (int u = 0; u < ND; ++u) {
+    // this lane's output dims: 16 (wave + 4 u) + 4 quad .. + 3 of head col
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float4 o = *(const float4*)(osum + ((size_t)w * HS + hc) * HD + 16 * wave + 64 * u + 4 * quad);
+      acc[0] += o.x; acc[1] += o.y; acc[2] += o.z; acc[3] += o.w;
+    }
+    const bf16_t* pr = pw + hc * PS + 8 * quad;
+#pragma unroll
+    for (int st = 0; st < NVP; ++st)
+      if (st < nvs) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv[u][st], *(const bf16x8*)(pr + 32 * st), acc, 0, 0, 0);
+    for (int st = NVP; st < nvs; ++st)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(load_vals(u, st), *(const bf16x8*)(pr + 32 * st), acc, 0, 0, 0);
+    if (col < gh) {
+      bf16x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = (__bf16)(acc[e] * winv);
+      *(bf16x4*)(a.out + ((size_t)c * a.Hq + (size_t)kvh * g + j0 + col) * HD + 16 * wave + 64 * u + 4 * quad) = o;
+    }
+  }
+}
+
+// The same merge for blocks whose scores do not fit the LDS above: one wavefront per (candidate, query head).
+template <int HD>
+__global__ void __launch_bounds__(64) attention_decode_merge_long_kernel(MergeArgs a) {
+  extern __shared__ float sm[];                 // [HD] query, [Lp] block scores then weights, [n_splits] run weights
+  float* qs = sm;
+  float* sc = sm + HD;
+  float* wrun = sc + a.Lp;
+  const int c = blockIdx.x, h = blockIdx.y, lane = threadIdx.x, t = a.t;
+  const int g = a.Hq / a.Hkv, kvh = h / g, j = h - kvh * g;
+  const int b = c / a.n, i = c - b * a.n;
+  const int P = a.len_override >= 0 ? a.len_override : a.lens[a.b0 + b];
+  const int ns = min((((P + 63) >> 6) + a.run_tiles - 1) / a.run_tiles, a.n_splits);
+  const size_t rows = (size_t)a.n * g;
+  const size_t prow0 = ((size_t)b * a.Hkv + kvh) * a.n_splits * rows + (size_t)i * g + j;   // + split*rows
+
+  const bf16_t* qr = a.q + ((size_t)c * a.Hq + h) * HD;
+  for (int d = lane; d < HD; d += 64) qs[d] = (float)qr[d];
+  __syncthreads();
   float mx = -INFINITY;
   for (int jk = lane; jk <= t; jk += 64) {
-    const bf16_t* kr = kb + (((size_t)c * Lk + jk) * Hkv + kvh) * hd;
-    bf16x8 kv[HD / 8];
-#pragma unroll
-    for (int i8 = 0; i8 < HD / 8; ++i8) kv[i8] = *(const bf16x8*)(kr + 8 * i8);
+    const bf16_t* kr = a.kb + (((size_t)c * a.Lk + jk) * a.Hkv + kvh) * HD;
     float dot = 0.f;
 #pragma unroll
-    for (int i8 = 0; i8 < HD / 8; ++i8)
+    for (int i8 = 0; i8 < HD / 8; ++i8) {
+      const bf16x8 kv = *(const bf16x8*)(kr + 8 * i8);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) dot = fmaf(qs[8 * i8 + e], (float)kv[i8][e], dot);
-    dot *= scale_log2e;
+      for (int e = 0; e < 8; ++e) dot = fmaf(qs[8 * i8 + e], (float)kv[e], dot);
+    }
+    dot *= a.scale_log2e;
     sc[jk] = dot;
     mx = fmaxf(mx, dot);
   }
-  for (int s = lane; s < n_splits; s += 64) mx = fmaxf(mx, part_m[prow0 + (size_t)s * 128]);
-  mx = ceilf(wave_max(mx));                     // finite (key t itself is always visible); an integer, so that
-                                                // the bf16 rounding of the weights does not depend on the reference
+  for (int s = lane; s < ns; s += 64) mx = fmaxf(mx, a.part_m[prow0 + s * rows]);
+  mx = ceilf(wave_max(mx));
   float l = 0.f;
   for (int jk = lane; jk <= t; jk += 64) {
-    float p = __builtin_amdgcn_exp2f(sc[jk] - mx);
+    const float p = __builtin_amdgcn_exp2f(sc[jk] - mx);
     l += p;
-    sc[jk] = (float)(bf16_t)p;                  // the weight that multiplies V is a bf16 operand
+    sc[jk] = (float)(bf16_t)p;
   }
-  for (int s = lane; s < n_splits; s += 64) {
-    float w = __builtin_amdgcn_exp2f(part_m[prow0 + (size_t)s * 128] - mx);   // exp2(-inf) = 0 for an empty split
-    wsplit[s] = w;
-    l += w * part_l[prow0 + (size_t)s * 128];
+  for (int s = lane; s < ns; s += 64) {
+    const float w = __builtin_amdgcn_exp2f(a.part_m[prow0 + s * rows] - mx);
+    wrun[s] = w;
+    l += w * a.part_l[prow0 + s * rows];
   }
   l = wave_sum(l);
   __syncthreads();
   const float inv = 1.0f / l;
-  const int t8 = (t + 8) & ~7;                  // columns 0 .. t rounded up to whole 16-byte groups
-#pragma unroll
   for (int d = lane; d < HD; d += 64) {
     float acc = 0.f;
-    for (int s0 = 0; s0 < n_splits; s0 += 8) {           // eight partial results at a time
-      float po[8];
+    for (int s = 0; s < ns; ++s) acc = fmaf(wrun[s], a.part_o[(prow0 + s * rows) * HD + d], acc);
+    const bf16_t* vr = a.vbT + (((size_t)c * a.Hkv + kvh) * HD + d) * a.Lp;
+    for (int k0 = 0; k0 <= t; k0 += 8) {
+      const bf16x8 vv = *(const bf16x8*)(vr + k0);
 #pragma unroll
-      for (int k = 0; k < 8; ++k) po[k] = s0 + k < n_splits ? part_o[(prow0 + (size_t)(s0 + k) * 128) * HD + d] : 0.f;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) acc = fmaf(s0 + k < n_splits ? wsplit[s0 + k] : 0.f, po[k], acc);
+      for (int e = 0; e < 8; ++e) acc = fmaf(k0 + e <= t ? sc[k0 + e] : 0.f, k0 + e <= t ? (float)vv[e] : 0.f, acc);
     }
-    const bf16_t* vr = vbT + (((size_t)c * Hkv + kvh) * HD + d) * Lp;
-    for (int j0 = 0; j0 < t8; j0 += 64) {                // eight 16-byte groups of block values at a time
-      bf16x8 vv[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) vv[k] = j0 + 8 * k < t8 ? *(const bf16x8*)(vr + j0 + 8 * k) : bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {                   // columns beyond t hold whatever an earlier call left there
-          const int jk = j0 + 8 * k + e;
-          acc = fmaf(jk <= t ? sc[jk] : 0.f, jk <= t ? (float)vv[k][e] : 0.f, acc);
-        }
-    }
-    out[((size_t)c * Hq + h) * HD + d] = (bf16_t)(acc * inv);
+    a.out[((size_t)c * a.Hq + h) * HD + d] = (bf16_t)(acc * inv);
   }
 }
 
-// The same merge for block buffers of at most 128 columns and at most 16 splits, with every load whose address
-// does not depend on computed values (block keys, split statistics, partial outputs, block values) issued up front
-// into registers, so that the kernel waits for memory once instead of once per phase.
-template <int HD>
-__global__ void __launch_bounds__(64) attention_decode_merge_fast_kernel(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ kb, const bf16_t* __restrict__ vbT,
-    const float* __restrict__ part_o, const float* __restrict__ part_m, const float* __restrict__ part_l,
-    bf16_t* __restrict__ out, int n, int Hq, int Hkv, int Lk, int Lp, int t, int q_tiles, int n_splits,
-    float scale_log2e) {
-  constexpr int ND = HD / 64;                   // output dims per lane
-  __shared__ float qs[HD];
-  __shared__ float sc[128];
-  __shared__ float wsplit[16];
-  const int c = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-  const int g = Hq / Hkv, kvh = h / g, j = h - kvh * g;
-  const int b = c / n, i = c - b * n;
-  const int r = i * g + j, qt = r >> 7, rin = r & 127;
-  const size_t prow0 = (((size_t)b * Hkv + kvh) * q_tiles + qt) * n_splits * 128 + rin;
-  const int t8 = (t + 8) & ~7;
-  const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
-
-  // ---- all loads
-  const bf16_t* qr = q + ((size_t)c * Hq + h) * HD;
-  float qv[ND];
-#pragma unroll
-  for (int u = 0; u < ND; ++u) qv[u] = (float)qr[lane + 64 * u];
-  bf16x8 kv[2][HD / 8];
-#pragma unroll
-  for (int kk = 0; kk < 2; ++kk) {
-    const int jk = lane + 64 * kk;
-    const bf16_t* kr = kb + (((size_t)c * Lk + (jk <= t ? jk : t)) * Hkv + kvh) * HD;
-#pragma unroll
-    for (int i8 = 0; i8 < HD / 8; ++i8) kv[kk][i8] = *(const bf16x8*)(kr + 8 * i8);
-  }
-  float pm = -INFINITY, pl = 0.f;
-  if (lane < n_splits) { pm = part_m[prow0 + (size_t)lane * 128]; pl = part_l[prow0 + (size_t)lane * 128]; }
-  float po[ND][16];
-  bf16x8 vv[ND][16];
-#pragma unroll
-  for (int u = 0; u < ND; ++u) {
-    const int d = lane + 64 * u;
-#pragma unroll
-    for (int s = 0; s < 16; ++s) po[u][s] = s < n_splits ? part_o[(prow0 + (size_t)s * 128) * HD + d] : 0.f;
-    const bf16_t* vr = vbT + (((size_t)c * Hkv + kvh) * HD + d) * Lp;
-#pragma unroll
-    for (int k = 0; k < 16; ++k) vv[u][k] = 8 * k < t8 ? *(const bf16x8*)(vr + 8 * k) : zero8;
-  }
-
-  // ---- scores of the candidate's own keys 0..t
-#pragma unroll
-  for (int u = 0; u < ND; ++u) qs[lane + 64 * u] = qv[u];
-  sc[lane] = 0.f;
-  sc[lane + 64] = 0.f;
-  __syncthreads();
-  float mx = pm;
-  float dots[2];
-#pragma unroll
-  for (int kk = 0; kk < 2; ++kk) {
-    float dot = 0.f;
-#pragma unroll
-    for (int i8 = 0; i8 < HD / 8; ++i8)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) dot = fmaf(qs[8 * i8 + e], (float)kv[kk][i8][e], dot);
-    dots[kk] = lane + 64 * kk <= t ? dot * scale_log2e : -INFINITY;
-    mx = fmaxf(mx, dots[kk]);
-  }
-  mx = ceilf(wave_max(mx));                     // finite (key t itself is always visible); an integer, so that
-                                                // the bf16 rounding of the weights does not depend on the reference
-  float l = 0.f;
-#pragma unroll
-  for (int kk = 0; kk < 2; ++kk) {
-    float p = __builtin_amdgcn_exp2f(dots[kk] - mx);       // exp2(-inf) = 0 beyond t
-    l += p;
-    sc[lane + 64 * kk] = (float)(bf16_t)p;      // the weight that multiplies V is a bf16 operand
-  }
-  const float w = __builtin_amdgcn_exp2f(pm - mx);         // 0 for an empty split and for lanes >= n_splits
-  if (lane < 16) wsplit[lane] = w;
-  l += w * pl;
-  l = wave_sum(l);
-  __syncthreads();
-  const float inv = 1.0f / l;
-#pragma unroll
-  for (int u = 0; u < ND; ++u) {
-    float acc = 0.f;
-#pragma unroll
-    for (int s = 0; s < 16; ++s) acc = fmaf(wsplit[s], po[u][s], acc);
-#pragma unroll
-    for (int k = 0; k < 16; ++k)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {             // weights beyond t are 0; the values there may be anything
-        const int jk = 8 * k + e;
-        acc = fmaf(sc[jk], jk <= t ? (float)vv[u][k][e] : 0.f, acc);
-      }
-    out[((size_t)c * Hq + h) * HD + lane + 64 * u] = (bf16_t)(acc * inv);
-  }
-}
-
-// Returns false when the shape is not taken (the caller then uses the plain kernel).
+// Returns false when the shape is not taken (the caller then uses the plain kernel). lens_host: the prefix lengths of
+// all beams of the prefix handle, as g.lens holds them on the device.
 bool launch_attention_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                              const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,
-                             int max_ctx, float* part, size_t part_floats, hipStream_t s) {
-  int q_tiles = 0, n_splits = 0;
-  if (!launch_attention_mfma_decode_prefix(q, poolK, poolV, g, md, max_ctx, part, part_floats, &q_tiles, &n_splits, s))
+                             const int32_t* lens_host, float* part, size_t part_floats, hipStream_t s) {
+  int run_tiles = 0, n_splits = 0;
+  if (!launch_attention_mfma_decode_prefix(q, poolK, poolV, g, md, lens_host, part, part_floats, &run_tiles, &n_splits, s))
     return false;
-  int base = g.B * md.Hkv * q_tiles;
-  size_t rows_all = (size_t)base * n_splits * 128;
-  const float* part_m = part + rows_all * md.hd;
-  const float* part_l = part_m + rows_all;
-  size_t lds = (size_t)(md.hd + Lp + n_splits) * sizeof(float);
-  float scale_log2e = 1.4426950408889634f / sqrtf((float)md.hd);
-  const bool fast = Lp <= 128 && n_splits <= 16;
-  if (fast && md.hd == 128)
-    attention_decode_merge_fast_kernel<128><<<dim3(g.B * g.n, md.Hq), 64, 0, s>>>(
-        q, kb, vbT, part, part_m, part_l, out, g.n, md.Hq, md.Hkv, g.Lk, Lp, g.t0, q_tiles, n_splits, scale_log2e);
-  else if (fast)
-    attention_decode_merge_fast_kernel<64><<<dim3(g.B * g.n, md.Hq), 64, 0, s>>>(
-        q, kb, vbT, part, part_m, part_l, out, g.n, md.Hq, md.Hkv, g.Lk, Lp, g.t0, q_tiles, n_splits, scale_log2e);
-  else if (md.hd == 128)
-    attention_decode_merge_kernel<128><<<dim3(g.B * g.n, md.Hq), 64, lds, s>>>(
-        q, kb, vbT, part, part_m, part_l, out, g.n, md.Hq, md.Hkv, g.Lk, Lp, g.t0, q_tiles, n_splits, scale_log2e);
-  else
-    attention_decode_merge_kernel<64><<<dim3(g.B * g.n, md.Hq), 64, lds, s>>>(
-        q, kb, vbT, part, part_m, part_l, out, g.n, md.Hq, md.Hkv, g.Lk, Lp, g.t0, q_tiles, n_splits, scale_log2e);
+  const size_t rows_all = (size_t)g.B * md.Hkv * n_splits * g.n * (md.Hq / md.Hkv);
+  MergeArgs a;
+  a.q = q; a.kb = kb; a.vbT = vbT; a.out = out;
+  a.part_o = part; a.part_m = part + rows_all * md.hd; a.part_l = a.part_m + rows_all;
+  a.lens = g.lens; a.b0 = g.b0; a.len_override = g.len_override;
+  a.n = g.n; a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lk = g.Lk; a.Lp = Lp; a.t = g.t0; a.run_tiles = run_tiles;
+  a.n_splits = n_splits;
+  a.scale_log2e = 1.4426950408889634f / sqrtf((float)md.hd);
+  const int gq = md.Hq / md.Hkv, HS = gq < 16 ? gq : 16, Lq = (Lp + 31) & ~31;
+  const size_t osum_off = ((size_t)HS * (4 * (Lq + 4) + 2 * (Lq + 8) + 8 * n_splits + 4) + 15) & ~(size_t)15;
+  const size_t lds = osum_off + 4 * (size_t)HS * md.hd * 4;
+  a.osum_off = (int)osum_off;
+  if (lds <= 64 * 1024) {                                // 300 block tokens with 16 query heads per kv head, more with fewer
+    const dim3 grid(g.B * g.n, md.Hkv, (gq + 15) / 16);
+    if (md.hd == 128) attention_decode_merge_kernel<128><<<grid, 256, lds, s>>>(a);
+    else attention_decode_merge_kernel<64><<<grid, 256, lds, s>>>(a);
+  } else {
+    const dim3 grid(g.B * g.n, md.Hq);
+    const size_t lds_long = (size_t)(md.hd + Lp + n_splits) * sizeof(float);
+    if (md.hd == 128) attention_decode_merge_long_kernel<128><<<grid, 64, lds_long, s>>>(a);
+    else attention_decode_merge_long_kernel<64><<<grid, 64, lds_long, s>>>(a);
+  }
   return true;
 }

@@ -39,10 +39,12 @@ struct AttnArgs {
   BatchGeom g;
   int Hq, Hkv, Lp, q_tiles, total_wg, wg_per_xcd;
   float scale_log2e;
-  // single-position launches (generation): the prefix keys are cut into n_splits runs of tiles and every
-  // workgroup leaves an un-normalised partial result for a second kernel to merge
+  // launches that cut the key list: n_splits runs of tiles per query tile, and every workgroup leaves an
+  // un-normalised partial result for a second kernel to merge
   int n_splits;
-  float* part_o;        // [(b*Hkv + kvh) (, candidate)][q_tile][split][128][HD]
+  int run_tiles;        // single positions (generation): tiles of a run; a beam has as many runs as its length asks for
+  float* part_o;        // whole blocks: [b*Hkv + kvh][candidate][q_tile][split][128][HD]
+                        // single positions: [b*Hkv + kvh][split][n*g rows][HD]
   float* part_m;        // [..][128] running maximum (log2 domain), -inf if the run was empty
   float* part_l;        // [..][128] sum of weights relative to that maximum
 };
@@ -64,9 +66,10 @@ __device__ __forceinline__ int k_swizzle(int row, int chunk) {
 }
 
 // MODE 0: whole blocks, as described above. MODE 1: one position per candidate; the stacked rows of a
-// (beam, kv head) are its n candidates x g query heads (row r = i*g + j), the workgroup covers only the prefix
-// tiles of its split and writes (O un-normalised, m, l) instead of the output; the candidate's own block keys
-// are added by the merge kernel. MODE 2: whole blocks, but the tile list (prefix tiles, then block tiles) is cut
+// (beam, kv head) are its n candidates x g query heads (row r = i*g + j), the workgroup covers only one run of
+// run_tiles prefix tiles and writes (O un-normalised, m, l) instead of the output; the candidate's own block keys
+// are added by the merge kernel. Runs are equally long over all beams, so a launch whose beams differ in length has
+// no long workgroups that the others wait for. MODE 2: whole blocks, but the tile list (prefix tiles, then block tiles) is cut
 // into n_splits runs handled by different workgroups, for launches that would otherwise leave most CUs idle; a
 // merge kernel combines the partial results.
 template <int HD, int QT, int MODE>
@@ -82,15 +85,22 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
   constexpr int BQ = 128 * QT;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
 
-  // workgroup id -> logical index: each XCD (id % 8) takes a contiguous run of the (beam, kv head, candidate, tile) list
-  const int logical = (blockIdx.x & 7) * a.wg_per_xcd + (blockIdx.x >> 3);
+  // workgroup id -> logical index: each XCD (id % 8) takes a contiguous run of the (beam, kv head, candidate, tile)
+  // list; single positions deal the (beam, kv head, run) list round, since beams of different lengths lie in a row, and
+  // keep the query tiles of one entry together
+  int logical = (blockIdx.x & 7) * a.wg_per_xcd + (blockIdx.x >> 3);
+  if (DEC) {
+    const int pass = (blockIdx.x >> 3) / a.q_tiles, qt = (blockIdx.x >> 3) - pass * a.q_tiles;
+    logical = (pass * 8 + (blockIdx.x & 7)) * a.q_tiles + qt;
+  }
   if (logical >= a.total_wg) return;
   const BatchGeom& G = a.g;
   const int g = a.Hq / a.Hkv;
   int rem = logical;
   int split = 0;
-  if (SPLIT) { split = rem % a.n_splits; rem /= a.n_splits; }
+  if (SPLIT && !DEC) { split = rem % a.n_splits; rem /= a.n_splits; }
   const int qt_idx = rem % a.q_tiles; rem /= a.q_tiles;
+  if (DEC) { split = rem % a.n_splits; rem /= a.n_splits; }
   int cand = 0;
   if (!DEC) { cand = rem % G.n; rem /= G.n; }
   const int kvh = rem % a.Hkv;
@@ -141,8 +151,12 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
   const int n_btiles = DEC ? 0 : ((r_wg0 < rows_total) ? (t_hi >> 6) + 1 : 0);
   // tiles [tile_lo, tile_lo + n_tiles) of the list (prefix tiles, then block tiles)
   const int n_list = n_ptiles + n_btiles;
-  const int tile_lo = SPLIT ? (int)((long)split * n_list / a.n_splits) : 0;
-  const int n_tiles = SPLIT ? (int)((long)(split + 1) * n_list / a.n_splits) - tile_lo : n_list;
+  const int tile_lo = DEC ? split * a.run_tiles : SPLIT ? (int)((long)split * n_list / a.n_splits) : 0;
+  // (the last run takes all that is left: a captured launch may be replayed on a prefix that has grown since)
+  const int n_tiles = DEC     ? (split == a.n_splits - 1 || n_list - tile_lo < a.run_tiles ? n_list - tile_lo : a.run_tiles)
+                      : SPLIT ? (int)((long)(split + 1) * n_list / a.n_splits) - tile_lo
+                              : n_list;
+  if (DEC && n_tiles <= 0) return;                     // a run beyond this beam's prefix: the merge does not read it
 
   // one wavefront stages one 16-key group (a page, or 16 block tokens) of the tile: K rows and V^T
   // physical page of this wavefront's 16-key group of a prefix tile (looked up one tile before it is staged, so
@@ -214,6 +228,7 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
       stage_tile(tile + 1, page_next, smem + ((it + 1) & 1) * STAGE);
       page_next = page_of(tile + 2);                   // lands while this tile is being multiplied
     }
+    if (DEC && r_wg0 + wave * QT * 32 >= rows_total) continue;   // no rows of its own: this wavefront only stages
     const char* Ks = smem + (it & 1) * STAGE;
     const char* Vs = Ks + K_BYTES;
     const bool is_block = tile >= n_ptiles;
@@ -338,8 +353,10 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
     int r = r_wg0 + (wave * QT + u) * 32 + lq;
     float l = half_wave_sum(l_run[u]);
     if (SPLIT) {
+      if (DEC && r >= rows_total) continue;
       const size_t group = DEC ? (size_t)b * a.Hkv + kvh : ((size_t)b * a.Hkv + kvh) * G.n + cand;
-      const size_t prow = ((group * a.q_tiles + qt_idx) * a.n_splits + split) * BQ + (wave * QT + u) * 32 + lq;
+      const size_t prow = DEC ? (group * a.n_splits + split) * rows_total + r
+                              : ((group * a.q_tiles + qt_idx) * a.n_splits + split) * BQ + (wave * QT + u) * 32 + lq;
       if (lh == 0) { a.part_m[prow] = m_run[u]; a.part_l[prow] = l; }
       float* dst = a.part_o + prow * HD;
 #pragma unroll
@@ -419,7 +436,7 @@ bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT,
   AttnArgs a;
   a.q = q; a.kb = kb; a.vbT = vbT; a.poolK = poolK; a.poolV = poolV; a.out = out; a.g = g;
   a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lp = Lp;
-  a.n_splits = 1; a.part_o = nullptr; a.part_m = nullptr; a.part_l = nullptr;
+  a.n_splits = 1; a.run_tiles = 0; a.part_o = nullptr; a.part_m = nullptr; a.part_l = nullptr;
   a.scale_log2e = 1.4426950408889634f / sqrtf((float)md.hd);
   int rows = g.L * (md.Hq / md.Hkv);
   // 256-row workgroups only when they waste less padding than 128-row ones (the latter run two per CU)
@@ -462,38 +479,54 @@ bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT,
   return true;
 }
 
-// Prefix part of a single-position launch (g.L == 1): partial results per (beam, kv head, row tile, split).
-// q_tiles_out / n_splits_out describe the partial buffers' layout to the merge kernel. part_floats: room in
+// Prefix part of a single-position launch (g.L == 1): partial results per (beam, kv head, run of key tiles, row).
+// run_tiles_out / n_splits_out describe the partial buffers' layout to the merge kernel. part_floats: room in
 // `part` (floats); returns false if the shape is not taken or the partials would not fit.
 bool launch_attention_mfma_decode_prefix(const bf16_t* q, const bf16_t* poolK, const bf16_t* poolV, const BatchGeom& g,
-                                         const ModelDims& md, int max_ctx, float* part, size_t part_floats,
-                                         int* q_tiles_out, int* n_splits_out, hipStream_t s) {
+                                         const ModelDims& md, const int32_t* lens_host, float* part, size_t part_floats,
+                                         int* run_tiles_out, int* n_splits_out, hipStream_t s) {
   if ((md.hd != 64 && md.hd != 128) || g.page_tokens != 16 || g.L != 1) return false;
   AttnArgs a;
   a.q = q; a.kb = nullptr; a.vbT = nullptr; a.poolK = poolK; a.poolV = poolV; a.out = nullptr; a.g = g;
   a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lp = 16;
   a.scale_log2e = 1.4426950408889634f / sqrtf((float)md.hd);
-  int rows = g.n * (md.Hq / md.Hkv);
+  const int rows = g.n * (md.Hq / md.Hkv);
   a.q_tiles = (rows + 127) / 128;
-  int base = g.B * md.Hkv * a.q_tiles;
-  int max_tiles = (max_ctx + 63) / 64;
-  int splits = (512 + base - 1) / base;                 // about two workgroups per CU ...
-  splits = splits > 16 ? 16 : splits;                   // ... but few enough partial results for the merge to stay cheap
-  splits = splits > max_tiles ? max_tiles : splits;
-  splits = splits < 1 ? 1 : splits;
-  size_t per_split = (size_t)base * 128 * (md.hd + 2);
-  if (per_split > part_floats) return false;
-  if ((size_t)splits * per_split > part_floats) splits = (int)(part_floats / per_split);
-  a.n_splits = splits;
-  size_t rows_all = (size_t)base * splits * 128;
+  auto tiles_of = [&](int b) { return ((g.len_override >= 0 ? g.len_override : lens_host[g.b0 + b]) + 63) / 64; };
+  int max_tiles = 1;
+  long sum_tiles = 0;
+  for (int b = 0; b < g.B; ++b) {
+    const int t = tiles_of(b);
+    max_tiles = t > max_tiles ? t : max_tiles;
+    sum_tiles += t;
+  }
+  // (An equal number of runs for every beam, 8 at 32 beams of 1k-8k tokens: 35.5 us, the longest beam's workgroups last;
+  // runs of equal length, and no stores for the 80 of 128 rows that hold no query: 30.7.)
+  // The shortest run that keeps all workgroups resident (two per CU), and at most DECODE_MAX_RUNS partial results per
+  // row for the merge to read.
+  const size_t per_split = (size_t)g.B * md.Hkv * rows * (md.hd + 2);
+  int run = (max_tiles + DECODE_MAX_RUNS - 1) / DECODE_MAX_RUNS;
+  const long least = sum_tiles * md.Hkv * a.q_tiles / 512;
+  if (least > run) run = least < max_tiles ? (int)least : max_tiles;
+  for (;; ++run) {
+    long wgs = 0;
+    for (int b = 0; b < g.B; ++b) wgs += (tiles_of(b) + run - 1) / run;
+    if (run >= max_tiles || (wgs * md.Hkv * a.q_tiles <= 512 && (size_t)((max_tiles + run - 1) / run) * per_split <= part_floats))
+      break;
+  }
+  a.run_tiles = run;
+  a.n_splits = (max_tiles + run - 1) / run;
+  if ((size_t)a.n_splits * per_split > part_floats) return false;
+  const size_t rows_all = (size_t)g.B * md.Hkv * a.n_splits * rows;
   a.part_o = part;
   a.part_m = part + rows_all * md.hd;
   a.part_l = a.part_m + rows_all;
-  a.total_wg = base * splits;
-  a.wg_per_xcd = (a.total_wg + 7) / 8;
+  const int entries = g.B * md.Hkv * a.n_splits;
+  a.total_wg = entries * a.q_tiles;
+  a.wg_per_xcd = (entries + 7) / 8 * a.q_tiles;
   if (md.hd == 128) launch_attn_variant<128, 1, 1>(a, s);
   else launch_attn_variant<64, 1, 1>(a, s);
-  *q_tiles_out = a.q_tiles;
-  *n_splits_out = splits;
+  *run_tiles_out = run;
+  *n_splits_out = a.n_splits;
   return true;
 }

@@ -114,11 +114,13 @@ bool launch_attention_pingpong(const bf16_t* q, const bf16_t* kb, const bf16_t* 
                                const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,
                                int max_ctx, float* part, size_t part_floats, hipStream_t s);
 
+enum { DECODE_MAX_RUNS = 32 };   // runs of prefix tiles a beam is cut into at most
 // One in-block position per candidate (g.L == 1, position g.t0): prefix keys by the MFMA kernel in split mode,
-// merged with the candidate's own block keys. part: scratch of part_floats floats. False if the shape is not taken.
+// merged with the candidate's own block keys. lens_host: what g.lens holds. part: scratch of part_floats floats. False
+// if the shape is not taken.
 bool launch_attention_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                              const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,
-                             int max_ctx, float* part, size_t part_floats, hipStream_t s);
+                             const int32_t* lens_host, float* part, size_t part_floats, hipStream_t s);
 
 // Fused vocabulary head: per (row, 64-column tile) partial (max, sum exp) and the target-token logit.
 template <typename T>

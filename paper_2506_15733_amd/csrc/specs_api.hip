@@ -443,7 +443,8 @@ int lmhead_partials<bf16_t>(const bf16_t* A, const bf16_t* W, const int32_t* tok
 // scratch: floats free for the duration of the call (partial results of single-position launches)
 template <typename T>
 static void attention(const T* q, const T* kb, const T* vbT, const T* pK, const T* pV, T* out, const BatchGeom& g,
-                      const ModelDims& md, int Lp, int max_ctx, float* scratch, size_t scratch_floats, hipStream_t s);
+                      const ModelDims& md, int Lp, int max_ctx, const int32_t* lens_host, float* scratch,
+                      size_t scratch_floats, hipStream_t s);
 
 // The trunk over g.M rows: every row attends to its beam's cached prefix and causally to the earlier
 // positions of its own block. Row m embeds tokens[m * tok_stride]. Leaves the final residual stream in x and the
@@ -494,7 +495,8 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
                launch_gather_last_rows<T>((const T*)ws.q, q1, (int)C, g.L, qd, s);
                launch_gather_last_rows<float>(x, ws.xs, (int)C, g.L, md.d, s));
       PROFILED(ctx, SPECS_K_ATTENTION, s,
-               attention<T>(q1, kb, vb, pK, pV, (T*)ws.attn, gl, md, Lp, max_ctx, ws.gu, (size_t)R * 2 * md.F, s));
+               attention<T>(q1, kb, vb, pK, pV, (T*)ws.attn, gl, md, Lp, max_ctx, p->lens.data(), ws.gu,
+                            (size_t)R * 2 * md.F, s));
       int pl = 0;
       PROFILED(ctx, SPECS_K_OPROJ, s,
                pl = gemm_residual_split<T>((const T*)ws.attn, (const T*)L.wo, ws.xs, ws.gu, max_split, gl.M, md.d, qd, s));
@@ -514,8 +516,8 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
       break;
     }
     PROFILED(ctx, SPECS_K_ATTENTION, s,
-             attention<T>((const T*)ws.q, kb, vb, pK, pV, (T*)ws.attn, g, md, Lp, max_ctx, ws.gu,
-                          (size_t)R * 2 * md.F, s));
+             attention<T>((const T*)ws.q, kb, vb, pK, pV, (T*)ws.attn, g, md, Lp, max_ctx, p->lens.data(),
+                          ws.gu, (size_t)R * 2 * md.F, s));
     if (commit_pages) launch_kv_commit<T>(kb, vb, pK, pV, g, md, Lp, nullptr, s);
     int parts = 0;
     PROFILED(ctx, SPECS_K_OPROJ, s,
@@ -870,14 +872,15 @@ extern "C" int specs_op_lmhead_logprob(specs_ctx* ctx, int32_t dtype, const void
 
 template <typename T>
 static void attention(const T* q, const T* kb, const T* vbT, const T* pK, const T* pV, T* out, const BatchGeom& g,
-                      const ModelDims& md, int Lp, int max_ctx, float* scratch, size_t scratch_floats, hipStream_t s) {
+                      const ModelDims& md, int Lp, int max_ctx, const int32_t* lens_host, float* scratch,
+                      size_t scratch_floats, hipStream_t s) {
   count_path(SPECS_PATH_ATTN_PLAIN);
   launch_attention_simple<T>(q, kb, vbT, pK, pV, out, g, md, Lp, max_ctx, s);
 }
 template <>
 void attention<bf16_t>(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* pK, const bf16_t* pV,
-                       bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp, int max_ctx, float* scratch,
-                       size_t scratch_floats, hipStream_t s) {
+                       bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp, int max_ctx,
+                       const int32_t* lens_host, float* scratch, size_t scratch_floats, hipStream_t s) {
   bool whole_blocks = g.t0 == 0 && g.Lk == g.L;
   // Launches with at least ~160 workgroups of 256 stacked rows take the two-phase kernel (measured 3-8 % faster
   // at the 7B shapes); smaller ones the one-phase kernel, which cuts long key lists over several workgroups.
@@ -892,7 +895,7 @@ void attention<bf16_t>(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, con
       return;
     }
   } else if (g.L == 1 && scratch &&
-             launch_attention_decode(q, kb, vbT, pK, pV, out, g, md, Lp, max_ctx, scratch, scratch_floats, s)) {
+             launch_attention_decode(q, kb, vbT, pK, pV, out, g, md, Lp, lens_host, scratch, scratch_floats, s)) {
     count_path(SPECS_PATH_ATTN_MFMA);
     return;
   }
@@ -917,11 +920,11 @@ extern "C" int specs_op_attention(specs_ctx* ctx, const specs_model* m, const sp
   if (d.dtype == SPECS_BF16) {
     launch_transpose_v<bf16_t>((const bf16_t*)vb, (bf16_t*)vT, cands, md.Hkv, md.hd, L, Lp, ctx->stream);
     attention<bf16_t>((const bf16_t*)q, (const bf16_t*)kb, (const bf16_t*)vT, pool_ptr<bf16_t>(p, d, layer, 0),
-                      pool_ptr<bf16_t>(p, d, layer, 1), (bf16_t*)out, g, md, Lp, max_ctx, nullptr, 0, ctx->stream);
+                      pool_ptr<bf16_t>(p, d, layer, 1), (bf16_t*)out, g, md, Lp, max_ctx, p->lens.data(), nullptr, 0, ctx->stream);
   } else {
     launch_transpose_v<float>((const float*)vb, (float*)vT, cands, md.Hkv, md.hd, L, Lp, ctx->stream);
     attention<float>((const float*)q, (const float*)kb, (const float*)vT, pool_ptr<float>(p, d, layer, 0),
-                     pool_ptr<float>(p, d, layer, 1), (float*)out, g, md, Lp, max_ctx, nullptr, 0, ctx->stream);
+                     pool_ptr<float>(p, d, layer, 1), (float*)out, g, md, Lp, max_ctx, p->lens.data(), nullptr, 0, ctx->stream);
   }
   HIP_TRY(hipGetLastError());
   ctx->last_model = nullptr;

@@ -251,6 +251,29 @@ def test_generation_equals_scoring_at_other_row_counts(B_, n, hq, hkv, lens, L):
     step.close()
 
 
+@pytest.mark.parametrize("B_,n,hq,hkv,hd,lens,L", [
+    (5, 6, 6, 1, 128, (20, 2900), 9),      # lengths far apart: one run for the shortest beam, many for the longest
+    (3, 20, 14, 2, 64, (500, 4000), 6),    # 140 stacked rows: two row tiles per run
+    (2, 3, 17, 1, 64, (90, 700), 40),      # 17 query heads on one kv head: two groups of columns in the merge
+    (1, 2, 16, 1, 128, (70, 71), 330)])    # a block whose scores exceed the merge's LDS: the one-wavefront merge
+def test_generation_equals_scoring_for_uneven_prefixes_and_wide_groups(B_, n, hq, hkv, hd, lens, L):
+    """Runs of prefix tiles and their merge, at the tolerance of the test above."""
+    from paper_2506_15733_amd import synthetic
+    mk = lambda role, layers, head: ModelDesc(role, layers, 128, hq, hkv, hd, 128, 777, "bf16", head)
+    wl = Workload("gen_runs", mk("target", 2, "lm"), mk("draft", 1, "lm"), mk("prm", 1, "prm"), B=B_, n=n, L=L,
+                  prefix_len=0, lens_range=lens, betas=(1.0,), token_dist="uniform", page_tokens=16, seed=33, u_seed=34)
+    step = synthetic.ScoringStep(wl)
+    step.prefill()
+    u = W.rng.uniform_f64(wl.u_seed, "gen/u6", wl.B * wl.n * wl.L).reshape(wl.B, wl.n, wl.L)
+    cand, logp, tok = gpu_generate(step, "target", u)
+    step.cand = torch.from_numpy(cand).to(step.device)
+    step.score("target")
+    torch.cuda.synchronize()
+    assert np.abs(step.tok["target"].cpu().numpy() - tok).max() < 2e-2
+    assert np.abs(step.out["target"].cpu().numpy() - logp).max() < 2e-2 * np.sqrt(wl.L)
+    step.close()
+
+
 def test_generation_equals_scoring_at_config_4_size():
     """Full benchmark size (1.5B draft of config 4: 16 candidates x 128 positions on a 4096-token prefix, the launch
     configuration `bench.py --generate draft` times): the block log-likelihoods that come out of generation equal
