@@ -5,6 +5,7 @@
 
 #define TS 64   // tile of C per block
 #define TK 16   // K step
+#define SMALL_MAX_WGS 4096   // 8 x 8 (8 x 64) tiles up to which the small kernels are taken
 // 256 threads, each a 4x4 patch of the 64x64 tile.
 
 template <typename T>
@@ -69,8 +70,82 @@ __global__ void __launch_bounds__(256) gemm_simple_kernel(const T* __restrict__ 
     }
 }
 
+// Few rows and columns: a 64 x 64 tile would put the product on a handful of CUs and walk K in dependent 16-deep steps
+// (64 x 64 x 256: one workgroup, 42 us). Here a workgroup owns 8 x 8 outputs, requests all its operand rows (256 columns
+// of them at a time) at once in 16-byte pieces, and its four wavefronts take a quarter of the columns each; their sums
+// are added in order. The kernel is bound by the latency of one round of loads.
+#define SK 256                                             // columns per round
+template <typename T>
+__device__ __forceinline__ float4 load_quad(const T* p);
+template <>
+__device__ __forceinline__ float4 load_quad<float>(const float* p) { return *(const float4*)p; }
+template <>
+__device__ __forceinline__ float4 load_quad<bf16_t>(const bf16_t* p) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  const bf16x4 v = *(const bf16x4*)p;
+  return float4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+}
+// rows r0 .. r0+ROWS of G, columns k0 .. k0+SK, zero outside the matrix, into dst[ROWS][SK + 4]
+template <typename T, int ROWS>
+__device__ __forceinline__ void stage_rows(const T* __restrict__ G, int r0, int rows, int K, int k0,
+                                           float (*dst)[SK + 4]) {
+#pragma unroll
+  for (int e = 0; e < ROWS * (SK / 4) / 256; ++e) {
+    const int q = e * 256 + threadIdx.x, r = q / (SK / 4), c = q % (SK / 4) * 4;
+    float4 v = {0.f, 0.f, 0.f, 0.f};
+    if (r0 + r < rows && k0 + c < K) v = load_quad<T>(G + (size_t)(r0 + r) * K + k0 + c);   // K % 4 == 0
+    *(float4*)&dst[r][c] = v;
+  }
+}
+__device__ __forceinline__ float dot_quad(float4 a, float4 w, float acc) {
+  acc = fmaf(a.x, w.x, acc);
+  acc = fmaf(a.y, w.y, acc);
+  acc = fmaf(a.z, w.z, acc);
+  return fmaf(a.w, w.w, acc);
+}
+template <typename T, int EPI>
+__global__ void __launch_bounds__(256) gemm_small_kernel(const T* __restrict__ A, const T* __restrict__ W,
+                                                         float* __restrict__ C, int M, int N, int K) {
+  __shared__ __attribute__((aligned(16))) float As[8][SK + 4];   // the row stride spreads 8 rows over the banks
+  __shared__ __attribute__((aligned(16))) float Ws[8][SK + 4];
+  __shared__ float red[4][64];
+  const int tid = threadIdx.x, wave = tid >> 6, r = (tid >> 3) & 7, c = tid & 7;
+  const int m0 = blockIdx.y * 8, n0 = blockIdx.x * 8;
+  float acc = 0.f;
+  for (int k0 = 0; k0 < K; k0 += SK) {
+    if (k0) __syncthreads();
+    stage_rows<T, 8>(A, m0, M, K, k0, As);
+    stage_rows<T, 8>(W, n0, N, K, k0, Ws);
+    __syncthreads();
+    const int kq = ((K - k0 < SK ? K - k0 : SK) + 15) / 16 * 4;   // columns per wavefront (what lies beyond K is zero)
+    for (int k = wave * kq; k < (wave + 1) * kq; k += 4)
+      acc = dot_quad(*(const float4*)&As[r][k], *(const float4*)&Ws[c][k], acc);
+  }
+  red[wave][tid & 63] = acc;
+  __syncthreads();
+  const int m = m0 + r, n = n0 + c;
+  if (wave == 0 && m < M && n < N) {
+    const float v = ((red[0][tid] + red[1][tid]) + red[2][tid]) + red[3][tid];
+    const size_t o = (size_t)m * N + n;
+    if (EPI == EPI_RESIDUAL_ADD) C[o] += v;
+    else C[o] = v;
+  }
+}
+
+// 16-byte (8-byte for bf16) loads of operand rows stay aligned
+template <typename T>
+static bool quads_ok(const T* A, const T* W, int K) {
+  return K % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & (4 * sizeof(T) - 1)) == 0;
+}
+
 template <typename T>
 void launch_gemm_simple(const T* A, const T* W, float* C, int M, int N, int K, GemmEpilogue epi, hipStream_t s) {
+  if ((long)((M + 7) / 8) * ((N + 7) / 8) <= SMALL_MAX_WGS && quads_ok(A, W, K)) {
+    dim3 grid((N + 7) / 8, (M + 7) / 8);
+    if (epi == EPI_RESIDUAL_ADD) gemm_small_kernel<T, EPI_RESIDUAL_ADD><<<grid, 256, 0, s>>>(A, W, C, M, N, K);
+    else gemm_small_kernel<T, EPI_STORE_F32><<<grid, 256, 0, s>>>(A, W, C, M, N, K);
+    return;
+  }
   dim3 grid((N + TS - 1) / TS, (M + TS - 1) / TS);
   if (epi == EPI_RESIDUAL_ADD) gemm_simple_kernel<T, EPI_RESIDUAL_ADD><<<grid, 256, 0, s>>>(A, W, C, M, N, K);
   else gemm_simple_kernel<T, EPI_STORE_F32><<<grid, 256, 0, s>>>(A, W, C, M, N, K);
@@ -118,15 +193,75 @@ __global__ void __launch_bounds__(256) lmhead_partials_simple_kernel(const T* __
   }
 }
 
+// The same for few rows: 8 rows x 64 columns per workgroup, a thread two columns of one row.
+template <typename T>
+__global__ void __launch_bounds__(256) lmhead_partials_small_kernel(const T* __restrict__ A, const T* __restrict__ W,
+                                                                    const int32_t* __restrict__ tok,
+                                                                    float* __restrict__ part_max,
+                                                                    float* __restrict__ part_sum, float* __restrict__ zt,
+                                                                    int M, int V, int K, int n_tiles) {
+  constexpr int KC = 64;
+  __shared__ __attribute__((aligned(16))) float As[8][KC + 4];
+  __shared__ __attribute__((aligned(16))) float Ws[TS][KC + 4];
+  const int tid = threadIdx.x, r = tid >> 5, c = tid & 31;
+  const int m0 = blockIdx.y * 8, n0 = blockIdx.x * TS, m = m0 + r;
+  float z[2] = {0.f, 0.f};
+  for (int k0 = 0; k0 < K; k0 += KC) {
+    if (k0) __syncthreads();
+    for (int q = tid; q < (8 + TS) * (KC / 4); q += 256) {
+      const int row = q / (KC / 4), col = q % (KC / 4) * 4;
+      float4 v = {0.f, 0.f, 0.f, 0.f};
+      if (row < 8) {
+        if (m0 + row < M && k0 + col < K) v = load_quad<T>(A + (size_t)(m0 + row) * K + k0 + col);
+        *(float4*)&As[row][col] = v;
+      } else {
+        if (n0 + row - 8 < V && k0 + col < K) v = load_quad<T>(W + (size_t)(n0 + row - 8) * K + k0 + col);
+        *(float4*)&Ws[row - 8][col] = v;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < KC; k += 4) {
+      const float4 a = *(const float4*)&As[r][k];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) z[j] = dot_quad(a, *(const float4*)&Ws[c + 32 * j][k], z[j]);
+    }
+  }
+  const int target = m < M ? tok[m] : -1;
+  float mx = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int n = n0 + c + 32 * j;
+    if (n < V) mx = fmaxf(mx, z[j]);
+    if (n == target) zt[m] = z[j];
+  }
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));   // the 32 lanes of a row
+  float sm = 0.f;
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+    if (n0 + c + 32 * j < V) sm += expf(z[j] - mx);
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) sm += __shfl_xor(sm, o, 64);
+  if (c == 0 && m < M) {
+    part_max[(size_t)m * n_tiles + blockIdx.x] = mx;
+    part_sum[(size_t)m * n_tiles + blockIdx.x] = sm;
+  }
+}
+
 int lmhead_simple_tiles(int V) { return (V + TS - 1) / TS; }
 
 template <typename T>
 void launch_lmhead_partials_simple(const T* A, const T* W, const int32_t* tok, float* part_max, float* part_sum,
                                    float* zt, int M, int V, int K, int* n_tiles_out, hipStream_t s) {
   int nt = lmhead_simple_tiles(V);
+  *n_tiles_out = nt;
+  if ((long)nt * ((M + 7) / 8) <= SMALL_MAX_WGS && quads_ok(A, W, K)) {
+    lmhead_partials_small_kernel<T><<<dim3(nt, (M + 7) / 8), 256, 0, s>>>(A, W, tok, part_max, part_sum, zt, M, V, K, nt);
+    return;
+  }
   dim3 grid(nt, (M + TS - 1) / TS);
   lmhead_partials_simple_kernel<T><<<grid, 256, 0, s>>>(A, W, tok, part_max, part_sum, zt, M, V, K, nt);
-  *n_tiles_out = nt;
 }
 template void launch_lmhead_partials_simple<float>(const float*, const float*, const int32_t*, float*, float*, float*,
                                                    int, int, int, int*, hipStream_t);

@@ -86,6 +86,23 @@ def test_linear_f32(ctx):
     close(out.cpu().numpy().astype(np.float64), oracle.linear(a, w), 2e-6)
 
 
+# 8 x 8 tiles: less than a tile, remainders in rows and columns, several rounds of 256 columns with a remainder, one
+# tile past the last product they take; rows of 72 floats that start at odd multiples of 4 bytes (64 x 64 tiles)
+@pytest.mark.parametrize("M,N,K,offset", [(1, 1, 4, 0), (7, 9, 60, 0), (64, 64, 256, 0), (13, 21, 1036, 0), (513, 517, 64, 0),
+                                          (37, 50, 72, 1), (37, 50, 71, 0)])
+def test_linear_f32_small(ctx, M, N, K, offset):
+    from paper_2506_15733_amd import binding as B
+    a, ta = draw(f"fa{M}.{K}", (M, K), 1.0, "f32")
+    w, _ = draw(f"fw{N}.{K}", (N, K), 0.05, "f32")
+    tw = torch.zeros(N * K + 4, dtype=torch.float32, device=DEV)[offset:offset + N * K].view(N, K)
+    tw.copy_(torch.from_numpy(w))
+    out = torch.zeros((M, N), dtype=torch.float32, device=DEV)
+    for times in (1, 2):
+        B.specs_op_linear(ctx, ta, tw, out, accumulate=times > 1)
+        torch.cuda.synchronize()
+        close(out.cpu().numpy().astype(np.float64), times * oracle.linear(a, w), 2e-6)   # the bound of test_linear_f32
+
+
 @pytest.mark.parametrize("M,F,K", [(45, 96, 64), (300, 160, 128), (300, 1120, 256), (256, 2816, 1024), (2048, 18944, 3584),
                                    (16, 18944, 3584), (7, 96, 128), (32, 8960, 1536), (19, 160, 384)])
 def test_gate_up_bf16(ctx, M, F, K):
