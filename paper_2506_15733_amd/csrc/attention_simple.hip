@@ -9,17 +9,6 @@
 // division and one page lookup each: 20 us for 16 rows of 4 heads on 100 to 230 keys).
 #include "common.h"
 
-template <typename T>
-__device__ __forceinline__ float4 load_quad(const T* p);
-template <>
-__device__ __forceinline__ float4 load_quad<float>(const float* p) { return *(const float4*)p; }
-template <>
-__device__ __forceinline__ float4 load_quad<bf16_t>(const bf16_t* p) {
-  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-  const bf16x4 v = *(const bf16x4*)p;
-  return float4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-}
-
 // QUADS: hd % 4 == 0 and key rows aligned for load_quad. pt_shift: log2(page_tokens), negative if it is no power of two.
 template <typename T, bool QUADS>
 __global__ void __launch_bounds__(64) attention_simple_kernel(const T* __restrict__ q, const T* __restrict__ kb,

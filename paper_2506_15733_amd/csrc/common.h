@@ -27,6 +27,17 @@ __device__ __forceinline__ float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
+// four consecutive values, aligned to four times their size
+template <typename T>
+__device__ __forceinline__ float4 load_quad(const T* p);
+template <>
+__device__ __forceinline__ float4 load_quad<float>(const float* p) { return *(const float4*)p; }
+template <>
+__device__ __forceinline__ float4 load_quad<bf16_t>(const bf16_t* p) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  const bf16x4 v = *(const bf16x4*)p;
+  return float4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+}
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
@@ -54,9 +65,10 @@ struct ModelDims {
 };
 
 // ---- launchers implemented across the .hip files (all enqueue on `s`) ----
+// x: row m embeds tok[m * tok_stride]; cs: row m's rotary angles, as launch_rope_table leaves them
 template <typename T>
-void launch_embed(const int32_t* tok, int tok_stride, const T* E, float* x, int M, int d, int V, int* status,
-                  hipStream_t s);   // row m embeds tok[m * tok_stride]
+void launch_embed_rope(const int32_t* tok, int tok_stride, const T* E, float* x, int d, int V, int* status, float* cs,
+                       const BatchGeom& g, int hd, float base, hipStream_t s);
 template <typename T>
 void launch_rmsnorm(const float* x, const float* gain, T* out, int M, int d, float eps, hipStream_t s);
 // lm_head operand: row (b,i,t) = norm(t == 0 ? h_last[b0+b] : x[row-1])
@@ -82,8 +94,9 @@ void launch_copy_rows(const float* x, float* h_last, const BatchGeom& g, int d, 
 // generation: xs[b*n + i] = h_last[b0 + b] (every candidate starts from the prefix's last hidden state)
 void launch_broadcast_hlast(const float* h_last, float* xs, const BatchGeom& g, int d, hipStream_t s);
 // dst[c][0..width) = src[(c*L + L-1)][0..width): the last row of every block
+// and the same of x[C*L][d] into xs
 template <typename T>
-void launch_gather_last_rows(const T* src, T* dst, int C, int L, int width, hipStream_t s);
+void launch_gather_last_rows(const T* src, T* dst, int width, const float* x, float* xs, int d, int C, int L, hipStream_t s);
 // x[(c*L + L-1)] = xs[c] for every candidate c (the state at the last block token, where scoring leaves it)
 void launch_scatter_last_rows(const float* xs, float* x, int C, int L, int d, hipStream_t s);
 // block_out[c] = sum_t tok_logp[c][t] in index order, accumulated in double
@@ -99,6 +112,11 @@ enum GemmEpilogue { EPI_STORE_F32 = 0, EPI_RESIDUAL_ADD = 1 };
 // C[M,N] (float) = A[M,K] * W[N,K]^T, or C += ... (residual add)
 template <typename T>
 void launch_gemm_simple(const T* A, const T* W, float* C, int M, int N, int K, GemmEpilogue epi, hipStream_t s);
+
+bool launch_small_qkv_rope(const float* x, const float* gain, const float* W, const float* cs, float* q, float* kblk,
+                           float* vT, const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s);
+bool launch_small_gate_up(const float* x, const float* gain, const float* Wgu, float* act, int M, int F, int K, float eps,
+                          hipStream_t s);
 
 template <typename T>
 void launch_attention_simple(const T* q, const T* kb, const T* vbT, const T* poolK, const T* poolV, T* out,

@@ -2,10 +2,25 @@
 // SiLU*mul, KV-page commit, PRM scalar head, log-softmax merge + block sum.
 #include "common.h"
 
-// ---------------------------------------------------------------- embedding
-template <typename T>
-__global__ void embed_kernel(const int32_t* __restrict__ tok, int tok_stride, const T* __restrict__ E,
-                             float* __restrict__ x, int d, int V, int* status) {
+// ---------------------------------------------------------------- embedding and rotary angles
+// cos/sin of pos * base^(-2i/hd), pos = context length + t, evaluated in double so that long
+// contexts lose nothing; one table per call, shared by all layers and heads.
+__device__ __forceinline__ void rope_row(float* __restrict__ cs, int m, int i, int pos, int half, int hd, double base) {
+  double ang = (double)pos * pow(base, -2.0 * (double)i / (double)hd);
+  double sn, cn;
+  sincos(ang, &sn, &cn);
+  cs[(size_t)m * hd + i] = (float)cn;
+  cs[(size_t)m * hd + half + i] = (float)sn;
+}
+
+// One block per row: its embedding and its row of the table, which nothing but the row's position enters, so that a
+// pass (and every position of a generated block) starts with one launch instead of two.
+template <typename T, bool QUADS>
+__global__ void __launch_bounds__(256) embed_rope_kernel(const int32_t* __restrict__ tok, int tok_stride,
+                                                         const T* __restrict__ E, float* __restrict__ x, int d, int V,
+                                                         int* status, float* __restrict__ cs, int nL, int L, int hd,
+                                                         double base, const int32_t* __restrict__ lens, int b0,
+                                                         int len_override, int t0) {
   int m = blockIdx.x;
   int id = tok[(size_t)m * tok_stride];
   if (id < 0 || id >= V) {
@@ -14,15 +29,29 @@ __global__ void embed_kernel(const int32_t* __restrict__ tok, int tok_stride, co
   }
   const T* row = E + (size_t)id * d;
   float* xo = x + (size_t)m * d;
-  for (int c = threadIdx.x; c < d; c += blockDim.x) xo[c] = to_f32<T>(row[c]);
+  if (QUADS)
+    for (int c = 4 * threadIdx.x; c < d; c += 4 * 256) *(float4*)(xo + c) = load_quad<T>(row + c);
+  else
+    for (int c = threadIdx.x; c < d; c += 256) xo[c] = to_f32<T>(row[c]);
+  const int half = hd / 2, b = m / nL, t = m % L;
+  const int ctx = len_override >= 0 ? len_override : lens[b0 + b];
+  for (int i = threadIdx.x; i < half; i += 256) rope_row(cs, m, i, ctx + t0 + t, half, hd, base);
 }
 template <typename T>
-void launch_embed(const int32_t* tok, int tok_stride, const T* E, float* x, int M, int d, int V, int* status,
-                  hipStream_t s) {
-  embed_kernel<T><<<M, 256, 0, s>>>(tok, tok_stride, E, x, d, V, status);
+void launch_embed_rope(const int32_t* tok, int tok_stride, const T* E, float* x, int d, int V, int* status, float* cs,
+                       const BatchGeom& g, int hd, float base, hipStream_t s) {
+  const bool quads = d % 4 == 0 && ((uintptr_t)E & (4 * sizeof(T) - 1)) == 0 && ((uintptr_t)x & 15) == 0;
+  if (quads)
+    embed_rope_kernel<T, true><<<g.M, 256, 0, s>>>(tok, tok_stride, E, x, d, V, status, cs, g.n * g.L, g.L, hd,
+                                                   (double)base, g.lens, g.b0, g.len_override, g.t0);
+  else
+    embed_rope_kernel<T, false><<<g.M, 256, 0, s>>>(tok, tok_stride, E, x, d, V, status, cs, g.n * g.L, g.L, hd,
+                                                    (double)base, g.lens, g.b0, g.len_override, g.t0);
 }
-template void launch_embed<float>(const int32_t*, int, const float*, float*, int, int, int, int*, hipStream_t);
-template void launch_embed<bf16_t>(const int32_t*, int, const bf16_t*, float*, int, int, int, int*, hipStream_t);
+template void launch_embed_rope<float>(const int32_t*, int, const float*, float*, int, int, int*, float*, const BatchGeom&,
+                                       int, float, hipStream_t);
+template void launch_embed_rope<bf16_t>(const int32_t*, int, const bf16_t*, float*, int, int, int*, float*,
+                                        const BatchGeom&, int, float, hipStream_t);
 
 // ---------------------------------------------------------------- RMSNorm
 // One 256-thread block per row. y = x * rsqrt(mean(x^2) + eps) * gain, float math, output in T.
@@ -214,8 +243,6 @@ template void launch_rmsnorm_shifted<bf16_t>(const float*, const float*, const f
                                              float, hipStream_t);
 
 // ---------------------------------------------------------------- rotary embedding
-// cos/sin of pos * base^(-2i/hd), pos = context length + t, evaluated in double so that long
-// contexts lose nothing; one table per call, shared by all layers and heads.
 __global__ void rope_table_kernel(float* __restrict__ cs, int M, int nL, int L, int half, int hd, double base,
                                   const int32_t* __restrict__ lens, int b0, int len_override, int t0) {
   int idx = blockIdx.x * blockDim.x + threadIdx.x;
@@ -223,11 +250,7 @@ __global__ void rope_table_kernel(float* __restrict__ cs, int M, int nL, int L, 
   int m = idx / half, i = idx % half;
   int b = m / nL, t = m % L;
   int ctx = len_override >= 0 ? len_override : lens[b0 + b];
-  double ang = (double)(ctx + t0 + t) * pow(base, -2.0 * (double)i / (double)hd);
-  double sn, cn;
-  sincos(ang, &sn, &cn);
-  cs[(size_t)m * hd + i] = (float)cn;
-  cs[(size_t)m * hd + half + i] = (float)sn;
+  rope_row(cs, m, i, ctx + t0 + t, half, hd, base);
 }
 void launch_rope_table(float* cs, const BatchGeom& g, int hd, float base, hipStream_t s) {
   int half = hd / 2;
@@ -392,16 +415,20 @@ void launch_broadcast_hlast(const float* h_last, float* xs, const BatchGeom& g, 
 }
 
 template <typename T>
-__global__ void gather_last_rows_kernel(const T* __restrict__ src, T* __restrict__ dst, int L, int width) {
-  size_t c = blockIdx.x;
-  for (int j = threadIdx.x; j < width; j += blockDim.x) dst[c * width + j] = src[(c * L + (L - 1)) * width + j];
+__global__ void gather_last_rows_kernel(const T* __restrict__ src, T* __restrict__ dst, int width,
+                                        const float* __restrict__ x, float* __restrict__ xs, int d, int L) {
+  size_t c = blockIdx.x, last = c * L + (L - 1);
+  for (int j = threadIdx.x; j < width; j += blockDim.x) dst[c * width + j] = src[last * width + j];
+  for (int j = threadIdx.x; j < d; j += blockDim.x) xs[c * d + j] = x[last * d + j];
 }
 template <typename T>
-void launch_gather_last_rows(const T* src, T* dst, int C, int L, int width, hipStream_t s) {
-  gather_last_rows_kernel<T><<<C, 256, 0, s>>>(src, dst, L, width);
+void launch_gather_last_rows(const T* src, T* dst, int width, const float* x, float* xs, int d, int C, int L,
+                             hipStream_t s) {
+  gather_last_rows_kernel<T><<<C, 256, 0, s>>>(src, dst, width, x, xs, d, L);
 }
-template void launch_gather_last_rows<float>(const float*, float*, int, int, int, hipStream_t);
-template void launch_gather_last_rows<bf16_t>(const bf16_t*, bf16_t*, int, int, int, hipStream_t);
+template void launch_gather_last_rows<float>(const float*, float*, int, const float*, float*, int, int, int, hipStream_t);
+template void launch_gather_last_rows<bf16_t>(const bf16_t*, bf16_t*, int, const float*, float*, int, int, int,
+                                              hipStream_t);
 
 __global__ void scatter_last_rows_kernel(const float* __restrict__ xs, float* __restrict__ x, int L, int d) {
   size_t c = blockIdx.x;
@@ -443,23 +470,40 @@ template void launch_prm_head<bf16_t>(const float*, const float*, const bf16_t*,
                                       hipStream_t);
 
 // ---------------------------------------------------------------- log-softmax merge + block sum
-// Kernel 1, one wavefront per row: merge the per-tile (max, sum exp) partials,
-// tok_logp = z[y] - (max + log sum). Kernel 2, one thread per candidate: add its L token terms in
-// index order (fixed order => run-to-run identical), in double because the sum reaches ~1e3.
-__global__ void lmhead_merge_kernel(const float* __restrict__ part_max, const float* __restrict__ part_sum,
-                                    const float* __restrict__ zt, int n_tiles, float* __restrict__ tok_logp, int M) {
-  int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  size_t m = (size_t)blockIdx.x * 4 + wave;
-  if (m >= (size_t)M) return;
-  const float* pm = part_max + m * n_tiles;
-  const float* ps = part_sum + m * n_tiles;
-  float mx = -INFINITY;
-  for (int j = lane; j < n_tiles; j += 64) mx = fmaxf(mx, pm[j]);
-  mx = wave_max(mx);
-  float sm = 0.f;
-  for (int j = lane; j < n_tiles; j += 64) sm += ps[j] * expf(pm[j] - mx);
-  sm = wave_sum(sm);
-  if (lane == 0) tok_logp[m] = (float)((double)zt[m] - ((double)mx + log((double)sm)));
+// One block per candidate. A wavefront merges the per-tile (max, sum exp) partials of a row,
+// tok_logp = z[y] - (max + log sum); one thread then adds the L token terms in index order (fixed
+// order => run-to-run identical), in double because the sum reaches ~1e3.
+// (As two launches, the second with one thread per candidate that read its terms one by one from memory: 15 + 12 us for
+// 16 candidates x 64 rows of 152k ids, 38 + 39 us at x 128 beside two other models.)
+__global__ void __launch_bounds__(1024) lmhead_merge_kernel(const float* __restrict__ part_max,
+                                                            const float* __restrict__ part_sum,
+                                                            const float* __restrict__ zt, int n_tiles,
+                                                            float* __restrict__ tok_logp, float* __restrict__ block_out,
+                                                            int L) {
+  constexpr int TERMS = 1024;                     // token terms kept at a time
+  __shared__ float terms[TERMS];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  double acc = 0.0;
+  for (int l0 = 0; l0 < L; l0 += TERMS) {
+    const int l1 = L - l0 < TERMS ? L : l0 + TERMS;
+    for (int l = l0 + wave; l < l1; l += waves) {
+      const size_t m = (size_t)blockIdx.x * L + l;
+      const float* pm = part_max + m * n_tiles;
+      const float* ps = part_sum + m * n_tiles;
+      float mx = -INFINITY;
+      for (int j = lane; j < n_tiles; j += 64) mx = fmaxf(mx, pm[j]);
+      mx = wave_max(mx);
+      float sm = 0.f;
+      for (int j = lane; j < n_tiles; j += 64) sm += ps[j] * expf(pm[j] - mx);
+      sm = wave_sum(sm);
+      if (lane == 0) terms[l - l0] = tok_logp[m] = (float)((double)zt[m] - ((double)mx + log((double)sm)));
+    }
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int l = l0; l < l1; ++l) acc += (double)terms[l - l0];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) block_out[blockIdx.x] = (float)acc;
 }
 
 __global__ void block_sum_kernel(const float* __restrict__ tok_logp, float* __restrict__ block_out, int L, int C) {
@@ -478,7 +522,5 @@ void launch_block_sum(const float* tok_logp, float* block_out, int L, int C, hip
 void launch_lmhead_merge(const float* part_max, const float* part_sum, const float* zt, int n_tiles, float* tok_logp,
                          float* tok_scratch, float* block_out, const BatchGeom& g, hipStream_t s) {
   float* tl = tok_logp ? tok_logp : tok_scratch;
-  lmhead_merge_kernel<<<(g.M + 3) / 4, 256, 0, s>>>(part_max, part_sum, zt, n_tiles, tl, g.M);
-  int C = g.B * g.n;
-  block_sum_kernel<<<(C + 63) / 64, 64, 0, s>>>(tl, block_out, g.L, C);
+  lmhead_merge_kernel<<<g.B * g.n, 64 * (g.L < 16 ? g.L : 16), 0, s>>>(part_max, part_sum, zt, n_tiles, tl, block_out, g.L);
 }

@@ -75,16 +75,6 @@ __global__ void __launch_bounds__(256) gemm_simple_kernel(const T* __restrict__ 
 // of them at a time) at once in 16-byte pieces, and its four wavefronts take a quarter of the columns each; their sums
 // are added in order. The kernel is bound by the latency of one round of loads.
 #define SK 256                                             // columns per round
-template <typename T>
-__device__ __forceinline__ float4 load_quad(const T* p);
-template <>
-__device__ __forceinline__ float4 load_quad<float>(const float* p) { return *(const float4*)p; }
-template <>
-__device__ __forceinline__ float4 load_quad<bf16_t>(const bf16_t* p) {
-  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-  const bf16x4 v = *(const bf16x4*)p;
-  return float4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-}
 // rows r0 .. r0+ROWS of G, columns k0 .. k0+SK, zero outside the matrix, into dst[ROWS][SK + 4]
 template <typename T, int ROWS>
 __device__ __forceinline__ void stage_rows(const T* __restrict__ G, int r0, int rows, int K, int k0,
@@ -150,6 +140,116 @@ void launch_gemm_simple(const T* A, const T* W, float* C, int M, int N, int K, G
   if (epi == EPI_RESIDUAL_ADD) gemm_simple_kernel<T, EPI_RESIDUAL_ADD><<<grid, 256, 0, s>>>(A, W, C, M, N, K);
   else gemm_simple_kernel<T, EPI_STORE_F32><<<grid, 256, 0, s>>>(A, W, C, M, N, K);
 }
+// A whole projection of a float layer in one launch, for models of at most SK columns: the rows of the residual stream
+// are normalised where they are staged (every workgroup holds them whole), and the epilogue applies the rotary embedding
+// and stores q, k and the transposed values, or multiplies SiLU(gate) with up. The products are so small that a pass is
+// bound by its number of launches: norm, product and elementwise kernel were three of them, 3.0 + 3.6 + 2.8 us of device
+// time and 12 us of launching for 64 rows of 64 columns.
+enum { SMALL_QKV = 0, SMALL_GATE_UP = 1 };
+struct SmallArgs {
+  const float* x;       // [M][K] residual stream
+  const float* gain;    // [K]
+  const float* W;
+  float eps;
+  int M, K;
+  float* act;           // SMALL_GATE_UP: [M][F]
+  int F;
+  const float* cs;      // SMALL_QKV: [M][hd] cos | sin; q [M][Hq][hd], kblk [cand*Lk + t][Hkv][hd], vT [cand][Hkv][hd][Lp]
+  float* q;
+  float* kblk;
+  float* vT;
+  int Hq, Hkv, hd, Lrows, t0, Lk, Lp;
+};
+
+template <int EPI>
+__global__ void __launch_bounds__(256) small_projection_kernel(SmallArgs a) {
+  __shared__ __attribute__((aligned(16))) float As[8][SK + 4];
+  __shared__ __attribute__((aligned(16))) float Ws[8][SK + 4];
+  __shared__ float red[4][64];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = (tid >> 3) & 7, c = tid & 7;
+  const int m0 = blockIdx.y * 8, K = a.K, col = lane * 4;
+  // columns 0..3 of the tile and columns 4..7 are partners: the two halves of a rotary head, or gate and up
+  const int half = a.hd >> 1;
+  const int head = EPI == SMALL_QKV ? blockIdx.x / (half / 4) : 0;
+  const int i0 = EPI == SMALL_QKV ? (blockIdx.x - head * (half / 4)) * 4 : blockIdx.x * 4;   // pair, or unit
+  const int row0 = EPI == SMALL_QKV ? head * a.hd + i0 : 64 * (i0 >> 5) + (i0 & 31);
+  const int partner = EPI == SMALL_QKV ? half : SPECS_GATE_UP_GROUP;
+
+  // wavefront w stages rows w and w + 4 of both operands
+  float4 xv[2], wv[2], gn = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    xv[e] = wv[e] = float4{0.f, 0.f, 0.f, 0.f};
+    const int rr = wave + 4 * e;
+    if (col < K) {
+      if (m0 + rr < a.M) xv[e] = *(const float4*)(a.x + (size_t)(m0 + rr) * K + col);
+      wv[e] = *(const float4*)(a.W + (size_t)(row0 + (rr & 3) + (rr >> 2) * partner) * K + col);
+    }
+  }
+  if (col < K) gn = *(const float4*)(a.gain + col);
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const float4 v = xv[e];
+    const float inv = 1.0f / sqrtf(wave_sum(v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w) / (float)K + a.eps);
+    *(float4*)&As[wave + 4 * e][col] = float4{v.x * inv * gn.x, v.y * inv * gn.y, v.z * inv * gn.z, v.w * inv * gn.w};
+    *(float4*)&Ws[wave + 4 * e][col] = wv[e];
+  }
+  __syncthreads();
+  float acc = 0.f;
+  const int kq = (K + 15) / 16 * 4;
+  for (int k = wave * kq; k < (wave + 1) * kq; k += 4)
+    acc = dot_quad(*(const float4*)&As[r][k], *(const float4*)&Ws[c][k], acc);
+  red[wave][lane] = acc;
+  __syncthreads();
+  if (wave != 0) return;
+  const int m = m0 + r, i = i0 + (c & 3);
+  const float v = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+  const float other = __shfl_xor(v, 4, 64);
+  if (m >= a.M) return;
+  if (EPI == SMALL_GATE_UP) {
+    if (c < 4) a.act[(size_t)m * a.F + i] = v / (1.0f + expf(-v)) * other;
+    return;
+  }
+  const int cand = m / a.Lrows, t = a.t0 + (m - cand * a.Lrows), d = i + (c < 4 ? 0 : half);
+  if (head < a.Hq + a.Hkv) {
+    const float cn = a.cs[(size_t)m * a.hd + i], sn = a.cs[(size_t)m * a.hd + half + i];
+    const float y = c < 4 ? v * cn - other * sn : v * cn + other * sn;
+    if (head < a.Hq) a.q[((size_t)m * a.Hq + head) * a.hd + d] = y;
+    else a.kblk[(((size_t)cand * a.Lk + t) * a.Hkv + (head - a.Hq)) * a.hd + d] = y;
+  } else {
+    float* dst = a.vT + (((size_t)cand * a.Hkv + (head - a.Hq - a.Hkv)) * a.hd + d) * a.Lp;
+    dst[t] = v;
+    if (t == a.Lk - 1)
+      for (int tt = a.Lk; tt < a.Lp; ++tt) dst[tt] = 0.f;
+  }
+}
+
+static bool small_projection_ok(const float* x, const float* gain, const float* W, int M, int N, int K) {
+  return K <= SK && K % 4 == 0 && (((uintptr_t)x | (uintptr_t)gain | (uintptr_t)W) & 15) == 0 &&
+         (long)((M + 7) / 8) * (N / 8) <= SMALL_MAX_WGS;
+}
+// RMSNorm(x) * gain, QKV projection, rotary embedding and value transposition. False if the shape is not taken.
+bool launch_small_qkv_rope(const float* x, const float* gain, const float* W, const float* cs, float* q, float* kblk,
+                           float* vT, const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s) {
+  const int N = (md.Hq + 2 * md.Hkv) * md.hd;
+  if (md.hd % 8 != 0 || !small_projection_ok(x, gain, W, g.M, N, md.d)) return false;
+  SmallArgs a = {};
+  a.x = x; a.gain = gain; a.W = W; a.eps = md.eps; a.M = g.M; a.K = md.d;
+  a.cs = cs; a.q = q; a.kblk = kblk; a.vT = vT;
+  a.Hq = md.Hq; a.Hkv = md.Hkv; a.hd = md.hd; a.Lrows = g.L; a.t0 = g.t0; a.Lk = g.Lk; a.Lp = Lp;
+  small_projection_kernel<SMALL_QKV><<<dim3(N / 8, (g.M + 7) / 8), 256, 0, s>>>(a);
+  return true;
+}
+// act = silu(gate) * up of RMSNorm(x) * gain. False if the shape is not taken.
+bool launch_small_gate_up(const float* x, const float* gain, const float* Wgu, float* act, int M, int F, int K, float eps,
+                          hipStream_t s) {
+  if (!small_projection_ok(x, gain, Wgu, M, 2 * F, K)) return false;
+  SmallArgs a = {};
+  a.x = x; a.gain = gain; a.W = Wgu; a.eps = eps; a.M = M; a.K = K; a.act = act; a.F = F;
+  small_projection_kernel<SMALL_GATE_UP><<<dim3(F / 4, (M + 7) / 8), 256, 0, s>>>(a);
+  return true;
+}
+
 template void launch_gemm_simple<float>(const float*, const float*, float*, int, int, int, GemmEpilogue, hipStream_t);
 template void launch_gemm_simple<bf16_t>(const bf16_t*, const bf16_t*, float*, int, int, int, GemmEpilogue,
                                          hipStream_t);

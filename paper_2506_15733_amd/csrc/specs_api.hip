@@ -399,6 +399,31 @@ bool qkv_rope_fused<bf16_t>(const bf16_t* A, const bf16_t* W, const float* cs, b
   return true;
 }
 
+// Normalisation, projection and what follows it in one launch, where there is a kernel for the shape.
+template <typename T>
+static bool norm_qkv_rope(const float*, const float*, const T*, const float*, T*, T*, T*, const BatchGeom&,
+                          const ModelDims&, int, hipStream_t) {
+  return false;
+}
+template <>
+bool norm_qkv_rope<float>(const float* x, const float* gain, const float* W, const float* cs, float* q, float* kb,
+                          float* vT, const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s) {
+  if (!launch_small_qkv_rope(x, gain, W, cs, q, kb, vT, g, md, Lp, s)) return false;
+  count_path(SPECS_PATH_GEMM_PLAIN);
+  return true;
+}
+template <typename T>
+static bool norm_gate_up(const float*, const float*, const T*, T*, int, int, int, float, hipStream_t) {
+  return false;
+}
+template <>
+bool norm_gate_up<float>(const float* x, const float* gain, const float* Wgu, float* act, int M, int F, int K, float eps,
+                         hipStream_t s) {
+  if (!launch_small_gate_up(x, gain, Wgu, act, M, F, K, eps, s)) return false;
+  count_path(SPECS_PATH_GEMM_PLAIN);
+  return true;
+}
+
 // act[M,F] = silu(A Wg^T) * (A Wu^T) with Wgu interleaved by 32 rows
 template <typename T>
 static void gate_up(const T* A, const T* Wgu, float* gu, T* act, int M, int F, int K, hipStream_t s) {
@@ -462,8 +487,8 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
   const int Lp = round16(g.Lk);
   int qd = md.Hq * md.hd, kvd = md.Hkv * md.hd;
   PROFILED(ctx, SPECS_K_OTHER, s,
-           launch_embed<T>(tokens, tok_stride, (const T*)m->w.embed, x, g.M, md.d, md.V, ws.status, s);
-           launch_rope_table(ws.cs, g, md.hd, md.rope_base, s));
+           launch_embed_rope<T>(tokens, tok_stride, (const T*)m->w.embed, x, md.d, md.V, ws.status, ws.cs, g, md.hd,
+                                md.rope_base, s));
   // ws.gu ([R, 2F] floats) is free while the residual projections run (the fused gate/up kernel never writes
   // it, the unfused path has consumed it by then), so it holds their K-split partial products.
   const int max_split = (int)((2 * (size_t)md.F) / (size_t)md.d);
@@ -474,10 +499,15 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
     T* vb = (T*)ws.vblk + (size_t)l * (R + 16 * C) * kvd;
     T* pK = pool_ptr<T>(p, d, l, 0);
     T* pV = pool_ptr<T>(p, d, l, 1);
-    if (!normed) PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(x, L.g_attn, (T*)ws.a, g.M, md.d, md.eps, s));
-    // whole-block bf16 launches: rotary embedding, conversion and value transposition inside the projection's epilogue
+    // small float models: normalisation and rotary embedding inside the projection
     bool fused_rope = false;
-    if (g.M > 32)
+    if (!normed)
+      PROFILED(ctx, SPECS_K_QKV, s,
+               fused_rope = norm_qkv_rope<T>(x, L.g_attn, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, s));
+    if (!normed && !fused_rope)
+      PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(x, L.g_attn, (T*)ws.a, g.M, md.d, md.eps, s));
+    // whole-block bf16 launches: rotary embedding, conversion and value transposition inside the projection's epilogue
+    if (!fused_rope && g.M > 32)
       PROFILED(ctx, SPECS_K_QKV, s,
                fused_rope = qkv_rope_fused<T>((const T*)ws.a, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, s));
     if (!fused_rope) {
@@ -492,8 +522,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
       gl.L = 1; gl.M = (int)C; gl.t0 = g.L - 1; gl.Lk = g.L;
       T* q1 = (T*)ws.a;                                  // the projection has consumed ws.a
       PROFILED(ctx, SPECS_K_OTHER, s,
-               launch_gather_last_rows<T>((const T*)ws.q, q1, (int)C, g.L, qd, s);
-               launch_gather_last_rows<float>(x, ws.xs, (int)C, g.L, md.d, s));
+               launch_gather_last_rows<T>((const T*)ws.q, q1, qd, x, ws.xs, md.d, (int)C, g.L, s));
       PROFILED(ctx, SPECS_K_ATTENTION, s,
                attention<T>(q1, kb, vb, pK, pV, (T*)ws.attn, gl, md, Lp, max_ctx, p->lens.data(), ws.gu,
                             (size_t)R * 2 * md.F, s));
@@ -503,10 +532,15 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
       if (pl)
         PROFILED(ctx, SPECS_K_OTHER, s,
                  launch_add_partials_rmsnorm<T>(ws.xs, ws.gu, pl, 0, L.g_ffn, (T*)ws.a, gl.M, md.d, md.eps, s));
-      else
+      bool fused_ffn = false;
+      if (!pl)
+        PROFILED(ctx, SPECS_K_GATE_UP, s,
+                 fused_ffn = norm_gate_up<T>(ws.xs, L.g_ffn, (const T*)L.wgu, (T*)ws.act, gl.M, md.F, md.d, md.eps, s));
+      if (!pl && !fused_ffn)
         PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(ws.xs, L.g_ffn, (T*)ws.a, gl.M, md.d, md.eps, s));
-      PROFILED(ctx, SPECS_K_GATE_UP, s,
-               gate_up<T>((const T*)ws.a, (const T*)L.wgu, ws.gu, (T*)ws.act, gl.M, md.F, md.d, s));
+      if (!fused_ffn)
+        PROFILED(ctx, SPECS_K_GATE_UP, s,
+                 gate_up<T>((const T*)ws.a, (const T*)L.wgu, ws.gu, (T*)ws.act, gl.M, md.F, md.d, s));
       PROFILED(ctx, SPECS_K_DOWN, s,
                pl = gemm_residual_split<T>((const T*)ws.act, (const T*)L.wd, ws.xs, ws.gu, max_split, gl.M, md.d, md.F, s));
       if (pl)
@@ -525,10 +559,15 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
     if (parts)
       PROFILED(ctx, SPECS_K_OTHER, s,
                launch_add_partials_rmsnorm<T>(x, ws.gu, parts, 0, L.g_ffn, (T*)ws.a, g.M, md.d, md.eps, s));
-    else
+    bool fused_ffn = false;
+    if (!parts)
+      PROFILED(ctx, SPECS_K_GATE_UP, s,
+               fused_ffn = norm_gate_up<T>(x, L.g_ffn, (const T*)L.wgu, (T*)ws.act, g.M, md.F, md.d, md.eps, s));
+    if (!parts && !fused_ffn)
       PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(x, L.g_ffn, (T*)ws.a, g.M, md.d, md.eps, s));
-    PROFILED(ctx, SPECS_K_GATE_UP, s,
-             gate_up<T>((const T*)ws.a, (const T*)L.wgu, ws.gu, (T*)ws.act, g.M, md.F, md.d, s));
+    if (!fused_ffn)
+      PROFILED(ctx, SPECS_K_GATE_UP, s,
+               gate_up<T>((const T*)ws.a, (const T*)L.wgu, ws.gu, (T*)ws.act, g.M, md.F, md.d, s));
     PROFILED(ctx, SPECS_K_DOWN, s,
              parts = gemm_residual_split<T>((const T*)ws.act, (const T*)L.wd, x, ws.gu, max_split, g.M, md.d, md.F, s));
     normed = false;
