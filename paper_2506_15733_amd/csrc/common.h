@@ -156,7 +156,7 @@ void launch_subsample(const float* lt, const float* lg, const float* r, const ui
 
 // bf16 MFMA GEMM family (gemm_mfma.hip). Returns false if the shape is not supported.
 enum { MFMA_STORE = 0, MFMA_RESIDUAL = 1, MFMA_SWIGLU = 2, MFMA_LMHEAD = 3 };
-enum { MFMA_TILES = 4 };        // tile shapes of the family; an index is what mfma_gemm_plan gives
+enum { MFMA_TILES = 5, MFMA_MAX_SPLIT = 16 };   // tile shapes of the family (an index is what mfma_gemm_plan gives)
 // ksplit > 1 (MFMA_STORE only): C is [ksplit][M][N], one partial product per K slice; tile < 0: chosen by the launch.
 bool launch_gemm_mfma(int epi, const bf16_t* A, const bf16_t* W, int M, int N, int K, float* C, bf16_t* act,
                       const int32_t* tok, float* part_max, float* part_sum, float* zt, int ksplit, int tile,
@@ -171,8 +171,3 @@ template <typename T>
 void launch_add_partials_rmsnorm(float* x, const float* P, int parts, int init, const float* gain, T* out, int M, int d,
                                  float eps, hipStream_t s);
 int mfma_lmhead_tiles(int V);
-// Weight-streaming GEMM for M <= 32 rows (gemm_skinny.hip): MFMA_STORE writes ksplit partial products
-// [ksplit][M][N]; MFMA_SWIGLU (ksplit 1) writes silu(gate)*up. Returns false if the shape is not taken.
-bool launch_gemm_skinny(int epi, const bf16_t* A, const bf16_t* W, int M, int N, int K, float* C, bf16_t* act,
-                        int ksplit, hipStream_t s);
-int skinny_gemm_split(int N, int K, int max_split);

@@ -277,6 +277,7 @@ __global__ void rope_split_kernel(const float* __restrict__ qkv, const float* __
   const int heads_here = (H - (int)blockIdx.y + (int)gridDim.y - 1) / (int)gridDim.y;
   auto rotate = [&](int h, int i) {
     float x1 = in[h * hd + i], x2 = in[h * hd + half + i];
+#pragma unroll 4
     for (int pidx = 1; pidx < parts; ++pidx) {           // K-split projection: add the slices up, in order
       x1 += in[pidx * part_stride + h * hd + i];
       x2 += in[pidx * part_stride + h * hd + half + i];

@@ -84,10 +84,7 @@ __device__ __forceinline__ float half_wave_sum(float v) {
 }
 
 // HD128 (ME_QKV_ROPE only): head_dim 128 instead of 64.
-// K-tiles in the ring of the small tiles: as many as 160 KiB of LDS hold, at most six
-constexpr int ring_stages(int bm, int bn) { return 160 * 1024 / ((bm + bn) * 128) > 6 ? 6 : 160 * 1024 / ((bm + bn) * 128); }
-
-template <int BM, int BN, int NWM, int EPI, bool HD128 = false>
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128 = false>
 __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
   constexpr int NWN = BN / 64;
   // Rotary pairs are columns (i, i + hd/2) of a head. With head_dim 64 a wavefront's 64 columns are one head and
@@ -243,7 +240,7 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
     // by the matrix pipe, so the ring holds S whole K-tiles and S-1 of them are in flight, activations as far ahead
     // as weights. (With the five-slot ring above the activations are requested one K-tile ahead only: 1.1 - 1.75 us a
     // k-step at 128 rows x 256 columns, most of it waiting.)
-    constexpr int S = ring_stages(BM, BN), STG = (BM + BN) * 128;
+    constexpr int STG = (BM + BN) * 128;
     auto read_frags = [&](const char* st, int ks, bf16x8 (&af)[TM], bf16x8 (&bfr)[TN]) {
 #pragma unroll
       for (int i = 0; i < TM; ++i) af[i] = lds_frag(st, wm * WM + i * 32 + lrow, ks * 2 + lhalf);
@@ -261,8 +258,10 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
     };
     // own loads of all but the newest `ahead` K-tiles have landed and own fragment reads are done, then everybody's
     auto wait_ahead = [&](int ahead) {
-      static_assert(S <= 6 && 4 * NLD < 63, "the counts below");
-      if (ahead >= 4) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(4 * NLD) : "memory");
+      static_assert(S <= 8 && (S - 2) * NLD < 63, "the counts below");
+      if (S > 7 && ahead >= 6) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(S > 7 ? 6 * NLD : 0) : "memory");
+      else if (S > 6 && ahead >= 5) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(S > 6 ? 5 * NLD : 0) : "memory");
+      else if (ahead >= 4) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(4 * NLD) : "memory");
       else if (ahead == 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(3 * NLD) : "memory");
       else if (ahead == 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NLD) : "memory");
       else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NLD) : "memory");
@@ -490,17 +489,17 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
   }
 }
 
-template <int BM, int BN, int NWM, int EPI, bool HD128 = false>
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128 = false>
 static void launch_variant(const GemmArgs& a, hipStream_t s) {
-  constexpr int smem = BM == 256 ? 5 * 256 * 128 : ring_stages(BM, BN) * (BM + BN) * 128;
+  constexpr int smem = BM == 256 ? 5 * 256 * 128 : S * (BM + BN) * 128;
   static bool configured = false;
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<BM, BN, NWM, EPI, HD128>,
+    (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     configured = true;
   }
   const int total = a.m_tiles * a.n_tiles * a.ksplit, per_xcd = 32 * (total / 256) + (total % 256 + 7) / 8;
-  gemm_mfma_kernel<BM, BN, NWM, EPI, HD128><<<8 * per_xcd, NWM * BN, smem, s>>>(a);
+  gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128><<<8 * per_xcd, NWM * BN, smem, s>>>(a);
 }
 
 int mfma_lmhead_tiles(int V) { return (V + 255) / 256; }
@@ -508,40 +507,53 @@ int mfma_lmhead_tiles(int V) { return (V + 255) / 256; }
 // The tile shapes, and what one 64-deep k-step of a workgroup costs (us) when a few CUs are busy and when all 256 are.
 // The two wide ones are for products that fill the chip, where operand traffic counts (2048 x 37888 x 3584: 457, 539,
 // 670, 834 us in this order); the narrow ones put four to eight times as many workgroups on a short product and have
-// more of its loads in flight (256 x 2048 x 1536: 33.7, 21.4, 15.2, 11.8 us).
+// more of its loads in flight (256 x 2048 x 1536: 33.7, 21.4, 15.2, 11.8 us). The last is for up to 32 rows (the
+// positions of a generated block), where all that counts is how fast the weights stream: with K in slices, 16 x 1536 x
+// 8960 takes 7.8 us and 16 x 3584 x 18944 25.3, HBM's rate, where a kernel that loaded weights to registers and walked
+// K wavefront by wavefront took 10.9 and 31.2.
 struct TileShape { int bm, bn; double lat, full; };
-static const TileShape kTiles[MFMA_TILES] = {{256, 256, 1.15, 1.7}, {128, 256, 0.68, 1.04}, {128, 128, 0.46, 0.65}, {64, 128, 0.33, 0.41}};
+static const TileShape kTiles[MFMA_TILES] = {{256, 256, 1.15, 1.7}, {128, 256, 0.68, 1.04}, {128, 128, 0.46, 0.65}, {64, 128, 0.33, 0.41}, {32, 128, 0.30, 0.36}};
 
 template <int EPI, bool HD128 = false>
 static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
   a.m_tiles = (a.M + kTiles[tile].bm - 1) / kTiles[tile].bm;
   a.n_tiles = (a.N + kTiles[tile].bn - 1) / kTiles[tile].bn;
-  if (tile == 0) launch_variant<256, 256, 2, EPI, HD128>(a, s);
-  else if (tile == 1) launch_variant<128, 256, 2, EPI, HD128>(a, s);
+  if (tile == 0) launch_variant<256, 256, 2, 5, EPI, HD128>(a, s);
+  else if (tile == 1) launch_variant<128, 256, 2, 3, EPI, HD128>(a, s);
   else if constexpr (EPI != ME_LMHEAD) {
     // four wavefronts along M: two per SIMD cover each other's LDS reads (69 -> 64 us at 256 x 1536 x 8960)
-    if (tile == 2) launch_variant<128, 128, 4, EPI, HD128>(a, s);
-    else launch_variant<64, 128, 2, EPI, HD128>(a, s);
+    if (tile == 2) launch_variant<128, 128, 4, 5, EPI, HD128>(a, s);
+    // 64 x 128: a ring of six K-tiles in one workgroup per CU where few workgroups walk a long K; else half the ring and
+    // two workgroups per CU, which fill it sooner and leave no nearly empty last round (16 x 37888 x 3584, 296
+    // workgroups: 62.2 -> 58.8 us)
+    else if (tile == 3 && (long)a.m_tiles * a.n_tiles * a.ksplit <= 256 && a.K / 64 > 11 * a.ksplit)
+      launch_variant<64, 128, 2, 6, EPI, HD128>(a, s);
+    else if (tile == 3) launch_variant<64, 128, 2, 3, EPI, HD128>(a, s);
+    else launch_variant<32, 128, 1, 4, EPI, HD128>(a, s);
   }
 }
 
 // Tile shape and K-split for an M x N x K product whose consumer can sum up to max_split partial products: the pair
 // with the least estimated time. Workgroups run in rounds of 256; a round that leaves CUs idle has k-steps between the
-// two costs of its tile; a launch costs about 4 us beside that, and every extra partial one more M x N float write here
-// and one more read in the consumer. The estimate is within 10 % of the measured times for 64..2048 rows of the
-// projections with K = 1024..18944, except that it misses up to 20 % of the narrow tiles' cost when they run in many
-// rounds, where the wide ones are ahead anyway.
+// two costs of its tile; the narrow tiles run two workgroups per CU, so their last round overlaps the one before. The
+// weights cannot arrive faster than HBM delivers them, and about half of that time does not overlap with a short walk
+// through K. A launch costs about 3 us beside that, and every extra partial one more M x N float write here and one
+// more read in the consumer. The estimate is within 15 % of the measured times for 8..2048 rows of the projections with
+// K = 1024..18944, except that it misses up to 20 % of the narrow tiles' cost when they run in many rounds, where the
+// wide ones are ahead anyway.
 void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* tile_out, int* split_out) {
-  const int KT = K / 64;
+  const int KT = K / 64, shapes = wide_only ? 2 : M <= 32 ? MFMA_TILES : MFMA_TILES - 1;
+  const double stream = (double)N * K * 2.0 / 5.2e6;
   double best = 1e30;
   *tile_out = 0; *split_out = 1;
-  for (int tile = 0; tile < (wide_only ? 2 : MFMA_TILES); ++tile) {
+  for (int tile = 0; tile < shapes; ++tile) {
     const TileShape& ts = kTiles[tile];
     const long tiles = (long)((M + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn);
-    for (int sp = 1; sp <= max_split && sp <= 8 && (sp == 1 || sp * 4 <= KT + 3); ++sp) {
-      const long whole = tiles * sp / 256, rest = tiles * sp % 256;
-      const double step = whole * ts.full + (rest ? ts.lat + (ts.full - ts.lat) * rest / 256.0 : 0.0);
-      const double t = 4.0 + step * ((KT + sp - 1) / sp) + (2 * sp - 2) * (double)M * N * 4.0 / 4e6;
+    for (int sp = 1; sp <= max_split && sp <= MFMA_MAX_SPLIT && (sp == 1 || sp * 4 <= KT + 3); ++sp) {
+      const long wgs = tiles * sp, whole = tile < 3 || wgs <= 256 ? wgs / 256 : 0, rest = wgs - 256 * whole;
+      const double last = rest > 256 ? ts.full * rest / 256.0 : rest ? ts.lat + (ts.full - ts.lat) * rest / 256.0 : 0.0;
+      const double walk = (whole * ts.full + last) * ((KT + sp - 1) / sp) + 0.45 * stream;
+      const double t = 3.0 + (walk > stream ? walk : stream) + (2 * sp - 2) * (double)M * N * 4.0 / 4e6;
       if (t < best - 1e-9) { best = t; *tile_out = tile; *split_out = sp; }
     }
   }

@@ -324,6 +324,9 @@ static ModelDims dims_of(const specs_model_desc& d) {
   return md;
 }
 
+// Products of a few rows, whose time is that of streaming the weights, are counted on their own.
+static void count_mfma(int M) { count_path(M <= 32 ? SPECS_PATH_GEMM_SKINNY : SPECS_PATH_GEMM_MFMA); }
+
 template <typename T>
 static void gemm(const T* A, const T* W, float* C, int M, int N, int K, GemmEpilogue epi, hipStream_t s) {
   count_path(SPECS_PATH_GEMM_PLAIN);
@@ -333,7 +336,7 @@ template <>
 void gemm<bf16_t>(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int K, GemmEpilogue epi, hipStream_t s) {
   int e = epi == EPI_RESIDUAL_ADD ? MFMA_RESIDUAL : MFMA_STORE;
   if (launch_gemm_mfma(e, A, W, M, N, K, C, nullptr, nullptr, nullptr, nullptr, nullptr, 1, -1, s)) {
-    count_path(SPECS_PATH_GEMM_MFMA);
+    count_mfma(M);
   } else {
     count_path(SPECS_PATH_GEMM_PLAIN);
     launch_gemm_simple<bf16_t>(A, W, C, M, N, K, epi, s);
@@ -352,17 +355,13 @@ static int gemm_residual_split(const T* A, const T* W, float* x, float* part, in
 template <>
 int gemm_residual_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* x, float* part, int max_split, int M, int N,
                                 int K, hipStream_t s) {
-  if (M <= 32 && max_split >= 1) {                       // a few rows: stream the weights once, K in slices
-    int sp = skinny_gemm_split(N, K, max_split);
-    if (launch_gemm_skinny(MFMA_STORE, A, W, M, N, K, part, nullptr, sp, s)) { count_path(SPECS_PATH_GEMM_SKINNY); return sp; }
-  }
   // Also with one slice the product goes to `part` and the normalisation kernel, which reads x anyway, adds it:
   // the GEMM's epilogue then only writes, instead of waiting for a read of x before every store.
   int tile = -1, split = 1;
   if (K % 64 == 0 && max_split > 1) mfma_gemm_plan(M, N, K, max_split, false, &tile, &split);
   if (max_split >= 1 &&
       launch_gemm_mfma(MFMA_STORE, A, W, M, N, K, part, nullptr, nullptr, nullptr, nullptr, nullptr, split, tile, s)) {
-    count_path(SPECS_PATH_GEMM_MFMA);
+    count_mfma(M);
     return split;
   }
   gemm<bf16_t>(A, W, x, M, N, K, EPI_RESIDUAL_ADD, s);
@@ -378,9 +377,11 @@ static int gemm_store_split(const T* A, const T* W, float* C, int max_split, int
 template <>
 int gemm_store_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* C, int max_split, int M, int N, int K,
                              hipStream_t s) {
-  if (M <= 32 && max_split >= 1) {
-    int sp = skinny_gemm_split(N, K, max_split);
-    if (launch_gemm_skinny(MFMA_STORE, A, W, M, N, K, C, nullptr, sp, s)) { count_path(SPECS_PATH_GEMM_SKINNY); return sp; }
+  int tile = -1, split = 1;
+  if (K % 64 == 0 && max_split > 1) mfma_gemm_plan(M, N, K, max_split, false, &tile, &split);
+  if (launch_gemm_mfma(MFMA_STORE, A, W, M, N, K, C, nullptr, nullptr, nullptr, nullptr, nullptr, split, tile, s)) {
+    count_mfma(M);
+    return split;
   }
   gemm<bf16_t>(A, W, C, M, N, K, EPI_STORE_F32, s);
   return 1;
@@ -433,9 +434,8 @@ static void gate_up(const T* A, const T* Wgu, float* gu, T* act, int M, int F, i
 }
 template <>
 void gate_up<bf16_t>(const bf16_t* A, const bf16_t* Wgu, float* gu, bf16_t* act, int M, int F, int K, hipStream_t s) {
-  if (M <= 32 && launch_gemm_skinny(MFMA_SWIGLU, A, Wgu, M, 2 * F, K, nullptr, act, 1, s)) { count_path(SPECS_PATH_GEMM_SKINNY); return; }
   if (launch_gemm_mfma(MFMA_SWIGLU, A, Wgu, M, 2 * F, K, nullptr, act, nullptr, nullptr, nullptr, nullptr, 1, -1, s)) {
-    count_path(SPECS_PATH_GEMM_MFMA);
+    count_mfma(M);
     return;
   }
   count_path(SPECS_PATH_GEMM_PLAIN);
@@ -491,7 +491,11 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
                                 md.rope_base, s));
   // ws.gu ([R, 2F] floats) is free while the residual projections run (the fused gate/up kernel never writes
   // it, the unfused path has consumed it by then), so it holds their K-split partial products.
-  const int max_split = (int)((2 * (size_t)md.F) / (size_t)md.d);
+  const auto max_split_of = [&](int rows) {
+    const size_t room = (size_t)R * 2 * md.F / ((size_t)rows * md.d);
+    return (int)(room < MFMA_MAX_SPLIT ? room : MFMA_MAX_SPLIT);
+  };
+  const int max_split = max_split_of(g.M);
   bool normed = false;                                   // ws.a already holds RMSNorm(x) * g_attn of this layer
   for (int l = 0; l < d.n_layers; ++l) {
     const specs_layer_weights& L = m->layers[l];
@@ -507,13 +511,15 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
     if (!normed && !fused_rope)
       PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(x, L.g_attn, (T*)ws.a, g.M, md.d, md.eps, s));
     // whole-block bf16 launches: rotary embedding, conversion and value transposition inside the projection's epilogue
-    if (!fused_rope && g.M > 32)
+    // (one position per block writes a column of the transposed values, a cache line per element, which the two or
+    // three workgroups of the value heads alone are slow at: those launches leave it to the kernel below)
+    if (!fused_rope && g.L > 1)
       PROFILED(ctx, SPECS_K_QKV, s,
                fused_rope = qkv_rope_fused<T>((const T*)ws.a, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, s));
     if (!fused_rope) {
       int qkv_parts = 1;                                 // ws.qkv has room for R / g.M slices of the projection
       PROFILED(ctx, SPECS_K_QKV, s,
-               qkv_parts = gemm_store_split<T>((const T*)ws.a, (const T*)L.wqkv, ws.qkv, (int)(R / g.M < 8 ? R / g.M : 8),
+               qkv_parts = gemm_store_split<T>((const T*)ws.a, (const T*)L.wqkv, ws.qkv, (int)(R / g.M < MFMA_MAX_SPLIT ? R / g.M : MFMA_MAX_SPLIT),
                                                g.M, qd + 2 * kvd, md.d, s));
       PROFILED(ctx, SPECS_K_OTHER, s, launch_rope_split<T>(ws.qkv, qkv_parts, ws.cs, (T*)ws.q, kb, vb, g, Lp, md, s));
     }
@@ -528,7 +534,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
                             (size_t)R * 2 * md.F, s));
       int pl = 0;
       PROFILED(ctx, SPECS_K_OPROJ, s,
-               pl = gemm_residual_split<T>((const T*)ws.attn, (const T*)L.wo, ws.xs, ws.gu, max_split, gl.M, md.d, qd, s));
+               pl = gemm_residual_split<T>((const T*)ws.attn, (const T*)L.wo, ws.xs, ws.gu, max_split_of(gl.M), gl.M, md.d, qd, s));
       if (pl)
         PROFILED(ctx, SPECS_K_OTHER, s,
                  launch_add_partials_rmsnorm<T>(ws.xs, ws.gu, pl, 0, L.g_ffn, (T*)ws.a, gl.M, md.d, md.eps, s));
@@ -542,7 +548,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
         PROFILED(ctx, SPECS_K_GATE_UP, s,
                  gate_up<T>((const T*)ws.a, (const T*)L.wgu, ws.gu, (T*)ws.act, gl.M, md.F, md.d, s));
       PROFILED(ctx, SPECS_K_DOWN, s,
-               pl = gemm_residual_split<T>((const T*)ws.act, (const T*)L.wd, ws.xs, ws.gu, max_split, gl.M, md.d, md.F, s));
+               pl = gemm_residual_split<T>((const T*)ws.act, (const T*)L.wd, ws.xs, ws.gu, max_split_of(gl.M), gl.M, md.d, md.F, s));
       if (pl)
         PROFILED(ctx, SPECS_K_OTHER, s,
                  launch_add_partials_rmsnorm<T>(ws.xs, ws.gu, pl, 0, nullptr, (T*)ws.a, gl.M, md.d, md.eps, s));
@@ -850,14 +856,9 @@ extern "C" int specs_op_linear(specs_ctx* ctx, int32_t dtype, const void* A, con
     size_t per = (size_t)M * N * sizeof(float);
     size_t room = ctx->workspace_bytes > 256 ? (ctx->workspace_bytes - 256) / per : 0;
     int tile = -1, split = 1;
-    if (K % 64 == 0 && room > 1) mfma_gemm_plan(M, N, K, room > 8 ? 8 : (int)room, false, &tile, &split);
+    if (K % 64 == 0 && room > 1) mfma_gemm_plan(M, N, K, room > MFMA_MAX_SPLIT ? MFMA_MAX_SPLIT : (int)room, false, &tile, &split);
     float* part = (float*)(ctx->workspace + 256);
-    int sk = M <= 32 && room >= 1 ? skinny_gemm_split(N, K, room > 8 ? 8 : (int)room) : 0;
-    if (sk && launch_gemm_skinny(MFMA_STORE, (const bf16_t*)A, (const bf16_t*)W, M, N, K, part, nullptr, sk,
-                                 ctx->stream)) {
-      launch_add_partials_rmsnorm<bf16_t>(C, part, sk, accumulate ? 0 : 1, nullptr, nullptr, M, N, 0.f, ctx->stream);
-      ctx->last_model = nullptr;
-    } else if (split > 1 && launch_gemm_mfma(MFMA_STORE, (const bf16_t*)A, (const bf16_t*)W, M, N, K, part, nullptr, nullptr,
+    if (split > 1 && launch_gemm_mfma(MFMA_STORE, (const bf16_t*)A, (const bf16_t*)W, M, N, K, part, nullptr, nullptr,
                                       nullptr, nullptr, nullptr, split, tile, ctx->stream)) {
       launch_add_partials_rmsnorm<bf16_t>(C, part, split, accumulate ? 0 : 1, nullptr, nullptr, M, N, 0.f, ctx->stream);
       ctx->last_model = nullptr;                         // the workspace no longer holds a scored block

@@ -64,8 +64,10 @@ def test_linear_bf16(ctx, M, N, K):
 # one workgroup tile shape per line: ragged in rows and columns, fewer K-tiles than the ring holds, as many, more
 @pytest.mark.parametrize("M,N,K", [(65, 136, 64), (63, 129, 384), (70, 300, 192), (129, 520, 448),        # 64 x 128
                                    (321, 8200, 320), (700, 4616, 384), (321, 8200, 64),                   # 128 x 128
-                                   (555, 37888, 192), (300, 17920, 128), (600, 9000, 256),                # 128 x 256
-                                   (1100, 33000, 128), (2060, 9000, 64)])                                 # 256 x 256
+                                   (555, 37888, 192), (300, 17920, 128), (2060, 9000, 64),                # 128 x 256
+                                   (1100, 33000, 128),                                                    # 256 x 256
+                                   (1, 64, 64), (5, 301, 192), (32, 2050, 1280), (17, 896, 4864),         # 32 x 128, up to 16 slices
+                                   (64, 1000, 832), (31, 37888, 448), (33, 896, 4864)])                   # 64 x 128, two per CU
 def test_linear_tile_shapes(ctx, M, N, K):
     from paper_2506_15733_amd import binding as B
     a, ta = draw(f"a{M}.{K}", (M, K))
