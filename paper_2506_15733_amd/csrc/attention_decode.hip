@@ -32,8 +32,8 @@ struct MergeArgs {
 // columns). The kernel is a chain of short dependent phases on a few KB, bound by latency, so whatever does not depend
 // on computed values (statistics and the first partial outputs of the runs, values) is requested before the scores.
 // (One wavefront per (candidate, query head), each lane with a key row of its own, touched 64 cache lines with every
-// load: 25.9 us at 256 candidates x 12 heads with 8 runs each; this form 9.2 us with up to 19 runs. At 16 x 12, where the
-// prefix kernel wants 32 runs instead of 16, it takes 9.5 us as the other did with 16, and the prefix 8.5 instead of 10.7.)
+// load: 25.9 us at 256 candidates x 12 heads with 8 runs each; this form 8.1 us with up to 19 runs. At 16 x 12, where the
+// prefix kernel wants 32 runs instead of 16 (8.7 us instead of 10.7), it takes 8.0 us, the other 9.3 with 16.)
 template <int HD>
 __global__ void __launch_bounds__(256) attention_decode_merge_kernel(MergeArgs a) {
   constexpr int KS = HD / 32;                   // MFMA K-steps of the scores
@@ -59,9 +59,6 @@ __global__ void __launch_bounds__(256) attention_decode_merge_kernel(MergeArgs a
   const int g = a.Hq / a.Hkv, gh = g - j0 < 16 ? g - j0 : 16;      // query heads of this workgroup
   const int b = c / a.n, i = c - b * a.n, t = a.t;
   const int P = a.len_override >= 0 ? a.len_override : a.lens[a.b0 + b];
-  const int ns = min((((P + 63) >> 6) + a.run_tiles - 1) / a.run_tiles, a.n_splits);   // runs of this beam
-  const size_t rows = (size_t)a.n * g;
-  const size_t prow0 = ((size_t)b * a.Hkv + kvh) * a.n_splits * rows + (size_t)i * g + j0;   // + split*rows + head
   const int hc = col < gh ? col : gh - 1;       // columns beyond the heads repeat the last one and are not stored
 
   bf16x8 qf[KS];
@@ -78,6 +75,26 @@ __global__ void __launch_bounds__(256) attention_decode_merge_kernel(MergeArgs a
     for (int ks = 0; ks < KS; ++ks) kf[ks] = *(const bf16x8*)(kr + 32 * ks);
   };
   if (wave < nkt) load_keys(wave);
+  const int nvs = (t + 32) >> 5;                // 32-key steps that hold a visible key
+  const bf16_t* vbase = a.vbT + (((size_t)c * a.Hkv + kvh) * HD + 16 * wave + col) * a.Lp;
+  // values of keys 32 st + 8 quad .. + 7; those beyond t are whatever an earlier call left there and become 0
+  auto load_vals = [&](int u, int st) {
+    const int key = 32 * st + 8 * quad;
+    return *(const bf16x8*)(vbase + (size_t)64 * u * a.Lp + (key < a.Lp ? key : 0));
+  };
+  auto visible_vals = [&](bf16x8 v, int st) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = 32 * st + 8 * quad + e <= t ? v[e] : (__bf16)0.f;
+    return v;
+  };
+  bf16x8 vv[ND][NVP];
+#pragma unroll
+  for (int u = 0; u < ND; ++u)
+#pragma unroll
+    for (int st = 0; st < NVP; ++st) vv[u][st] = load_vals(u, st < nvs ? st : 0);
+  const int ns = min((((P + 63) >> 6) + a.run_tiles - 1) / a.run_tiles, a.n_splits);   // runs of this beam
+  const size_t rows = (size_t)a.n * g;
+  const size_t prow0 = ((size_t)b * a.Hkv + kvh) * a.n_splits * rows + (size_t)i * g + j0;   // + split*rows + head
   for (int e = tid; e < gh * ns; e += 256) {
     const int s = e / gh, h = e - s * gh;
     wm[h * a.n_splits + s] = a.part_m[prow0 + s * rows + h];
@@ -98,22 +115,6 @@ __global__ void __launch_bounds__(256) attention_decode_merge_kernel(MergeArgs a
     }
   };
   load_parts(0);
-  const int nvs = (t + 32) >> 5;                // 32-key steps that hold a visible key
-  const bf16_t* vbase = a.vbT + (((size_t)c * a.Hkv + kvh) * HD + 16 * wave + col) * a.Lp;
-  // values of keys 32 st + 8 quad .. + 7; keys beyond t hold whatever an earlier call left there and become 0
-  auto load_vals = [&](int u, int st) {
-    const int key = 32 * st + 8 * quad;
-    bf16x8 v = *(const bf16x8*)(vbase + (size_t)64 * u * a.Lp + (key < a.Lp ? key : 0));
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = key + e <= t ? v[e] : (__bf16)0.f;
-    return v;
-  };
-  bf16x8 vv[ND][NVP];
-#pragma unroll
-  for (int u = 0; u < ND; ++u)
-#pragma unroll
-    for (int st = 0; st < NVP; ++st) vv[u][st] = load_vals(u, st < nvs ? st : 0);
-
   // scores of the block keys: lane holds keys 16 kt + 4 quad + e of head col
   for (int kt = wave; kt < nkt; kt += 4) {
     floatx4 s4 = {0.f, 0.f, 0.f, 0.f};
@@ -125,26 +126,30 @@ __global__ void __launch_bounds__(256) attention_decode_merge_kernel(MergeArgs a
       if (col < gh) sc[col * SS + 16 * kt + 4 * quad + e] = s4[e] * a.scale_log2e;
   }
   __syncthreads();
-  // softmax statistics, heads dealt to the wavefronts
-  for (int h = wave; h < gh; h += 4) {
+  // softmax statistics: 16 lanes per head, all heads at a time
+  const int h = tid >> 4, sub = tid & 15;
+  if (h < gh) {
     float mx = -INFINITY;
-    for (int k = lane; k <= t; k += 64) mx = fmaxf(mx, sc[h * SS + k]);
-    for (int s = lane; s < ns; s += 64) mx = fmaxf(mx, wm[h * a.n_splits + s]);
-    mx = ceilf(wave_max(mx));                   // finite (key t itself is always visible); an integer, so that
+    for (int k = sub; k <= t; k += 16) mx = fmaxf(mx, sc[h * SS + k]);
+    for (int s = sub; s < ns; s += 16) mx = fmaxf(mx, wm[h * a.n_splits + s]);
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 16));
+    mx = ceilf(mx);                             // finite (key t itself is always visible); an integer, so that
                                                 // the bf16 rounding of the weights does not depend on the reference
     float l = 0.f;
-    for (int k = lane; k < Lq; k += 64) {
+    for (int k = sub; k < Lq; k += 16) {
       const float p = k <= t ? __builtin_amdgcn_exp2f(sc[h * SS + k] - mx) : 0.f;
       l += p;
       pw[h * PS + k] = (bf16_t)p;               // the weight that multiplies V is a bf16 operand
     }
-    for (int s = lane; s < ns; s += 64) {
+    for (int s = sub; s < ns; s += 16) {
       const float w = __builtin_amdgcn_exp2f(wm[h * a.n_splits + s] - mx);
       l += w * wl[h * a.n_splits + s];
       wm[h * a.n_splits + s] = w;
     }
-    l = wave_sum(l);
-    if (lane == 0) inv[h] = 1.0f / l;
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) l += __shfl_xor(l, o, 16);
+    if (sub == 0) inv[h] = 1.0f / l;
   }
   __syncthreads();
   for (int g0 = 0; g0 * 64 < ncol; g0 += NPG) {
@@ -181,9 +186,9 @@ __global__ void __launch_bounds__(256) attention_decode_merge_kernel(MergeArgs a
     const bf16_t* pr = pw + hc * PS + 8 * quad;
 #pragma unroll
     for (int st = 0; st < NVP; ++st)
-      if (st < nvs) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vv[u][st], *(const bf16x8*)(pr + 32 * st), acc, 0, 0, 0);
+      if (st < nvs) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(visible_vals(vv[u][st], st), *(const bf16x8*)(pr + 32 * st), acc, 0, 0, 0);
     for (int st = NVP; st < nvs; ++st)
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(load_vals(u, st), *(const bf16x8*)(pr + 32 * st), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(visible_vals(load_vals(u, st), st), *(const bf16x8*)(pr + 32 * st), acc, 0, 0, 0);
     if (col < gh) {
       bf16x4 o;
 #pragma unroll

@@ -55,11 +55,19 @@ __global__ void __launch_bounds__(64) subsample_kernel(const float* __restrict__
       report_status(status, SPECS_ERANGE);
     } else {
       double total = 0.0;
+#pragma unroll 8
       for (int i = 0; i < n; ++i) total += w[i];
       double thr = uu * total, run = 0.0;
-      for (int i = 0; i < n; ++i) {
-        run += w[i];
-        if (run > thr) { pick = i; break; }
+      // eight weights are read ahead of the eight dependent additions
+      for (int i0 = 0; i0 < n && pick < 0; i0 += 8) {
+        double v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = i0 + k < n ? w[i0 + k] : 0.0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          run += v[k];
+          if (pick < 0 && i0 + k < n && run > thr) pick = i0 + k;
+        }
       }
       if (pick < 0)
         for (int i = n - 1; i >= 0; --i)
