@@ -32,7 +32,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 struct AttnArgs {
   const bf16_t* q;      // [M][Hq][hd]
   const bf16_t* kb;     // [M][Hkv][hd] block keys
-  const bf16_t* vbT;    // [B*n][Hkv][hd][Lp] block values, transposed, zero padded
+  const bf16_t* vbT;    // [B*n][Hkv][hd][g.vs] block values, transposed; columns below Lp are values or zeros
   const bf16_t* poolK;  // [pages][Hkv][16][hd]
   const bf16_t* poolV;  // [pages][Hkv][hd][16]
   bf16_t* out;          // [M][Hq*hd]
@@ -42,6 +42,7 @@ struct AttnArgs {
   // launches that cut the key list: n_splits runs of tiles per query tile, and every workgroup leaves an
   // un-normalised partial result for a second kernel to merge
   int n_splits;
+  int last_first;       // one block of one beam (prefill): query tiles dealt to the XCDs from the last one down
   int run_tiles;        // single positions (generation): tiles of a run; a beam has as many runs as its length asks for
   float* part_o;        // whole blocks: [b*Hkv + kvh][candidate][q_tile][split][128][HD]
                         // single positions: [b*Hkv + kvh][split][n*g rows][HD]
@@ -93,18 +94,28 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
     const int pass = (blockIdx.x >> 3) / a.q_tiles, qt = (blockIdx.x >> 3) - pass * a.q_tiles;
     logical = (pass * 8 + (blockIdx.x & 7)) * a.q_tiles + qt;
   }
-  if (logical >= a.total_wg) return;
+  if ((DEC || !a.last_first) && logical >= a.total_wg) return;
   const BatchGeom& G = a.g;
   const int g = a.Hq / a.Hkv;
   int rem = logical;
   int split = 0;
-  if (SPLIT && !DEC) { split = rem % a.n_splits; rem /= a.n_splits; }
-  const int qt_idx = rem % a.q_tiles; rem /= a.q_tiles;
+  if (SPLIT && !DEC && !a.last_first) { split = rem % a.n_splits; rem /= a.n_splits; }
+  int qt_idx = rem % a.q_tiles; rem /= a.q_tiles;
   if (DEC) { split = rem % a.n_splits; rem /= a.n_splits; }
   int cand = 0;
   if (!DEC) { cand = rem % G.n; rem /= G.n; }
-  const int kvh = rem % a.Hkv;
-  const int b = rem / a.Hkv;
+  int kvh = rem % a.Hkv;
+  int b = rem / a.Hkv;
+  if (!DEC && a.last_first) {
+    // A prompt: the keys of a query tile grow with its position; dealt round from the longest down, all XCDs finish
+    // together (a contiguous run of tiles gave an XCD the short or the long ones)
+    const int unit = blockIdx.x / a.Hkv;
+    if ((int)blockIdx.x >= a.total_wg) return;
+    b = 0;
+    kvh = blockIdx.x - unit * a.Hkv;
+    split = unit % a.n_splits;
+    qt_idx = a.q_tiles - 1 - unit / a.n_splits;
+  }
 
   // the wavefront index as a scalar: page ids, page bases and LDS destinations then live in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -200,14 +211,14 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
         const bf16_t* src = a.kb + ((m_c0 + key) * a.Hkv + kvh) * HD + chunk * 8;
         __builtin_amdgcn_global_load_lds(GLB_PTR(src), LDS_PTR(kdst + i * 1024), 16, 0, 0);
       }
-      const bf16_t* vsrc = a.vbT + ((size_t)cand_idx * a.Hkv + kvh) * HD * a.Lp;
+      const bf16_t* vsrc = a.vbT + ((size_t)cand_idx * a.Hkv + kvh) * HD * a.g.vs;
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
         int qi = i * 64 + lane;
         int d = qi >> 1, half = (qi & 1) ^ ((d >> 3) & 1);
         int key = key0 + half * 8;
         key = key < a.Lp ? key : a.Lp - 8;
-        __builtin_amdgcn_global_load_lds(GLB_PTR(vsrc + (size_t)d * a.Lp + key), LDS_PTR(vdst + i * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(GLB_PTR(vsrc + (size_t)d * a.g.vs + key), LDS_PTR(vdst + i * 1024), 16, 0, 0);
       }
     }
   };
@@ -436,6 +447,7 @@ bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT,
   AttnArgs a;
   a.q = q; a.kb = kb; a.vbT = vbT; a.poolK = poolK; a.poolV = poolV; a.out = out; a.g = g;
   a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lp = Lp;
+  a.last_first = g.B == 1 && g.n == 1;
   a.n_splits = 1; a.run_tiles = 0; a.part_o = nullptr; a.part_m = nullptr; a.part_l = nullptr;
   a.scale_log2e = 1.4426950408889634f / sqrtf((float)md.hd);
   int rows = g.L * (md.Hq / md.Hkv);
@@ -487,6 +499,7 @@ bool launch_attention_mfma_decode_prefix(const bf16_t* q, const bf16_t* poolK, c
                                          int* run_tiles_out, int* n_splits_out, hipStream_t s) {
   if ((md.hd != 64 && md.hd != 128) || g.page_tokens != 16 || g.L != 1) return false;
   AttnArgs a;
+  a.last_first = 0;
   a.q = q; a.kb = nullptr; a.vbT = nullptr; a.poolK = poolK; a.poolV = poolV; a.out = nullptr; a.g = g;
   a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lp = 16;
   a.scale_log2e = 1.4426950408889634f / sqrtf((float)md.hd);

@@ -14,8 +14,7 @@ template <typename T, bool QUADS>
 __global__ void __launch_bounds__(64) attention_simple_kernel(const T* __restrict__ q, const T* __restrict__ kb,
                                                               const T* __restrict__ vbT, const T* __restrict__ poolK,
                                                               const T* __restrict__ poolV, T* __restrict__ out,
-                                                              BatchGeom g, int Hq, int Hkv, int hd, int Lp, int pt_shift,
-                                                              float scale) {
+                                                              BatchGeom g, int Hq, int Hkv, int hd, int pt_shift, float scale) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
   float* qs = smem;                             // [hd] query staged in LDS as float
   float* sc = smem + hd;                        // [ctx + t + 1] scores, then weights
@@ -72,7 +71,7 @@ __global__ void __launch_bounds__(64) attention_simple_kernel(const T* __restric
   sm = wave_sum(sm);
   __syncthreads();
   float inv = 1.0f / sm;
-  // values are stored transposed: pages [page][Hkv][hd][pt], block [cand][Hkv][hd][Lp]
+  // values are stored transposed: pages [page][Hkv][hd][pt], block [cand][Hkv][hd][vs]
   size_t cand = (size_t)(m / g.L);
   auto weighted_sum = [&](int c, int first, int step) {
     float acc = 0.f;
@@ -85,7 +84,7 @@ __global__ void __launch_bounds__(64) attention_simple_kernel(const T* __restric
       const int page = page_slot(j, slot);
       acc = fmaf(sc[j], to_f32<T>(vpool[page * page_stride + slot]), acc);
     }
-    const T* vblk = vbT + ((cand * Hkv + kvh) * hd + c) * Lp;
+    const T* vblk = vbT + ((cand * Hkv + kvh) * hd + c) * g.vs;
 #pragma unroll 4
     for (; j < nkeys; j += step) acc = fmaf(sc[j], to_f32<T>(vblk[j - ctx]), acc);
     return acc;
@@ -105,7 +104,7 @@ __global__ void __launch_bounds__(64) attention_simple_kernel(const T* __restric
 
 template <typename T>
 void launch_attention_simple(const T* q, const T* kb, const T* vbT, const T* poolK, const T* poolV, T* out,
-                             const BatchGeom& g, const ModelDims& md, int Lp, int max_ctx, hipStream_t s) {
+                             const BatchGeom& g, const ModelDims& md, int max_ctx, hipStream_t s) {
   const size_t lds = (size_t)(max_ctx + g.Lk + md.hd) * sizeof(float);
   const float scale = 1.4426950408889634f / sqrtf((float)md.hd);
   int shift = 0;
@@ -116,12 +115,12 @@ void launch_attention_simple(const T* q, const T* kb, const T* vbT, const T* poo
   (void)hipFuncSetAttribute((const void*)attention_simple_kernel<T, Q>, hipFuncAttributeMaxDynamicSharedMemorySize,    \
                             (int)lds);                                                                                 \
   attention_simple_kernel<T, Q><<<dim3(g.M, md.Hq), 64, lds, s>>>(q, kb, vbT, poolK, poolV, out, g, md.Hq, md.Hkv,     \
-                                                                  md.hd, Lp, shift, scale)
+                                                                  md.hd, shift, scale)
   if (quads) { GO(true); } else { GO(false); }
 #undef GO
 }
 template void launch_attention_simple<float>(const float*, const float*, const float*, const float*, const float*,
-                                             float*, const BatchGeom&, const ModelDims&, int, int, hipStream_t);
+                                             float*, const BatchGeom&, const ModelDims&, int, hipStream_t);
 template void launch_attention_simple<bf16_t>(const bf16_t*, const bf16_t*, const bf16_t*, const bf16_t*,
-                                              const bf16_t*, bf16_t*, const BatchGeom&, const ModelDims&, int, int,
+                                              const bf16_t*, bf16_t*, const BatchGeom&, const ModelDims&, int,
                                               hipStream_t);

@@ -54,6 +54,8 @@ struct BatchGeom {
   int t0;                   // in-block position of a row's first token: 0 when a launch covers whole blocks,
                             // t when it covers the single position t of every block (token-by-token generation)
   int Lk;                   // block length of the block key/value buffers (= L unless t0 > 0 launches are in use)
+  int vs;                   // columns of a row of the transposed block values: Lk rounded up to 16, or more where several
+                            // pieces of prompts lie side by side in one buffer (prefill)
   const int32_t* lens;      // device [B_total]
   const int32_t* page_table;// device [B_total][max_pages]
   int max_pages, page_tokens;
@@ -65,10 +67,11 @@ struct ModelDims {
 };
 
 // ---- launchers implemented across the .hip files (all enqueue on `s`) ----
-// x: row m embeds tok[m * tok_stride]; cs: row m's rotary angles, as launch_rope_table leaves them
+// x: row m embeds tok[m * tok_stride], rows from `rows` on the token of row rows - 1; cs: row m's rotary angles, as
+// launch_rope_table leaves them
 template <typename T>
-void launch_embed_rope(const int32_t* tok, int tok_stride, const T* E, float* x, int d, int V, int* status, float* cs,
-                       const BatchGeom& g, int hd, float base, hipStream_t s);
+void launch_embed_rope(const int32_t* tok, int tok_stride, int rows, const T* E, float* x, int d, int V, int* status,
+                       float* cs, const BatchGeom& g, int hd, float base, hipStream_t s);
 template <typename T>
 void launch_rmsnorm(const float* x, const float* gain, T* out, int M, int d, float eps, hipStream_t s);
 // lm_head operand: row (b,i,t) = norm(t == 0 ? h_last[b0+b] : x[row-1])
@@ -120,7 +123,7 @@ bool launch_small_gate_up(const float* x, const float* gain, const float* Wgu, f
 
 template <typename T>
 void launch_attention_simple(const T* q, const T* kb, const T* vbT, const T* poolK, const T* poolV, T* out,
-                             const BatchGeom& g, const ModelDims& md, int Lp, int max_ctx, hipStream_t s);
+                             const BatchGeom& g, const ModelDims& md, int max_ctx, hipStream_t s);
 // part / part_floats: float scratch for launches that split the key tiles over workgroups (null: never split)
 bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                            const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,

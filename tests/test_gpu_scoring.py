@@ -552,3 +552,53 @@ def test_multi_step_loop_with_commit_and_switching_matches_oracle(fast_path):
     assert gen.any() and not gen.all()          # the run exercises both generators
     assert step.prefixes["target"].lens_dev.cpu().tolist() == [len(t) for t in traces]
     step.close()
+
+
+@pytest.mark.parametrize("dtype,hd,page_tokens,lens,rows", [
+    ("bf16", 64, 16, (1, 16, 17, 200, 333, 15), 1024),   # one launch: stretches of less than a page, of a page and one more
+    ("bf16", 64, 16, (300, 70, 129), 40),                # several launches, prompts cut inside and their rest with the next
+    ("bf16", 128, 16, (700, 64), 1024),
+    ("bf16", 16, 4, (5, 90, 33), 64),                    # the plain attention kernel
+    ("f32", 16, 4, (1, 5, 90, 33), 24), ("f32", 16, 16, (40, 7), 5)])
+def test_prefill_of_several_prompts_equals_one_by_one(dtype, hd, page_tokens, lens, rows):
+    """Prompts that share launches (and are cut by them) leave the pages and last states that each leaves alone. Float:
+    sums in another order; bf16: a value on a rounding boundary moves by a bf16 unit, as elsewhere in this file."""
+    from paper_2506_15733_amd import synthetic, binding as B
+    desc = ModelDesc("target", 2, 192, 6, 2, hd, 320, 301, dtype, "lm")
+    stream = torch.cuda.current_stream()
+    toks = [torch.from_numpy(W.rng.uniform_tokens(41, f"pf{i}", n, 301)).to("cuda:0") for i, n in enumerate(lens)]
+    need = [(n + page_tokens - 1) // page_tokens for n in lens]
+
+    def run(which, max_rows):
+        dm = synthetic.DeviceModel(desc, "cuda:0", stream, max_rows, 1)
+        table = np.full((len(which), max(need[i] for i in which)), -1, np.int32)
+        o = 0
+        for k, i in enumerate(which):
+            table[k, :need[i]] = np.arange(o, o + need[i])
+            o += need[i]
+        pf = synthetic.DevicePrefix(dm, np.array([lens[i] for i in which], np.int32), table, o, page_tokens)
+        pf.kv_pool.zero_()
+        B.specs_prefill(dm.ctx, dm.model, pf.handle, torch.cat([toks[i] for i in which]))
+        torch.cuda.synchronize()
+        assert B.specs_ctx_status(dm.ctx) == 0
+        out = pf.kv_pool.double().cpu().numpy(), pf.h_last.double().cpu().numpy()
+        pf.close()
+        dm.close()
+        return out
+
+    kv, h = run(range(len(lens)), rows)
+    tol = 1e-5 if dtype == "f32" else 2e-2
+    page = 0
+    for i, n in enumerate(lens):
+        kv1, h1 = run([i], 2048)
+        got, want = kv[:, :, page:page + need[i]], kv1
+        page += need[i]
+        keys, vals = slice(0, 1), slice(1, 2)                # a page's slots beyond the prompt are nobody's
+        used = np.zeros((need[i], page_tokens), bool)
+        used.reshape(-1)[:n] = True
+        gk = got[:, keys].reshape(desc.n_layers, need[i], 2, page_tokens, hd).transpose(0, 2, 1, 3, 4)[:, :, used]
+        wk = want[:, keys].reshape(desc.n_layers, need[i], 2, page_tokens, hd).transpose(0, 2, 1, 3, 4)[:, :, used]
+        gv = got[:, vals].reshape(desc.n_layers, need[i], 2, hd, page_tokens).transpose(0, 2, 1, 4, 3)[:, :, used]
+        wv = want[:, vals].reshape(desc.n_layers, need[i], 2, hd, page_tokens).transpose(0, 2, 1, 4, 3)[:, :, used]
+        for g, w in ((gk, wk), (gv, wv), (h[i], h1[0])):
+            assert np.abs(g - w).max() < tol * max(1.0, np.abs(w).max()), (i, n)
