@@ -89,7 +89,8 @@ template <typename T>
 void launch_silu_mul(const float* gu, T* act, int M, int F, hipStream_t s);
 template <typename T>
 void launch_kv_commit(const T* kb, const T* vbT, T* poolK, T* poolV, const BatchGeom& g, const ModelDims& md,
-                      int Lp, const int32_t* chosen, hipStream_t s);
+                      int Lp, const int32_t* chosen, int layers, size_t kb_layer, size_t vb_layer, size_t pool_layer,
+                      hipStream_t s);
 template <typename T>
 void launch_prm_head(const float* x, const float* gain, const T* w, float* out, const BatchGeom& g, int d, float eps,
                      hipStream_t s);

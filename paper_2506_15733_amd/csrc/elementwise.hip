@@ -368,12 +368,17 @@ template void launch_silu_mul<bf16_t>(const float*, bf16_t*, int, int, hipStream
 // ---------------------------------------------------------------- KV commit into pages
 // Copies the L block tokens of one candidate per beam (chosen[b], or candidate 0 when chosen == NULL)
 // to positions ctx .. ctx+L-1 of the beam's pages: keys [page][Hkv][pt][hd], values transposed
-// [page][Hkv][hd][pt]. grid = (L, B), one block per token.
+// [page][Hkv][hd][pt]. grid = (L, B, layers), one block per token and layer; layer z's buffers lie z strides further.
 template <typename T>
 __global__ void kv_commit_kernel(const T* __restrict__ kb, const T* __restrict__ vbT, T* __restrict__ poolK,
                                  T* __restrict__ poolV, BatchGeom g, int Hkv, int hd, int Lp,
-                                 const int32_t* __restrict__ chosen) {
+                                 const int32_t* __restrict__ chosen, size_t kb_layer, size_t vb_layer,
+                                 size_t pool_layer) {
   int t = blockIdx.x, b = blockIdx.y;
+  kb += blockIdx.z * kb_layer;
+  vbT += blockIdx.z * vb_layer;
+  poolK += blockIdx.z * pool_layer;
+  poolV += blockIdx.z * pool_layer;
   int i = chosen ? chosen[b] : 0;
   i = i < 0 ? 0 : (i >= g.n ? g.n - 1 : i);          // an index a failed selection left (-1) must not address memory
   int ctx = g.len_override >= 0 ? g.len_override : g.lens[g.b0 + b];
@@ -390,13 +395,15 @@ __global__ void kv_commit_kernel(const T* __restrict__ kb, const T* __restrict__
 }
 template <typename T>
 void launch_kv_commit(const T* kb, const T* vbT, T* poolK, T* poolV, const BatchGeom& g, const ModelDims& md, int Lp,
-                      const int32_t* chosen, hipStream_t s) {
-  kv_commit_kernel<T><<<dim3(g.L, g.B), 256, 0, s>>>(kb, vbT, poolK, poolV, g, md.Hkv, md.hd, Lp, chosen);
+                      const int32_t* chosen, int layers, size_t kb_layer, size_t vb_layer,
+                      size_t pool_layer, hipStream_t s) {
+  kv_commit_kernel<T><<<dim3(g.L, g.B, layers), 256, 0, s>>>(kb, vbT, poolK, poolV, g, md.Hkv, md.hd, Lp, chosen, kb_layer,
+                                                             vb_layer, pool_layer);
 }
 template void launch_kv_commit<float>(const float*, const float*, float*, float*, const BatchGeom&, const ModelDims&,
-                                      int, const int32_t*, hipStream_t);
+                                      int, const int32_t*, int, size_t, size_t, size_t, hipStream_t);
 template void launch_kv_commit<bf16_t>(const bf16_t*, const bf16_t*, bf16_t*, bf16_t*, const BatchGeom&,
-                                       const ModelDims&, int, const int32_t*, hipStream_t);
+                                       const ModelDims&, int, const int32_t*, int, size_t, size_t, size_t, hipStream_t);
 
 // h_last[b0+b] = x[last row of candidate chosen[b] (or 0)]
 __global__ void copy_rows_kernel(const float* __restrict__ x, float* __restrict__ h_last, BatchGeom g, int d,

@@ -158,11 +158,95 @@ __global__ void __launch_bounds__(256) sample_pick_kernel(const float* __restric
   }
 }
 
+// Vocabularies of at most 4096 permitted ids: one block per row holds its logits in registers, four consecutive ids per
+// thread, and makes the same choice with one scan (two kernels: 4.3 + 6.8 us at 16 rows of 512 ids; 8.3 so. With 32
+// ids per thread for 32k ids the exponentials of a row, on one CU, take 38 us; the two kernels 4.5 + 9.2).
+__global__ void __launch_bounds__(1024) sample_row_kernel(const float* __restrict__ logits, int V, int limit,
+                                                          const double* __restrict__ u, int32_t* __restrict__ cand,
+                                                          float* __restrict__ tok_logp, int L, int t, int* status) {
+  constexpr int RUN = 4;
+  __shared__ float wmax[16];
+  __shared__ double wtotal[16];
+  __shared__ int first, last;
+  const int waves = blockDim.x >> 6;
+  const size_t row = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, k0 = tid * RUN;
+  const float* z = logits + row * (size_t)V;
+  const double uu = u[row * L + t];
+  float zr[RUN];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < RUN; ++k) zr[k] = k0 + k < limit ? z[k0 + k] : -INFINITY;
+#pragma unroll
+  for (int k = 0; k < RUN; ++k) mx = fmaxf(mx, zr[k]);
+  mx = wave_max(mx);
+  if (lane == 0) wmax[wave] = mx;
+  if (tid == 0) { first = INT_MAX; last = -1; }
+  __syncthreads();
+  for (int w = 0; w < waves; ++w) mx = fmaxf(mx, wmax[w]);
+  const double m = (double)mx;
+  double wt[RUN], mine = 0.0;
+#pragma unroll
+  for (int k = 0; k < RUN; ++k) {
+    wt[k] = k0 + k < limit ? exp((double)zr[k] - m) : 0.0;
+    mine += wt[k];
+  }
+  double incl = mine;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const double other = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += other;
+  }
+  if (lane == 63) wtotal[wave] = incl;
+  const double up = __shfl_up(incl, 1, 64);
+  __syncthreads();
+  double before = 0.0, total = 0.0;
+  for (int w = 0; w < waves; ++w) {
+    if (w == wave) before = total;
+    total += wtotal[w];
+  }
+  incl += before;
+  const double thr = uu * total;
+  const bool bad_u = !(uu >= 0.0 && uu < 1.0);
+  const bool bad_z = !(total > 0.0) || !(total < INFINITY) || !(mx > -INFINITY);
+  if (bad_u || bad_z) {
+    if (tid == 0) {
+      report_status(status, bad_u ? SPECS_ERANGE : SPECS_ENONFINITE);
+      cand[row * L + t] = 0;
+      tok_logp[row * L + t] = -INFINITY;
+    }
+    return;
+  }
+  // the first run of positive weight that crosses the threshold; none (rounding): the last run of positive weight
+  if (mine > 0.0) {
+    if (incl > thr) atomicMin(&first, tid);
+    atomicMax(&last, tid);
+  }
+  __syncthreads();
+  if (tid != (first != INT_MAX ? first : last)) return;
+  double c = before + (lane ? up : 0.0);
+  int pick = -1, positive = -1;
+#pragma unroll
+  for (int k = 0; k < RUN; ++k)
+    if (k0 + k < limit) {
+      c += wt[k];
+      if (wt[k] > 0.0) positive = k0 + k;
+      if (pick < 0 && first != INT_MAX && c > thr) pick = k0 + k;
+    }
+  if (pick < 0) pick = positive;
+  cand[row * L + t] = pick;
+  tok_logp[row * L + t] = (float)((double)z[pick] - m - log(total));
+}
+
 size_t sample_scratch_bytes(int rows) { return (size_t)rows * SAMPLE_CHUNKS * (sizeof(double) + sizeof(float)); }
 
 // scratch: sample_scratch_bytes(rows) bytes, 8-byte aligned
 void launch_sample_tokens(const float* logits, int rows, int V, int limit, const double* u, int32_t* cand,
                           float* tok_logp, int L, int t, void* scratch, int* status, hipStream_t s) {
+  if (limit <= 4096) {
+    sample_row_kernel<<<rows, (limit + 255) / 256 * 64, 0, s>>>(logits, V, limit, u, cand, tok_logp, L, t, status);
+    return;
+  }
   double* csum = (double*)scratch;
   float* cmax = (float*)(csum + (size_t)rows * SAMPLE_CHUNKS);
   sample_chunks_kernel<<<dim3(rows, SAMPLE_CHUNKS), 256, 0, s>>>(logits, V, limit, cmax, csum);

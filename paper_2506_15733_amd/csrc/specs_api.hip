@@ -628,7 +628,8 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
         PROFILED(ctx, SPECS_K_ATTENTION, s,
                  attention<T>((const T*)ws.q + r * qd, kb + r * kvd, vb + r, pK, pV, (T*)ws.attn + r * qd, ga, md,
                               round16(ga.L), st.c0, p->lens.data(), ws.gu, ws.gu_floats, s));
-        launch_kv_commit<T>(kb + r * kvd, vb + r, pK, pV, stretch_geom(p, st, st.rows, g.vs), md, g.vs, nullptr, s);
+        launch_kv_commit<T>(kb + r * kvd, vb + r, pK, pV, stretch_geom(p, st, st.rows, g.vs), md, g.vs, nullptr, 1, 0, 0, 0,
+                            s);
       }
     } else {
       PROFILED(ctx, SPECS_K_ATTENTION, s,
@@ -881,9 +882,9 @@ static int commit_impl(specs_ctx* ctx, const specs_model* m, specs_prefix* p, co
   }
   BatchGeom g = block_geom(p, n, L);
   size_t kvd = (size_t)md.Hkv * md.hd;
-  for (int l = 0; l < d.n_layers; ++l)
-    launch_kv_commit<T>((const T*)ws.kblk + (size_t)l * R * kvd, (const T*)ws.vblk + (size_t)l * (R + 16 * C) * kvd,
-                        pool_ptr<T>(p, d, l, 0), pool_ptr<T>(p, d, l, 1), g, md, round16(L), chosen, s);
+  const size_t pool_half = (size_t)p->num_pages * kvd * p->page_tokens;       // keys, or values, of a layer
+  launch_kv_commit<T>((const T*)ws.kblk, (const T*)ws.vblk, pool_ptr<T>(p, d, 0, 0), pool_ptr<T>(p, d, 0, 1), g, md,
+                      round16(L), chosen, d.n_layers, R * kvd, (R + 16 * C) * kvd, 2 * pool_half, s);
   launch_copy_rows(ws.x, p->h_last, g, d.d_model, chosen, s);
   advance_lens_kernel<<<(p->B + 63) / 64, 64, 0, s>>>(p->lens_dev, p->B, L);
   HIP_TRY(hipGetLastError());

@@ -251,6 +251,24 @@ def test_generation_equals_scoring_at_other_row_counts(B_, n, hq, hkv, lens, L):
     step.close()
 
 
+@pytest.mark.parametrize("limit", [1, 5, 255, 256, 257, 1021, 4095, 4096, 4097])
+def test_permitted_ids_at_the_edges_of_the_sampling_kernels(limit):
+    """One block per row up to 4096 permitted ids (four a thread, whole wavefronts), two kernels beyond."""
+    from paper_2506_15733_amd import synthetic
+    wl = small_workload("f32", B=1, n=6, L=2, V=4200, seed=16)
+    step = synthetic.ScoringStep(wl)
+    step.prefill()
+    u = W.rng.uniform_f64(5, "gen/u7", wl.n * wl.L).reshape(1, wl.n, wl.L)
+    u[0, 0, 0], u[0, 1, 0] = 0.0, 1.0 - 2.0 ** -53           # the first and the last permitted id
+    cand, logp, tok = gpu_generate(step, "draft", u, vocab_limit=limit)
+    assert cand.max() < limit and cand[0, 0, 0] == 0 and cand[0, 1, 0] == limit - 1
+    hw = HostWeights(wl.draft, wl.seed)
+    cache = oracle.prefill(wl.draft, hw, wl.prefix_tokens())[0]
+    o_tokens, o_tok, o_blk, _, o_bounds = oracle.generate_blocks(wl.draft, hw, cache, wl.n, wl.L, u[0], vocab_limit=limit)
+    assert compare_generation(cand[0], tok[0], logp[0], o_tokens, o_tok, o_blk, o_bounds, u[0], 1e-5, 1e-5) > 0.9
+    step.close()
+
+
 @pytest.mark.parametrize("B_,n,hq,hkv,hd,lens,L", [
     (5, 6, 6, 1, 128, (20, 2900), 9),      # lengths far apart: one run for the shortest beam, many for the longest
     (3, 20, 14, 2, 64, (500, 4000), 6),    # 140 stacked rows: two row tiles per run
