@@ -483,11 +483,37 @@ template void launch_prm_head<bf16_t>(const float*, const float*, const bf16_t*,
                                       hipStream_t);
 
 // ---------------------------------------------------------------- log-softmax merge + block sum
-// One block per candidate. A wavefront merges the per-tile (max, sum exp) partials of a row,
-// tok_logp = z[y] - (max + log sum); one thread then adds the L token terms in index order (fixed
+// The log-probability of a row's token from the per-tile (max, sum exp) partials of the row, by one wavefront:
+// z[y] - (max + log sum). A row's statistics are requested at once, since the kernels below are bound by the latency of
+// these loads (one after the other, 16 candidates x 128 rows of 152k ids took 78 us in the one-launch form, 36 so).
+__device__ __forceinline__ float row_logp(const float* __restrict__ pm, const float* __restrict__ ps, float z, int n_tiles,
+                                          int lane) {
+  constexpr int AHEAD = 16;                       // 1024 tiles
+  float pv[AHEAD], sv[AHEAD];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < AHEAD; ++k)
+    if (64 * k < n_tiles) {
+      const int j = min(64 * k + lane, n_tiles - 1);
+      pv[k] = pm[j];
+      sv[k] = ps[j];
+    }
+#pragma unroll
+  for (int k = 0; k < AHEAD; ++k)
+    if (64 * k < n_tiles) mx = fmaxf(mx, pv[k]);
+  for (int j = 64 * AHEAD + lane; j < n_tiles; j += 64) mx = fmaxf(mx, pm[j]);
+  mx = wave_max(mx);
+  float sm = 0.f;
+#pragma unroll
+  for (int k = 0; k < AHEAD; ++k)
+    if (64 * k + lane < n_tiles) sm += sv[k] * expf(pv[k] - mx);
+  for (int j = 64 * AHEAD + lane; j < n_tiles; j += 64) sm += ps[j] * expf(pm[j] - mx);
+  sm = wave_sum(sm);
+  return (float)((double)z - ((double)mx + log((double)sm)));
+}
+
+// One block per candidate: its wavefronts take the rows, then one thread adds the L token terms in index order (fixed
 // order => run-to-run identical), in double because the sum reaches ~1e3.
-// (As two launches, the second with one thread per candidate that read its terms one by one from memory: 15 + 12 us for
-// 16 candidates x 64 rows of 152k ids, 38 + 39 us at x 128 beside two other models.)
 __global__ void __launch_bounds__(1024) lmhead_merge_kernel(const float* __restrict__ part_max,
                                                             const float* __restrict__ part_sum,
                                                             const float* __restrict__ zt, int n_tiles,
@@ -501,39 +527,66 @@ __global__ void __launch_bounds__(1024) lmhead_merge_kernel(const float* __restr
     const int l1 = L - l0 < TERMS ? L : l0 + TERMS;
     for (int l = l0 + wave; l < l1; l += waves) {
       const size_t m = (size_t)blockIdx.x * L + l;
-      const float* pm = part_max + m * n_tiles;
-      const float* ps = part_sum + m * n_tiles;
-      float mx = -INFINITY;
-      for (int j = lane; j < n_tiles; j += 64) mx = fmaxf(mx, pm[j]);
-      mx = wave_max(mx);
-      float sm = 0.f;
-      for (int j = lane; j < n_tiles; j += 64) sm += ps[j] * expf(pm[j] - mx);
-      sm = wave_sum(sm);
-      if (lane == 0) terms[l - l0] = tok_logp[m] = (float)((double)zt[m] - ((double)mx + log((double)sm)));
+      const float v = row_logp(part_max + m * n_tiles, part_sum + m * n_tiles, zt[m], n_tiles, lane);
+      if (lane == 0) terms[l - l0] = tok_logp[m] = v;
     }
     __syncthreads();
     if (threadIdx.x == 0)
+#pragma unroll 8
       for (int l = l0; l < l1; ++l) acc += (double)terms[l - l0];
     __syncthreads();
   }
   if (threadIdx.x == 0) block_out[blockIdx.x] = (float)acc;
 }
 
-__global__ void block_sum_kernel(const float* __restrict__ tok_logp, float* __restrict__ block_out, int L, int C) {
-  int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= C) return;
+// The same without the sum, a row per wavefront, so that few candidates with many rows use the whole chip.
+__global__ void __launch_bounds__(256) lmhead_rows_kernel(const float* __restrict__ part_max,
+                                                          const float* __restrict__ part_sum,
+                                                          const float* __restrict__ zt, int n_tiles,
+                                                          float* __restrict__ tok_logp, int M) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const size_t m = (size_t)blockIdx.x * 4 + wave;
+  if (m >= (size_t)M) return;
+  const float v = row_logp(part_max + m * n_tiles, part_sum + m * n_tiles, zt[m], n_tiles, lane);
+  if (lane == 0) tok_logp[m] = v;
+}
+
+// One wavefront per candidate: it fetches 1024 terms at a time, one thread adds them in order.
+__global__ void __launch_bounds__(64) block_sum_kernel(const float* __restrict__ tok_logp, float* __restrict__ block_out,
+                                                       int L) {
+  constexpr int TERMS = 1024;
+  __shared__ float terms[TERMS];
+  const float* row = tok_logp + (size_t)blockIdx.x * L;
   double acc = 0.0;
-  for (int t = 0; t < L; ++t) acc += (double)tok_logp[(size_t)c * L + t];
-  block_out[c] = (float)acc;
+  for (int l0 = 0; l0 < L; l0 += TERMS) {
+    const int cnt = L - l0 < TERMS ? L - l0 : TERMS;
+    for (int l = threadIdx.x; l < cnt; l += 64) terms[l] = row[l0 + l];
+    __syncthreads();
+    if (threadIdx.x == 0)
+#pragma unroll 8
+      for (int l = 0; l < cnt; ++l) acc += (double)terms[l];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) block_out[blockIdx.x] = (float)acc;
 }
 
 void launch_block_sum(const float* tok_logp, float* block_out, int L, int C, hipStream_t s) {
-  block_sum_kernel<<<(C + 63) / 64, 64, 0, s>>>(tok_logp, block_out, L, C);
+  block_sum_kernel<<<C, 64, 0, s>>>(tok_logp, block_out, L);
 }
 
 // tok_scratch: [M] floats used when the caller does not want the per-token terms
 void launch_lmhead_merge(const float* part_max, const float* part_sum, const float* zt, int n_tiles, float* tok_logp,
                          float* tok_scratch, float* block_out, const BatchGeom& g, hipStream_t s) {
   float* tl = tok_logp ? tok_logp : tok_scratch;
-  lmhead_merge_kernel<<<g.B * g.n, 64 * (g.L < 16 ? g.L : 16), 0, s>>>(part_max, part_sum, zt, n_tiles, tl, block_out, g.L);
+  const int C = g.B * g.n;
+  // Few candidates with many statistics each: one block per candidate leaves most CUs idle, so the rows are dealt to the
+  // whole chip and a second launch adds them (16 x 64 rows x 594 tiles: 5.1 + 4.4 us against 19.0; 16 x 128 x 594: 6.6 +
+  // 4.5 against 35.9). With few statistics (8 x 32 x 125: 9.8 us) the second launch and its gap cost more than it gives, and
+  // from 256 candidates on one launch fills the chip.
+  if (C < 256 && (long)g.L * n_tiles > 16384) {
+    lmhead_rows_kernel<<<(g.M + 3) / 4, 256, 0, s>>>(part_max, part_sum, zt, n_tiles, tl, g.M);
+    launch_block_sum(tl, block_out, g.L, C, s);
+  } else {
+    lmhead_merge_kernel<<<C, 64 * (g.L < 16 ? g.L : 16), 0, s>>>(part_max, part_sum, zt, n_tiles, tl, block_out, g.L);
+  }
 }
