@@ -71,7 +71,7 @@ __global__ void __launch_bounds__(256) sample_pick_kernel(const float* __restric
                                                           float* __restrict__ tok_logp, int L, int t, int* status) {
   __shared__ double buf[256], wave_total[4];
   __shared__ float wmax[4];
-  __shared__ int sel;
+  __shared__ int sel, last;
   const size_t row = blockIdx.x;
   const int tid = threadIdx.x;
   const float* z = logits + row * (size_t)V;
@@ -80,7 +80,7 @@ __global__ void __launch_bounds__(256) sample_pick_kernel(const float* __restric
   float mx = tid < SAMPLE_CHUNKS ? cmax[row * SAMPLE_CHUNKS + tid] : -INFINITY;
   mx = wave_max(mx);
   if ((tid & 63) == 0) wmax[tid >> 6] = mx;
-  if (tid == 0) sel = INT_MAX;
+  if (tid == 0) { sel = INT_MAX; last = 0; }
   __syncthreads();
   mx = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
   const double m = (double)mx;
@@ -104,21 +104,15 @@ __global__ void __launch_bounds__(256) sample_pick_kernel(const float* __restric
     return;
   }
   // First chunk OF POSITIVE WEIGHT whose inclusive sum exceeds the threshold; none (rounding) -> the last chunk of
-  // positive weight. The scan adds the same terms in a different grouping for every position, so its values need
-  // not be monotone to the last bit: "first" is taken as a minimum over the threads that qualify (an LDS atomic),
-  // never as "the one whose predecessor does not qualify", which may hold for several threads or for a chunk of
-  // zero weight beyond the permitted ids.
+  // positive weight that the sum grows in. The scan adds the same terms in a different grouping for every position, so
+  // its values need not be monotone to the last bit: "first" is taken as a minimum over the threads that qualify (an
+  // LDS atomic), never as "the one whose predecessor does not qualify", and growth alone is no sign of weight; both
+  // may hold for a chunk of zero weight beyond the permitted ids. The two are written before the barrier and only read
+  // after it, so that all wavefronts take the same chunk.
   if (w > 0.0 && incl > thr) atomicMin(&sel, tid);
+  if (w > 0.0 && (tid == 0 || buf[tid] > buf[tid - 1])) atomicMax(&last, tid);
   __syncthreads();
-  if (sel == INT_MAX) {
-    if (tid == 0) {
-      int c = SAMPLE_CHUNKS - 1;
-      while (c > 0 && !(buf[c] > buf[c - 1])) --c;
-      sel = c;
-    }
-    __syncthreads();
-  }
-  const int chunk = sel;
+  const int chunk = sel != INT_MAX ? sel : last;
   const double before = chunk ? buf[chunk - 1] : 0.0;
   __syncthreads();                                     // buf is reused below
   // the same scan inside the chunk, over per-thread runs of ids

@@ -269,6 +269,23 @@ def test_permitted_ids_at_the_edges_of_the_sampling_kernels(limit):
     step.close()
 
 
+def test_uniforms_just_below_one_draw_the_last_permitted_id():
+    """4097 permitted ids fill 125 of the sampling kernel's 128 chunks, so the total and the running sum of the last
+    chunk in use are grouped differently, and with u = 1 - 2^-53 no chunk exceeds u times the total in about one row of
+    eleven (its sums modelled in numpy, normal logits): the kernel then falls back on the last chunk of positive weight.
+    Every id has about 1/4097 of the probability, far above a rounding error, so the draw is the last permitted id."""
+    from paper_2506_15733_amd import synthetic
+    wl = small_workload("f32", B=8, n=8, L=8, V=4200, seed=17)
+    step = synthetic.ScoringStep(wl)
+    step.prefill()
+    u = W.rng.uniform_f64(6, "gen/u8", wl.B * wl.n * wl.L).reshape(wl.B, wl.n, wl.L)
+    u[:, :, 1::2] = 1.0 - 2.0 ** -53                         # every second position, so that the histories differ
+    cand, _, _ = gpu_generate(step, "draft", u, vocab_limit=4097)
+    assert np.all(cand[:, :, 1::2] == 4096)
+    assert len(np.unique(cand[:, :, ::2])) > 100
+    step.close()
+
+
 @pytest.mark.parametrize("B_,n,hq,hkv,hd,lens,L", [
     (5, 6, 6, 1, 128, (20, 2900), 9),      # lengths far apart: one run for the shortest beam, many for the longest
     (3, 20, 14, 2, 64, (500, 4000), 6),    # 140 stacked rows: two row tiles per run
