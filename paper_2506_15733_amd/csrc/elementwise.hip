@@ -485,7 +485,8 @@ template void launch_prm_head<bf16_t>(const float*, const float*, const bf16_t*,
 // ---------------------------------------------------------------- log-softmax merge + block sum
 // The log-probability of a row's token from the per-tile (max, sum exp) partials of the row, by one wavefront:
 // z[y] - (max + log sum). A row's statistics are requested at once, since the kernels below are bound by the latency of
-// these loads (one after the other, 16 candidates x 128 rows of 152k ids took 78 us in the one-launch form, 36 so).
+// these loads (16 candidates x 128 rows of 152k ids, a wavefront walking eight rows: 78 us with one load after the
+// other, 36 so).
 __device__ __forceinline__ float row_logp(const float* __restrict__ pm, const float* __restrict__ ps, float z, int n_tiles,
                                           int lane) {
   constexpr int AHEAD = 16;                       // 1024 tiles
@@ -512,34 +513,27 @@ __device__ __forceinline__ float row_logp(const float* __restrict__ pm, const fl
   return (float)((double)z - ((double)mx + log((double)sm)));
 }
 
-// One block per candidate: its wavefronts take the rows, then one thread adds the L token terms in index order (fixed
-// order => run-to-run identical), in double because the sum reaches ~1e3.
+// One block per candidate of at most 16 rows, a wavefront per row; one thread then adds the L token terms in index order
+// (fixed order => run-to-run identical), in double because the sum reaches ~1e3.
 __global__ void __launch_bounds__(1024) lmhead_merge_kernel(const float* __restrict__ part_max,
                                                             const float* __restrict__ part_sum,
                                                             const float* __restrict__ zt, int n_tiles,
                                                             float* __restrict__ tok_logp, float* __restrict__ block_out,
                                                             int L) {
-  constexpr int TERMS = 1024;                     // token terms kept at a time
-  __shared__ float terms[TERMS];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, waves = blockDim.x >> 6;
+  __shared__ float terms[16];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const size_t m = (size_t)blockIdx.x * L + wave;
+  const float v = row_logp(part_max + m * n_tiles, part_sum + m * n_tiles, zt[m], n_tiles, lane);
+  if (lane == 0) terms[wave] = tok_logp[m] = v;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
   double acc = 0.0;
-  for (int l0 = 0; l0 < L; l0 += TERMS) {
-    const int l1 = L - l0 < TERMS ? L : l0 + TERMS;
-    for (int l = l0 + wave; l < l1; l += waves) {
-      const size_t m = (size_t)blockIdx.x * L + l;
-      const float v = row_logp(part_max + m * n_tiles, part_sum + m * n_tiles, zt[m], n_tiles, lane);
-      if (lane == 0) terms[l - l0] = tok_logp[m] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0)
 #pragma unroll 8
-      for (int l = l0; l < l1; ++l) acc += (double)terms[l - l0];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) block_out[blockIdx.x] = (float)acc;
+  for (int l = 0; l < L; ++l) acc += (double)terms[l];
+  block_out[blockIdx.x] = (float)acc;
 }
 
-// The same without the sum, a row per wavefront, so that few candidates with many rows use the whole chip.
+// The same without the sum, for any number of rows.
 __global__ void __launch_bounds__(256) lmhead_rows_kernel(const float* __restrict__ part_max,
                                                           const float* __restrict__ part_sum,
                                                           const float* __restrict__ zt, int n_tiles,
@@ -579,14 +573,15 @@ void launch_lmhead_merge(const float* part_max, const float* part_sum, const flo
                          float* tok_scratch, float* block_out, const BatchGeom& g, hipStream_t s) {
   float* tl = tok_logp ? tok_logp : tok_scratch;
   const int C = g.B * g.n;
-  // Few candidates with many statistics each: one block per candidate leaves most CUs idle, so the rows are dealt to the
-  // whole chip and a second launch adds them (16 x 64 rows x 594 tiles: 5.1 + 4.4 us against 19.0; 16 x 128 x 594: 6.6 +
-  // 4.5 against 35.9). With few statistics (8 x 32 x 125: 9.8 us) the second launch and its gap cost more than it gives, and
-  // from 256 candidates on one launch fills the chip.
-  if (C < 256 && (long)g.L * n_tiles > 16384) {
+  // A row takes its wavefront about 3.5 us whatever the number of tiles (loads, exponentials and a double logarithm, one
+  // after the other), so every row gets a wavefront of its own. One launch does for blocks of at most 16 rows, up to the
+  // rows that the chip holds at once: 4 x 16 rows x 8 tiles 6.3 us, 256 x 16 x 594 6.9, against 6.8 and 8.4 in two
+  // launches; but 1024 x 16 x 594 24.6 against 19.2. Wavefronts that walk the rows of a longer block are behind from two
+  // rows on: 8 x 32 x 125 9.8 against 6.6, 8 x 128 x 8 30.4 against 7.0, 8 x 2048 x 8 439 against 47.
+  if (g.L <= 16 && g.M <= 4096) {
+    lmhead_merge_kernel<<<C, 64 * g.L, 0, s>>>(part_max, part_sum, zt, n_tiles, tl, block_out, g.L);
+  } else {
     lmhead_rows_kernel<<<(g.M + 3) / 4, 256, 0, s>>>(part_max, part_sum, zt, n_tiles, tl, g.M);
     launch_block_sum(tl, block_out, g.L, C, s);
-  } else {
-    lmhead_merge_kernel<<<C, 64 * (g.L < 16 ? g.L : 16), 0, s>>>(part_max, part_sum, zt, n_tiles, tl, block_out, g.L);
   }
 }

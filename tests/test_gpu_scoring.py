@@ -604,24 +604,26 @@ def test_prefill_of_several_prompts_equals_one_by_one(dtype, hd, page_tokens, le
             assert np.abs(g - w).max() < tol * max(1.0, np.abs(w).max()), (i, n)
 
 
-def test_block_sums_on_both_sides_of_the_merge_rule():
-    """Statistics of a candidate (rows x 129 tiles of 256 ids) up to which one block merges and adds them (127 rows), and
-    beyond (128: a wavefront per row, then the sum): the sum is the one in index order, bit for bit, and the terms of the
+@pytest.mark.parametrize("sizes", [((3, 16), (3, 17)), ((3, 1), (3, 2)), ((256, 16), (257, 16)), ((3, 127), (3, 128))])
+def test_block_sums_on_both_sides_of_the_merge_rule(sizes):
+    """(Candidates, rows) up to which one block merges and adds a candidate's statistics (16 rows, 4096 over all), and
+    beyond (a wavefront per row, then the sum): the sum is the one in index order, bit for bit, and the terms of the
     rows both have agree (bf16: products of other shapes, the bound used elsewhere in this file)."""
     from paper_2506_15733_amd import synthetic
-    toks = {}
-    for L in (127, 128):
+    toks = []
+    for n, L in sizes:
         mk = lambda role, head: ModelDesc(role, 1, 128, 4, 2, 64, 128, 33000, "bf16", head)
-        wl = Workload("merge_rule", mk("target", "lm"), mk("draft", "lm"), mk("prm", "prm"), B=1, n=3, L=L, prefix_len=40,
+        wl = Workload("merge_rule", mk("target", "lm"), mk("draft", "lm"), mk("prm", "prm"), B=1, n=n, L=L, prefix_len=40,
                       betas=(1.0,), token_dist="uniform", page_tokens=16, seed=51, u_seed=52)
         step = synthetic.ScoringStep(wl)
         step.prefill()
-        cand = W.rng.uniform_tokens(53, "merge", 3 * 128, 33000).reshape(1, 3, 128)[:, :, :L]
+        cand = W.rng.uniform_tokens(53, "merge", 257 * 128, 33000).reshape(1, 257, 128)[:, :n, :L]
         step.cand = torch.from_numpy(np.ascontiguousarray(cand)).to(step.device)
         step.score("target")
         torch.cuda.synchronize()
-        toks[L] = step.tok["target"].cpu().numpy().reshape(3, L)
-        want = np.float32([np.cumsum(r.astype(np.float64))[-1] for r in toks[L]])
-        assert np.array_equal(step.out["target"].cpu().numpy().reshape(3), want)
+        toks.append(step.tok["target"].cpu().numpy().reshape(n, L))
+        want = np.float32([np.cumsum(r.astype(np.float64))[-1] for r in toks[-1]])
+        assert np.array_equal(step.out["target"].cpu().numpy().reshape(n), want)
         step.close()
-    assert np.abs(toks[127] - toks[128][:, :127]).max() < 2e-2
+    n, L = np.minimum(*sizes)
+    assert np.abs(toks[0][:n, :L] - toks[1][:n, :L]).max() < 2e-2
