@@ -269,6 +269,16 @@ extern "C" int specs_ctx_profile_read(specs_ctx* ctx, float* total_ms, int32_t* 
       } else { stmt; }                                                \
     } else { stmt; }                                                  \
   } while (0)
+// The same for an attempt that may find no kernel for the shape: counted only if `taken` became true.
+#define PROFILED_IF(ctx, cls, s, taken, attempt)                      \
+  do {                                                                \
+    const size_t recs_ = (ctx)->prof.recs.size();                     \
+    PROFILED(ctx, cls, s, taken = attempt);                           \
+    if (!(taken) && (ctx)->prof.recs.size() > recs_) {                \
+      (ctx)->prof.recs.pop_back();                                    \
+      (ctx)->prof.used -= 2;                                          \
+    }                                                                 \
+  } while (0)
 
 extern "C" int specs_ctx_status(specs_ctx* ctx, int* device_status) {
   if (!ctx || !device_status) return SPECS_EINVAL;
@@ -571,16 +581,16 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
     // small float models: normalisation and rotary embedding inside the projection
     bool fused_rope = false;
     if (!normed)
-      PROFILED(ctx, SPECS_K_QKV, s,
-               fused_rope = norm_qkv_rope<T>(x, L.g_attn, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, s));
+      PROFILED_IF(ctx, SPECS_K_QKV, s, fused_rope,
+                  norm_qkv_rope<T>(x, L.g_attn, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, s));
     if (!normed && !fused_rope)
       PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(x, L.g_attn, (T*)ws.a, g.M, md.d, md.eps, s));
     // whole-block bf16 launches: rotary embedding, conversion and value transposition inside the projection's epilogue
     // (one position per block writes a column of the transposed values, a cache line per element, which the two or
     // three workgroups of the value heads alone are slow at: those launches leave it to the kernel below)
     if (!fused_rope && g.L > 1)
-      PROFILED(ctx, SPECS_K_QKV, s,
-               fused_rope = qkv_rope_fused<T>((const T*)ws.a, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, s));
+      PROFILED_IF(ctx, SPECS_K_QKV, s, fused_rope,
+                  qkv_rope_fused<T>((const T*)ws.a, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, s));
     if (!fused_rope) {
       int qkv_parts = 1;                                 // ws.qkv has room for R / g.M slices of the projection
       PROFILED(ctx, SPECS_K_QKV, s,
@@ -605,8 +615,8 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
                  launch_add_partials_rmsnorm<T>(ws.xs, ws.gu, pl, 0, L.g_ffn, (T*)ws.a, gl.M, md.d, md.eps, s));
       bool fused_ffn = false;
       if (!pl)
-        PROFILED(ctx, SPECS_K_GATE_UP, s,
-                 fused_ffn = norm_gate_up<T>(ws.xs, L.g_ffn, (const T*)L.wgu, (T*)ws.act, gl.M, md.F, md.d, md.eps, s));
+        PROFILED_IF(ctx, SPECS_K_GATE_UP, s, fused_ffn,
+                    norm_gate_up<T>(ws.xs, L.g_ffn, (const T*)L.wgu, (T*)ws.act, gl.M, md.F, md.d, md.eps, s));
       if (!pl && !fused_ffn)
         PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(ws.xs, L.g_ffn, (T*)ws.a, gl.M, md.d, md.eps, s));
       if (!fused_ffn)
@@ -644,8 +654,8 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
                launch_add_partials_rmsnorm<T>(x, ws.gu, parts, 0, L.g_ffn, (T*)ws.a, g.M, md.d, md.eps, s));
     bool fused_ffn = false;
     if (!parts)
-      PROFILED(ctx, SPECS_K_GATE_UP, s,
-               fused_ffn = norm_gate_up<T>(x, L.g_ffn, (const T*)L.wgu, (T*)ws.act, g.M, md.F, md.d, md.eps, s));
+      PROFILED_IF(ctx, SPECS_K_GATE_UP, s, fused_ffn,
+                  norm_gate_up<T>(x, L.g_ffn, (const T*)L.wgu, (T*)ws.act, g.M, md.F, md.d, md.eps, s));
     if (!parts && !fused_ffn)
       PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(x, L.g_ffn, (T*)ws.a, g.M, md.d, md.eps, s));
     if (!fused_ffn)

@@ -627,3 +627,24 @@ def test_block_sums_on_both_sides_of_the_merge_rule(sizes):
         step.close()
     n, L = np.minimum(*sizes)
     assert np.abs(toks[0][:n, :L] - toks[1][:n, :L]).max() < 2e-2
+
+
+@pytest.mark.parametrize("kind", ["f32", "bf16", "bf16_mfma"])
+def test_kernel_timings_count_one_launch_per_layer(kind):
+    """Fused kernels (small float models), the plain ones (odd bf16 shapes) and the matrix-unit ones: an attempt that finds
+    no kernel for a shape is no launch. The reward model computes its last layer for one row per block, with the same
+    number of projections."""
+    from paper_2506_15733_amd import synthetic, binding as B
+    wl = mfma_ragged_workload() if kind == "bf16_mfma" else ragged_workload(kind)
+    step = synthetic.ScoringStep(wl)
+    step.prefill()
+    for role in ("target", "draft", "prm"):
+        ctx, layers = step.models[role].ctx, wl.models()[role].n_layers
+        B.specs_ctx_profile(ctx, True)
+        step.score(role)
+        torch.cuda.synchronize()
+        got = {k: n for k, (_, n) in B.specs_ctx_profile_read(ctx).items()}
+        B.specs_ctx_profile(ctx, False)
+        assert [got[k] for k in ("qkv", "attention", "oproj", "gate_up", "down")] == [layers] * 5, (role, got)
+        assert got["lmhead"] == (role != "prm"), (role, got)
+    step.close()
