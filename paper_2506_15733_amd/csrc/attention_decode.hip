@@ -6,8 +6,8 @@
 #include "common.h"
 
 bool launch_attention_mfma_decode_prefix(const bf16_t* q, const bf16_t* poolK, const bf16_t* poolV, const BatchGeom& g,
-                                         const ModelDims& md, const int32_t* lens_host, float* part, size_t part_floats,
-                                         int* run_tiles_out, int* n_splits_out, hipStream_t s);
+                                         const ModelDims& md, const DecodeRuns& runs, float* part, size_t part_floats,
+                                         hipStream_t s);
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -259,20 +259,18 @@ __global__ void __launch_bounds__(64) attention_decode_merge_long_kernel(MergeAr
   }
 }
 
-// Returns false when the shape is not taken (the caller then uses the plain kernel). lens_host: the prefix lengths of
-// all beams of the prefix handle, as g.lens holds them on the device.
+// Returns false when the shape is not taken (the caller then uses the plain kernel).
 bool launch_attention_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                              const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,
-                             const int32_t* lens_host, float* part, size_t part_floats, hipStream_t s) {
-  int run_tiles = 0, n_splits = 0;
-  if (!launch_attention_mfma_decode_prefix(q, poolK, poolV, g, md, lens_host, part, part_floats, &run_tiles, &n_splits, s))
-    return false;
+                             const DecodeRuns& runs, float* part, size_t part_floats, hipStream_t s) {
+  if (!launch_attention_mfma_decode_prefix(q, poolK, poolV, g, md, runs, part, part_floats, s)) return false;
+  const int n_splits = runs.count;
   const size_t rows_all = (size_t)g.B * md.Hkv * n_splits * g.n * (md.Hq / md.Hkv);
   MergeArgs a;
   a.q = q; a.kb = kb; a.vbT = vbT; a.out = out;
   a.part_o = part; a.part_m = part + rows_all * md.hd; a.part_l = a.part_m + rows_all;
   a.lens = g.lens; a.b0 = g.b0; a.len_override = g.len_override;
-  a.n = g.n; a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lk = g.Lk; a.Lp = Lp; a.t = g.t0; a.run_tiles = run_tiles;
+  a.n = g.n; a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lk = g.Lk; a.Lp = Lp; a.t = g.t0; a.run_tiles = runs.tiles;
   a.n_splits = n_splits;
   a.scale_log2e = 1.4426950408889634f / sqrtf((float)md.hd);
   const int gq = md.Hq / md.Hkv, HS = gq < 16 ? gq : 16, Lq = (Lp + 31) & ~31;

@@ -505,13 +505,51 @@ bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT,
   return true;
 }
 
-// Prefix part of a single-position launch (g.L == 1): partial results per (beam, kv head, run of key tiles, row).
-// run_tiles_out / n_splits_out describe the partial buffers' layout to the merge kernel. part_floats: room in
-// `part` (floats); returns false if the shape is not taken or the partials would not fit.
+// How a single-position launch cuts prefixes of lens[0 .. B) tokens: the shortest run that keeps all workgroups resident
+// (two per CU), and at most DECODE_MAX_RUNS partial results per row for the merge to read. units: workgroups per run of a
+// beam; per_split: floats of the partial results of one run of every beam. (An equal number of runs for every beam, 8 at
+// 32 beams of 1k-8k tokens: 35.5 us, the longest beam's workgroups last; runs of equal length, and no stores for the 80 of
+// 128 rows that hold no query: 30.7.)
+// Longer runs give fewer workgroups and fewer partial results, so the search is by bisection: where no run length meets
+// the limits (more than 512 units) it would otherwise go through every length of the longest prefix and all beams.
+DecodeRuns plan_decode_runs(const int32_t* lens, int B, int len_override, long units, size_t per_split, size_t part_floats) {
+  auto tiles_of = [&](int b) { return ((len_override >= 0 ? len_override : lens[b]) + 63) / 64; };
+  int max_tiles = 1;
+  long sum_tiles = 0;
+  for (int b = 0; b < B; ++b) {
+    const int t = tiles_of(b);
+    max_tiles = t > max_tiles ? t : max_tiles;
+    sum_tiles += t;
+  }
+  auto fits = [&](int run) {
+    if ((size_t)((max_tiles + run - 1) / run) * per_split > part_floats) return false;
+    long wgs = 0;
+    for (int b = 0; b < B; ++b) wgs += (tiles_of(b) + run - 1) / run;
+    return wgs * units <= 512;
+  };
+  const long least = sum_tiles * units / 512;
+  int lo = (max_tiles + DECODE_MAX_RUNS - 1) / DECODE_MAX_RUNS, hi = max_tiles;
+  if (least > lo) lo = least < max_tiles ? (int)least : max_tiles;
+  while (lo < hi) {
+    const int mid = (lo + hi) / 2;
+    if (fits(mid)) hi = mid;
+    else lo = mid + 1;
+  }
+  return {lo, (max_tiles + lo - 1) / lo};
+}
+DecodeRuns plan_decode_runs(const BatchGeom& g, const ModelDims& md, const int32_t* lens_host, size_t part_floats) {
+  const int rows = g.n * (md.Hq / md.Hkv);
+  return plan_decode_runs(lens_host + g.b0, g.B, g.len_override, (long)md.Hkv * ((rows + 127) / 128),
+                          (size_t)g.B * md.Hkv * rows * (md.hd + 2), part_floats);
+}
+
+// Prefix part of a single-position launch (g.L == 1): partial results per (beam, kv head, run of key tiles, row), in runs
+// as plan_decode_runs gives them. part_floats: room in `part` (floats); returns false if the shape is not taken or the
+// partials would not fit.
 bool launch_attention_mfma_decode_prefix(const bf16_t* q, const bf16_t* poolK, const bf16_t* poolV, const BatchGeom& g,
-                                         const ModelDims& md, const int32_t* lens_host, float* part, size_t part_floats,
-                                         int* run_tiles_out, int* n_splits_out, hipStream_t s) {
-  if ((md.hd != 64 && md.hd != 128) || g.page_tokens != 16 || g.L != 1) return false;
+                                         const ModelDims& md, const DecodeRuns& runs, float* part, size_t part_floats,
+                                         hipStream_t s) {
+  if ((md.hd != 64 && md.hd != 128) || g.page_tokens != 16 || g.L != 1 || runs.count < 1) return false;
   AttnArgs a;
   a.last_first = 0;
   a.q = q; a.kb = nullptr; a.vbT = nullptr; a.poolK = poolK; a.poolV = poolV; a.out = nullptr; a.g = g;
@@ -519,32 +557,10 @@ bool launch_attention_mfma_decode_prefix(const bf16_t* q, const bf16_t* poolK, c
   a.scale_log2e = 1.4426950408889634f / sqrtf((float)md.hd);
   const int rows = g.n * (md.Hq / md.Hkv);
   a.q_tiles = (rows + 127) / 128;
-  auto tiles_of = [&](int b) { return ((g.len_override >= 0 ? g.len_override : lens_host[g.b0 + b]) + 63) / 64; };
-  int max_tiles = 1;
-  long sum_tiles = 0;
-  for (int b = 0; b < g.B; ++b) {
-    const int t = tiles_of(b);
-    max_tiles = t > max_tiles ? t : max_tiles;
-    sum_tiles += t;
-  }
-  // (An equal number of runs for every beam, 8 at 32 beams of 1k-8k tokens: 35.5 us, the longest beam's workgroups last;
-  // runs of equal length, and no stores for the 80 of 128 rows that hold no query: 30.7.)
-  // The shortest run that keeps all workgroups resident (two per CU), and at most DECODE_MAX_RUNS partial results per
-  // row for the merge to read.
-  const size_t per_split = (size_t)g.B * md.Hkv * rows * (md.hd + 2);
-  int run = (max_tiles + DECODE_MAX_RUNS - 1) / DECODE_MAX_RUNS;
-  const long least = sum_tiles * md.Hkv * a.q_tiles / 512;
-  if (least > run) run = least < max_tiles ? (int)least : max_tiles;
-  for (;; ++run) {
-    long wgs = 0;
-    for (int b = 0; b < g.B; ++b) wgs += (tiles_of(b) + run - 1) / run;
-    if (run >= max_tiles || (wgs * md.Hkv * a.q_tiles <= 512 && (size_t)((max_tiles + run - 1) / run) * per_split <= part_floats))
-      break;
-  }
-  a.run_tiles = run;
-  a.n_splits = (max_tiles + run - 1) / run;
-  if ((size_t)a.n_splits * per_split > part_floats) return false;
+  a.run_tiles = runs.tiles;
+  a.n_splits = runs.count;
   const size_t rows_all = (size_t)g.B * md.Hkv * a.n_splits * rows;
+  if (rows_all * (md.hd + 2) > part_floats) return false;
   a.part_o = part;
   a.part_m = part + rows_all * md.hd;
   a.part_l = a.part_m + rows_all;
@@ -553,7 +569,5 @@ bool launch_attention_mfma_decode_prefix(const bf16_t* q, const bf16_t* poolK, c
   a.wg_per_xcd = (entries + 7) / 8 * a.q_tiles;
   if (md.hd == 128) launch_attn_variant<128, 1, 1>(a, s);
   else launch_attn_variant<64, 1, 1>(a, s);
-  *run_tiles_out = run;
-  *n_splits_out = a.n_splits;
   return true;
 }

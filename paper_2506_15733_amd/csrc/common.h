@@ -138,11 +138,14 @@ bool launch_attention_pingpong(const bf16_t* q, const bf16_t* kb, const bf16_t* 
 
 enum { DECODE_MAX_RUNS = 32 };   // runs of prefix tiles a beam is cut into at most
 // One in-block position per candidate (g.L == 1, position g.t0): prefix keys by the MFMA kernel in split mode,
-// merged with the candidate's own block keys. lens_host: what g.lens holds. part: scratch of part_floats floats. False
-// if the shape is not taken.
+// merged with the candidate's own block keys. runs: how the prefixes are cut, from the host's lengths (lens_host: of all
+// beams of the prefix handle, as g.lens holds them on the device); it depends on nothing that changes inside a pass.
+// part: scratch of part_floats floats. False if the shape is not taken.
+struct DecodeRuns { int tiles, count; };   // key tiles of a run, runs of the longest prefix
+DecodeRuns plan_decode_runs(const BatchGeom& g, const ModelDims& md, const int32_t* lens_host, size_t part_floats);
 bool launch_attention_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                              const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,
-                             const int32_t* lens_host, float* part, size_t part_floats, hipStream_t s);
+                             const DecodeRuns& runs, float* part, size_t part_floats, hipStream_t s);
 
 // Fused vocabulary head: per (row, 64-column tile) partial (max, sum exp) and the target-token logit.
 template <typename T>

@@ -510,10 +510,11 @@ int lmhead_partials<bf16_t>(const bf16_t* A, const bf16_t* W, const int32_t* tok
   return tiles;
 }
 
-// scratch: floats free for the duration of the call (partial results of single-position launches)
+// runs, scratch (floats free for the duration of the call): how a single-position launch cuts the prefixes, and the room
+// for its partial results
 template <typename T>
 static void attention(const T* q, const T* kb, const T* vbT, const T* pK, const T* pV, T* out, const BatchGeom& g,
-                      const ModelDims& md, int Lp, int max_ctx, const int32_t* lens_host, float* scratch,
+                      const ModelDims& md, int Lp, int max_ctx, const DecodeRuns& runs, float* scratch,
                       size_t scratch_floats, hipStream_t s);
 
 // A stretch of one beam's prompt in a prefill launch: tokens c0 .. c0 + rows - 1 of beam b, in rows `row` .. of the
@@ -570,6 +571,9 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
     return (int)(room < MFMA_MAX_SPLIT ? room : MFMA_MAX_SPLIT);
   };
   const int max_split = max_split_of(g.M);
+  DecodeRuns runs = {};
+  if (d.dtype == SPECS_BF16 && !stretches && (g.L == 1 || last_token_only))
+    runs = plan_decode_runs(g, md, p->lens.data(), ws.gu_floats);
   bool normed = false;                                   // ws.a already holds RMSNorm(x) * g_attn of this layer
   for (int l = 0; l < d.n_layers; ++l) {
     const specs_layer_weights& L = m->layers[l];
@@ -605,7 +609,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
       PROFILED(ctx, SPECS_K_OTHER, s,
                launch_gather_last_rows<T>((const T*)ws.q, q1, qd, x, ws.xs, md.d, (int)C, g.L, s));
       PROFILED(ctx, SPECS_K_ATTENTION, s,
-               attention<T>(q1, kb, vb, pK, pV, (T*)ws.attn, gl, md, Lp, max_ctx, p->lens.data(), ws.gu,
+               attention<T>(q1, kb, vb, pK, pV, (T*)ws.attn, gl, md, Lp, max_ctx, runs, ws.gu,
                             ws.gu_floats, s));
       int pl = 0;
       PROFILED(ctx, SPECS_K_OPROJ, s,
@@ -637,13 +641,13 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
         const BatchGeom ga = stretch_geom(p, st, span(i), g.vs);
         PROFILED(ctx, SPECS_K_ATTENTION, s,
                  attention<T>((const T*)ws.q + r * qd, kb + r * kvd, vb + r, pK, pV, (T*)ws.attn + r * qd, ga, md,
-                              round16(ga.L), st.c0, p->lens.data(), ws.gu, ws.gu_floats, s));
+                              round16(ga.L), st.c0, runs, ws.gu, ws.gu_floats, s));
         launch_kv_commit<T>(kb + r * kvd, vb + r, pK, pV, stretch_geom(p, st, st.rows, g.vs), md, g.vs, nullptr, 1, 0, 0, 0,
                             s);
       }
     } else {
       PROFILED(ctx, SPECS_K_ATTENTION, s,
-               attention<T>((const T*)ws.q, kb, vb, pK, pV, (T*)ws.attn, g, md, Lp, max_ctx, p->lens.data(),
+               attention<T>((const T*)ws.q, kb, vb, pK, pV, (T*)ws.attn, g, md, Lp, max_ctx, runs,
                             ws.gu, ws.gu_floats, s));
     }
     int parts = 0;
@@ -1022,7 +1026,7 @@ extern "C" int specs_op_lmhead_logprob(specs_ctx* ctx, int32_t dtype, const void
 
 template <typename T>
 static void attention(const T* q, const T* kb, const T* vbT, const T* pK, const T* pV, T* out, const BatchGeom& g,
-                      const ModelDims& md, int Lp, int max_ctx, const int32_t* lens_host, float* scratch,
+                      const ModelDims& md, int Lp, int max_ctx, const DecodeRuns& runs, float* scratch,
                       size_t scratch_floats, hipStream_t s) {
   count_path(SPECS_PATH_ATTN_PLAIN);
   launch_attention_simple<T>(q, kb, vbT, pK, pV, out, g, md, max_ctx, s);
@@ -1030,7 +1034,7 @@ static void attention(const T* q, const T* kb, const T* vbT, const T* pK, const 
 template <>
 void attention<bf16_t>(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* pK, const bf16_t* pV,
                        bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp, int max_ctx,
-                       const int32_t* lens_host, float* scratch, size_t scratch_floats, hipStream_t s) {
+                       const DecodeRuns& runs, float* scratch, size_t scratch_floats, hipStream_t s) {
   bool whole_blocks = g.t0 == 0 && g.Lk == g.L;
   // Launches with at least ~160 workgroups of 256 stacked rows take the two-phase kernel (measured 3-8 % faster
   // at the 7B shapes); smaller ones the one-phase kernel, which cuts long key lists over several workgroups.
@@ -1045,7 +1049,7 @@ void attention<bf16_t>(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, con
       return;
     }
   } else if (g.L == 1 && scratch &&
-             launch_attention_decode(q, kb, vbT, pK, pV, out, g, md, Lp, lens_host, scratch, scratch_floats, s)) {
+             launch_attention_decode(q, kb, vbT, pK, pV, out, g, md, Lp, runs, scratch, scratch_floats, s)) {
     count_path(SPECS_PATH_ATTN_MFMA);
     return;
   }
@@ -1070,11 +1074,11 @@ extern "C" int specs_op_attention(specs_ctx* ctx, const specs_model* m, const sp
   if (d.dtype == SPECS_BF16) {
     launch_transpose_v<bf16_t>((const bf16_t*)vb, (bf16_t*)vT, cands, md.Hkv, md.hd, L, Lp, ctx->stream);
     attention<bf16_t>((const bf16_t*)q, (const bf16_t*)kb, (const bf16_t*)vT, pool_ptr<bf16_t>(p, d, layer, 0),
-                      pool_ptr<bf16_t>(p, d, layer, 1), (bf16_t*)out, g, md, Lp, max_ctx, p->lens.data(), nullptr, 0, ctx->stream);
+                      pool_ptr<bf16_t>(p, d, layer, 1), (bf16_t*)out, g, md, Lp, max_ctx, DecodeRuns{}, nullptr, 0, ctx->stream);
   } else {
     launch_transpose_v<float>((const float*)vb, (float*)vT, cands, md.Hkv, md.hd, L, Lp, ctx->stream);
     attention<float>((const float*)q, (const float*)kb, (const float*)vT, pool_ptr<float>(p, d, layer, 0),
-                     pool_ptr<float>(p, d, layer, 1), (float*)out, g, md, Lp, max_ctx, p->lens.data(), nullptr, 0, ctx->stream);
+                     pool_ptr<float>(p, d, layer, 1), (float*)out, g, md, Lp, max_ctx, DecodeRuns{}, nullptr, 0, ctx->stream);
   }
   HIP_TRY(hipGetLastError());
   ctx->last_model = nullptr;
