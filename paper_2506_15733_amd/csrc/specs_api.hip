@@ -432,6 +432,9 @@ int gemm_store_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* C, int max
   return 1;
 }
 
+// Rotary embedding, conversion and value transposition inside the projection's epilogue: bf16 launches of whole blocks.
+// (One position per block writes a column of the transposed values, a cache line per element, which the two or three
+// workgroups of the value heads alone are slow at: those launches leave it to the rotary kernel.)
 template <typename T>
 static bool qkv_rope_fused(const T*, const T*, const float*, T*, T*, T*, const BatchGeom&, const ModelDims&, int,
                            hipStream_t) {
@@ -440,7 +443,7 @@ static bool qkv_rope_fused(const T*, const T*, const float*, T*, T*, T*, const B
 template <>
 bool qkv_rope_fused<bf16_t>(const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q, bf16_t* kb, bf16_t* vT,
                             const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s) {
-  if (!launch_gemm_mfma_qkv_rope(A, W, cs, q, kb, vT, g, md, Lp, -1, s)) return false;
+  if (g.L == 1 || !launch_gemm_mfma_qkv_rope(A, W, cs, q, kb, vT, g, md, Lp, -1, s)) return false;
   count_path(SPECS_PATH_GEMM_MFMA);
   return true;
 }
@@ -589,10 +592,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
                   norm_qkv_rope<T>(x, L.g_attn, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, s));
     if (!normed && !fused_rope)
       PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(x, L.g_attn, (T*)ws.a, g.M, md.d, md.eps, s));
-    // whole-block bf16 launches: rotary embedding, conversion and value transposition inside the projection's epilogue
-    // (one position per block writes a column of the transposed values, a cache line per element, which the two or
-    // three workgroups of the value heads alone are slow at: those launches leave it to the kernel below)
-    if (!fused_rope && g.L > 1)
+    if (!fused_rope)
       PROFILED_IF(ctx, SPECS_K_QKV, s, fused_rope,
                   qkv_rope_fused<T>((const T*)ws.a, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, s));
     if (!fused_rope) {
@@ -1103,10 +1103,11 @@ extern "C" int specs_op_qkv_rope(specs_ctx* ctx, const specs_model* m, const spe
   HIP_TRY(hipSetDevice(ctx->device));
   launch_rope_table(cs, g, md.hd, md.rope_base, s);
   if (d.dtype == SPECS_BF16) {
-    bool fused = g.M > 32 && qkv_rope_fused<bf16_t>((const bf16_t*)A, (const bf16_t*)Wqkv, cs, (bf16_t*)q, (bf16_t*)kblk,
-                                                    (bf16_t*)vT, g, md, Lp, s);
-    if (!fused) {
-      int parts = gemm_store_split<bf16_t>((const bf16_t*)A, (const bf16_t*)Wqkv, qkv, 1, g.M, (int)width, md.d, s);
+    if (!qkv_rope_fused<bf16_t>((const bf16_t*)A, (const bf16_t*)Wqkv, cs, (bf16_t*)q, (bf16_t*)kblk, (bf16_t*)vT, g, md,
+                                Lp, s)) {
+      const size_t room = (ctx->workspace_bytes - 256 - cs_bytes) / ((size_t)g.M * width * sizeof(float));
+      int parts = gemm_store_split<bf16_t>((const bf16_t*)A, (const bf16_t*)Wqkv, qkv,
+                                           (int)(room < MFMA_MAX_SPLIT ? room : MFMA_MAX_SPLIT), g.M, (int)width, md.d, s);
       launch_rope_split<bf16_t>(qkv, parts, cs, (bf16_t*)q, (bf16_t*)kblk, (bf16_t*)vT, g, Lp, md, s);
     }
   } else {

@@ -236,7 +236,9 @@ def test_attention_bf16(ctx, Hq, Hkv, hd, Bn, n, L, lens, pt):
 @pytest.mark.parametrize("dtype,Hq,Hkv,hd,d_model,Bn,n,L,lens", [
     ("bf16", 28, 4, 128, 3584, 1, 4, 128, [4096]),        # 7B layer: rotary embedding inside the GEMM epilogue, head_dim 128
     ("bf16", 6, 2, 64, 384, 3, 2, 70, [100, 17, 333]),    # head_dim 64, block length off every tile: zeroed padding of vT
-    ("bf16", 12, 2, 128, 1536, 2, 8, 2, [50, 2000]),      # 32 rows: the few-row path (projection, then the rotary kernel)
+    ("bf16", 12, 2, 128, 1536, 2, 8, 2, [50, 2000]),      # 32 rows: the 32 x 128 tile with the same epilogue
+    ("bf16", 12, 2, 128, 1536, 2, 8, 1, [50, 2000]),      # one token a block: projection in K slices, then the rotary kernel
+    ("bf16", 6, 2, 64, 384, 3, 17, 1, [100, 17, 333]),    # the same with more than 32 rows
     ("f32", 6, 2, 16, 96, 3, 3, 5, [38, 8, 20]),          # float: plain kernels
 ])
 def test_qkv_projection_with_rotary_embedding(ctx, dtype, Hq, Hkv, hd, d_model, Bn, n, L, lens):
@@ -267,9 +269,15 @@ def test_qkv_projection_with_rotary_embedding(ctx, dtype, Hq, Hkv, hd, d_model, 
     q = torch.full((M, Hq, hd), 7.0, dtype=tdt, device=DEV)
     kb = torch.full((M, Hkv, hd), 7.0, dtype=tdt, device=DEV)
     vT = torch.full((Bn * n, Hkv, hd, Lp), 7.0, dtype=tdt, device=DEV)
-    B.specs_op_qkv_rope(ctx, model, prefix, tA, tW, n, L, q, kb, vT)
+    # a context of its own: where the epilogue rotates, no float product passes through the workspace, as in the pass
+    ws = torch.full((64 << 20,), 0x5a, dtype=torch.uint8, device=DEV)
+    own = B.specs_ctx_create(0, torch.cuda.current_stream().cuda_stream, ws)
+    B.specs_op_qkv_rope(own, model, prefix, tA, tW, n, L, q, kb, vT)
     torch.cuda.synchronize()
-    assert B.specs_ctx_status(ctx) == 0
+    assert B.specs_ctx_status(own) == 0
+    B.specs_ctx_destroy(own)
+    product = ws[256 + (M * hd * 4 + 255) // 256 * 256:]
+    assert bool((product == 0x5a).all()) == (dtype == "bf16" and L > 1)
     B.specs_prefix_destroy(prefix)
     B.specs_model_destroy(model)
     y = A.astype(np.float64) @ Wm.astype(np.float64).T
