@@ -229,12 +229,12 @@ int specs_select_and_switch(specs_ctx* ctx, const float* logp_target, const floa
                             uint8_t* gen_is_draft, int32_t* idx, float* max_reward);
 
 /* Which implementation the launches of this process took since the counters were last reset: the matrix-unit
- * (MFMA) kernels, the weight-streaming kernel for at most 32 rows, or the plain kernels that serve the float
+ * (MFMA) kernels, with products of at most 32 rows counted apart, or the plain kernels that serve the float
  * configuration and shapes the others do not take (K not a multiple of 64, head sizes other than 64/128, pages other
  * than 16 tokens). counts: host int32 [SPECS_PATH_COUNT]; reset != 0 clears the counters after reading them. */
 enum {
-  SPECS_PATH_GEMM_MFMA = 0,   /* block-tiled MFMA GEMM family */
-  SPECS_PATH_GEMM_SKINNY,     /* weight-streaming MFMA GEMM (generation) */
+  SPECS_PATH_GEMM_MFMA = 0,   /* block-tiled MFMA GEMM family (vocabulary head included), more than 32 rows */
+  SPECS_PATH_GEMM_SKINNY,     /* the same family, at most 32 rows: bound by streaming the weights */
   SPECS_PATH_GEMM_PLAIN,      /* plain GEMM / vocabulary-head kernels */
   SPECS_PATH_ATTN_MFMA,       /* MFMA attention kernels (whole blocks or single positions) */
   SPECS_PATH_ATTN_PLAIN,      /* plain attention kernel */

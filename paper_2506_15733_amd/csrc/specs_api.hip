@@ -369,7 +369,7 @@ static ModelDims dims_of(const specs_model_desc& d) {
   return md;
 }
 
-// Products of a few rows, whose time is that of streaming the weights, are counted on their own.
+// Products of at most 32 rows, whose time is that of streaming the weights, are counted on their own.
 static void count_mfma(int M) { count_path(M <= 32 ? SPECS_PATH_GEMM_SKINNY : SPECS_PATH_GEMM_MFMA); }
 
 template <typename T>
@@ -444,7 +444,7 @@ template <>
 bool qkv_rope_fused<bf16_t>(const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q, bf16_t* kb, bf16_t* vT,
                             const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s) {
   if (g.L == 1 || !launch_gemm_mfma_qkv_rope(A, W, cs, q, kb, vT, g, md, Lp, -1, s)) return false;
-  count_path(SPECS_PATH_GEMM_MFMA);
+  count_mfma(g.M);
   return true;
 }
 
@@ -504,7 +504,7 @@ template <>
 int lmhead_partials<bf16_t>(const bf16_t* A, const bf16_t* W, const int32_t* tok, float* pm, float* ps, float* zt, int M,
                             int V, int K, hipStream_t s) {
   if (launch_gemm_mfma(MFMA_LMHEAD, A, W, M, V, K, nullptr, nullptr, tok, pm, ps, zt, 1, -1, s)) {
-    count_path(SPECS_PATH_GEMM_MFMA);
+    count_mfma(M);
     return mfma_lmhead_tiles(V);
   }
   count_path(SPECS_PATH_GEMM_PLAIN);
@@ -974,6 +974,7 @@ extern "C" int specs_op_linear(specs_ctx* ctx, int32_t dtype, const void* A, con
     float* part = (float*)(ctx->workspace + 256);
     if (split > 1 && launch_gemm_mfma(MFMA_STORE, (const bf16_t*)A, (const bf16_t*)W, M, N, K, part, nullptr, nullptr,
                                       nullptr, nullptr, nullptr, split, tile, ctx->stream)) {
+      count_mfma(M);
       launch_add_partials_rmsnorm<bf16_t>(C, part, split, accumulate ? 0 : 1, nullptr, nullptr, M, N, 0.f, ctx->stream);
       ctx->last_model = nullptr;                         // the workspace no longer holds a scored block
     } else {

@@ -343,7 +343,7 @@ def test_generation_equals_scoring_at_config_4_size():
 def test_full_width_one_layer_generators_match_the_stored_oracle():
     """Both language models of config 4 at their full widths (7B: d 3584, F 18944, V 152064; 1.5B: d 1536, F 8960)
     with their first layer only, on the 4096-token prefix, generating 8 positions for 16 candidates: the launches
-    generation uses at the benchmark size (few-row weight-streaming GEMMs, one-position attention over the paged
+    generation uses at the benchmark size (few-row GEMMs with K in slices, one-position attention over the paged
     prefix merged with the block's own keys, the sampler over the full vocabulary) against oracle.generate_blocks,
     whose ids, log-probabilities and uniform intervals make_oracle_golden.py --generate stored. The 7B model's
     vocabulary exceeds the token vocabulary, so it draws from the restricted law (vocab_limit). Ids must equal the

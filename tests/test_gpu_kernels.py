@@ -40,7 +40,7 @@ LINEAR_SHAPES = [(45, 100, 64), (256, 256, 64), (300, 1152, 128), (130, 257, 192
                  (1024, 1536, 8960), (256, 1024, 2816), (2048, 3584, 18944),
                  # tile counts that are no multiple of the CU count, with ragged edges
                  (2000, 4500, 3584), (1000, 3000, 1024), (4100, 1500, 2048), (2048, 1536, 8960), (4096, 8960, 1536),
-                 # a few rows (one position of every candidate during generation): the weight-streaming kernel
+                 # a few rows (one position of every candidate during generation): K in slices
                  (16, 4608, 3584), (16, 3584, 18944), (5, 301, 128), (32, 2050, 1280), (17, 1536, 8960), (1, 64, 256)]
 
 
@@ -76,6 +76,25 @@ def test_linear_tile_shapes(ctx, M, N, K):
     B.specs_op_linear(ctx, ta, tw, out, accumulate=False)
     torch.cuda.synchronize()
     close(out.cpu().numpy().astype(np.float64), oracle.linear(a, w), 2e-5)   # the bound of test_linear_bf16
+
+
+@pytest.mark.parametrize("M", [1, 32, 33, 300])
+def test_products_of_at_most_32_rows_are_counted_apart(ctx, M):
+    """Every product of the matrix-unit family goes to one counter, chosen by its rows: sliced and whole, stored, with
+    SwiGLU, and the vocabulary head (the QKV epilogue's count is checked with its values below)."""
+    from paper_2506_15733_amd import binding as B
+    _, ta = draw(f"ca{M}", (M, 1280))
+    _, tw = draw("cw", (2050, 1280), 0.02)
+    _, tg = draw("cg", (320, 1280), 0.02)
+    B.specs_path_counts(reset=True)
+    B.specs_op_linear(ctx, ta, tw, torch.zeros((M, 2050), dtype=torch.float32, device=DEV))
+    B.specs_op_linear(ctx, ta[:, :64].contiguous(), tw[:, :64].contiguous(), torch.zeros((M, 2050), dtype=torch.float32, device=DEV))
+    B.specs_op_gate_up(ctx, ta, tg, torch.zeros((M, 160), dtype=torch.bfloat16, device=DEV))
+    B.specs_op_lmhead_logprob(ctx, ta, tw, torch.zeros(M, dtype=torch.int32, device=DEV), torch.zeros(M, dtype=torch.float32, device=DEV))
+    torch.cuda.synchronize()
+    got = B.specs_path_counts(reset=True)
+    want = dict.fromkeys(got, 0) | {"gemm_skinny" if M <= 32 else "gemm_mfma": 4}
+    assert got == want, got
 
 
 def test_linear_f32(ctx):
@@ -272,7 +291,9 @@ def test_qkv_projection_with_rotary_embedding(ctx, dtype, Hq, Hkv, hd, d_model, 
     # a context of its own: where the epilogue rotates, no float product passes through the workspace, as in the pass
     ws = torch.full((64 << 20,), 0x5a, dtype=torch.uint8, device=DEV)
     own = B.specs_ctx_create(0, torch.cuda.current_stream().cuda_stream, ws)
+    B.specs_path_counts(reset=True)
     B.specs_op_qkv_rope(own, model, prefix, tA, tW, n, L, q, kb, vT)
+    assert B.specs_path_counts(reset=True)["gemm_plain" if dtype == "f32" else "gemm_skinny" if M <= 32 else "gemm_mfma"] == 1
     torch.cuda.synchronize()
     assert B.specs_ctx_status(own) == 0
     B.specs_ctx_destroy(own)
