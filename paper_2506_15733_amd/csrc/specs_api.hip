@@ -521,9 +521,16 @@ static void attention(const T* q, const T* kb, const T* vbT, const T* pK, const 
                       size_t scratch_floats, hipStream_t s);
 
 // A stretch of one beam's prompt in a prefill launch: tokens c0 .. c0 + rows - 1 of beam b, in rows `row` .. of the
-// launch. All but the last stretch occupy rows rounded up to 16, the surplus ones being copies of their last token that
-// nothing reads, so that every stretch's values start at a 32-byte boundary of the transposed buffer.
+// launch. All but the last stretch occupy rows rounded up to stretch_unit, the surplus ones being copies of their last
+// token that nothing reads, so that every stretch's values start at a 32-byte boundary of the transposed buffer where the
+// matrix-unit attention reads them in 16-byte pieces. Elsewhere there are none: the plain kernel keeps a row's scores in
+// LDS, and with surplus rows a prompt could exceed it that alone does not.
 struct Stretch { int b, c0, rows, row; int64_t token; };
+
+static int stretch_unit(const specs_model_desc& d, const specs_prefix* p) {
+  return d.dtype == SPECS_BF16 && (d.head_dim == 64 || d.head_dim == 128) && p->page_tokens == 16 ? 16 : 1;
+}
+static inline int64_t round_to(int64_t v, int unit) { return (v + unit - 1) / unit * unit; }
 
 static BatchGeom stretch_geom(const specs_prefix* p, const Stretch& st, int rows, int vs) {
   BatchGeom g = block_geom(p, 1, rows);
@@ -552,7 +559,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
   // rows of the launch that stretch i occupies
   auto span = [&](size_t i) {
     const Stretch& st = (*stretches)[i];
-    return i + 1 < stretches->size() ? round16(st.rows) : st.rows;
+    return i + 1 < stretches->size() ? (int)round_to(st.rows, stretch_unit(d, p)) : st.rows;
   };
   if (stretches) {
     for (size_t i = 0; i < stretches->size(); ++i) {
@@ -821,8 +828,9 @@ static int prefill_impl(specs_ctx* ctx, const specs_model* m, specs_prefix* p, c
   // equal size, as large as the workspace holds, up to 8192 rows: the weights are then read once per launch instead of
   // once per beam and 2048 tokens, and no launch has a last row of tiles to itself (7B, prompts of 611, 1121 and 2733
   // tokens: 65.4 -> 59.0 ms).
+  const int unit = stretch_unit(d, p);
   int64_t total = 0;
-  for (int b = 0; b < p->B; ++b) total += round16(p->lens[b]);
+  for (int b = 0; b < p->B; ++b) total += round_to(p->lens[b], unit);
   int64_t R = total < 8192 ? total : 8192;
   while (R > 16 && carve_prefill(nullptr, d, R).total > ctx->workspace_bytes) R = (R - 1) & ~(int64_t)15;
   while (R > 0 && carve_prefill(nullptr, d, R).total > ctx->workspace_bytes) --R;
@@ -849,7 +857,7 @@ static int prefill_impl(specs_ctx* ctx, const specs_model* m, specs_prefix* p, c
   for (int b = 0; b < p->B; ++b) {
     const int len = p->lens[b];
     for (int c0 = 0; c0 < len;) {
-      const int64_t row = (used + 15) & ~(int64_t)15;
+      const int64_t row = round_to(used, unit);
       if (row >= fill) { run(); continue; }
       const int rows = len - c0 < fill - row ? len - c0 : (int)(fill - row);
       stretches.push_back({b, c0, rows, (int)row, off + c0});

@@ -559,7 +559,8 @@ def test_multi_step_loop_with_commit_and_switching_matches_oracle(fast_path):
     ("bf16", 64, 16, (300, 70, 129), 40),                # several launches, prompts cut inside and their rest with the next
     ("bf16", 128, 16, (700, 64), 1024),
     ("bf16", 16, 4, (5, 90, 33), 64),                    # the plain attention kernel
-    ("f32", 16, 4, (1, 5, 90, 33), 24), ("f32", 16, 16, (40, 7), 5)])
+    ("f32", 16, 4, (1, 5, 90, 33), 24), ("f32", 16, 16, (40, 7), 5),
+    ("f32", 10, 16, (40945, 30), 1024)])                 # the plain kernel's limit: 40960 floats of LDS hold scores and query
 def test_prefill_of_several_prompts_equals_one_by_one(dtype, hd, page_tokens, lens, rows):
     """Prompts that share launches (and are cut by them) leave the pages and last states that each leaves alone. Float:
     sums in another order; bf16: a value on a rounding boundary moves by a bf16 unit, as elsewhere in this file."""
