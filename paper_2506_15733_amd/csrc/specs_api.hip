@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -530,6 +531,7 @@ struct Stretch { int b, c0, rows, row; int64_t token; };
 static int stretch_unit(const specs_model_desc& d, const specs_prefix* p) {
   return d.dtype == SPECS_BF16 && (d.head_dim == 64 || d.head_dim == 128) && p->page_tokens == 16 ? 16 : 1;
 }
+struct Stretches { Stretch* at; size_t count; };        // those of one launch
 static inline int64_t round_to(int64_t v, int unit) { return (v + unit - 1) / unit * unit; }
 
 static BatchGeom stretch_geom(const specs_prefix* p, const Stretch& st, int rows, int vs) {
@@ -550,7 +552,7 @@ static BatchGeom stretch_geom(const specs_prefix* p, const Stretch& st, int rows
 template <typename T>
 static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* p, const Workspace& ws,
                       const BatchGeom& g, float* x, const int32_t* tokens, int tok_stride, int max_ctx,
-                      const std::vector<Stretch>* stretches, int64_t R, int64_t C, hipStream_t s,
+                      const Stretches* stretches, int64_t R, int64_t C, hipStream_t s,
                       bool last_token_only = false) {
   const specs_model_desc& d = m->desc;
   ModelDims md = dims_of(d);
@@ -558,12 +560,12 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
   int qd = md.Hq * md.hd, kvd = md.Hkv * md.hd;
   // rows of the launch that stretch i occupies
   auto span = [&](size_t i) {
-    const Stretch& st = (*stretches)[i];
-    return i + 1 < stretches->size() ? (int)round_to(st.rows, stretch_unit(d, p)) : st.rows;
+    const Stretch& st = stretches->at[i];
+    return i + 1 < stretches->count ? (int)round_to(st.rows, stretch_unit(d, p)) : st.rows;
   };
   if (stretches) {
-    for (size_t i = 0; i < stretches->size(); ++i) {
-      const Stretch& st = (*stretches)[i];
+    for (size_t i = 0; i < stretches->count; ++i) {
+      const Stretch& st = stretches->at[i];
       PROFILED(ctx, SPECS_K_OTHER, s,
                launch_embed_rope<T>(tokens + st.token, 1, st.rows, (const T*)m->w.embed, x + (size_t)st.row * md.d, md.d,
                                     md.V, ws.status, ws.cs + (size_t)st.row * md.hd, stretch_geom(p, st, span(i), g.vs),
@@ -642,8 +644,8 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
       break;
     }
     if (stretches) {
-      for (size_t i = 0; i < stretches->size(); ++i) {
-        const Stretch& st = (*stretches)[i];
+      for (size_t i = 0; i < stretches->count; ++i) {
+        const Stretch& st = stretches->at[i];
         const size_t r = st.row;
         const BatchGeom ga = stretch_geom(p, st, span(i), g.vs);
         PROFILED(ctx, SPECS_K_ATTENTION, s,
@@ -840,17 +842,22 @@ static int prefill_impl(specs_ctx* ctx, const specs_model* m, specs_prefix* p, c
   int64_t fill = ((total + launches - 1) / launches + 255) & ~(int64_t)255;
   if (fill > R) fill = R;
   hipStream_t s = ctx->stream;
-  std::vector<Stretch> stretches;
+  // a launch holds one stretch of a prompt at most
+  const std::unique_ptr<Stretch[]> room(new (std::nothrow) Stretch[p->B]);
+  if (!room) return SPECS_EINVAL;
+  Stretches stretches = {room.get(), 0};
   int64_t used = 0;                                      // rows of the launch under construction
   auto run = [&]() {
     BatchGeom g = block_geom(p, 1, (int)used);
     g.B = 1; g.M = (int)used;
     run_trunk<T>(ctx, m, p, ws, g, ws.x, tokens, 1, 0, &stretches, R, 1, s);
-    for (const Stretch& st : stretches)
+    for (size_t i = 0; i < stretches.count; ++i) {
+      const Stretch& st = stretches.at[i];
       if (st.c0 + st.rows == p->lens[st.b])
         launch_copy_rows(ws.x + (size_t)st.row * d.d_model, p->h_last, stretch_geom(p, st, st.rows, g.vs), d.d_model,
                          nullptr, s);
-    stretches.clear();
+    }
+    stretches.count = 0;
     used = 0;
   };
   int64_t off = 0;
@@ -860,7 +867,7 @@ static int prefill_impl(specs_ctx* ctx, const specs_model* m, specs_prefix* p, c
       const int64_t row = round_to(used, unit);
       if (row >= fill) { run(); continue; }
       const int rows = len - c0 < fill - row ? len - c0 : (int)(fill - row);
-      stretches.push_back({b, c0, rows, (int)row, off + c0});
+      stretches.at[stretches.count++] = {b, c0, rows, (int)row, off + c0};
       used = row + rows;
       c0 += rows;
       if (c0 < len) run();                               // the rest attends to pages that this launch writes
