@@ -309,6 +309,68 @@ def test_generation_equals_scoring_for_uneven_prefixes_and_wide_groups(B_, n, hq
     step.close()
 
 
+def test_captured_generation_covers_prefixes_that_grew_since():
+    """A launch of generation attention cuts the prefixes into runs by the lengths the host knows. Captured in a graph and
+    replayed after the device lengths have grown beyond the last run (and, for the short beam, from one run to all), it
+    must see every key: log-likelihoods equal scoring of the same blocks on a handle of the grown lengths, at the
+    tolerance of the tests above. Values beyond the captured runs have another mean, so a pass that left those keys out
+    would be off by far more (checked: scoring on the covered part alone is)."""
+    from paper_2506_15733_amd import synthetic, binding as B
+    n, L, V = 3, 5, 777
+    desc = ModelDesc("target", 2, 384, 6, 2, 64, 256, V, "bf16", "lm")
+    before, covered, after = (80, 2100), (80, 2176), (2600, 4000)   # 33 tiles of 64 keys: 17 runs of 2 tiles
+    stream = torch.cuda.Stream(device="cuda:0")
+    pages = [(x + L + 15) // 16 for x in after]
+    table = np.full((2, max(pages)), -1, np.int32)
+    order = np.random.default_rng(3).permutation(sum(pages)).astype(np.int32)
+    table[0, :pages[0]], table[1, :pages[1]] = order[:pages[0]], order[pages[0]:]
+    u = torch.from_numpy(W.rng.uniform_f64(35, "gen/u9", 2 * n * L).reshape(2, n, L)).to("cuda:0")
+    cand = torch.zeros((2, n, L), dtype=torch.int32, device="cuda:0")
+    logp, tok = torch.zeros((2, n), device="cuda:0"), torch.zeros((2, n, L), device="cuda:0")
+    with torch.cuda.stream(stream):
+        dm = synthetic.DeviceModel(desc, "cuda:0", stream, 2 * n * L, 2 * n)
+        pf = synthetic.DevicePrefix(dm, before, table, sum(pages), 16)
+        g = torch.Generator(device="cuda:0").manual_seed(4)
+        pf.kv_pool.normal_(generator=g)
+        pf.h_last.normal_(generator=g)
+        for b in range(2):
+            beyond = torch.from_numpy(table[b, covered[b] // 16:pages[b]].astype(np.int64)).to("cuda:0")
+            pf.kv_pool[:, 1, beyond] += 3.0
+
+        def scores_at(lens):
+            at = torch.tensor(lens, dtype=torch.int32, device="cuda:0")
+            handle = B.specs_prefix_create(dm.ctx, dm.model, list(lens), at, 16, pf.kv_pool, sum(pages), pf.page_table, pf.h_last)
+            out, t = torch.zeros_like(logp), torch.zeros_like(tok)
+            B.specs_score_blocks(dm.ctx, dm.model, handle, cand, out, t)
+            torch.cuda.synchronize()
+            B.specs_prefix_destroy(handle)
+            return t
+
+        def generate():
+            B.specs_generate_blocks(dm.ctx, dm.model, pf.handle, u, cand, logp, tok, 0)
+
+        generate()
+        torch.cuda.synchronize()
+        assert float((scores_at(before) - tok).abs().max()) < 2e-2
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            generate()
+        pf.lens_dev.copy_(torch.tensor(after, dtype=torch.int32))
+        for _ in range(3):
+            cand.fill_(-1)
+            tok.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert B.specs_ctx_status(dm.ctx) == 0
+            got = tok.clone()
+            assert float((scores_at(after) - got).abs().max()) < 2e-2
+            assert float((scores_at(covered) - got).abs().amax(dim=(1, 2)).min()) > 0.2
+        del graph
+    pf.close()
+    dm.close()
+
+
 def test_generation_equals_scoring_at_config_4_size():
     """Full benchmark size (1.5B draft of config 4: 16 candidates x 128 positions on a 4096-token prefix, the launch
     configuration `bench.py --generate draft` times): the block log-likelihoods that come out of generation equal
