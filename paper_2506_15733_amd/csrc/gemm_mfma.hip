@@ -258,10 +258,8 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
     };
     // own loads of all but the newest `ahead` K-tiles have landed and own fragment reads are done, then everybody's
     auto wait_ahead = [&](int ahead) {
-      static_assert(S <= 8 && (S - 2) * NLD < 63, "the counts below");
-      if (S > 7 && ahead >= 6) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(S > 7 ? 6 * NLD : 0) : "memory");
-      else if (S > 6 && ahead >= 5) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(S > 6 ? 5 * NLD : 0) : "memory");
-      else if (ahead >= 4) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(4 * NLD) : "memory");
+      static_assert(S <= 6 && (S - 2) * NLD < 63, "the counts below");
+      if (ahead >= 4) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(4 * NLD) : "memory");
       else if (ahead == 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(3 * NLD) : "memory");
       else if (ahead == 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NLD) : "memory");
       else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NLD) : "memory");
