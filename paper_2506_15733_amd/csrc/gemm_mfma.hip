@@ -42,13 +42,13 @@ struct GemmArgs {
   int ksplit;            // ME_STORE only: slices of K, slice s writes its partial product to C + s*M*N
   // ME_QKV_ROPE: the product is the QKV projection [M, (Hq + 2 Hkv) * hd]; the epilogue rotates the q and k heads
   // (pairs (i, i + hd/2), angles from the table cs[M][hd] = cos | sin) and writes bf16 q [M][Hq][hd], block keys
-  // kblk[cand*Lk + t][Hkv][hd] and block values transposed per candidate vT[cand][Hkv][hd][Lp], where row m is
-  // in-block position t = t0 + m % Lrows of candidate m / Lrows.
+  // kblk[M][Hkv][hd] and block values transposed per candidate vT[cand][Hkv][hd][Lp], where row m is in-block position
+  // t = m % Lrows of candidate m / Lrows.
   const float* cs;
   bf16_t* q;
   bf16_t* kblk;
   bf16_t* vT;
-  int Hq, Hkv, hd, Lrows, t0, Lk, Lp;
+  int Hq, Hkv, Lrows, Lp;
 };
 
 // One direct-to-LDS load instruction: the workgroup's NW wavefronts write NW consecutive 1 KiB spans
@@ -386,11 +386,11 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
       for (int i = 0; i < TM; ++i) {
         const int row = m0 + wm * WM + i * 32 + lrow;
         if (row >= a.M) continue;
-        const int cand = row / a.Lrows, t = a.t0 + (row - cand * a.Lrows);
+        const int cand = row / a.Lrows, t = row - cand * a.Lrows;
         if (head < a.Hq + a.Hkv) {
           const float* cs = a.cs + (size_t)row * HDIM;
           bf16_t* dst = head < a.Hq ? a.q + ((size_t)row * a.Hq + head) * HDIM
-                                    : a.kblk + (((size_t)cand * a.Lk + t) * a.Hkv + (head - a.Hq)) * HDIM;
+                                    : a.kblk + ((size_t)row * a.Hkv + (head - a.Hq)) * HDIM;
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
             const int i0 = i_base + 8 * g;
@@ -409,7 +409,7 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
         } else {
           // values: not rotated, stored transposed; the 32 lanes of a half-wave write 32 consecutive positions
           bf16_t* dst = a.vT + (((size_t)cand * a.Hkv + (head - a.Hq - a.Hkv)) * HDIM) * a.Lp + t;
-          const bool pad = t == a.Lk - 1 && a.Lp > a.Lk;
+          const bool pad = t == a.Lrows - 1 && a.Lp > a.Lrows;
 #pragma unroll
           for (int g = 0; g < 4; ++g)
 #pragma unroll
@@ -559,17 +559,17 @@ void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* til
 
 // QKV projection with the rotary embedding, the bf16 conversion and the per-candidate transposition of the values
 // in the epilogue: no float [M, (Hq+2Hkv)*hd] round trip through memory and no separate kernel. Row m is in-block
-// position g.t0 + m % g.L of candidate m / g.L. Returns false when the shape is not taken (head_dim other than
-// 64/128, K % 64 != 0, misaligned buffers); the caller then runs the projection and the rotary kernel separately.
+// position m % g.L of candidate m / g.L. Returns false when the shape is not taken (head_dim other than 64/128,
+// K % 64 != 0, misaligned buffers, launches of one position of longer blocks); the caller then runs the projection and the rotary kernel separately.
 bool launch_gemm_mfma_qkv_rope(const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q, bf16_t* kblk, bf16_t* vT,
                                const BatchGeom& g, const ModelDims& md, int Lp, int tile, hipStream_t s) {
   const int M = g.M, N = (md.Hq + 2 * md.Hkv) * md.hd, K = md.d;
-  if (K % 64 != 0 || M <= 0 || (md.hd != 64 && md.hd != 128)) return false;
+  if (K % 64 != 0 || M <= 0 || (md.hd != 64 && md.hd != 128) || g.t0 != 0 || g.Lk != g.L) return false;
   if (((uintptr_t)cs & 15) || ((uintptr_t)q & 7) || ((uintptr_t)kblk & 7)) return false;
   GemmArgs a = {};
   a.A = A; a.W = W; a.M = M; a.N = N; a.K = K; a.ksplit = 1;
   a.cs = cs; a.q = q; a.kblk = kblk; a.vT = vT;
-  a.Hq = md.Hq; a.Hkv = md.Hkv; a.hd = md.hd; a.Lrows = g.L; a.t0 = g.t0; a.Lk = g.Lk; a.Lp = Lp;
+  a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lrows = g.L; a.Lp = Lp;
   int split = 1;
   if (tile < 0) mfma_gemm_plan(M, N, K, 1, false, &tile, &split);
   if (md.hd == 128) launch_tile<ME_QKV_ROPE, true>(a, tile, s);
