@@ -47,10 +47,6 @@ struct PPArgs {
   int balanced;         // (beam, kv head) units dealt to the XCDs by decreasing prefix length (see the kernel)
   int last_first;       // one block of one beam (prefill): row tiles dealt to the XCDs from the last one down
   float scale_log2e;
-  int n_splits;         // > 1: the prefix tiles are cut into runs, the last run also takes the block tiles; every
-  float* part_o;        //      workgroup leaves (O un-normalised, m, l) per row for the merge kernel:
-  float* part_m;        //      [(b*Hkv + kvh)][wg_tile][split][256] rows, part_o [..][HD]
-  float* part_l;
 };
 
 __device__ __forceinline__ float half_wave_max(float v) {
@@ -83,18 +79,17 @@ __global__ void __launch_bounds__(512, 2) attention_pingpong_kernel(PPArgs a) {
 
   const BatchGeom& G = a.g;
   const int g = a.Hq / a.Hkv;
-  // Workgroup -> (beam, kv head, row tile, run). Workgroups whose ids are congruent mod 8 share an XCD, and all
+  // Workgroup -> (beam, kv head, row tile). Workgroups whose ids are congruent mod 8 share an XCD, and all
   // workgroups of a (beam, kv head) go to one XCD, whose L2 then fetches that head's pages once.
-  int b, kvh, rem;
+  int b, kvh, wg_tile;
   if (a.balanced) {
     // Ragged batches: a workgroup's duration follows its beam's prefix length, so the (beam, kv head) units are dealt
     // to the XCDs in order of decreasing length, back and forth (ranks 0..7, then 15..8, ...): every XCD gets the same
     // sum to within a unit and starts with its longest ones. The rank -> beam look-up is recomputed by every
     // wavefront (at most 64 beams).
-    const int per_unit = a.wg_tiles * a.n_splits;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int pos = slot / per_unit;
-    rem = slot - pos * per_unit;
+    const int pos = slot / a.wg_tiles;
+    wg_tile = slot - pos * a.wg_tiles;
     const int unit_rank = (pos & 1) ? pos * 8 + 7 - xcd : pos * 8 + xcd;
     if (unit_rank >= G.B * a.Hkv) return;
     const int rank = unit_rank / a.Hkv;
@@ -116,17 +111,15 @@ __global__ void __launch_bounds__(512, 2) attention_pingpong_kernel(PPArgs a) {
     const int tile = blockIdx.x / a.Hkv;
     b = 0;
     kvh = blockIdx.x - tile * a.Hkv;
-    rem = a.wg_tiles - 1 - tile;
+    wg_tile = a.wg_tiles - 1 - tile;
   } else {
     const int logical = (blockIdx.x & 7) * a.wg_per_xcd + (blockIdx.x >> 3);
     if (logical >= a.total_wg) return;
-    b = logical / (a.Hkv * a.wg_tiles * a.n_splits);
-    rem = logical - b * (a.Hkv * a.wg_tiles * a.n_splits);
-    kvh = rem / (a.wg_tiles * a.n_splits);
-    rem -= kvh * (a.wg_tiles * a.n_splits);
+    b = logical / (a.Hkv * a.wg_tiles);
+    wg_tile = logical - b * (a.Hkv * a.wg_tiles);
+    kvh = wg_tile / a.wg_tiles;
+    wg_tile -= kvh * a.wg_tiles;
   }
-  const int split = rem % a.n_splits;
-  const int wg_tile = rem / a.n_splits;
 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int grp = wave >> 2;                 // wavefronts w and w + 4 share a SIMD and belong to different groups
@@ -165,11 +158,9 @@ __global__ void __launch_bounds__(512, 2) attention_pingpong_kernel(PPArgs a) {
     for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
 
-  // ---- tile list of this workgroup: prefix tiles [pt_lo, pt_lo + npt), then the block tiles of its candidates
-  const int n_ptiles = (P + 63) >> 6;
+  // ---- tile list of this workgroup: the prefix tiles, then the block tiles of its candidates
+  const int npt = (P + 63) >> 6;
   const int n_pages = (P + 15) >> 4;
-  const int pt_lo = (int)((long)split * n_ptiles / a.n_splits);
-  const int npt = (int)((long)(split + 1) * n_ptiles / a.n_splits) - pt_lo;
   const int c_lo = r_wg0 / Lg, c_hi = r_wg1 / Lg;
   // block tiles of candidate c that some row of the workgroup can see: 0 .. (last token of c among the rows) / 64
   auto block_tiles_of = [&](int c) {
@@ -178,8 +169,7 @@ __global__ void __launch_bounds__(512, 2) attention_pingpong_kernel(PPArgs a) {
     return (((last - c * Lg) / g) >> 6) + 1;
   };
   int T = npt;
-  if (split == a.n_splits - 1)
-    for (int c = c_lo; c <= c_hi; ++c) T += block_tiles_of(c);
+  for (int c = c_lo; c <= c_hi; ++c) T += block_tiles_of(c);
 
   // The block tiles (candidate, tile number) are listed once in LDS behind the staging ring; the tile loop looks an
   // entry up instead of walking the candidates again for every tile (an instruction a wavefront issues costs four
@@ -189,7 +179,7 @@ __global__ void __launch_bounds__(512, 2) attention_pingpong_kernel(PPArgs a) {
   int* tile_table = (int*)(smem + NSTAGE * STAGE);
   int* page_lds = tile_table + kMaxBlockTiles;
   for (int i = threadIdx.x; i < n_pages; i += 512) page_lds[i] = ptab[i];
-  if (threadIdx.x == 0 && T > npt) {
+  if (threadIdx.x == 0) {
     int k = 0;
     for (int c = c_lo; c <= c_hi; ++c) {
       const int nb = block_tiles_of(c);
@@ -200,7 +190,7 @@ __global__ void __launch_bounds__(512, 2) attention_pingpong_kernel(PPArgs a) {
   struct Tile { bool is_block; int c, idx; };          // idx: prefix tile number, or block tile number of candidate c
   auto tile_at = [&](int tau) {
     Tile t;
-    if (tau < npt) { t.is_block = false; t.c = 0; t.idx = pt_lo + tau; return t; }
+    if (tau < npt) { t.is_block = false; t.c = 0; t.idx = tau; return t; }
     const int e = __builtin_amdgcn_readfirstlane(tile_table[tau - npt]);
     t.is_block = true; t.c = e & 0xffff; t.idx = e >> 16;
     return t;
@@ -221,7 +211,7 @@ __global__ void __launch_bounds__(512, 2) attention_pingpong_kernel(PPArgs a) {
   const bool loads_keys = grp == 1;
   auto page_of = [&](int tau) -> int {
     if (tau >= npt) return 0;
-    int p16 = (pt_lo + tau) * 4 + pg;
+    int p16 = tau * 4 + pg;
     p16 = p16 < n_pages ? p16 : n_pages - 1;
     return __builtin_amdgcn_readfirstlane(page_lds[p16]);
   };
@@ -456,18 +446,7 @@ __global__ void __launch_bounds__(512, 2) attention_pingpong_kernel(PPArgs a) {
 
   // ---- normalise and store: lane = query column, accumulator value r of d-tile dt is d = dt*32 + 8*(r/4) + 4*lh + r%4
   const float l = half_wave_sum(l_run);
-  if (a.n_splits > 1) {
-    const size_t prow = ((((size_t)b * a.Hkv + kvh) * a.wg_tiles + wg_tile) * a.n_splits + split) * BQ + wave * 32 + lq;
-    if (lh == 0) { a.part_m[prow] = m_run; a.part_l[prow] = l; }
-    float* dst = a.part_o + prow * HD;
-#pragma unroll
-    for (int dt = 0; dt < NI; ++dt)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        float4 v = {o[dt][r4 * 4], o[dt][r4 * 4 + 1], o[dt][r4 * 4 + 2], o[dt][r4 * 4 + 3]};
-        *(float4*)(dst + dt * 32 + 8 * r4 + 4 * lh) = v;
-      }
-  } else if (r_lane < R) {
+  if (r_lane < R) {
     const float inv = 1.0f / l;
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
     bf16_t* dst = a.out + (m_lane * a.Hq + (size_t)kvh * g + j_lane) * HD;
@@ -481,38 +460,6 @@ __global__ void __launch_bounds__(512, 2) attention_pingpong_kernel(PPArgs a) {
         *(bf16x4*)(dst + dt * 32 + 8 * r4 + 4 * lh) = v;
       }
   }
-}
-
-// Merge of the partial results of a split launch: one wavefront per (row, query head).
-template <int HD>
-__global__ void __launch_bounds__(64) attention_pingpong_merge_kernel(const float* __restrict__ part_o,
-                                                                      const float* __restrict__ part_m,
-                                                                      const float* __restrict__ part_l,
-                                                                      bf16_t* __restrict__ out, int n, int L, int Hq,
-                                                                      int Hkv, int wg_tiles, int n_splits) {
-  const size_t m = blockIdx.x;
-  const int h = blockIdx.y, lane = threadIdx.x;
-  const int g = Hq / Hkv, kvh = h / g, j = h - kvh * g;
-  const size_t cand_idx = m / L;                           // b*n + i
-  const int t = (int)(m - cand_idx * L);
-  const size_t b = cand_idx / n, i = cand_idx - b * n;
-  const size_t r = i * (size_t)L * g + (size_t)t * g + j;
-  const size_t prow0 = (((b * Hkv + kvh) * wg_tiles + (r >> 8)) * n_splits) * 256 + (r & 255);   // + split*256
-  float mx = -INFINITY;
-  for (int s = 0; s < n_splits; ++s) mx = fmaxf(mx, part_m[prow0 + (size_t)s * 256]);
-  float l = 0.f, acc[HD / 64];
-#pragma unroll
-  for (int u = 0; u < HD / 64; ++u) acc[u] = 0.f;
-  for (int s = 0; s < n_splits; ++s) {
-    const size_t pr = prow0 + (size_t)s * 256;
-    const float w = __builtin_amdgcn_exp2f(part_m[pr] - mx);   // 0 for a run that saw no visible key
-    l = fmaf(w, part_l[pr], l);
-#pragma unroll
-    for (int u = 0; u < HD / 64; ++u) acc[u] = fmaf(w, part_o[pr * HD + lane + 64 * u], acc[u]);
-  }
-  const float inv = 1.0f / l;
-#pragma unroll
-  for (int u = 0; u < HD / 64; ++u) out[(m * Hq + h) * HD + lane + 64 * u] = (bf16_t)(acc[u] * inv);
 }
 
 template <int HD>
@@ -530,10 +477,10 @@ void launch_pp_variant(const PPArgs& a, hipStream_t s) {
 }  // namespace
 
 // Whole-block launches (g.t0 == 0, g.Lk == g.L). Returns false if the shape is not taken (head_dim 64/128, 16-token
-// pages, 8-byte aligned output rows). part / part_floats: float scratch for launches that cut the prefix into runs.
+// pages, 8-byte aligned output rows).
 bool launch_attention_pingpong(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                                const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,
-                               int max_ctx, float* part, size_t part_floats, hipStream_t s) {
+                               int max_ctx, hipStream_t s) {
   if ((md.hd != 64 && md.hd != 128) || g.page_tokens != 16 || Lp % 16 != 0 || g.t0 != 0 || g.Lk != g.L) return false;
   if (((uintptr_t)out & 7) || md.Hq % md.Hkv || g.n > 0xffff) return false;   // the tile table packs (candidate, tile) in 16 + 16 bits
   PPArgs a;
@@ -544,40 +491,11 @@ bool launch_attention_pingpong(const bf16_t* q, const bf16_t* kb, const bf16_t* 
   const long cands_per_wg = 255 / Lg + 2 < g.n ? 255 / Lg + 2 : g.n;
   if (cands_per_wg * ((g.L + 63) / 64) > kMaxBlockTiles || (max_ctx + 15) / 16 > kMaxPages) return false;
   a.wg_tiles = (int)((rows + 255) / 256);
-  const int base = g.B * md.Hkv * a.wg_tiles;
-  // Few workgroups and a long prefix: cut the prefix tiles into runs so that about one workgroup per CU exists,
-  // at least eight tiles per run, at most eight runs; a second kernel merges the partial results. (Measured: the
-  // one-phase kernel's split mode, with 128-row workgroups, is faster for such launches; the caller prefers it.)
-  const int prefix_tiles = (max_ctx + 63) / 64;
-  int splits = 1;
-  if (part && base < 160 && prefix_tiles >= 16) {
-    splits = 256 / base;
-    splits = splits > 8 ? 8 : splits;
-    splits = splits > prefix_tiles / 8 ? prefix_tiles / 8 : splits;
-    const size_t per_split = (size_t)base * 256 * (md.hd + 2);
-    if (splits > 1 && (size_t)splits * per_split > part_floats) splits = (int)(part_floats / per_split);
-    if (splits < 1) splits = 1;
-  }
-  a.n_splits = splits;
-  a.part_o = nullptr; a.part_m = nullptr; a.part_l = nullptr;
-  if (splits > 1) {
-    const size_t rows_all = (size_t)base * splits * 256;
-    a.part_o = part; a.part_m = part + rows_all * md.hd; a.part_l = a.part_m + rows_all;
-  }
-  a.total_wg = base * splits;
+  a.total_wg = g.B * md.Hkv * a.wg_tiles;
   a.wg_per_xcd = (a.total_wg + 7) / 8;
-  a.last_first = g.B == 1 && g.n == 1 && splits == 1;
+  a.last_first = g.B == 1 && g.n == 1;
   a.balanced = g.B >= 16 && g.B <= 64 && g.len_override < 0;
-  if (a.balanced) a.wg_per_xcd = ((g.B * md.Hkv + 7) / 8) * a.wg_tiles * splits;
+  if (a.balanced) a.wg_per_xcd = ((g.B * md.Hkv + 7) / 8) * a.wg_tiles;
   if (md.hd == 128) launch_pp_variant<128>(a, s); else launch_pp_variant<64>(a, s);
-  if (splits > 1) {
-    dim3 grid(g.M, md.Hq);
-    if (md.hd == 128)
-      attention_pingpong_merge_kernel<128><<<grid, 64, 0, s>>>(a.part_o, a.part_m, a.part_l, out, g.n, g.L, md.Hq,
-                                                              md.Hkv, a.wg_tiles, splits);
-    else
-      attention_pingpong_merge_kernel<64><<<grid, 64, 0, s>>>(a.part_o, a.part_m, a.part_l, out, g.n, g.L, md.Hq,
-                                                             md.Hkv, a.wg_tiles, splits);
-  }
   return true;
 }

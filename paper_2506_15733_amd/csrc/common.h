@@ -134,7 +134,7 @@ bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT,
 // (beam, kv head) per workgroup. False if the shape is not taken.
 bool launch_attention_pingpong(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                                const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,
-                               int max_ctx, float* part, size_t part_floats, hipStream_t s);
+                               int max_ctx, hipStream_t s);
 
 enum { DECODE_MAX_RUNS = 32 };   // runs of prefix tiles a beam is cut into at most
 // One in-block position per candidate (g.L == 1, position g.t0): prefix keys by the MFMA kernel in split mode,

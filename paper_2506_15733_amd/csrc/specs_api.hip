@@ -1056,7 +1056,7 @@ void attention<bf16_t>(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, con
   // at the 7B shapes); smaller ones the one-phase kernel, which cuts long key lists over several workgroups.
   const long stacked = (long)g.B * md.Hkv * (((long)g.n * g.L * (md.Hq / md.Hkv) + 255) / 256);
   if (whole_blocks) {
-    if (stacked >= 160 && launch_attention_pingpong(q, kb, vbT, pK, pV, out, g, md, Lp, max_ctx, nullptr, 0, s)) {
+    if (stacked >= 160 && launch_attention_pingpong(q, kb, vbT, pK, pV, out, g, md, Lp, max_ctx, s)) {
       count_path(SPECS_PATH_ATTN_MFMA);
       return;
     }
