@@ -512,6 +512,16 @@ int mfma_lmhead_tiles(int V) { return (V + 255) / 256; }
 struct TileShape { int bm, bn; double lat, full; };
 static const TileShape kTiles[MFMA_TILES] = {{256, 256, 1.15, 1.7}, {128, 256, 0.68, 1.04}, {128, 128, 0.46, 0.65}, {64, 128, 0.33, 0.41}, {32, 128, 0.30, 0.36}};
 
+// K-tiles in the LDS ring of the kernel that takes a product. 64 x 128: six, in one workgroup per CU, where few
+// workgroups walk a long K; else half of that and two workgroups per CU, which fill it sooner and leave no nearly empty
+// last round (16 x 37888 x 3584, 296 workgroups: 62.2 -> 58.8 us).
+int mfma_gemm_ring(int tile, int M, int N, int K, int ksplit) {
+  const TileShape& ts = kTiles[tile];
+  const long wgs = (long)((M + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn) * ksplit;
+  static const int ring[MFMA_TILES] = {5, 3, 5, 3, 4};
+  return tile == 3 && wgs <= 256 && K / 64 > 11 * ksplit ? 6 : ring[tile];
+}
+
 template <int EPI, bool HD128 = false>
 static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
   a.m_tiles = (a.M + kTiles[tile].bm - 1) / kTiles[tile].bm;
@@ -521,11 +531,7 @@ static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
   else if constexpr (EPI != ME_LMHEAD) {
     // four wavefronts along M: two per SIMD cover each other's LDS reads (69 -> 64 us at 256 x 1536 x 8960)
     if (tile == 2) launch_variant<128, 128, 4, 5, EPI, HD128>(a, s);
-    // 64 x 128: a ring of six K-tiles in one workgroup per CU where few workgroups walk a long K; else half the ring and
-    // two workgroups per CU, which fill it sooner and leave no nearly empty last round (16 x 37888 x 3584, 296
-    // workgroups: 62.2 -> 58.8 us)
-    else if (tile == 3 && (long)a.m_tiles * a.n_tiles * a.ksplit <= 256 && a.K / 64 > 11 * a.ksplit)
-      launch_variant<64, 128, 2, 6, EPI, HD128>(a, s);
+    else if (mfma_gemm_ring(tile, a.M, a.N, a.K, a.ksplit) == 6) launch_variant<64, 128, 2, 6, EPI, HD128>(a, s);
     else if (tile == 3) launch_variant<64, 128, 2, 3, EPI, HD128>(a, s);
     else launch_variant<32, 128, 1, 4, EPI, HD128>(a, s);
   }
@@ -560,7 +566,8 @@ void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* til
 // QKV projection with the rotary embedding, the bf16 conversion and the per-candidate transposition of the values
 // in the epilogue: no float [M, (Hq+2Hkv)*hd] round trip through memory and no separate kernel. Row m is in-block
 // position m % g.L of candidate m / g.L. Returns false when the shape is not taken (head_dim other than 64/128,
-// K % 64 != 0, misaligned buffers, launches of one position of longer blocks); the caller then runs the projection and the rotary kernel separately.
+// K % 64 != 0, misaligned buffers, launches of one position of longer blocks); the caller then runs the projection and
+// the rotary kernel separately.
 bool launch_gemm_mfma_qkv_rope(const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q, bf16_t* kblk, bf16_t* vT,
                                const BatchGeom& g, const ModelDims& md, int Lp, int tile, hipStream_t s) {
   const int M = g.M, N = (md.Hq + 2 * md.Hkv) * md.hd, K = md.d;

@@ -1,0 +1,37 @@
+"""Host-side rules of the library that choose kernels and cut launches, called by their C++ names. No GPU needed."""
+import ctypes as C
+import os
+
+
+def library():
+    from paper_2506_15733_amd import binding
+    if not os.path.exists(binding.LIB_PATH):
+        import __graft_entry__
+        __graft_entry__.build()
+    return binding.load_library()
+
+
+class DecodeRuns(C.Structure):
+    _fields_ = [("tiles", C.c_int32), ("count", C.c_int32)]
+
+
+def decode_runs(lens, units, per_split, part_floats):
+    f = library()._Z16plan_decode_runsPKiiilmm
+    f.restype = DecodeRuns
+    f.argtypes = [C.POINTER(C.c_int32), C.c_int, C.c_int, C.c_long, C.c_size_t, C.c_size_t]
+    r = f((C.c_int32 * len(lens))(*lens), len(lens), -1, units, per_split, part_floats)
+    return r.tiles, r.count
+
+
+TILES = ("256x256", "128x256", "128x128", "64x128", "32x128")
+
+
+def gemm_kernel(M, N, K, max_split=1):
+    """Tile, K-tiles of its LDS ring and number of K slices that a bf16 product of the matrix-unit family gets."""
+    lib = library()
+    plan, ring = lib._Z14mfma_gemm_planiiiibPiS_, lib._Z14mfma_gemm_ringiiiii
+    plan.restype, ring.restype = None, C.c_int
+    plan.argtypes, ring.argtypes = [C.c_int] * 4 + [C.c_bool] + [C.POINTER(C.c_int)] * 2, [C.c_int] * 5
+    tile, split = C.c_int(), C.c_int()
+    plan(M, N, K, max_split, False, tile, split)
+    return TILES[tile.value], ring(tile.value, M, N, K, split.value), split.value

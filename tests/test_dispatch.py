@@ -1,31 +1,11 @@
-"""Host-side rules that choose how a launch is cut, called in the built library by their C++ names. No GPU needed."""
-import ctypes as C
-import os
+"""Host-side rules that choose kernels and cut launches. No GPU needed."""
 import random
 import time
 
 import pytest
 
-
-@pytest.fixture(scope="module")
-def lib():
-    from paper_2506_15733_amd import binding
-    if not os.path.exists(binding.LIB_PATH):
-        import __graft_entry__
-        __graft_entry__.build()
-    return binding.load_library()
-
-
-class DecodeRuns(C.Structure):
-    _fields_ = [("tiles", C.c_int32), ("count", C.c_int32)]
-
-
-def decode_runs(lib, lens, units, per_split, part_floats):
-    f = lib._Z16plan_decode_runsPKiiilmm
-    f.restype = DecodeRuns
-    f.argtypes = [C.POINTER(C.c_int32), C.c_int, C.c_int, C.c_long, C.c_size_t, C.c_size_t]
-    r = f((C.c_int32 * len(lens))(*lens), len(lens), -1, units, per_split, part_floats)
-    return r.tiles, r.count
+from host_rules import decode_runs, gemm_kernel
+import test_gpu_kernels as kernels
 
 
 def decode_runs_by_definition(lens, units, per_split, part_floats):
@@ -37,23 +17,23 @@ def decode_runs_by_definition(lens, units, per_split, part_floats):
     return run, -(-longest // run)
 
 
-def test_runs_of_generation_attention_are_the_shortest_that_fit(lib):
+def test_runs_of_generation_attention_are_the_shortest_that_fit():
     rng = random.Random(3)
     for _ in range(300):
         lens = [int(2 ** rng.uniform(0, 14)) for _ in range(rng.choice((1, 2, 3, 17, 64, 300)))]
         units = rng.choice((1, 2, 4, 9, 64, 513))
         per_split = rng.randint(1, 1 << 20)
         args = lens, units, per_split, rng.choice((0, per_split, 3 * per_split, 1 << 40))
-        assert decode_runs(lib, *args) == decode_runs_by_definition(*args), args
-    assert decode_runs(lib, [0], 1, 1, 100) == (1, 1)
+        assert decode_runs(*args) == decode_runs_by_definition(*args), args
+    assert decode_runs([0], 1, 1, 100) == (1, 1)
 
 
-def test_runs_are_found_quickly_where_no_length_fits(lib):
+def test_runs_are_found_quickly_where_no_length_fits():
     """256 beams, one of them long, and more workgroups than are resident: a search through all run lengths takes about
     half a million divisions, a bisection a few thousand. The bound lies an order of magnitude from both."""
     lens = [1024] * 255 + [131072]
-    best = min(_timed(lambda: decode_runs(lib, lens, 4, 1, 1 << 40)) for _ in range(20))
-    assert decode_runs(lib, lens, 4, 1, 1 << 40) == (2048, 1)
+    best = min(_timed(lambda: decode_runs(lens, 4, 1, 1 << 40)) for _ in range(20))
+    assert decode_runs(lens, 4, 1, 1 << 40) == (2048, 1)
     assert best < 3e-4, best
 
 
@@ -61,3 +41,21 @@ def _timed(f):
     t = time.perf_counter()
     f()
     return time.perf_counter() - t
+
+
+@pytest.mark.parametrize("kernel,max_split,M,N,K", [(*c[:2], *c[2:]) for c in kernels.TILE_SHAPES] +
+                         [(c[0], 1, c[1], 2 * c[2], c[3]) for c in kernels.GATE_UP_SHAPES] +
+                         [(c[0], 1, c[5] * c[6] * c[7], (c[1] + 2 * c[2]) * c[3], c[4]) for c in kernels.QKV_TILES])
+def test_kernel_tests_reach_the_kernels_they_name(kernel, max_split, M, N, K):
+    """The GPU tests of the tile shapes choose products by size; this ties every size to the tile, ring and slices that the
+    plan gives it, so that a change of the plan cannot leave a kernel without its test unnoticed."""
+    tile, ring, split = gemm_kernel(M, N, K, max_split)
+    assert f"{tile}/{ring}" == kernel and (split > 1) == (max_split > 1), (tile, ring, split)
+
+
+def test_every_kernel_has_its_test():
+    every = {"256x256/5", "128x256/3", "128x128/5", "64x128/6", "64x128/3", "32x128/4"}
+    assert {c[0] for c in kernels.TILE_SHAPES if c[1] == 1} == every            # plain store and residual add
+    assert {c[0] for c in kernels.GATE_UP_SHAPES} == every
+    for hd in (64, 128):
+        assert {c[0] for c in kernels.QKV_TILES if c[3] == hd} == every

@@ -61,21 +61,33 @@ def test_linear_bf16(ctx, M, N, K):
     close(out.cpu().numpy().astype(np.float64), want + c0, 2e-5)
 
 
-# one workgroup tile shape per line: ragged in rows and columns, fewer K-tiles than the ring holds, as many, more
-@pytest.mark.parametrize("M,N,K", [(65, 136, 64), (63, 129, 384), (70, 300, 192), (129, 520, 448),        # 64 x 128
-                                   (321, 8200, 320), (700, 4616, 384), (321, 8200, 64),                   # 128 x 128
-                                   (555, 37888, 192), (300, 17920, 128), (2060, 9000, 64),                # 128 x 256
-                                   (1100, 33000, 128),                                                    # 256 x 256
-                                   (1, 64, 64), (5, 301, 192), (32, 2050, 1280), (17, 896, 4864),         # 32 x 128, up to 16 slices
-                                   (64, 1000, 832), (31, 37888, 448), (33, 896, 4864)])                   # 64 x 128, two per CU
-def test_linear_tile_shapes(ctx, M, N, K):
+# (tile/K-tiles of its ring, K slices at most, M, N, K), ragged in rows and columns: fewer K-tiles than the ring holds, as
+# many, more. test_dispatch.py checks that each product takes the kernel it is listed for.
+TILE_SHAPES = [("256x256/5", 1, 1100, 33000, 128), ("256x256/5", 1, 1601, 5003, 384),
+               ("128x256/3", 1, 555, 37888, 192), ("128x256/3", 1, 2060, 9000, 64), ("128x256/3", 1, 1100, 4100, 320),
+               ("128x128/5", 1, 321, 8200, 320), ("128x128/5", 1, 700, 4616, 384), ("128x128/5", 1, 321, 8200, 64),
+               ("64x128/6", 1, 70, 300, 768), ("64x128/6", 1, 255, 4104, 832), ("64x128/6", 1, 33, 100, 1600),
+               ("64x128/3", 1, 65, 136, 64), ("64x128/3", 1, 70, 300, 192), ("64x128/3", 1, 201, 904, 704), ("64x128/3", 1, 33, 38000, 832),
+               ("32x128/4", 1, 1, 64, 64), ("32x128/4", 1, 5, 301, 192), ("32x128/4", 1, 31, 1000, 256), ("32x128/4", 1, 17, 516, 704),
+               ("64x128/3", 16, 63, 129, 384), ("64x128/3", 16, 129, 520, 448), ("64x128/3", 16, 64, 1000, 832), ("64x128/3", 16, 33, 896, 4864),
+               ("32x128/4", 16, 32, 2050, 1280), ("32x128/4", 16, 17, 896, 4864)]
+
+
+@pytest.mark.parametrize("kernel,max_split,M,N,K", TILE_SHAPES)
+def test_linear_tile_shapes(ctx, kernel, max_split, M, N, K):
     from paper_2506_15733_amd import binding as B
     a, ta = draw(f"a{M}.{K}", (M, K))
     w, tw = draw(f"w{N}.{K}", (N, K), 0.02)
     out = torch.zeros((M, N), dtype=torch.float32, device=DEV)
-    B.specs_op_linear(ctx, ta, tw, out, accumulate=False)
-    torch.cuda.synchronize()
-    close(out.cpu().numpy().astype(np.float64), oracle.linear(a, w), 2e-5)   # the bound of test_linear_bf16
+    # slices of K pass through the workspace: with no room for two the epilogue stores, or adds to, the whole product
+    ws = torch.zeros(256 + (max_split > 1) * max_split * M * N * 4, dtype=torch.uint8, device=DEV)
+    own = B.specs_ctx_create(0, torch.cuda.current_stream().cuda_stream, ws)
+    want = oracle.linear(a, w)
+    for times in (1, 2):
+        B.specs_op_linear(own, ta, tw, out, accumulate=times > 1)
+        torch.cuda.synchronize()
+        close(out.cpu().numpy().astype(np.float64), times * want, times * 2e-5)   # the bound of test_linear_bf16, per product
+    B.specs_ctx_destroy(own)
 
 
 @pytest.mark.parametrize("M", [1, 32, 33, 300])
@@ -124,9 +136,15 @@ def test_linear_f32_small(ctx, M, N, K, offset):
         close(out.cpu().numpy().astype(np.float64), times * oracle.linear(a, w), 2e-6)   # the bound of test_linear_f32
 
 
-@pytest.mark.parametrize("M,F,K", [(45, 96, 64), (300, 160, 128), (300, 1120, 256), (256, 2816, 1024), (2048, 18944, 3584),
-                                   (16, 18944, 3584), (7, 96, 128), (32, 8960, 1536), (19, 160, 384)])
-def test_gate_up_bf16(ctx, M, F, K):
+GATE_UP_SHAPES = [("64x128/3", 45, 96, 64), ("64x128/3", 300, 160, 128), ("64x128/3", 300, 1120, 256),
+                  ("64x128/6", 256, 2816, 1024), ("256x256/5", 2048, 18944, 3584), ("64x128/3", 16, 18944, 3584),
+                  ("32x128/4", 7, 96, 128), ("32x128/4", 32, 8960, 1536), ("32x128/4", 19, 160, 384),
+                  ("256x256/5", 420, 8224, 384), ("128x256/3", 321, 5792, 320), ("128x128/5", 321, 4000, 384),
+                  ("64x128/6", 129, 96, 768), ("64x128/6", 201, 928, 832), ("64x128/3", 129, 96, 704)]
+
+
+@pytest.mark.parametrize("kernel,M,F,K", GATE_UP_SHAPES)
+def test_gate_up_bf16(ctx, kernel, M, F, K):
     from paper_2506_15733_amd import binding as B
     from paper_2506_15733_amd.synthetic import pack_gate_up
     a, ta = draw(f"ga{M}.{K}", (M, K))
@@ -252,6 +270,17 @@ def test_attention_bf16(ctx, Hq, Hkv, hd, Bn, n, L, lens, pt):
     # below 2 when hundreds of keys are averaged and below 4 when a row sees only two or three keys
     assert err < 2.0 ** -7 or (min(lens) < 64 and err <= 2.0 ** -6), err
 
+
+# every kernel the rotary epilogue exists for, ragged in rows, with block lengths off 16: (kernel, Hq, Hkv, hd, d_model,
+# beams, candidates, L)
+QKV_TILES = [("256x256/5", 24, 8, 128, 384, 1, 23, 70), ("256x256/5", 40, 8, 64, 384, 1, 23, 101),
+             ("128x256/3", 24, 8, 128, 320, 1, 23, 37), ("128x256/3", 40, 8, 64, 320, 1, 29, 43),
+             ("128x128/5", 40, 8, 128, 384, 3, 1, 130), ("128x128/5", 48, 8, 64, 384, 1, 7, 101),
+             ("64x128/6", 3, 1, 128, 768, 1, 7, 5), ("64x128/6", 6, 3, 64, 832, 2, 3, 21),
+             ("64x128/3", 1, 1, 128, 704, 1, 7, 5), ("64x128/3", 1, 1, 64, 128, 1, 7, 5),
+             ("32x128/4", 3, 1, 128, 320, 1, 1, 5), ("32x128/4", 5, 1, 64, 64, 1, 3, 7)]
+
+
 @pytest.mark.parametrize("dtype,Hq,Hkv,hd,d_model,Bn,n,L,lens", [
     ("bf16", 28, 4, 128, 3584, 1, 4, 128, [4096]),        # 7B layer: rotary embedding inside the GEMM epilogue, head_dim 128
     ("bf16", 6, 2, 64, 384, 3, 2, 70, [100, 17, 333]),    # head_dim 64, block length off every tile: zeroed padding of vT
@@ -259,7 +288,7 @@ def test_attention_bf16(ctx, Hq, Hkv, hd, Bn, n, L, lens, pt):
     ("bf16", 12, 2, 128, 1536, 2, 8, 1, [50, 2000]),      # one token a block: projection in K slices, then the rotary kernel
     ("bf16", 6, 2, 64, 384, 3, 17, 1, [100, 17, 333]),    # the same with more than 32 rows
     ("f32", 6, 2, 16, 96, 3, 3, 5, [38, 8, 20]),          # float: plain kernels
-])
+    *[("bf16", *c[1:8], [100 + 37 * b for b in range(c[5])]) for c in QKV_TILES]])
 def test_qkv_projection_with_rotary_embedding(ctx, dtype, Hq, Hkv, hd, d_model, Bn, n, L, lens):
     """q, k, v of one layer on given operands against the definition: y = A W^T in float64, q and k heads rotated
     by oracle.rope at absolute position lens[b] + t, everything rounded once to the operand type; block keys per row,
