@@ -649,3 +649,59 @@ def test_kernel_timings_count_one_launch_per_layer(kind):
         assert [got[k] for k in ("qkv", "attention", "oproj", "gate_up", "down")] == [layers] * 5, (role, got)
         assert got["lmhead"] == (role != "prm"), (role, got)
     step.close()
+
+
+@pytest.mark.parametrize("d_model,hq,hkv,hd,ffn,n,L", [
+    (20, 3, 1, 8, 32, 1, 1),            # less than a wavefront's 16-byte columns, one row
+    (60, 4, 2, 24, 96, 3, 7),           # columns off 16, rows off 8
+    (252, 2, 2, 40, 160, 3, 17), (256, 6, 3, 16, 64, 2, 8),     # up to the widest that one staged row holds
+    (260, 6, 3, 16, 64, 3, 7)])         # wider: the plain product with the kernels before and after it
+def test_float_projections_with_their_norm_and_epilogue(d_model, hq, hkv, hd, ffn, n, L):
+    """Small float models normalise, project and rotate (or gate) in one launch, counted by the launches left outside the
+    products. Queries and the gated product show in the log-probabilities; keys and values are read back from the pages,
+    where a commit puts those of a scored block and then those of a generated one (one position a launch)."""
+    from paper_2506_15733_amd import synthetic, binding as B
+    mk = lambda role, head: ModelDesc(role, 1, d_model, hq, hkv, hd, ffn, 301, "f32", head)
+    wl = Workload("float_fused", mk("target", "lm"), mk("draft", "lm"), mk("prm", "prm"), B=2, n=n, L=L, prefix_len=0,
+                  lens_range=(7, 40), betas=(1.0,), token_dist="uniform", page_tokens=4, seed=61, u_seed=62)
+    desc, hw = wl.target, HostWeights(wl.target, wl.seed)
+    step = synthetic.ScoringStep(wl, extra_tokens=2 * L)
+    step.prefill()
+    dm, pf = step.models["target"], step.prefixes["target"]
+
+    def check_pages(traces):
+        torch.cuda.synchronize()
+        assert B.specs_ctx_status(dm.ctx) == 0
+        pool, table = pf.kv_pool[0].double().cpu().numpy(), pf.page_table.cpu().numpy()
+        for b, want in enumerate(oracle.prefill(desc, hw, traces)):
+            pages = table[b, :(want.length + 3) // 4]
+            k = pool[0, pages].reshape(-1, hkv, 4, hd).transpose(0, 2, 1, 3).reshape(-1, hkv, hd)[:want.length]
+            v = pool[1, pages].reshape(-1, hkv, hd, 4).transpose(0, 3, 1, 2).reshape(-1, hkv, hd)[:want.length]
+            for got, exp in ((k, want.K[0]), (v, want.V[0])):
+                assert np.abs(got - exp).max() < 1e-5 * max(1.0, np.abs(exp).max()), b
+
+    traces = [np.asarray(t) for t in wl.prefix_tokens()]
+    check_pages(traces)
+    cand = wl.candidates()
+    want = oracle.score_cached(desc, hw, oracle.prefill(desc, hw, traces), cand)[1]
+    B.specs_ctx_profile(dm.ctx, True)
+    step.score("target")
+    torch.cuda.synchronize()
+    launches = {k: c for k, (_, c) in B.specs_ctx_profile_read(dm.ctx).items()}
+    B.specs_ctx_profile(dm.ctx, False)
+    # embedding, final norm and merge; unfused also two norms and the rotary kernel
+    assert launches["other"] == (3 if d_model <= 256 else 6) and launches["qkv"] == launches["gate_up"] == 1, launches
+    assert np.abs(step.tok["target"].cpu().numpy() - want).max() < 1e-5
+    B.specs_commit_block(dm.ctx, dm.model, pf.handle, [n - 1, 0])
+    traces = [np.concatenate([t, cand[b, (n - 1, 0)[b]]]) for b, t in enumerate(traces)]
+    check_pages(traces)
+    u = torch.from_numpy(W.rng.uniform_f64(63, "float_fused", 2 * n * L).reshape(2, n, L)).to("cuda:0")
+    ids, logp, tok = torch.zeros((2, n, L), dtype=torch.int32, device="cuda:0"), torch.zeros((2, n), device="cuda:0"), torch.zeros((2, n, L), device="cuda:0")
+    B.specs_generate_blocks(dm.ctx, dm.model, pf.handle, u, ids, logp, tok, 0)
+    torch.cuda.synchronize()
+    ids = ids.cpu().numpy()
+    want = oracle.score_cached(desc, hw, oracle.prefill(desc, hw, traces), ids)[1]
+    assert np.abs(tok.cpu().numpy() - want).max() < 1e-5
+    B.specs_commit_block(dm.ctx, dm.model, pf.handle, [0, n - 1])
+    check_pages([np.concatenate([t, ids[b, (0, n - 1)[b]]]) for b, t in enumerate(traces)])
+    step.close()
