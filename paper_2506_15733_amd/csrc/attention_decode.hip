@@ -32,8 +32,9 @@ struct MergeArgs {
 // columns). The kernel is a chain of short dependent phases on a few KB, bound by latency, so whatever does not depend
 // on computed values (statistics and the first partial outputs of the runs, values) is requested before the scores.
 // (One wavefront per (candidate, query head), each lane with a key row of its own, touched 64 cache lines with every
-// load: 25.9 us at 256 candidates x 12 heads with 8 runs each; this form 8.1 us with up to 19 runs. At 16 x 12, where the
-// prefix kernel wants 32 runs instead of 16 (8.7 us instead of 10.7), it takes 8.0 us, the other 9.3 with 16.)
+// load: 25.9 us at 256 candidates x 12 heads with 8 runs each; this form 8.1 us with up to 19 runs. At 16 x 12 the two take
+// the same, 9.3 us on average over the 128 positions of a block, but this one with the 32 runs that the prefix kernel
+// wants, 8.7 us instead of 10.7 with 16.)
 template <int HD>
 __global__ void __launch_bounds__(256) attention_decode_merge_kernel(MergeArgs a) {
   constexpr int KS = HD / 32;                   // MFMA K-steps of the scores
@@ -277,7 +278,8 @@ bool launch_attention_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vb
   const size_t osum_off = ((size_t)HS * (4 * (Lq + 4) + 2 * (Lq + 8) + 8 * n_splits + 4) + 15) & ~(size_t)15;
   const size_t lds = osum_off + 4 * (size_t)HS * md.hd * 4;
   a.osum_off = (int)osum_off;
-  if (lds <= 64 * 1024) {                                // 300 block tokens with 16 query heads per kv head, more with fewer
+  // 6 Lq + 8 n_splits + 16 hd + 36 bytes per head row: with 16 rows of 128 and 32 runs blocks of up to 288 tokens
+  if (lds <= 64 * 1024) {
     const dim3 grid(g.B * g.n, md.Hkv, (gq + 15) / 16);
     if (md.hd == 128) attention_decode_merge_kernel<128><<<grid, 256, lds, s>>>(a);
     else attention_decode_merge_kernel<64><<<grid, 256, lds, s>>>(a);
