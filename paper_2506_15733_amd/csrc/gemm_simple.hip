@@ -5,7 +5,10 @@
 
 #define TS 64   // tile of C per block
 #define TK 16   // K step
-#define SMALL_MAX_WGS 4096   // 8 x 8 (8 x 64) tiles up to which the small kernels are taken
+// 8 x 8 tiles up to which the small kernels are taken. 512 x 512 is 4096 of them: 5.7, 8.1, 23.9, 93.7 us with 64, 256,
+// 1000, 4096 columns, against 10.5, 33.9, 129, 587 in 64 x 64 tiles. The two cross further up, where depends on the columns:
+// 1024 x 1024 takes 14.9 against 11.1 with 64, but 24 against 34 with 256.
+#define SMALL_MAX_WGS 4096
 // 256 threads, each a 4x4 patch of the 64x64 tile.
 
 template <typename T>
@@ -71,7 +74,7 @@ __global__ void __launch_bounds__(256) gemm_simple_kernel(const T* __restrict__ 
 }
 
 // Few rows and columns: a 64 x 64 tile would put the product on a handful of CUs and walk K in dependent 16-deep steps
-// (64 x 64 x 256: one workgroup, 42 us). Here a workgroup owns 8 x 8 outputs, requests all its operand rows (256 columns
+// (64 x 64 x 256: one workgroup, 32.9 us against 3.5). Here a workgroup owns 8 x 8 outputs, requests all its operand rows (256 columns
 // of them at a time) at once in 16-byte pieces, and its four wavefronts take a quarter of the columns each; their sums
 // are added in order. The kernel is bound by the latency of one round of loads.
 #define SK 256                                             // columns per round
@@ -224,6 +227,8 @@ __global__ void __launch_bounds__(256) small_projection_kernel(SmallArgs a) {
   }
 }
 
+// Up to as many tiles as the small products: at 4096 of them (512 rows x 512 outputs of 256 columns) a layer of the fused
+// kernels takes 8 us less than one with norm, product and rotary or gate kernel of their own (four layers 183 against 216).
 static bool small_projection_ok(const float* x, const float* gain, const float* W, int M, int N, int K) {
   return K <= SK && K % 4 == 0 && (((uintptr_t)x | (uintptr_t)gain | (uintptr_t)W) & 15) == 0 &&
          (long)((M + 7) / 8) * (N / 8) <= SMALL_MAX_WGS;
@@ -356,7 +361,10 @@ void launch_lmhead_partials_simple(const T* A, const T* W, const int32_t* tok, f
                                    float* zt, int M, int V, int K, int* n_tiles_out, hipStream_t s) {
   int nt = lmhead_simple_tiles(V);
   *n_tiles_out = nt;
-  if ((long)nt * ((M + 7) / 8) <= SMALL_MAX_WGS && quads_ok(A, W, K)) {
+  // 8-row tiles up to three rounds of the chip: 3072 of them take 14.3 us with 64 columns and 132 with 1024, the 64-row
+  // kernel 16.4 and 164 for the same product; 4096 (64 rows x 32768 ids) 17.1 and 172 against 16.5 and 164. With at most 32
+  // rows the 64-row tile is half empty, and 4096 still pay: 17.1 and 175 against 20.2 and 221 (32 rows x 65536 ids).
+  if ((long)nt * ((M + 7) / 8) <= (M <= 32 ? 4096 : 3072) && quads_ok(A, W, K)) {
     lmhead_partials_small_kernel<T><<<dim3(nt, (M + 7) / 8), 256, 0, s>>>(A, W, tok, part_max, part_sum, zt, M, V, K, nt);
     return;
   }

@@ -179,12 +179,15 @@ def test_lmhead_logprob_bf16(ctx, M, V, K):
     assert np.abs(out.cpu().numpy() - want).max() < 2e-5 * max(1.0, np.abs(want).max())
 
 
-def test_lmhead_logprob_f32(ctx):
+# (rows, ids, columns): one odd tile, then both sides of the two lines between 8-row and 64-row tiles (3072 tiles of 8 rows x
+# 64 ids, 4096 of them up to 32 rows)
+@pytest.mark.parametrize("M,V,K", [(37, 515, 72), (192, 8190, 36), (193, 8190, 36), (32, 65500, 20), (32, 65540, 20), (33, 39400, 20)])
+def test_lmhead_logprob_f32(ctx, M, V, K):
     from paper_2506_15733_amd import binding as B
-    a, ta = draw("lfa", (37, 72), 1.0, "f32")
-    w, tw = draw("lfw", (515, 72), 0.3, "f32")
-    tok = W.rng.uniform_tokens(3, "lft", 37, 515)
-    out = torch.zeros(37, dtype=torch.float32, device=DEV)
+    a, ta = draw(f"lfa{M}.{K}", (M, K), 1.0, "f32")
+    w, tw = draw(f"lfw{V}.{K}", (V, K), 0.3, "f32")
+    tok = W.rng.uniform_tokens(3, f"lft{M}", M, V)
+    out = torch.zeros(M, dtype=torch.float32, device=DEV)
     B.specs_op_lmhead_logprob(ctx, ta, tw, torch.from_numpy(tok).to(DEV), out)
     torch.cuda.synchronize()
     assert np.abs(out.cpu().numpy() - oracle.token_logprob(a, w, tok)).max() < 5e-6
