@@ -33,7 +33,7 @@ struct MergeArgs {
 // on computed values (statistics and the first partial outputs of the runs, values) is requested before the scores.
 // (One wavefront per (candidate, query head), each lane with a key row of its own, touched 64 cache lines with every
 // load: 25.9 us at 256 candidates x 12 heads with 8 runs each; this form 8.1 us with up to 19 runs. At 16 x 12 the two take
-// the same, 9.3 us on average over the 128 positions of a block, but this one with the 32 runs that the prefix kernel
+// the same, 9.3 - 9.5 us on average over the 128 positions of a block, but this one with the 32 runs that the prefix kernel
 // wants, 8.7 us instead of 10.7 with 16.)
 template <int HD>
 __global__ void __launch_bounds__(256) attention_decode_merge_kernel(MergeArgs a) {

@@ -58,7 +58,8 @@ __global__ void __launch_bounds__(64) subsample_kernel(const float* __restrict__
 #pragma unroll 8
       for (int i = 0; i < n; ++i) total += w[i];
       double thr = uu * total, run = 0.0;
-      // eight weights are read ahead of the eight dependent additions
+      // eight weights are read ahead of the eight dependent additions, in both passes (32 x 4 draws from 256 candidates 21.4
+      // -> 16.7 us, 4 x 4 from 1024 75 -> 54; up to 64 the launch hides it, 6.9 us both ways)
       for (int i0 = 0; i0 < n && pick < 0; i0 += 8) {
         double v[8];
 #pragma unroll
