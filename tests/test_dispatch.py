@@ -43,7 +43,7 @@ def _timed(f):
     return time.perf_counter() - t
 
 
-@pytest.mark.parametrize("kernel,max_split,M,N,K", [(*c[:2], *c[2:]) for c in kernels.TILE_SHAPES] +
+@pytest.mark.parametrize("kernel,max_split,M,N,K", kernels.TILE_SHAPES +
                          [(c[0], 1, c[1], 2 * c[2], c[3]) for c in kernels.GATE_UP_SHAPES] +
                          [(c[0], 1, c[5] * c[6] * c[7], (c[1] + 2 * c[2]) * c[3], c[4]) for c in kernels.QKV_TILES])
 def test_kernel_tests_reach_the_kernels_they_name(kernel, max_split, M, N, K):
