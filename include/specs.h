@@ -234,7 +234,7 @@ int specs_select_and_switch(specs_ctx* ctx, const float* logp_target, const floa
  * than 16 tokens). counts: host int32 [SPECS_PATH_COUNT]; reset != 0 clears the counters after reading them. */
 enum {
   SPECS_PATH_GEMM_MFMA = 0,   /* block-tiled MFMA GEMM family (vocabulary head included), more than 32 rows */
-  SPECS_PATH_GEMM_SKINNY,     /* the same family, at most 32 rows: bound by streaming the weights */
+  SPECS_PATH_GEMM_SKINNY,     /* the same and the kernels for few rows, at most 32 rows: bound by streaming the weights */
   SPECS_PATH_GEMM_PLAIN,      /* plain GEMM / vocabulary-head kernels */
   SPECS_PATH_ATTN_MFMA,       /* MFMA attention kernels (whole blocks or single positions) */
   SPECS_PATH_ATTN_PLAIN,      /* plain attention kernel */
@@ -272,7 +272,8 @@ int specs_op_attention(specs_ctx* ctx, const specs_model* m, const specs_prefix*
  * kblk[B*n*L][Hkv][hd] and the values transposed per candidate, vT[B*n][Hkv][hd][Lp] with Lp = L rounded
  * up to 16 and the padding zeroed: the layouts specs_op_attention's kernels read. bf16: the kernels the pass
  * runs for this shape (blocks of several tokens: the rotary embedding in the GEMM epilogue; of one token: the
- * product in as many K slices as the workspace has room for, then the rotary kernel). float: the plain product,
+ * product in as many K slices as the workspace has room for, then the rotary kernel; at most 32 such rows have a
+ * kernel of their own inside the pass). float: the plain product,
  * then the rotary kernel (the pass of a small float model fuses them with the normalisation, which is not part of
  * this call). */
 int specs_op_qkv_rope(specs_ctx* ctx, const specs_model* m, const specs_prefix* p, const void* A, const void* Wqkv,

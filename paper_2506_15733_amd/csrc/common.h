@@ -122,6 +122,17 @@ bool launch_small_qkv_rope(const float* x, const float* gain, const float* W, co
 bool launch_small_gate_up(const float* x, const float* gain, const float* Wgu, float* act, int M, int F, int K, float eps,
                           hipStream_t s);
 
+// Projections of at most 32 rows with their normalisation and epilogue (few_rows.hip). False if the shape is not taken.
+// The operand of the first is RMSNorm(x) * gain if A is null, else A [M, K].
+bool launch_few_rows_qkv_rope(const float* x, const float* gain, const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q,
+                              bf16_t* kblk, bf16_t* vT, const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s);
+bool launch_few_rows_gate_up(const float* x, const float* gain, const bf16_t* Wgu, bf16_t* act, int M, int F, int K, float eps,
+                             hipStream_t s);
+bool launch_few_rows_logits(const float* x, const float* gain, const bf16_t* W, float* C, int M, int N, int K, float eps,
+                            hipStream_t s);
+// x[M, N] += A[M, K] W[N, K]^T
+bool launch_few_rows_residual(const bf16_t* A, const bf16_t* W, float* x, int M, int N, int K, hipStream_t s);
+
 template <typename T>
 void launch_attention_simple(const T* q, const T* kb, const T* vbT, const T* poolK, const T* poolV, T* out,
                              const BatchGeom& g, const ModelDims& md, int max_ctx, hipStream_t s);

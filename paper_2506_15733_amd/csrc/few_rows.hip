@@ -1,0 +1,461 @@
+// The projections of a layer for at most 32 rows of bf16 operands (one position of every generated block, the reward
+// model's last tokens), each in one launch with what surrounds it: the normalisation of its operand in front, rotary
+// embedding, SiLU x up or the residual addition behind. Such a launch is bound by how soon and how fast its weights
+// stream in, so the layout serves that alone:
+//   - 16 rows of W are one operand of v_mfma_f32_16x16x32_bf16, the rows of activations the other; the wavefronts of a
+//     workgroup cut K into equal parts, and each holds its part of the (normalised) activations in registers;
+//   - every wavefront has a ring of LDS slots of its own, 16 rows x 64 columns of W each, which it fills with
+//     global -> LDS loads and empties itself, so nothing but its own loads is waited for. The ring is filled before
+//     the normalisation begins, which the latency of these loads hides. (Loads to registers in operand order have 16
+//     different rows in 16 consecutive lanes, i.e. a cache line per lane: 13 bytes a cycle and CU.);
+//   - the wavefronts' partial products meet in LDS, one barrier per batch of tiles, and one wavefront finishes a tile.
+// The launches of a layer and position take 52 us instead of 61 (seven, not nine) at 16 rows of d = 1536, F = 8960, and 123
+// instead of 134 at d = 3584, F = 18944; 27 instead of 37 (six) at 8 rows of d = 1024, F = 2816.
+#include "common.h"
+#include <type_traits>
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+#define LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
+#define GLB_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
+
+enum FewEpilogue { FE_STORE = 0, FE_SWIGLU = 1, FE_QKV_ROPE = 2, FE_RESIDUAL = 3 };
+constexpr int FEW_ROWS = 32;
+constexpr int NW = 8;                                    // wavefronts of a workgroup
+constexpr int PANEL = 2048;                              // bytes of 16 rows x 64 columns
+constexpr int CU_LDS = 160 * 1024;
+
+struct FewArgs {
+  const float* x;        // [M, K] residual stream: the operand is RMSNorm(x) * gain, rounded to bf16
+  const float* gain;
+  const bf16_t* A;       // [M, K] the operand, where the kernel does not normalise
+  const bf16_t* W;       // [N, K]
+  int M, N, K;
+  float eps;
+  int tiles, per_wg;     // tiles of 16 rows of W, and how many in a row a workgroup takes
+  float* C;              // FE_STORE: [M, N]
+  bf16_t* act;           // FE_SWIGLU: [M, N / 2]
+  const float* cs;       // FE_QKV_ROPE: cos | sin per row, outputs as in the tile kernel; row m is position t of block m
+  bf16_t* q;
+  bf16_t* kblk;
+  bf16_t* vT;
+  int Hq, Hkv, hd, Lk, Lp, t;
+  float* xo;             // FE_RESIDUAL: [M, N], xo += A W^T
+};
+
+// A panel in LDS: row r at 128 r, its 16-byte chunk c at position c ^ (r / 2), so that the 16 rows of a fragment read
+// spread over all banks. The lane that loads 16 bytes of row r to position p fetches chunk p ^ (r / 2).
+__device__ __forceinline__ int panel_at(int row, int chunk) { return row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4); }
+
+// Two loads fill a panel: rows 0..7 from r0 + lane's row, rows 8..15 from r1. lane -> row lane / 8 (+ 8), position lane % 8.
+__device__ __forceinline__ void load_panel(const bf16_t* r0, const bf16_t* r1, char* panel) {
+  __builtin_amdgcn_global_load_lds(GLB_PTR(r0), LDS_PTR(panel), 16, 0, 0);
+  __builtin_amdgcn_global_load_lds(GLB_PTR(r1), LDS_PTR(panel + 1024), 16, 0, 0);
+}
+__device__ __forceinline__ bf16x8 fragment(const char* panel, int r16, int chunk) {
+  return *(const bf16x8*)(panel + panel_at(r16, chunk));
+}
+
+// Waits until at most n of this wavefront's loads, PER at a time, are outstanding.
+template <int PER>
+__device__ __forceinline__ void wait_loads(int n) {
+  static_assert(7 * PER < 63, "the counter's range");
+  if (n >= 7) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(7 * PER) : "memory");
+  else if (n == 6) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(6 * PER) : "memory");
+  else if (n == 5) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(5 * PER) : "memory");
+  else if (n == 4) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * PER) : "memory");
+  else if (n == 3) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * PER) : "memory");
+  else if (n == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * PER) : "memory");
+  else if (n == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PER) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+#define BARRIER() asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory")
+
+// The first of the 8 rows of W that are rows 0..7 of a tile, and how much further on its rows 8..15 begin.
+template <int EPI>
+__device__ __forceinline__ int first_row(const FewArgs& a, int tile) {
+  if (EPI == FE_SWIGLU) return (tile >> 2) * 64 + (tile & 3) * 8;        // gate rows of 8 units, then their up rows
+  if (EPI != FE_QKV_ROPE) return 16 * tile;
+  const int per_head = a.hd >> 4, head = tile / per_head;                // 8 rotary pairs of a head
+  return head * a.hd + (tile - head * per_head) * 8;
+}
+template <int EPI>
+__device__ __forceinline__ int second_rows(const FewArgs& a) {
+  return EPI == FE_SWIGLU ? 32 : EPI == FE_QKV_ROPE ? a.hd >> 1 : 8;
+}
+
+// What one wavefront does with the sums of a tile, p [NW][MT][16 rows of x][16 rows of W]: lane -> row lane / 4 of x and,
+// of the tile's 16 columns, four in a row (FE_STORE), or two of the first eight and the same two of the last eight.
+template <int MT, int EPI>
+__device__ __forceinline__ void finish_tile(const FewArgs& a, int tile, const float* p) {
+  const int lane = threadIdx.x & 63;
+  const int m16 = lane >> 2, c = lane & 3;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {
+    const int m = 16 * mt + m16;
+    if (EPI == FE_STORE) {
+      float4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int u = 0; u < NW; ++u) {
+        const float4 o = *(const float4*)(p + (u * MT + mt) * 256 + m16 * 16 + 4 * c);
+        v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+      }
+      if (m < a.M) *(float4*)(a.C + (size_t)m * a.N + 16 * tile + 4 * c) = v;
+      continue;
+    }
+    floatx2 v1 = {0.f, 0.f}, v2 = {0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < NW; ++u) {
+      const float* row = p + (u * MT + mt) * 256 + m16 * 16 + 2 * c;
+      v1 += *(const floatx2*)row;
+      v2 += *(const floatx2*)(row + 8);
+    }
+    if (m >= a.M) continue;
+    if (EPI == FE_SWIGLU) {
+      bf16x2 o;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) o[e] = (__bf16)(v1[e] * __builtin_amdgcn_rcpf(1.0f + __expf(-v1[e])) * v2[e]);
+      *(bf16x2*)(a.act + (size_t)m * (a.N >> 1) + 8 * tile + 2 * c) = o;
+      continue;
+    }
+    const int half = a.hd >> 1, per_head = a.hd >> 4, head = tile / per_head;
+    const int i = (tile - head * per_head) * 8 + 2 * c;
+    if (head < a.Hq + a.Hkv) {
+      const float2 cn = *(const float2*)(a.cs + (size_t)m * a.hd + i), sn = *(const float2*)(a.cs + (size_t)m * a.hd + half + i);
+      bf16_t* dst = head < a.Hq ? a.q + ((size_t)m * a.Hq + head) * a.hd
+                                : a.kblk + (((size_t)m * a.Lk + a.t) * a.Hkv + (head - a.Hq)) * a.hd;
+      *(bf16x2*)(dst + i) = bf16x2{(__bf16)(v1[0] * cn.x - v2[0] * sn.x), (__bf16)(v1[1] * cn.y - v2[1] * sn.y)};
+      *(bf16x2*)(dst + half + i) = bf16x2{(__bf16)(v2[0] * cn.x + v1[0] * sn.x), (__bf16)(v2[1] * cn.y + v1[1] * sn.y)};
+    } else {
+      bf16_t* dst = a.vT + (((size_t)m * a.Hkv + (head - a.Hq - a.Hkv)) * a.hd + i) * a.Lp;
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        bf16_t *d1 = dst + (size_t)e * a.Lp, *d2 = d1 + (size_t)half * a.Lp;
+        d1[a.t] = (__bf16)v1[e];
+        d2[a.t] = (__bf16)v2[e];
+        if (a.t == a.Lk - 1)                           // columns that pad the block to whole 16s are zeros
+          for (int k = a.Lk; k < a.Lp; ++k) d1[k] = d2[k] = (__bf16)0.f;
+      }
+    }
+  }
+}
+
+// KU: panels of a wavefront's part of K at most, or exactly (EXACT). MT: tiles of 16 rows of x.
+// The normalised rows pass through LDS on their way to the registers, in two halves of K where they are large.
+constexpr int norm_phases(int KU, int MT) { return MT * KU > 4 ? 2 : 1; }
+constexpr int norm_stage(int KU, int MT) { return NW * KU * MT * PANEL / norm_phases(KU, MT); }
+constexpr int norm_ring(int KU, int MT) { return (CU_LDS - norm_stage(KU, MT)) / (NW * PANEL) < 8 ? (CU_LDS - norm_stage(KU, MT)) / (NW * PANEL) : 8; }
+
+template <int KU, bool EXACT, int MT, int EPI>
+__global__ void __launch_bounds__(512) few_rows_norm_kernel(FewArgs a) {
+  constexpr int PHASES = norm_phases(KU, MT), STAGE = norm_stage(KU, MT), R = norm_ring(KU, MT);
+  static_assert(STAGE >= 2 * NW * MT * 1024 && MT * KU <= 8, "LDS of the sums, registers of the rows");
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  char* stage = smem;                                    // [panel of K][MT] normalised rows, later
+  float* part = (float*)smem;                            // [tile][NW][MT][16 rows of x][16 rows of W] partial products
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  char* ring = smem + STAGE + wave * R * PANEL;
+  const int r16 = lane & 15, quad = lane >> 4;
+  const int U = a.K >> 6, ub = EXACT ? wave * KU : wave * U / NW, cnt = EXACT ? KU : (wave + 1) * U / NW - ub;
+  const int tile0 = blockIdx.x * a.per_wg, end = min(a.tiles, tile0 + a.per_wg);
+
+  const size_t second = (size_t)second_rows<EPI>(a) * a.K;
+  // the panels this wavefront loads, tile by tile, in a running pointer
+  const int lrow = lane >> 3, chunk0 = (lane & 7) ^ (lrow >> 1), chunk1 = chunk0 ^ 4;    // of rows lrow and lrow + 8
+  const bf16_t* src = nullptr;
+  int next_tile = tile0, next_u = 0, issued = 0, in_slot = 0;
+  const int total = (end - tile0) * cnt;
+  auto issue = [&]() {
+    if (next_u == 0) src = a.W + (size_t)(first_row<EPI>(a, next_tile) + lrow) * a.K + ub * 64;
+    load_panel(src + chunk0 * 8, src + second + chunk1 * 8, ring + in_slot * PANEL);
+    src += 64;
+    if (++next_u == cnt) { next_u = 0; ++next_tile; }
+    in_slot = in_slot + 1 == R ? 0 : in_slot + 1;
+    ++issued;
+  };
+
+  // RMSNorm(x) * gain: a wavefront has 2 MT whole rows in registers
+  bf16x8 af[MT][KU][2];
+  {
+    const int nv = a.K >> 2;
+    float4 xv[2 * MT][2 * KU], gv[2 * KU];
+    float inv[2 * MT];
+#pragma unroll
+    for (int r = 0; r < 2 * MT; ++r) {
+      const float4* row = (const float4*)(a.x + (size_t)min(2 * MT * wave + r, a.M - 1) * a.K);
+#pragma unroll
+      for (int i = 0; i < 2 * KU; ++i) {
+        xv[r][i] = float4{0.f, 0.f, 0.f, 0.f};
+        if (EXACT || lane + 64 * i < nv) xv[r][i] = row[lane + 64 * i];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 2 * KU; ++i) gv[i] = ((const float4*)a.gain)[EXACT ? lane + 64 * i : min(lane + 64 * i, nv - 1)];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll 1
+    for (int i = 0; i < R && i < total; ++i) issue();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < 2 * MT; ++r) {
+      float ss = 0.f;
+#pragma unroll
+      for (int i = 0; i < 2 * KU; ++i)
+        ss += xv[r][i].x * xv[r][i].x + xv[r][i].y * xv[r][i].y + xv[r][i].z * xv[r][i].z + xv[r][i].w * xv[r][i].w;
+      inv[r] = 1.0f / sqrtf(wave_sum(ss) / (float)a.K + a.eps);
+    }
+#pragma unroll
+    for (int ph = 0; ph < PHASES; ++ph) {
+      const int lo = U * ph / PHASES, hi = U * (ph + 1) / PHASES;        // panels of K in LDS
+      if (ph) BARRIER();
+#pragma unroll
+      for (int i = 0; i < 2 * KU; ++i) {
+        const int v = lane + 64 * i, u = v >> 4;
+        if (u < lo || u >= hi) continue;
+#pragma unroll
+        for (int r = 0; r < 2 * MT; ++r) {
+          const int row = 2 * MT * wave + r;
+          const float4 x4 = xv[r][i];
+          *(bf16x4*)(stage + ((u - lo) * MT + (row >> 4)) * PANEL + panel_at(row & 15, (v >> 1) & 7) + (v & 1) * 8) =
+              bf16x4{(__bf16)(x4.x * inv[r] * gv[i].x), (__bf16)(x4.y * inv[r] * gv[i].y), (__bf16)(x4.z * inv[r] * gv[i].z),
+                     (__bf16)(x4.w * inv[r] * gv[i].w)};
+        }
+      }
+      BARRIER();
+      if (wave / (NW / PHASES) == ph) {
+#pragma unroll
+        for (int u = 0; u < KU; ++u)
+          if (EXACT || u < cnt)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+              for (int h = 0; h < 2; ++h)
+                af[mt][u][h] = fragment(stage + ((ub + u - lo) * MT + mt) * PANEL, r16, 4 * h + quad);
+      }
+    }
+    BARRIER();                                           // the sums take the place of the rows
+  }
+
+  // All tiles of the workgroup in one batch if their partial sums fit the LDS of the rows, else batches that take turns
+  // with its two halves.
+  constexpr int ROOM = STAGE / (NW * MT * 1024);
+  const int batch = end - tile0 <= ROOM ? end - tile0 : ROOM / 2;
+  int consumed = 0, out_slot = 0, filled = 0, buffer = 0, turn = 0;
+  for (int tile = tile0; tile < end; ++tile) {
+    floatx4 acc[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < KU; ++u)
+      if (EXACT || u < cnt) {
+        ++consumed;
+        wait_loads<2>(issued - consumed);
+        const char* panel = ring + out_slot * PANEL;
+        out_slot = out_slot + 1 == R ? 0 : out_slot + 1;
+        bf16x8 w[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) w[h] = fragment(panel, r16, 4 * h + quad);
+        if (issued < total) {
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");             // the slot has been read
+          issue();
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[h], af[mt][u][h], acc[mt], 0, 0, 0);
+      }
+    float* p = part + (buffer * batch + filled) * NW * MT * 256;
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) *(floatx4*)(p + (wave * MT + mt) * 256 + r16 * 16 + 4 * quad) = acc[mt];
+    if (++filled < batch && tile + 1 < end) continue;
+    BARRIER();                                           // with two batches: the sums of the one before have been read by now
+    for (int i = (wave - turn) & (NW - 1); i < filled; i += NW) finish_tile<MT, EPI>(a, tile + 1 - filled + i, part + (buffer * batch + i) * NW * MT * 256);
+    turn = (turn + filled) & (NW - 1);
+    filled = 0;
+    buffer ^= 1;
+  }
+}
+
+// The same for an operand that is bf16 already: NT tiles of 16 rows of W per workgroup, and a slot of the ring holds a panel
+// of each with the MT panels of A beside them.
+constexpr int plain_ring(int MT, int NT) { return (CU_LDS - NW * MT * NT * 1024) / (NW * (MT + NT) * PANEL); }
+template <int MT, int NT, int EPI>
+__global__ void __launch_bounds__(512) few_rows_plain_kernel(FewArgs a) {
+  constexpr int R = plain_ring(MT, NT), SLOT = (NT + MT) * PANEL;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  float* part = (float*)(smem + NW * R * SLOT);          // [NT][NW][MT][16 rows of x][16 rows of W]
+  char* ring = smem + wave * R * SLOT;
+  const int r16 = lane & 15, quad = lane >> 4, tile0 = NT * blockIdx.x;
+  const int U = a.K >> 6, ub = wave * U / NW, cnt = (wave + 1) * U / NW - ub;
+  const int lrow = lane >> 3, chunk0 = (lane & 7) ^ (lrow >> 1), chunk1 = chunk0 ^ 4;    // of rows lrow and lrow + 8
+  const bf16_t* src[NT + MT][2];
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {                         // a tile beyond the last repeats it and is not finished
+    const bf16_t* row = a.W + (size_t)(first_row<EPI>(a, min(tile0 + i, a.tiles - 1)) + lrow) * a.K + ub * 64;
+    src[i][0] = row + chunk0 * 8;
+    src[i][1] = row + (size_t)second_rows<EPI>(a) * a.K + chunk1 * 8;
+  }
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt) {                      // rows beyond M repeat the last one and are not stored
+    src[NT + mt][0] = a.A + (size_t)min(16 * mt + lrow, a.M - 1) * a.K + ub * 64 + chunk0 * 8;
+    src[NT + mt][1] = a.A + (size_t)min(16 * mt + lrow + 8, a.M - 1) * a.K + ub * 64 + chunk1 * 8;
+  }
+  int issued = 0, in_slot = 0;
+  auto issue = [&]() {
+    char* slot = ring + in_slot * SLOT;
+#pragma unroll
+    for (int i = 0; i < NT + MT; ++i) load_panel(src[i][0] + 64 * issued, src[i][1] + 64 * issued, slot + i * PANEL);
+    in_slot = in_slot + 1 == R ? 0 : in_slot + 1;
+    ++issued;
+  };
+  // FE_RESIDUAL: the element of the tile that this thread finishes, if there is one
+  static_assert(EPI != FE_RESIDUAL || NT == 1, "one element per thread");
+  const int m = tid >> 4, n = 16 * tile0 + (tid & 15);
+  const bool mine = EPI == FE_RESIDUAL && tid < 256 * MT && m < a.M;
+  float old = 0.f;
+  if (mine) old = a.xo[(size_t)m * a.N + n];
+#pragma unroll 1
+  for (int i = 0; i < R && i < cnt; ++i) issue();
+  floatx4 acc[NT][MT];
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[i][mt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  int out_slot = 0;
+  for (int u = 0; u < cnt; ++u) {
+    wait_loads<2 * (NT + MT)>(issued - u - 1);
+    const char* slot = ring + out_slot * SLOT;
+    out_slot = out_slot + 1 == R ? 0 : out_slot + 1;
+    bf16x8 f[NT + MT][2];
+#pragma unroll
+    for (int i = 0; i < NT + MT; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) f[i][h] = fragment(slot + i * PANEL, r16, 4 * h + quad);
+    if (issued < cnt) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                 // the slot has been read
+      issue();
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+          acc[i][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[i][h], f[NT + mt][h], acc[i][mt], 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) *(floatx4*)(part + ((i * NW + wave) * MT + mt) * 256 + r16 * 16 + 4 * quad) = acc[i][mt];
+  BARRIER();
+  if constexpr (EPI == FE_RESIDUAL) {
+    if (!mine) return;
+    float v = 0.f;
+#pragma unroll
+    for (int u = 0; u < NW; ++u) v += part[(u * MT + (m >> 4)) * 256 + (m & 15) * 16 + (tid & 15)];
+    a.xo[(size_t)m * a.N + n] = old + v;
+  } else if (wave < NT && tile0 + wave < a.tiles) {
+    finish_tile<MT, EPI>(a, tile0 + wave, part + wave * NW * MT * 256);
+  }
+}
+
+static bool aligned16(const void* a, const void* b, const void* c) {
+  return (((uintptr_t)a | (uintptr_t)b | (uintptr_t)c) & 15) == 0;
+}
+template <typename F>
+static void allow_lds(F* kernel, int bytes) {
+  (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
+template <int KU, bool EXACT, int MT, int EPI>
+static void launch_norm(FewArgs& a, hipStream_t s) {
+  constexpr int lds = norm_stage(KU, MT) + NW * norm_ring(KU, MT) * PANEL;
+  static const bool configured = (allow_lds(few_rows_norm_kernel<KU, EXACT, MT, EPI>, lds), true);
+  (void)configured;
+  a.per_wg = (a.tiles + 255) / 256;
+  few_rows_norm_kernel<KU, EXACT, MT, EPI><<<(a.tiles + a.per_wg - 1) / a.per_wg, 512, lds, s>>>(a);
+}
+// Longest row that is normalised inside. Every workgroup reads all rows of x, which up to 2048 values is cheaper than a
+// launch (16 rows, us inside / product with its own normalisation: 8 x 2048 x 1024 5.6 / 11.8 and 16 x 2048 x 1536 7.3 / 12.7
+// with the rotary embedding, 16 x 151936 x 1536 93 / 94.5); of longer ones it takes too much of a short launch
+// (16 x 4608 x 3584: 15.3, and 4.8 + 11.4 where the kernel that adds the partial products of the down projection leaves
+// the normalised rows in bf16) but not of the long one of gate and up (16 x 37888 x 3584: 54.8 / 63.2; 17920 x 1536
+// 14.7 / 19.2).
+template <int EPI>
+static bool norm_product(FewArgs& a, hipStream_t s) {
+  if (a.K > (EPI == FE_SWIGLU && a.M <= 16 ? 3584 : 2048) || !aligned16(a.x, a.gain, a.W)) return false;
+  if (a.M <= 16) {
+    if (a.K == 1024) launch_norm<2, true, 1, EPI>(a, s);
+    else if (a.K == 1536) launch_norm<3, true, 1, EPI>(a, s);
+    else if (a.K <= 2048) launch_norm<4, false, 1, EPI>(a, s);
+    else if constexpr (EPI == FE_SWIGLU) {
+      if (a.K == 3584) launch_norm<7, true, 1, EPI>(a, s);
+      else launch_norm<7, false, 1, EPI>(a, s);
+    }
+  } else {
+    if (a.K == 1024) launch_norm<2, true, 2, EPI>(a, s);
+    else if (a.K == 1536) launch_norm<3, true, 2, EPI>(a, s);
+    else launch_norm<4, false, 2, EPI>(a, s);
+  }
+  return true;
+}
+template <int MT, int NT, int EPI>
+static void launch_plain(FewArgs& a, hipStream_t s) {
+  constexpr int lds = NW * plain_ring(MT, NT) * (MT + NT) * PANEL + NW * MT * NT * 1024;
+  static const bool configured = (allow_lds(few_rows_plain_kernel<MT, NT, EPI>, lds), true);
+  (void)configured;
+  few_rows_plain_kernel<MT, NT, EPI><<<(a.tiles + NT - 1) / NT, 512, lds, s>>>(a);
+}
+static bool few_rows(int M, int K, const bf16_t* W) { return M >= 1 && M <= FEW_ROWS && K % 64 == 0 && ((uintptr_t)W & 15) == 0; }
+
+// Each returns false if the shape is not taken.
+// A null: the rows are normalised inside.
+bool launch_few_rows_qkv_rope(const float* x, const float* gain, const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q,
+                              bf16_t* kblk, bf16_t* vT, const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s) {
+  if (!few_rows(g.M, md.d, W) || g.L != 1 || md.hd % 16 != 0) return false;
+  if (((uintptr_t)cs & 7) | ((uintptr_t)q & 3) | ((uintptr_t)kblk & 3)) return false;
+  FewArgs a = {};
+  a.x = x; a.gain = gain; a.A = A; a.W = W; a.M = g.M; a.K = md.d; a.N = (md.Hq + 2 * md.Hkv) * md.hd; a.eps = md.eps;
+  a.tiles = a.N / 16;
+  a.cs = cs; a.q = q; a.kblk = kblk; a.vT = vT;
+  a.Hq = md.Hq; a.Hkv = md.Hkv; a.hd = md.hd; a.Lk = g.Lk; a.Lp = Lp; a.t = g.t0;
+  if (!A) return norm_product<FE_QKV_ROPE>(a, s);
+  if (!aligned16(A, A, A)) return false;
+  if (a.tiles <= 256) {
+    if (a.M <= 16) launch_plain<1, 1, FE_QKV_ROPE>(a, s);
+    else launch_plain<2, 1, FE_QKV_ROPE>(a, s);
+  } else {
+    if (a.M <= 16) launch_plain<1, 2, FE_QKV_ROPE>(a, s);
+    else launch_plain<2, 2, FE_QKV_ROPE>(a, s);
+  }
+  return true;
+}
+bool launch_few_rows_gate_up(const float* x, const float* gain, const bf16_t* Wgu, bf16_t* act, int M, int F, int K, float eps,
+                             hipStream_t s) {
+  if (!few_rows(M, K, Wgu) || ((uintptr_t)act & 3)) return false;
+  FewArgs a = {};
+  a.x = x; a.gain = gain; a.W = Wgu; a.M = M; a.K = K; a.N = 2 * F; a.eps = eps; a.tiles = F / 8; a.act = act;
+  return norm_product<FE_SWIGLU>(a, s);
+}
+bool launch_few_rows_logits(const float* x, const float* gain, const bf16_t* W, float* C, int M, int N, int K, float eps,
+                            hipStream_t s) {
+  if (!few_rows(M, K, W) || N % 16 != 0 || ((uintptr_t)C & 15)) return false;
+  FewArgs a = {};
+  a.x = x; a.gain = gain; a.W = W; a.M = M; a.K = K; a.N = N; a.eps = eps; a.tiles = N / 16; a.C = C;
+  return norm_product<FE_STORE>(a, s);
+}
+// A longer K is left to the tile kernel, which puts more workgroups on it, and to the addition of its partial products in
+// the next normalisation (16 x 1536 x 8960: 13.2 us here, 7.9 + 4.0 there; 16 x 3584 x 18944: 31.9 and 26.9 + 4.8; but
+// 16 x 1536 x 1536 4.6 and 5.3 + 4.0, 16 x 3584 x 3584 7.5 and 8.1 + 4.8, 8 x 1024 x 2816 4.7 and 4.7 + 3.4).
+bool launch_few_rows_residual(const bf16_t* A, const bf16_t* W, float* x, int M, int N, int K, hipStream_t s) {
+  if (!few_rows(M, K, W) || N % 16 != 0 || !aligned16(A, A, A) || K > 4096) return false;
+  FewArgs a = {};
+  a.A = A; a.W = W; a.xo = x; a.M = M; a.N = N; a.K = K; a.tiles = N / 16;
+  if (M <= 16) launch_plain<1, 1, FE_RESIDUAL>(a, s);
+  else launch_plain<2, 1, FE_RESIDUAL>(a, s);
+  return true;
+}

@@ -401,6 +401,10 @@ static int gemm_residual_split(const T* A, const T* W, float* x, float* part, in
 template <>
 int gemm_residual_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* x, float* part, int max_split, int M, int N,
                                 int K, hipStream_t s) {
+  if (launch_few_rows_residual(A, W, x, M, N, K, s)) {
+    count_mfma(M);
+    return 0;
+  }
   // Also with one slice the product goes to `part` and the normalisation kernel, which reads x anyway, adds it:
   // the GEMM's epilogue then only writes, instead of waiting for a read of x before every store.
   int tile = -1, split = 1;
@@ -435,7 +439,8 @@ int gemm_store_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* C, int max
 
 // Rotary embedding, conversion and value transposition inside the projection's epilogue: bf16 launches of whole blocks.
 // (One position per block writes a column of the transposed values, a cache line per element, which the two or three
-// workgroups of the value heads alone are slow at: those launches leave it to the rotary kernel.)
+// workgroups of the value heads alone are slow at: those launches leave it to the rotary kernel, or to the kernel for few
+// rows, whose tiles are narrow.)
 template <typename T>
 static bool qkv_rope_fused(const T*, const T*, const float*, T*, T*, T*, const BatchGeom&, const ModelDims&, int,
                            hipStream_t) {
@@ -444,33 +449,46 @@ static bool qkv_rope_fused(const T*, const T*, const float*, T*, T*, T*, const B
 template <>
 bool qkv_rope_fused<bf16_t>(const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q, bf16_t* kb, bf16_t* vT,
                             const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s) {
-  if (g.L == 1 || !launch_gemm_mfma_qkv_rope(A, W, cs, q, kb, vT, g, md, Lp, -1, s)) return false;
+  if (g.L == 1 ? !launch_few_rows_qkv_rope(nullptr, nullptr, A, W, cs, q, kb, vT, g, md, Lp, s)
+               : !launch_gemm_mfma_qkv_rope(A, W, cs, q, kb, vT, g, md, Lp, -1, s))
+    return false;
   count_mfma(g.M);
   return true;
 }
 
-// Normalisation, projection and what follows it in one launch, where there is a kernel for the shape.
-template <typename T>
-static bool norm_qkv_rope(const float*, const float*, const T*, const float*, T*, T*, T*, const BatchGeom&,
-                          const ModelDims&, int, hipStream_t) {
-  return false;
-}
-template <>
-bool norm_qkv_rope<float>(const float* x, const float* gain, const float* W, const float* cs, float* q, float* kb,
+// Normalisation, projection and what follows it in one launch, where there is a kernel for the shape: small float models,
+// and at most 32 rows of bf16 ones.
+static bool norm_qkv_rope(const float* x, const float* gain, const float* W, const float* cs, float* q, float* kb,
                           float* vT, const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s) {
   if (!launch_small_qkv_rope(x, gain, W, cs, q, kb, vT, g, md, Lp, s)) return false;
   count_path(SPECS_PATH_GEMM_PLAIN);
   return true;
 }
-template <typename T>
-static bool norm_gate_up(const float*, const float*, const T*, T*, int, int, int, float, hipStream_t) {
-  return false;
+static bool norm_qkv_rope(const float* x, const float* gain, const bf16_t* W, const float* cs, bf16_t* q,
+                          bf16_t* kb, bf16_t* vT, const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s) {
+  if (!launch_few_rows_qkv_rope(x, gain, nullptr, W, cs, q, kb, vT, g, md, Lp, s)) return false;
+  count_mfma(g.M);
+  return true;
 }
-template <>
-bool norm_gate_up<float>(const float* x, const float* gain, const float* Wgu, float* act, int M, int F, int K, float eps,
-                         hipStream_t s) {
+static bool norm_gate_up(const float* x, const float* gain, const float* Wgu, float* act, int M, int F, int K,
+                         float eps, hipStream_t s) {
   if (!launch_small_gate_up(x, gain, Wgu, act, M, F, K, eps, s)) return false;
   count_path(SPECS_PATH_GEMM_PLAIN);
+  return true;
+}
+static bool norm_gate_up(const float* x, const float* gain, const bf16_t* Wgu, bf16_t* act, int M, int F,
+                         int K, float eps, hipStream_t s) {
+  if (!launch_few_rows_gate_up(x, gain, Wgu, act, M, F, K, eps, s)) return false;
+  count_mfma(M);
+  return true;
+}
+static bool norm_logits(const float*, const float*, const float*, float*, int, int, int, float, hipStream_t) {
+  return false;
+}
+static bool norm_logits(const float* x, const float* gain, const bf16_t* W, float* logits, int M, int N, int K,
+                        float eps, hipStream_t s) {
+  if (!launch_few_rows_logits(x, gain, W, logits, M, N, K, eps, s)) return false;
+  count_mfma(M);
   return true;
 }
 
@@ -594,11 +612,11 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
     T* vb = (T*)ws.vblk + kv_layer * (R + 16 * C) * kvd;
     T* pK = pool_ptr<T>(p, d, l, 0);
     T* pV = pool_ptr<T>(p, d, l, 1);
-    // small float models: normalisation and rotary embedding inside the projection
+    // normalisation and rotary embedding inside the projection
     bool fused_rope = false;
     if (!normed)
       PROFILED_IF(ctx, SPECS_K_QKV, s, fused_rope,
-                  norm_qkv_rope<T>(x, L.g_attn, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, s));
+                  norm_qkv_rope(x, L.g_attn, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, s));
     if (!normed && !fused_rope)
       PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(x, L.g_attn, (T*)ws.a, g.M, md.d, md.eps, s));
     if (!fused_rope)
@@ -629,7 +647,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
       bool fused_ffn = false;
       if (!pl)
         PROFILED_IF(ctx, SPECS_K_GATE_UP, s, fused_ffn,
-                    norm_gate_up<T>(ws.xs, L.g_ffn, (const T*)L.wgu, (T*)ws.act, gl.M, md.F, md.d, md.eps, s));
+                    norm_gate_up(ws.xs, L.g_ffn, (const T*)L.wgu, (T*)ws.act, gl.M, md.F, md.d, md.eps, s));
       if (!pl && !fused_ffn)
         PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(ws.xs, L.g_ffn, (T*)ws.a, gl.M, md.d, md.eps, s));
       if (!fused_ffn)
@@ -668,7 +686,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
     bool fused_ffn = false;
     if (!parts)
       PROFILED_IF(ctx, SPECS_K_GATE_UP, s, fused_ffn,
-                  norm_gate_up<T>(x, L.g_ffn, (const T*)L.wgu, (T*)ws.act, g.M, md.F, md.d, md.eps, s));
+                  norm_gate_up(x, L.g_ffn, (const T*)L.wgu, (T*)ws.act, g.M, md.F, md.d, md.eps, s));
     if (!parts && !fused_ffn)
       PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(x, L.g_ffn, (T*)ws.a, g.M, md.d, md.eps, s));
     if (!fused_ffn)
@@ -791,9 +809,14 @@ static int generate_impl(specs_ctx* ctx, const specs_model* m, const specs_prefi
   launch_broadcast_hlast(p->h_last, ws.xs, g, d.d_model, s);
   for (int t = 0; t < L; ++t) {
     g.t0 = t;
-    PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(ws.xs, m->w.g_final, (T*)ws.a, g.M, d.d_model, d.rms_eps, s));
-    PROFILED(ctx, SPECS_K_LMHEAD, s,
-             gemm_store_split<T>((const T*)ws.a, (const T*)m->w.head, ws.logits, 1, g.M, d.vocab, d.d_model, s));
+    bool fused_norm = false;
+    PROFILED_IF(ctx, SPECS_K_LMHEAD, s, fused_norm,
+                norm_logits(ws.xs, m->w.g_final, (const T*)m->w.head, ws.logits, g.M, d.vocab, d.d_model, d.rms_eps, s));
+    if (!fused_norm) {
+      PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(ws.xs, m->w.g_final, (T*)ws.a, g.M, d.d_model, d.rms_eps, s));
+      PROFILED(ctx, SPECS_K_LMHEAD, s,
+               gemm_store_split<T>((const T*)ws.a, (const T*)m->w.head, ws.logits, 1, g.M, d.vocab, d.d_model, s));
+    }
     PROFILED(ctx, SPECS_K_OTHER, s,
              launch_sample_tokens(ws.logits, g.M, d.vocab, limit, u, cand, tl, L, t, ws.sample, ws.status, s));
     run_trunk<T>(ctx, m, p, ws, g, ws.xs, cand + t, L, max_ctx, nullptr, R, C, s);
@@ -1119,8 +1142,10 @@ extern "C" int specs_op_qkv_rope(specs_ctx* ctx, const specs_model* m, const spe
   HIP_TRY(hipSetDevice(ctx->device));
   launch_rope_table(cs, g, md.hd, md.rope_base, s);
   if (d.dtype == SPECS_BF16) {
-    if (!qkv_rope_fused<bf16_t>((const bf16_t*)A, (const bf16_t*)Wqkv, cs, (bf16_t*)q, (bf16_t*)kblk, (bf16_t*)vT, g, md,
-                                Lp, s)) {
+    // One position per block: the product and the rotary kernel, which the pass runs for more than 32 such rows. (The kernel
+    // for fewer is reached through the pass.)
+    if (L == 1 || !qkv_rope_fused<bf16_t>((const bf16_t*)A, (const bf16_t*)Wqkv, cs, (bf16_t*)q, (bf16_t*)kblk, (bf16_t*)vT, g,
+                                          md, Lp, s)) {
       const size_t room = (ctx->workspace_bytes - 256 - cs_bytes) / ((size_t)g.M * width * sizeof(float));
       int parts = gemm_store_split<bf16_t>((const bf16_t*)A, (const bf16_t*)Wqkv, qkv,
                                            (int)(room < MFMA_MAX_SPLIT ? room : MFMA_MAX_SPLIT), g.M, (int)width, md.d, s);

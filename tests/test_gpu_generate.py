@@ -309,6 +309,32 @@ def test_generation_equals_scoring_for_uneven_prefixes_and_wide_groups(B_, n, hq
     step.close()
 
 
+@pytest.mark.parametrize("n,d,hq,hkv,hd,F,V", [
+    (1, 64, 1, 1, 64, 32, 784),            # one row, a K of one panel for eight wavefronts
+    (16, 576, 6, 2, 64, 96, 784),          # a full tile of rows, 9 panels: parts of K of one and two
+    (17, 1024, 4, 2, 128, 352, 777),       # two tiles of rows, one of them nearly empty; a vocabulary of no whole tiles
+    (32, 1536, 12, 2, 128, 2080, 784),     # the most rows; more tiles of gate and up than workgroups
+    (16, 2112, 4, 1, 128, 6176, 784),      # rows normalised outside for QKV and inside for gate and up; a long K of down
+    (20, 2048, 30, 2, 128, 256, 784)])     # two tiles of W per workgroup of the QKV projection
+def test_generation_equals_scoring_at_the_edges_of_the_few_row_kernels(n, d, hq, hkv, hd, F, V):
+    """Projections of at most 32 rows with their normalisation and epilogue against the tile kernels of the scoring pass;
+    two evaluations of the same rounding contract, at the tolerance of the tests above."""
+    from paper_2506_15733_amd import synthetic
+    mk = lambda role, layers, head: ModelDesc(role, layers, d, hq, hkv, hd, F, V, "bf16", head)
+    wl = Workload("gen_few", mk("target", 2, "lm"), mk("draft", 1, "lm"), mk("prm", 1, "prm"), B=1, n=n, L=5,
+                  prefix_len=0, lens_range=(40, 41), betas=(1.0,), token_dist="uniform", page_tokens=16, seed=35, u_seed=36)
+    step = synthetic.ScoringStep(wl)
+    step.prefill()
+    u = W.rng.uniform_f64(wl.u_seed, "gen/u9", wl.n * wl.L).reshape(1, wl.n, wl.L)
+    cand, logp, tok = gpu_generate(step, "target", u)
+    step.cand = torch.from_numpy(cand).to(step.device)
+    step.score("target")
+    torch.cuda.synchronize()
+    assert np.abs(step.tok["target"].cpu().numpy() - tok).max() < 2e-2
+    assert np.abs(step.out["target"].cpu().numpy() - logp).max() < 2e-2 * np.sqrt(wl.L)
+    step.close()
+
+
 def test_captured_generation_covers_prefixes_that_grew_since():
     """A launch of generation attention cuts the prefixes into runs by the lengths the host knows. Captured in a graph and
     replayed after the device lengths have grown beyond the last run (and, for the short beam, from one run to all), it
