@@ -1,13 +1,13 @@
 // Attention for launches that cover one in-block position t of every candidate (token-by-token generation).
-// The prefix keys, shared by the n candidates of a beam, are handled by the MFMA kernel in its single-position mode,
-// which stacks the n*g query rows of a (beam, kv head) and leaves partial results per run of key tiles (O
-// un-normalised, running maximum m in the log2 domain, weight sum l). This file merges them with the candidate's own
-// block keys 0..t (at most a block length of them).
+// The MFMA kernel in its single-position mode stacks the n*g query rows of a (beam, kv head) against the prefix keys, which
+// the n candidates share, and leaves partial results per run of key tiles (O un-normalised, running maximum m in the log2
+// domain, weight sum l). Where the prefix leaves room on the chip its launch covers the candidates' own block keys 0..t as
+// well, with one more partial result per row; this file merges, or merges and covers the block keys.
 #include "common.h"
 
-bool launch_attention_mfma_decode_prefix(const bf16_t* q, const bf16_t* poolK, const bf16_t* poolV, const BatchGeom& g,
-                                         const ModelDims& md, const DecodeRuns& runs, float* part, size_t part_floats,
-                                         hipStream_t s);
+bool launch_attention_mfma_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
+                                  const bf16_t* poolV, const BatchGeom& g, const ModelDims& md, int Lp, const DecodeRuns& runs,
+                                  float* part, size_t part_floats, bool* with_block, hipStream_t s);
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -17,16 +17,78 @@ struct MergeArgs {
   const bf16_t* q;      // [C][Hq][HD]
   const bf16_t* kb;     // [C*Lk][Hkv][HD]
   const bf16_t* vbT;    // [C][Hkv][HD][Lp]
-  const float* part_o;  // [beam*Hkv + kvh][split][n*g][HD]
+  const float* part_o;  // [beam*Hkv + kvh][split][n*g][HD]: the runs, then the block keys (not the long kernel)
   const float* part_m;
   const float* part_l;
   bf16_t* out;          // [C][Hq*HD]
   const int32_t* lens;
   int b0, len_override;
-  int n, Hq, Hkv, Lk, Lp, t, run_tiles, n_splits, osum_off;
+  int n, Hq, Hkv, Lk, Lp, t, run_tiles, n_splits, osum_off, rows_total, all_runs;
   float scale_log2e;
 };
 
+// One wavefront per (candidate, query head): HD / 4 lanes hold 16 bytes each of a partial output, 64 / (HD / 4) partial
+// outputs at a time; lane s holds the statistics of run s, the lane after the runs those of the block keys. Bound by the latency of
+// its loads, which are all requested at once; a single beam's do not even wait for its length, since it has all the runs
+// unless its prefix has changed since the launch was captured.
+template <int HD>
+__global__ void __launch_bounds__(256) attention_decode_merge_kernel(MergeArgs a) {
+  constexpr int LANES = HD / 4, GROUPS = 64 / LANES, NP = (DECODE_MAX_RUNS + 1 + GROUPS - 1) / GROUPS;
+  static_assert(DECODE_MAX_RUNS < 64, "a lane per partial result");
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int row = blockIdx.x * 4 + wave;                 // candidate * Hq + query head
+  if (row >= a.rows_total) return;
+  const int c = row / a.Hq, h = row - c * a.Hq;
+  const int g = a.Hq / a.Hkv, kvh = h / g, j = h - kvh * g;
+  const int b = c / a.n, i = c - b * a.n;
+  const int P = a.len_override >= 0 ? a.len_override : a.lens[a.b0 + b];
+  const size_t rows = (size_t)a.n * g;
+  const size_t prow0 = ((size_t)b * a.Hkv + kvh) * (a.n_splits + 1) * rows + (size_t)i * g + j;   // + split*rows
+  // runs of this beam: what others hold is whatever an earlier launch left there
+  const int ns = min((((P + 63) >> 6) + a.run_tiles - 1) / a.run_tiles, a.n_splits);
+  const int loaded = a.all_runs ? a.n_splits : ns;
+  const int st = lane < loaded ? lane : a.n_splits;
+  float m = a.part_m[prow0 + st * rows], l = a.part_l[prow0 + st * rows];
+  const int grp = lane / LANES, col = lane % LANES;
+  const float4* po = (const float4*)(a.part_o + prow0 * HD) + col;
+  float4 v[NP];
+#pragma unroll
+  for (int k = 0; k < NP; ++k) {
+    const int s = k * GROUPS + grp;
+    if (k * GROUPS <= loaded) v[k] = po[(size_t)(s < loaded ? s : a.n_splits) * rows * LANES];
+  }
+  const bool valid = lane < ns || lane == loaded;
+  m = valid ? m : -INFINITY;
+  const float mx = wave_max(m);                          // finite: a position sees its own key
+  const float w = __builtin_amdgcn_exp2f(m - mx);
+  l = wave_sum(valid ? w * l : 0.f);
+  float4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k = 0; k < NP; ++k) {
+    const int s = k * GROUPS + grp;
+    if (k * GROUPS > loaded) break;
+    const float ws = __shfl(w, s < 64 ? s : 63, 64);
+    if (s < ns || s == loaded) {
+      acc.x = fmaf(ws, v[k].x, acc.x);
+      acc.y = fmaf(ws, v[k].y, acc.y);
+      acc.z = fmaf(ws, v[k].z, acc.z);
+      acc.w = fmaf(ws, v[k].w, acc.w);
+    }
+  }
+#pragma unroll
+  for (int o = LANES; o < 64; o <<= 1) {
+    acc.x += __shfl_xor(acc.x, o, 64);
+    acc.y += __shfl_xor(acc.y, o, 64);
+    acc.z += __shfl_xor(acc.z, o, 64);
+    acc.w += __shfl_xor(acc.w, o, 64);
+  }
+  const float inv = 1.0f / l;
+  if (grp == 0)
+    *(bf16x4*)(a.out + (size_t)row * HD + 4 * col) =
+        bf16x4{(__bf16)(acc.x * inv), (__bf16)(acc.y * inv), (__bf16)(acc.z * inv), (__bf16)(acc.w * inv)};
+}
+
+// The merge where the prefix fills the chip by itself: it covers the block keys too.
 // One workgroup of four wavefronts per (candidate, kv head, 16 of its query heads): the g query heads share the block
 // keys and values, which are therefore read once, in whole cache lines, and multiplied by MFMA (heads are the 16
 // columns). The kernel is a chain of short dependent phases on a few KB, bound by latency, so whatever does not depend
@@ -36,7 +98,7 @@ struct MergeArgs {
 // the same, 9.3 - 9.5 us on average over the 128 positions of a block, but this one with the 32 runs that the prefix kernel
 // wants, 8.7 us instead of 10.7 with 16.)
 template <int HD>
-__global__ void __launch_bounds__(256) attention_decode_merge_kernel(MergeArgs a) {
+__global__ void __launch_bounds__(256) attention_decode_merge_block_kernel(MergeArgs a) {
   constexpr int KS = HD / 32;                   // MFMA K-steps of the scores
   constexpr int ND = HD / 64;                   // 16-dim tiles of the output per wavefront
   constexpr int NPG = 4, NPS = DECODE_MAX_RUNS / 4;   // partial outputs requested up front: 64-lane groups of 16-byte
@@ -199,7 +261,7 @@ __global__ void __launch_bounds__(256) attention_decode_merge_kernel(MergeArgs a
   }
 }
 
-// The same merge for blocks whose scores do not fit the LDS above: one wavefront per (candidate, query head).
+// The same for blocks whose scores do not fit the LDS above: one wavefront per (candidate, query head).
 template <int HD>
 __global__ void __launch_bounds__(64) attention_decode_merge_long_kernel(MergeArgs a) {
   extern __shared__ float sm[];                 // [HD] query, [Lp] block scores then weights, [n_splits] run weights
@@ -264,16 +326,25 @@ __global__ void __launch_bounds__(64) attention_decode_merge_long_kernel(MergeAr
 bool launch_attention_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                              const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,
                              const DecodeRuns& runs, float* part, size_t part_floats, hipStream_t s) {
-  if (!launch_attention_mfma_decode_prefix(q, poolK, poolV, g, md, runs, part, part_floats, s)) return false;
+  bool with_block = false;
+  if (!launch_attention_mfma_decode(q, kb, vbT, poolK, poolV, g, md, Lp, runs, part, part_floats, &with_block, s)) return false;
   const int n_splits = runs.count;
-  const size_t rows_all = (size_t)g.B * md.Hkv * n_splits * g.n * (md.Hq / md.Hkv);
+  const size_t rows_all = (size_t)g.B * md.Hkv * (n_splits + (with_block ? 1 : 0)) * g.n * (md.Hq / md.Hkv);
   MergeArgs a;
   a.q = q; a.kb = kb; a.vbT = vbT; a.out = out;
   a.part_o = part; a.part_m = part + rows_all * md.hd; a.part_l = a.part_m + rows_all;
   a.lens = g.lens; a.b0 = g.b0; a.len_override = g.len_override;
   a.n = g.n; a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lk = g.Lk; a.Lp = Lp; a.t = g.t0; a.run_tiles = runs.tiles;
   a.n_splits = n_splits;
+  a.rows_total = g.B * g.n * md.Hq;
+  a.all_runs = g.B == 1;
   a.scale_log2e = 1.4426950408889634f / sqrtf((float)md.hd);
+  if (with_block) {
+    const dim3 grid((a.rows_total + 3) / 4);
+    if (md.hd == 128) attention_decode_merge_kernel<128><<<grid, 256, 0, s>>>(a);
+    else attention_decode_merge_kernel<64><<<grid, 256, 0, s>>>(a);
+    return true;
+  }
   const int gq = md.Hq / md.Hkv, HS = gq < 16 ? gq : 16, Lq = (Lp + 31) & ~31;
   const size_t osum_off = ((size_t)HS * (4 * (Lq + 4) + 2 * (Lq + 8) + 8 * n_splits + 4) + 15) & ~(size_t)15;
   const size_t lds = osum_off + 4 * (size_t)HS * md.hd * 4;
@@ -281,8 +352,8 @@ bool launch_attention_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vb
   // 6 Lq + 8 n_splits + 16 hd + 36 bytes per head row: with 16 rows of 128 and 32 runs blocks of up to 288 tokens
   if (lds <= 64 * 1024) {
     const dim3 grid(g.B * g.n, md.Hkv, (gq + 15) / 16);
-    if (md.hd == 128) attention_decode_merge_kernel<128><<<grid, 256, lds, s>>>(a);
-    else attention_decode_merge_kernel<64><<<grid, 256, lds, s>>>(a);
+    if (md.hd == 128) attention_decode_merge_block_kernel<128><<<grid, 256, lds, s>>>(a);
+    else attention_decode_merge_block_kernel<64><<<grid, 256, lds, s>>>(a);
   } else {
     const dim3 grid(g.B * g.n, md.Hq);
     const size_t lds_long = (size_t)(md.hd + Lp + n_splits) * sizeof(float);

@@ -44,8 +44,10 @@ struct AttnArgs {
   int n_splits;
   int last_first;       // one block of one beam (prefill): query tiles dealt to the XCDs from the last one down
   int run_tiles;        // single positions (generation): tiles of a run; a beam has as many runs as its length asks for
+  int part_splits;      // single positions: partial results of a row, n_splits and, where the launch covers the block keys
+  int block_wgs;        // too, one more for these, which the first block_wgs workgroups leave
   float* part_o;        // whole blocks: [b*Hkv + kvh][candidate][q_tile][split][128][HD]
-                        // single positions: [b*Hkv + kvh][split][n*g rows][HD]
+                        // single positions: [b*Hkv + kvh][part_splits][n*g rows][HD]
   float* part_m;        // [..][128] running maximum (log2 domain), -inf if the run was empty
   float* part_l;        // [..][128] sum of weights relative to that maximum
 };
@@ -66,10 +68,113 @@ __device__ __forceinline__ int k_swizzle(int row, int chunk) {
   return HD == 128 ? (chunk ^ (row & 15)) : (chunk ^ ((row >> 1) & 7));
 }
 
+// MODE 1's block keys: one workgroup of four wavefronts per (candidate, kv head, 16 of its query heads), which share the
+// block keys 0..t and values. The chain of short dependent phases on a few KB, bound by latency, is as long as that of a
+// prefix workgroup, so these come first in the launch (10.2 us instead of 8.3 with the prefix workgroups in front).
+constexpr int BLOCK_LDS = 32 * 1024;
+__host__ __device__ constexpr int block_part_lds(int heads, int Lq) { return heads * (4 * (Lq + 4) + 2 * (Lq + 8)); }
+
+template <int HD>
+__device__ __forceinline__ void block_part(const AttnArgs& a, int id, char* smem) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  typedef float floatx4 __attribute__((ext_vector_type(4)));
+  constexpr int KS = HD / 32;                   // MFMA K-steps of the scores
+  constexpr int ND = HD / 64;                   // 16-dim tiles of the output per wavefront
+  constexpr int NVP = 4;                        // 32-key value steps requested up front
+  const BatchGeom& G = a.g;
+  const int g = a.Hq / a.Hkv, groups = (g + 15) >> 4, t = G.t0;
+  const int j0 = id % groups * 16, kvh = id / groups % a.Hkv, c = id / (groups * a.Hkv);
+  const int gh = g - j0 < 16 ? g - j0 : 16;     // query heads of this workgroup
+  const int Lq = (a.Lp + 31) & ~31;             // keys of the weights, whole MFMA K-steps
+  const int SS = Lq + 4, PS = Lq + 8;           // row strides: reads of 16 rows spread over the banks
+  const int HS = g < 16 ? g : 16;
+  float* sc = (float*)smem;                     // [HS][SS] scores
+  bf16_t* pw = (bf16_t*)(sc + HS * SS);         // [HS][PS] weights
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int col = lane & 15, quad = lane >> 4;
+  const int b = c / G.n, i = c - b * G.n;
+  const int hc = col < gh ? col : gh - 1;       // columns beyond the heads repeat the last one and are not stored
+
+  bf16x8 qf[KS];
+  const bf16_t* qr = a.q + ((size_t)c * a.Hq + (size_t)kvh * g + j0 + hc) * HD + 8 * quad;
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8*)(qr + 32 * ks);
+  const int nkt = (t + 16) >> 4;                // 16-key tiles that hold a visible key
+  const bf16_t* kbase = a.kb + ((size_t)c * G.Lk * a.Hkv + kvh) * HD + 8 * quad;
+  bf16x8 kf[KS];
+  auto load_keys = [&](int kt) {
+    const int key = 16 * kt + col;
+    const bf16_t* kr = kbase + (size_t)(key <= t ? key : t) * a.Hkv * HD;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) kf[ks] = *(const bf16x8*)(kr + 32 * ks);
+  };
+  if (wave < nkt) load_keys(wave);
+  const int nvs = (t + 32) >> 5;                // 32-key steps that hold a visible key
+  const bf16_t* vbase = a.vbT + (((size_t)c * a.Hkv + kvh) * HD + 16 * wave + col) * a.Lp;
+  // values of keys 32 st + 8 quad .. + 7; those beyond t are whatever an earlier call left there and become 0
+  auto load_vals = [&](int u, int st) {
+    const int key = 32 * st + 8 * quad;
+    return *(const bf16x8*)(vbase + (size_t)64 * u * a.Lp + (key < a.Lp ? key : 0));
+  };
+  auto visible_vals = [&](bf16x8 v, int st) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = 32 * st + 8 * quad + e <= t ? v[e] : (__bf16)0.f;
+    return v;
+  };
+  bf16x8 vv[ND][NVP];
+#pragma unroll
+  for (int u = 0; u < ND; ++u)
+#pragma unroll
+    for (int st = 0; st < NVP; ++st) vv[u][st] = load_vals(u, st < nvs ? st : 0);
+  // scores of the block keys: lane holds keys 16 kt + 4 quad + e of head col
+  for (int kt = wave; kt < nkt; kt += 4) {
+    floatx4 s4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) s4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qf[ks], s4, 0, 0, 0);
+    if (kt + 4 < nkt) load_keys(kt + 4);
+    if (col < gh) *(floatx4*)(sc + col * SS + 16 * kt + 4 * quad) = s4 * a.scale_log2e;
+  }
+  __syncthreads();
+  // rows of this workgroup in the partial results
+  const size_t prow = (((size_t)b * a.Hkv + kvh) * a.part_splits + a.n_splits) * G.n * g + (size_t)i * g + j0;
+  // softmax statistics: 16 lanes per head, all heads at a time
+  const int h = tid >> 4, sub = tid & 15;
+  if (h < gh) {
+    float mx = -INFINITY;
+    for (int k = sub; k <= t; k += 16) mx = fmaxf(mx, sc[h * SS + k]);
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 16));
+    mx = ceilf(mx);                             // finite (key t itself is always visible); an integer, so that
+                                                // the bf16 rounding of the weights does not depend on the reference
+    float l = 0.f;
+    for (int k = sub; k < Lq; k += 16) {
+      const float p = k <= t ? __builtin_amdgcn_exp2f(sc[h * SS + k] - mx) : 0.f;
+      l += p;
+      pw[h * PS + k] = (bf16_t)p;               // the weight that multiplies V is a bf16 operand
+    }
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) l += __shfl_xor(l, o, 16);
+    if (sub == 0) { a.part_m[prow + h] = mx; a.part_l[prow + h] = l; }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < ND; ++u) {
+    // this lane's output dims: 16 (wave + 4 u) + 4 quad .. + 3 of head col
+    floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    const bf16_t* pr = pw + hc * PS + 8 * quad;
+#pragma unroll
+    for (int st = 0; st < NVP; ++st)
+      if (st < nvs) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(visible_vals(vv[u][st], st), *(const bf16x8*)(pr + 32 * st), acc, 0, 0, 0);
+    for (int st = NVP; st < nvs; ++st)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(visible_vals(load_vals(u, st), st), *(const bf16x8*)(pr + 32 * st), acc, 0, 0, 0);
+    if (col < gh) *(floatx4*)(a.part_o + (prow + col) * HD + 16 * wave + 64 * u + 4 * quad) = acc;
+  }
+}
+
 // MODE 0: whole blocks, as described above. MODE 1: one position per candidate; the stacked rows of a
 // (beam, kv head) are its n candidates x g query heads (row r = i*g + j), the workgroup covers only one run of
 // run_tiles prefix tiles and writes (O un-normalised, m, l) instead of the output; the candidate's own block keys
-// are added by the merge kernel. Runs are equally long over all beams, so a launch whose beams differ in length has
+// are covered by further workgroups (block_part), and a second kernel merges. Runs are equally long over all beams, so a launch whose beams differ in length has
 // no long workgroups that the others wait for. MODE 2: whole blocks, but the tile list (prefix tiles, then block tiles) is cut
 // into n_splits runs handled by different workgroups, for launches that would otherwise leave most CUs idle; a
 // merge kernel combines the partial results.
@@ -90,9 +195,14 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
   // list; single positions deal the (beam, kv head, run) list round, since beams of different lengths lie in a row, and
   // keep the query tiles of one entry together
   int logical = (blockIdx.x & 7) * a.wg_per_xcd + (blockIdx.x >> 3);
-  if (DEC) {
-    const int pass = (blockIdx.x >> 3) / a.q_tiles, qt = (blockIdx.x >> 3) - pass * a.q_tiles;
-    logical = (pass * 8 + (blockIdx.x & 7)) * a.q_tiles + qt;
+  if constexpr (DEC) {
+    if ((int)blockIdx.x < a.block_wgs) {
+      block_part<HD>(a, blockIdx.x, smem);
+      return;
+    }
+    const int id = blockIdx.x - a.block_wgs;
+    const int pass = (id >> 3) / a.q_tiles, qt = (id >> 3) - pass * a.q_tiles;
+    logical = (pass * 8 + (id & 7)) * a.q_tiles + qt;
   }
   if ((DEC || !a.last_first) && logical >= a.total_wg) return;
   const BatchGeom& G = a.g;
@@ -366,7 +476,7 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
     if (SPLIT) {
       if (DEC && r >= rows_total) continue;
       const size_t group = DEC ? (size_t)b * a.Hkv + kvh : ((size_t)b * a.Hkv + kvh) * G.n + cand;
-      const size_t prow = DEC ? (group * a.n_splits + split) * rows_total + r
+      const size_t prow = DEC ? (group * a.part_splits + split) * rows_total + r
                               : ((group * a.q_tiles + qt_idx) * a.n_splits + split) * BQ + (wave * QT + u) * 32 + lq;
       if (lh == 0) { a.part_m[prow] = m_run[u]; a.part_l[prow] = l; }
       float* dst = a.part_o + prow * HD;
@@ -396,13 +506,14 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
 template <int HD, int QT, int MODE = 0>
 static void launch_attn_variant(const AttnArgs& a, hipStream_t s) {
   constexpr int smem = 2 * (64 * HD * 2 + 4 * HD * 32);
+  static_assert(smem >= BLOCK_LDS, "MODE 1's block keys");
   static bool configured = false;
   if (!configured) {
     (void)hipFuncSetAttribute((const void*)attention_mfma_kernel<HD, QT, MODE>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     configured = true;
   }
-  attention_mfma_kernel<HD, QT, MODE><<<dim3(a.wg_per_xcd * 8), 256, smem, s>>>(a);
+  attention_mfma_kernel<HD, QT, MODE><<<dim3(a.wg_per_xcd * 8 + a.block_wgs), 256, smem, s>>>(a);
 }
 
 // Merge of the partial results of a MODE 2 launch: HD / 4 lanes per (row, query head), each 16 bytes of it, with all of the
@@ -462,7 +573,7 @@ bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT,
   a.q = q; a.kb = kb; a.vbT = vbT; a.poolK = poolK; a.poolV = poolV; a.out = out; a.g = g;
   a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lp = Lp;
   a.last_first = g.B == 1 && g.n == 1;
-  a.n_splits = 1; a.run_tiles = 0; a.part_o = nullptr; a.part_m = nullptr; a.part_l = nullptr;
+  a.n_splits = 1; a.run_tiles = 0; a.part_splits = 0; a.block_wgs = 0; a.part_o = nullptr; a.part_m = nullptr; a.part_l = nullptr;
   a.scale_log2e = 1.4426950408889634f / sqrtf((float)md.hd);
   int rows = g.L * (md.Hq / md.Hkv);
   // 256-row workgroups only when they waste less padding than 128-row ones (the latter run two per CU)
@@ -539,34 +650,43 @@ DecodeRuns plan_decode_runs(const int32_t* lens, int B, int len_override, long u
 }
 DecodeRuns plan_decode_runs(const BatchGeom& g, const ModelDims& md, const int32_t* lens_host, size_t part_floats) {
   const int rows = g.n * (md.Hq / md.Hkv);
-  return plan_decode_runs(lens_host + g.b0, g.B, g.len_override, (long)md.Hkv * ((rows + 127) / 128),
-                          (size_t)g.B * md.Hkv * rows * (md.hd + 2), part_floats);
+  const size_t per_split = (size_t)g.B * md.Hkv * rows * (md.hd + 2);
+  if (part_floats >= 2 * per_split) part_floats -= per_split;           // the block keys' partial result
+  return plan_decode_runs(lens_host + g.b0, g.B, g.len_override, (long)md.Hkv * ((rows + 127) / 128), per_split, part_floats);
 }
 
-// Prefix part of a single-position launch (g.L == 1): partial results per (beam, kv head, run of key tiles, row), in runs
-// as plan_decode_runs gives them. part_floats: room in `part` (floats); returns false if the shape is not taken or the
-// partials would not fit.
-bool launch_attention_mfma_decode_prefix(const bf16_t* q, const bf16_t* poolK, const bf16_t* poolV, const BatchGeom& g,
-                                         const ModelDims& md, const DecodeRuns& runs, float* part, size_t part_floats,
-                                         hipStream_t s) {
+// Partial results of a single-position launch (g.L == 1) per (beam, kv head, run of key tiles, row), in runs as
+// plan_decode_runs gives them, and after the runs those of the block keys if *with_block: where all workgroups are resident
+// at once, two per CU (16 x 12 heads, 4096 keys: 8.3 us + 4.7 for the merge, 8.0 + 7.1 with the block keys in the merge;
+// 32 beams x 8 x 12, 1024 to 8192 keys: 35.3 + 8.2 and 31.0 + 8.0), the scores of the block fit the LDS and the partial
+// results the scratch. part_floats: room in `part` (floats); returns false if the shape is not taken or the partials of the
+// prefix would not fit.
+bool launch_attention_mfma_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
+                                  const bf16_t* poolV, const BatchGeom& g, const ModelDims& md, int Lp, const DecodeRuns& runs,
+                                  float* part, size_t part_floats, bool* with_block, hipStream_t s) {
   if ((md.hd != 64 && md.hd != 128) || g.page_tokens != 16 || g.L != 1 || runs.count < 1) return false;
   AttnArgs a;
   a.last_first = 0;
-  a.q = q; a.kb = nullptr; a.vbT = nullptr; a.poolK = poolK; a.poolV = poolV; a.out = nullptr; a.g = g;
-  a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lp = 16;
+  a.q = q; a.kb = kb; a.vbT = vbT; a.poolK = poolK; a.poolV = poolV; a.out = nullptr; a.g = g;
+  a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lp = Lp;
   a.scale_log2e = 1.4426950408889634f / sqrtf((float)md.hd);
-  const int rows = g.n * (md.Hq / md.Hkv);
+  const int gq = md.Hq / md.Hkv, rows = g.n * gq;
   a.q_tiles = (rows + 127) / 128;
   a.run_tiles = runs.tiles;
   a.n_splits = runs.count;
-  const size_t rows_all = (size_t)g.B * md.Hkv * a.n_splits * rows;
+  const size_t rows_one = (size_t)g.B * md.Hkv * rows;
+  const int entries = g.B * md.Hkv * a.n_splits, block_wgs = g.B * g.n * md.Hkv * ((gq + 15) / 16);
+  a.total_wg = entries * a.q_tiles;
+  a.wg_per_xcd = (entries + 7) / 8 * a.q_tiles;
+  *with_block = a.total_wg + block_wgs <= 512 && block_part_lds(gq < 16 ? gq : 16, (Lp + 31) & ~31) <= BLOCK_LDS &&
+                (a.n_splits + 1) * rows_one * (md.hd + 2) <= part_floats;
+  a.part_splits = a.n_splits + (*with_block ? 1 : 0);
+  const size_t rows_all = rows_one * a.part_splits;
   if (rows_all * (md.hd + 2) > part_floats) return false;
   a.part_o = part;
   a.part_m = part + rows_all * md.hd;
   a.part_l = a.part_m + rows_all;
-  const int entries = g.B * md.Hkv * a.n_splits;
-  a.total_wg = entries * a.q_tiles;
-  a.wg_per_xcd = (entries + 7) / 8 * a.q_tiles;
+  a.block_wgs = *with_block ? block_wgs : 0;
   if (md.hd == 128) launch_attn_variant<128, 1, 1>(a, s);
   else launch_attn_variant<64, 1, 1>(a, s);
   return true;

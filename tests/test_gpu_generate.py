@@ -309,6 +309,15 @@ def test_generation_equals_scoring_for_uneven_prefixes_and_wide_groups(B_, n, hq
     step.close()
 
 
+@pytest.mark.parametrize("B_,n,hq,hkv,hd,lens,L", [
+    (8, 31, 4, 2, 64, (20, 900), 40),      # 496 workgroups of block keys and those of the prefix: too many for one launch
+    (9, 30, 2, 2, 128, (20, 900), 17),     # the same for the other head size
+    (2, 4, 4, 2, 128, (2000, 2100), 36)])  # all in one launch, more than one beam
+def test_generation_equals_scoring_on_both_sides_of_the_block_key_rule(B_, n, hq, hkv, hd, lens, L):
+    """Block keys beside the prefix or in the merge, at the tolerance of the tests above."""
+    test_generation_equals_scoring_for_uneven_prefixes_and_wide_groups(B_, n, hq, hkv, hd, lens, L)
+
+
 @pytest.mark.parametrize("n,d,hq,hkv,hd,F,V", [
     (1, 64, 1, 1, 64, 32, 784),            # one row, a K of one panel for eight wavefronts
     (16, 576, 6, 2, 64, 96, 784),          # a full tile of rows, 9 panels: parts of K of one and two
