@@ -385,9 +385,9 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const int row = m0 + wm * WM + i * 32 + lrow;
-        if (row >= a.M) continue;
         const int cand = row / a.Lrows, t = row - cand * a.Lrows;
         if (head < a.Hq + a.Hkv) {
+          if (row >= a.M) continue;
           const float* cs = a.cs + (size_t)row * HDIM;
           bf16_t* dst = head < a.Hq ? a.q + ((size_t)row * a.Hq + head) * HDIM
                                     : a.kblk + ((size_t)row * a.Hkv + (head - a.Hq)) * HDIM;
@@ -408,21 +408,29 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
           }
         } else {
           // values: not rotated, stored transposed; the 32 lanes of a half-wave write 32 consecutive positions
-          bf16_t* dst = a.vT + (((size_t)cand * a.Hkv + (head - a.Hq - a.Hkv)) * HDIM) * a.Lp + t;
-          const bool pad = t == a.Lrows - 1 && a.Lp > a.Lrows;
+          bf16_t* head_v = a.vT + (size_t)(head - a.Hq - a.Hkv) * HDIM * a.Lp;
+          const size_t cand_v = (size_t)a.Hkv * HDIM * a.Lp;
+          if (row < a.M) {
+            bf16_t* dst = head_v + cand * cand_v + t;
 #pragma unroll
-          for (int g = 0; g < 4; ++g)
+            for (int g = 0; g < 4; ++g)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int d = i_base + 8 * g + e;
-              dst[(size_t)d * a.Lp] = (__bf16)acc[i][0][4 * g + e];
-              dst[(size_t)(HALF + d) * a.Lp] = (__bf16)acc[i][1][4 * g + e];
-              if (pad)
-                for (int tt = 1; tt < a.Lp - t; ++tt) {
-                  dst[(size_t)d * a.Lp + tt] = (__bf16)0.f;
-                  dst[(size_t)(HALF + d) * a.Lp + tt] = (__bf16)0.f;
-                }
-            }
+              for (int e = 0; e < 4; ++e) {
+                const int d = i_base + 8 * g + e;
+                dst[(size_t)d * a.Lp] = (__bf16)acc[i][0][4 * g + e];
+                dst[(size_t)(HALF + d) * a.Lp] = (__bf16)acc[i][1][4 * g + e];
+              }
+          }
+          // The positions that pad a candidate's block to whole 16s: the wavefront that holds its last row clears them, a
+          // lane per column (the two lanes of that row on their own took 32 stores a position).
+          unsigned ends = (unsigned)__ballot(row < a.M && t == a.Lrows - 1 && a.Lp > a.Lrows);
+          while (ends) {
+            const int of = __builtin_amdgcn_readlane(cand, __builtin_ctz(ends));
+            ends &= ends - 1;
+            const int d = HD128 ? (wn & 1) * 32 + (lane & 31) + (lane >> 5) * HALF : lane;
+            bf16_t* pad = head_v + of * cand_v + (size_t)d * a.Lp;
+            for (int k = a.Lrows; k < a.Lp; ++k) pad[k] = (__bf16)0.f;
+          }
         }
       }
     }
