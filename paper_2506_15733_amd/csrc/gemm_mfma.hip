@@ -36,10 +36,12 @@ struct GemmArgs {
   float* C;              // ME_STORE / ME_RESIDUAL: [M, N]
   bf16_t* act;           // ME_SWIGLU: [M, N/2]
   const int32_t* tok;    // ME_LMHEAD: target token per row
-  float* part_max;       // ME_LMHEAD: [M, n_tiles]
+  float* part_max;       // ME_LMHEAD: [M, part_tiles]
   float* part_sum;
   float* zt;             // ME_LMHEAD: [M]
   int ksplit;            // ME_STORE only: slices of K, slice s writes its partial product to C + s*M*N
+  int rest_block, rest_m_tiles, rest_n_tiles;   // REST kernels: the first workgroup of the rest, its tiles
+  int part_tiles;        // ME_LMHEAD: entries of a row in part_max and part_sum
   // ME_QKV_ROPE: the product is the QKV projection [M, (Hq + 2 Hkv) * hd]; the epilogue rotates the q and k heads
   // (pairs (i, i + hd/2), angles from the table cs[M][hd] = cos | sin) and writes bf16 q [M][Hq][hd], block keys
   // kblk[M][Hkv][hd] and block values transposed per candidate vT[cand][Hkv][hd][Lp], where row m is in-block position
@@ -83,9 +85,44 @@ __device__ __forceinline__ float half_wave_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// HD128 (ME_QKV_ROPE only): head_dim 128 instead of 64.
-template <int BM, int BN, int NWM, int S, int EPI, bool HD128 = false>
-__global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
+// Workgroup -> (K slice, m_tile, n_tile): ids congruent mod 8 share an XCD. The tile list goes through bands of 32 N-tiles,
+// in a band through blocks of 8 M-tiles, in a block through sub-bands of 4 N-tiles, so that 32 consecutive entries are
+// 8 M-tiles x 4 N-tiles: an XCD that runs them at one time fetches every A panel into its L2 once per 4 users and
+// every W tile once per 8 users. Every 256 entries the XCDs take 32 each: they then work on the same 8 A panels at the
+// same time (with one contiguous eighth of the list each they drift apart in M: 16384 x 37888 x 3584 then takes 5 %
+// longer). What is left, and all of a short list, is cut into eight equal runs. The list has no gaps: a grid padded to whole blocks leaves the
+// shader engines of an XCD unevenly loaded (with 70 tiles of one M-tile all of them met on one engine of four and ran
+// in two rounds: 48 us instead of 26 at 64 x 17920 x 1536).
+struct TileAt { int kslice, m, n; };
+__device__ __forceinline__ bool tile_of(int block, int m_tiles, int n_tiles, int ksplit, TileAt& at) {
+  const int tiles = m_tiles * n_tiles, total = tiles * ksplit;
+  const int xcd = block & 7, slot = block >> 3, dealt = total >> 8;
+  int idx;
+  if (slot < 32 * dealt) {
+    idx = (slot >> 5) * 256 + xcd * 32 + (slot & 31);
+  } else {
+    const int rest = total - 256 * dealt, run = (rest + 7) >> 3, i = xcd * run + slot - 32 * dealt;
+    if (i >= rest) return false;                         // slot - 32 * dealt < run by the size of the grid
+    idx = 256 * dealt + i;
+  }
+  at.kslice = idx / tiles;
+  idx -= at.kslice * tiles;
+  const int band = idx / (32 * m_tiles);
+  idx -= band * 32 * m_tiles;
+  const int bw = n_tiles - 32 * band < 32 ? n_tiles - 32 * band : 32;
+  const int mb = idx / (8 * bw);
+  idx -= mb * 8 * bw;
+  const int mh = m_tiles - 8 * mb < 8 ? m_tiles - 8 * mb : 8;
+  at.m = 8 * mb + idx % mh;
+  at.n = 32 * band + idx / mh;
+  return true;
+}
+static int tile_grid(int total) { return 8 * (32 * (total / 256) + (total % 256 + 7) / 8); }
+
+// The BM x BN tile of the product at (m0, n0), K slice kslice.
+// HD128 (ME_QKV_ROPE only): head_dim 128 instead of 64. part: ME_LMHEAD, the tile's entry in a row of part_max.
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128>
+__device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
   constexpr int NWN = BN / 64;
   // Rotary pairs are columns (i, i + hd/2) of a head. With head_dim 64 a wavefront's 64 columns are one head and
   // its two accumulator columns the two halves. With head_dim 128 a head spans two wavefronts, so the W tile is
@@ -98,37 +135,6 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
   // four consecutive COLUMNS of one row of C. The storing epilogues write them as one 16-byte (8-byte bf16) piece
   // (four times fewer store instructions than with single elements of four rows), and the vocabulary head reduces
   // its rows inside the lane instead of across lanes.
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
-
-  // id -> (K slice, m_tile, n_tile): ids congruent mod 8 share an XCD. The tile list goes through bands of 32 N-tiles,
-  // in a band through blocks of 8 M-tiles, in a block through sub-bands of 4 N-tiles, so that 32 consecutive entries are
-  // 8 M-tiles x 4 N-tiles: an XCD that runs them at one time fetches every A panel into its L2 once per 4 users and
-  // every W tile once per 8 users. Every 256 entries the XCDs take 32 each: they then work on the same 8 A panels at the
-  // same time (with one contiguous eighth of the list each they drift apart in M: 16384 x 37888 x 3584 then takes 5 %
-  // longer). What is left, and all of a short list, is cut into eight equal runs. The list has no gaps: a grid padded to whole blocks leaves the
-  // shader engines of an XCD unevenly loaded (with 70 tiles of one M-tile all of them met on one engine of four and ran
-  // in two rounds: 48 us instead of 26 at 64 x 17920 x 1536).
-  const int tiles = a.m_tiles * a.n_tiles, total = tiles * a.ksplit;
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, dealt = total >> 8;
-  int idx;
-  if (slot < 32 * dealt) {
-    idx = (slot >> 5) * 256 + xcd * 32 + (slot & 31);
-  } else {
-    const int rest = total - 256 * dealt, run = (rest + 7) >> 3, at = xcd * run + slot - 32 * dealt;
-    if (at >= rest) return;                              // slot - 32 * dealt < run by the size of the grid
-    idx = 256 * dealt + at;
-  }
-  const int kslice = idx / tiles;
-  idx -= kslice * tiles;
-  const int band = idx / (32 * a.m_tiles);
-  idx -= band * 32 * a.m_tiles;
-  const int bw = a.n_tiles - 32 * band < 32 ? a.n_tiles - 32 * band : 32;
-  const int mb = idx / (8 * bw);
-  idx -= mb * 8 * bw;
-  const int mh = a.m_tiles - 8 * mb < 8 ? a.m_tiles - 8 * mb : 8;
-  const int m_tile = 8 * mb + idx % mh, n_tile = 32 * band + idx / mh;
-  const int m0 = m_tile * BM, n0 = n_tile * BN;
-
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wm = wave / NWN, wn = wave % NWN;
   const int lrow = lane & 31, lhalf = lane >> 5;
@@ -317,34 +323,43 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
   // accumulator element r of a lane: row lrow, column 8*(r/4) + 4*lhalf + r%4 of the 32x32 tile
   if (EPI == ME_STORE || EPI == ME_RESIDUAL) {
     float* __restrict__ Cs = a.C + (size_t)kslice * a.M * a.N;
-    const bool vec = (a.N & 3) == 0 && ((uintptr_t)a.C & 15) == 0;   // 16-byte pieces stay aligned and inside a row
+    // PIECES: 16 bytes at a time, aligned and wholly inside a row or outside. One decision for the workgroup: a tile inside
+    // the matrix stores without bounds checks. (Where a check per piece chooses between 16 bytes and elements, the compiler
+    // splits the pieces to share a tail: 256 x 131072 x 1536 152 us instead of 134.)
+    auto emit = [&](auto pieces, auto checked) {
+      constexpr bool PIECES = decltype(pieces)::value, CHECK = decltype(checked)::value;
 #pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int row = m0 + wm * WM + i * 32 + lrow;
-      if (row >= a.M) continue;
+      for (int i = 0; i < TM; ++i) {
+        const int row = m0 + wm * WM + i * 32 + lrow;
+        if (CHECK && row >= a.M) continue;
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int col = n0 + wn * WN + j * 32 + 8 * g + 4 * lhalf;
-          float* dst = Cs + (size_t)row * a.N + col;
-          if (vec && col + 3 < a.N) {
-            float4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-            if (EPI == ME_RESIDUAL) {
-              float4 o = *(const float4*)dst;
-              v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
-            }
-            *(float4*)dst = v;
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (col + e < a.N) {
-                if (EPI == ME_RESIDUAL) dst[e] += acc[i][j][4 * g + e];
-                else dst[e] = acc[i][j][4 * g + e];
+          for (int g = 0; g < 4; ++g) {
+            const int col = n0 + wn * WN + j * 32 + 8 * g + 4 * lhalf;
+            float* dst = Cs + (size_t)row * a.N + col;
+            if constexpr (PIECES) {
+              if (CHECK && col >= a.N) continue;
+              float4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+              if (EPI == ME_RESIDUAL) {
+                float4 o = *(const float4*)dst;
+                v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
               }
+              *(float4*)dst = v;
+            } else {
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (col + e < a.N) {
+                  if (EPI == ME_RESIDUAL) dst[e] += acc[i][j][4 * g + e];
+                  else dst[e] = acc[i][j][4 * g + e];
+                }
+            }
           }
-        }
-    }
+      }
+    };
+    if ((a.N & 3) != 0 || ((uintptr_t)a.C & 15) != 0) emit(std::false_type{}, std::true_type{});
+    else if (m0 + BM <= a.M && n0 + BN <= a.N) emit(std::true_type{}, std::false_type{});
+    else emit(std::true_type{}, std::true_type{});
   } else if (EPI == ME_SWIGLU) {
     const int F = a.N >> 1;                            // a multiple of 32: whole 4-unit pieces
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -488,24 +503,43 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
 #pragma unroll
         for (int w = 0; w < NWN; ++w)
           if (red_max[lr * NWN + w] > -INFINITY) sm += red_sum[lr * NWN + w] * expf(red_max[lr * NWN + w] - mx);
-        a.part_max[(size_t)row * a.n_tiles + n_tile] = mx;
-        a.part_sum[(size_t)row * a.n_tiles + n_tile] = sm;
+        a.part_max[(size_t)row * a.part_tiles + part] = mx;
+        a.part_sum[(size_t)row * a.part_tiles + part] = sm;
       }
     }
   }
 }
 
-template <int BM, int BN, int NWM, int S, int EPI, bool HD128 = false>
+// REST: the tiles cover the first columns only, in whole rounds of the 256 CUs; what is left, too little for another round,
+// is cut into tiles of 128 rows and REST columns, which further workgroups of the same launch take as CUs come free.
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128, int REST>
+__global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  TileAt at;
+  if constexpr (REST != 0) {
+    const int block = (int)blockIdx.x - a.rest_block;
+    if (block >= 0) {
+      if (!tile_of(block, a.rest_m_tiles, a.rest_n_tiles, 1, at)) return;
+      tile_product<128, REST, REST == 256 ? 2 : 4, REST == 256 ? 3 : 5, EPI, HD128>(a, at.m * 128, a.n_tiles * BN + at.n * REST, 0,
+                                                                                   a.n_tiles + at.n, smem);
+      return;
+    }
+  }
+  if (!tile_of(blockIdx.x, a.m_tiles, a.n_tiles, a.ksplit, at)) return;
+  tile_product<BM, BN, NWM, S, EPI, HD128>(a, at.m * BM, at.n * BN, at.kslice, at.n, smem);
+}
+
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128, int REST = 0>
 static void launch_variant(const GemmArgs& a, hipStream_t s) {
   constexpr int smem = BM == 256 ? 5 * 256 * 128 : S * (BM + BN) * 128;
   static bool configured = false;
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128>,
+    (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128, REST>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     configured = true;
   }
-  const int total = a.m_tiles * a.n_tiles * a.ksplit, per_xcd = 32 * (total / 256) + (total % 256 + 7) / 8;
-  gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128><<<8 * per_xcd, NWM * BN, smem, s>>>(a);
+  const int grid = REST ? a.rest_block + tile_grid(a.rest_m_tiles * a.rest_n_tiles) : tile_grid(a.m_tiles * a.n_tiles * a.ksplit);
+  gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128, REST><<<grid, NWM * BN, smem, s>>>(a);
 }
 
 int mfma_lmhead_tiles(int V) { return (V + 255) / 256; }
@@ -530,11 +564,26 @@ int mfma_gemm_ring(int tile, int M, int N, int K, int ksplit) {
   return tile == 3 && wgs <= 256 && K / 64 > 11 * ksplit ? 6 : ring[tile];
 }
 
+int mfma_gemm_rest(int M, int N, int K, bool wide_only, int* n_tiles);
 template <int EPI, bool HD128 = false>
 static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
   a.m_tiles = (a.M + kTiles[tile].bm - 1) / kTiles[tile].bm;
   a.n_tiles = (a.N + kTiles[tile].bn - 1) / kTiles[tile].bn;
-  if (tile == 0) launch_variant<256, 256, 2, 5, EPI, HD128>(a, s);
+  a.part_tiles = mfma_lmhead_tiles(a.N);
+  if (tile == 0) {
+    const int rest = EPI == ME_RESIDUAL || a.ksplit > 1 ? 0 : mfma_gemm_rest(a.M, a.N, a.K, EPI == ME_LMHEAD, &a.n_tiles);
+    if (rest) {
+      a.rest_block = tile_grid(a.m_tiles * a.n_tiles);
+      a.rest_m_tiles = (a.M + 127) / 128;
+      a.rest_n_tiles = (a.N - 256 * a.n_tiles + rest - 1) / rest;
+    }
+    if constexpr (EPI != ME_RESIDUAL) {
+      if (rest == 256) launch_variant<256, 256, 2, 5, EPI, HD128, 256>(a, s);
+      if constexpr (EPI != ME_LMHEAD)
+        if (rest == 128) launch_variant<256, 256, 2, 5, EPI, HD128, 128>(a, s);
+    }
+    if (!rest) launch_variant<256, 256, 2, 5, EPI, HD128>(a, s);
+  }
   else if (tile == 1) launch_variant<128, 256, 2, 3, EPI, HD128>(a, s);
   else if constexpr (EPI != ME_LMHEAD) {
     // four wavefronts along M: two per SIMD cover each other's LDS reads (69 -> 64 us at 256 x 1536 x 8960)
@@ -545,9 +594,41 @@ static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
   }
 }
 
+// Time that wgs workgroups of a tile shape take for a k-step each: in rounds of 256; a round that leaves CUs idle has k-steps
+// between the two costs of its tile; the narrow tiles run two workgroups per CU, so their last round overlaps the one before.
+static double rounds(int tile, long wgs) {
+  const TileShape& ts = kTiles[tile];
+  const long whole = tile < 3 || wgs <= 256 ? wgs / 256 : 0, rest = wgs - 256 * whole;
+  return whole * ts.full + (rest > 256 ? ts.full * rest / 256.0 : rest ? ts.lat + (ts.full - ts.lat) * rest / 256.0 : 0.0);
+}
+
+// Products of more than a round of 256 x 256 tiles: the columns (in tiles, *n_tiles) that fill whole rounds, and the width of
+// the 128-row tiles that the rest is cut into, 0 where another round of the large ones takes no longer. *cost: time of a
+// k-step over all rounds. A last round of few tiles leaves most CUs idle for as long as a full one (us without a rest / with):
+// 1024 x 17920 x 1536, 280 tiles, 80 / 66; 2048 rows, 560 tiles, 127 / 110; 256 x 151936 x 1536, 594 tiles, 173 / 162;
+// 4493 x 37888 x 3584, 2664 tiles, 978 / 961. About 3 us go to the epilogue and the first loads of the rest.
+static int rest_plan(int M, int N, int K, bool wide_only, int* n_tiles, double* cost) {
+  const int m_tiles = (M + 255) / 256, all = (N + 255) / 256;
+  const long whole = (long)m_tiles * all / 256;
+  *n_tiles = all;
+  *cost = rounds(0, (long)m_tiles * all);
+  const int nb = (int)(256 * whole / m_tiles);
+  if (nb == 0 || nb >= all) return 0;
+  int width = 0;
+  for (int tile = 1; tile <= (wide_only ? 1 : 2); ++tile) {
+    const int bn = kTiles[tile].bn;
+    const double c = whole * kTiles[0].full + rounds(tile, (long)((M + 127) / 128) * ((N - 256 * nb + bn - 1) / bn)) + 3.0 * 64 / K;
+    if (c < *cost) { *cost = c; *n_tiles = nb; width = bn; }
+  }
+  return width;
+}
+int mfma_gemm_rest(int M, int N, int K, bool wide_only, int* n_tiles) {
+  double cost;
+  return rest_plan(M, N, K, wide_only, n_tiles, &cost);
+}
+
 // Tile shape and K-split for an M x N x K product whose consumer can sum up to max_split partial products: the pair
-// with the least estimated time. Workgroups run in rounds of 256; a round that leaves CUs idle has k-steps between the
-// two costs of its tile; the narrow tiles run two workgroups per CU, so their last round overlaps the one before. The
+// with the least estimated time. The
 // weights cannot arrive faster than HBM delivers them, and about half of that time does not overlap with a short walk
 // through K. A launch costs about 3 us beside that, and every extra partial one more M x N float write here and one
 // more read in the consumer. The estimate is within 15 % of the measured times for 8..2048 rows of the projections with
@@ -562,9 +643,10 @@ void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* til
     const TileShape& ts = kTiles[tile];
     const long tiles = (long)((M + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn);
     for (int sp = 1; sp <= max_split && sp <= MFMA_MAX_SPLIT && (sp == 1 || sp * 4 <= KT + 3); ++sp) {
-      const long wgs = tiles * sp, whole = tile < 3 || wgs <= 256 ? wgs / 256 : 0, rest = wgs - 256 * whole;
-      const double last = rest > 256 ? ts.full * rest / 256.0 : rest ? ts.lat + (ts.full - ts.lat) * rest / 256.0 : 0.0;
-      const double walk = (whole * ts.full + last) * ((KT + sp - 1) / sp) + 0.45 * stream;
+      double step = rounds(tile, tiles * sp);
+      int n_tiles;
+      if (tile == 0 && sp == 1) rest_plan(M, N, K, wide_only, &n_tiles, &step);
+      const double walk = step * ((KT + sp - 1) / sp) + 0.45 * stream;
       const double t = 3.0 + (walk > stream ? walk : stream) + (2 * sp - 2) * (double)M * N * 4.0 / 4e6;
       if (t < best - 1e-9) { best = t; *tile_out = tile; *split_out = sp; }
     }

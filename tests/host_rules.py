@@ -35,3 +35,12 @@ def gemm_kernel(M, N, K, max_split=1):
     tile, split = C.c_int(), C.c_int()
     plan(M, N, K, max_split, False, tile, split)
     return TILES[tile.value], ring(tile.value, M, N, K, split.value), split.value
+
+
+def gemm_rest(M, N, K, wide_only=False):
+    """Width of the tiles that the last columns of a product of 256 x 256 tiles are cut into (0: none), and the tile columns
+    in front of them."""
+    f = library()._Z14mfma_gemm_restiiibPi
+    f.restype, f.argtypes = C.c_int, [C.c_int] * 3 + [C.c_bool, C.POINTER(C.c_int)]
+    n = C.c_int()
+    return f(M, N, K, wide_only, n), n.value

@@ -4,7 +4,7 @@ import time
 
 import pytest
 
-from host_rules import decode_runs, gemm_kernel
+from host_rules import decode_runs, gemm_kernel, gemm_rest
 import test_gpu_kernels as kernels
 
 
@@ -59,3 +59,15 @@ def test_every_kernel_has_its_test():
     assert {c[0] for c in kernels.GATE_UP_SHAPES} == every
     for hd in (64, 128):
         assert {c[0] for c in kernels.QKV_TILES if c[3] == hd} == every
+
+
+@pytest.mark.parametrize("width,epilogue,M,N,K", kernels.REST_PRODUCTS)
+def test_rest_products_have_the_rest_they_name(width, epilogue, M, N, K):
+    assert gemm_kernel(M, N, K)[0] == "256x256"
+    got, before = gemm_rest(M, N, K, epilogue == "lmhead")
+    assert got == width and 0 < before < -(-N // 256)
+
+
+def test_no_rest_where_the_rounds_are_full_or_half_full():
+    for M, N, K in ((1024, 16384, 1536), (2048, 37888, 3584), (2048, 152064, 3584), (256, 17920, 1536), (2100, 7400, 64)):
+        assert gemm_rest(M, N, K) == (0, -(-N // 256)), (M, N, K)

@@ -352,3 +352,24 @@ def test_qkv_projection_with_rotary_embedding(ctx, dtype, Hq, Hkv, hd, d_model, 
             delta = 2e-5 * np.sqrt((y ** 2).mean())
             assert np.all(np.abs(got - want) <= 0.5 * ulp + delta), float((np.abs(got - want) - 0.5 * ulp).max())
             assert np.mean(got == oracle.operand(want, "bf16")) > 0.99   # and nearly all values round identically
+
+
+# More than whole rounds of 256 x 256 tiles: (width of the tiles the last columns are cut into, epilogue, M, N, K), ragged in
+# rows, columns and the K-tiles of either ring. test_dispatch.py checks that each product has that rest.
+REST_PRODUCTS = [(128, "linear", 1100, 14533, 448), (256, "linear", 1023, 20548, 512), (128, "linear", 255, 65605, 512),
+                 (128, "gate_up", 1023, 16448, 448), (256, "gate_up", 1100, 16704, 768), (256, "lmhead", 1100, 14533, 448),
+                 (256, "lmhead", 255, 66000, 512), (128, "qkv128", 520, 206 * 128, 448), (128, "qkv64", 520, 412 * 64, 448),
+                 (256, "qkv128", 520, 222 * 128, 768), (256, "qkv64", 520, 444 * 64, 768)]
+
+
+@pytest.mark.parametrize("width,epilogue,M,N,K", REST_PRODUCTS)
+def test_products_with_a_rest(ctx, width, epilogue, M, N, K):
+    if epilogue == "linear":
+        test_linear_tile_shapes(ctx, "256x256/5", 1, M, N, K)
+    elif epilogue == "gate_up":
+        test_gate_up_bf16(ctx, "256x256/5", M, N // 2, K)
+    elif epilogue == "lmhead":
+        test_lmhead_logprob_bf16(ctx, M, N, K)
+    else:
+        hd = int(epilogue[3:])
+        test_qkv_projection_with_rotary_embedding(ctx, "bf16", N // hd - 4, 2, hd, K, 1, 4, M // 4, [77])
