@@ -56,11 +56,13 @@ struct GemmArgs {
 // One direct-to-LDS load instruction: the workgroup's NW wavefronts write NW consecutive 1 KiB spans
 // (8 rows of 128 bytes each) of an operand tile.
 // SWAP56: LDS row r holds tile row r with bits 5 and 6 exchanged (see the ME_QKV_ROPE epilogue).
-template <int NW, bool SWAP56 = false>
+// SPANS: of the whole tile; where the wavefronts outnumber the last of them, some fetch the last one again.
+template <int NW, int SPANS, bool SWAP56 = false>
 __device__ __forceinline__ void load_span_async(const bf16_t* __restrict__ G, int row0, int rows_total, int K, int k0,
                                                 char* lds_tile, int p, int wave) {
   const int lane = threadIdx.x & 63;
   int span = p * NW + wave;                  // 1 KiB of LDS = 8 rows, written by one wavefront
+  if (SPANS % NW != 0) span = span < SPANS ? span : SPANS - 1;
   int q = span * 64 + lane;
   int row = q >> 3, slot = q & 7;
   int chunk = slot ^ ((row >> 1) & 7);
@@ -157,7 +159,7 @@ __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, 
       for (int j = 0; j < TN; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
   };
-  constexpr int LA = BM / (8 * NW), LB = BN / (8 * NW);   // direct-to-LDS loads per thread per operand tile
+  constexpr int LA = (BM / 8 + NW - 1) / NW, LB = (BN / 8 + NW - 1) / NW;   // direct-to-LDS loads per thread per operand tile
   constexpr int NLD = LA + LB;
   auto share_size = [](int sh) { int c = 0; for (int j = 0; j < NLD; ++j) c += (j * 4 / NLD == sh); return c; };
   constexpr int S0 = share_size(0), S1 = share_size(1), S2 = share_size(2), S3 = share_size(3);
@@ -189,12 +191,12 @@ __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, 
   auto issue_w = [&](int t) {                           // prologue only: t < 5 is its own phase
     const int src = t < KT ? t : KT - 1;
 #pragma unroll
-    for (int i = 0; i < LB; ++i) load_span_async<NW, SWAP>(a.W, n0, a.N, a.K, (kt0 + src) * 64, wslot(t), i, wave);
+    for (int i = 0; i < LB; ++i) load_span_async<NW, BN / 8, SWAP>(a.W, n0, a.N, a.K, (kt0 + src) * 64, wslot(t), i, wave);
   };
   auto issue_a = [&](int t) {
     const int src = t < KT ? t : KT - 1;
 #pragma unroll
-    for (int i = 0; i < LA; ++i) load_span_async<NW>(a.A, m0, a.M, a.K, (kt0 + src) * 64, aslot(t), i, wave);
+    for (int i = 0; i < LA; ++i) load_span_async<NW, BM / 8>(a.A, m0, a.M, a.K, (kt0 + src) * 64, aslot(t), i, wave);
   };
   static_assert(LB == 4 && (S0 == 2) && S1 <= 2 && S2 <= 2 && S3 <= 2, "the waits below are written for these counts");
   // share SH of the loads of A-tile ta (phase pa) and W-tile tw (phase pw)
@@ -204,8 +206,8 @@ __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, 
 #pragma unroll
     for (int j = 0; j < NLD; ++j) {
       if (j * 4 / NLD != SH) continue;
-      if (j < LA) load_span_async<NW>(a.A, m0, a.M, a.K, (kt0 + sa) * 64, aslot(pa), j, wave);
-      else load_span_async<NW, SWAP>(a.W, n0, a.N, a.K, (kt0 + sw) * 64, wslot(pw), j - LA, wave);
+      if (j < LA) load_span_async<NW, BM / 8>(a.A, m0, a.M, a.K, (kt0 + sa) * 64, aslot(pa), j, wave);
+      else load_span_async<NW, BN / 8, SWAP>(a.W, n0, a.N, a.K, (kt0 + sw) * 64, wslot(pw), j - LA, wave);
     }
   };
   issue_w(0); issue_a(0); issue_w(1);
@@ -258,8 +260,8 @@ __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, 
 #pragma unroll
       for (int j = 0; j < NLD; ++j) {
         if (SH < 4 && j * 4 / NLD != SH) continue;
-        if (j < LA) load_span_async<NW>(a.A, m0, a.M, a.K, (kt0 + t) * 64, st, j, wave);
-        else load_span_async<NW, SWAP>(a.W, n0, a.N, a.K, (kt0 + t) * 64, st + BM * 128, j - LA, wave);
+        if (j < LA) load_span_async<NW, BM / 8>(a.A, m0, a.M, a.K, (kt0 + t) * 64, st, j, wave);
+        else load_span_async<NW, BN / 8, SWAP>(a.W, n0, a.N, a.K, (kt0 + t) * 64, st + BM * 128, j - LA, wave);
       }
     };
     // own loads of all but the newest `ahead` K-tiles have landed and own fragment reads are done, then everybody's
@@ -565,8 +567,16 @@ int mfma_gemm_ring(int tile, int M, int N, int K, int ksplit) {
 }
 
 int mfma_gemm_rest(int M, int N, int K, bool wide_only, int* n_tiles);
+bool mfma_gate_up_192(int M, int N, int K, int tile);
 template <int EPI, bool HD128 = false>
 static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
+  if constexpr (EPI == ME_SWIGLU)
+    if (mfma_gate_up_192(a.M, a.N, a.K, tile)) {
+      a.m_tiles = (a.M + 127) / 128;
+      a.n_tiles = (a.N + 191) / 192;
+      launch_variant<128, 192, 2, 4, EPI, HD128>(a, s);
+      return;
+    }
   a.m_tiles = (a.M + kTiles[tile].bm - 1) / kTiles[tile].bm;
   a.n_tiles = (a.N + kTiles[tile].bn - 1) / kTiles[tile].bn;
   a.part_tiles = mfma_lmhead_tiles(a.N);
@@ -594,12 +604,28 @@ static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
   }
 }
 
+// Gate and up in 128 x 192 tiles where the plan says 128 x 256 and a single round does: a few hundred rows then occupy a third
+// more CUs, each with 120 KB of operands in flight instead of 96, which is what bounds such a product while its weights come
+// from HBM (256 x 1024 x 8192 in 128 x 256 tiles: 101 us, 96 without the product). us before / so: 256 x 17920 x 1536 29.1 /
+// 26.1, 200 rows 27.4 / 24.6, 100 x 37888 x 3584 64.6 / 56.7, 512 x 9728 x 896 17.9 / 17.2; in two rounds it is behind (321 x
+// 17920 x 1536: 27.7 / 44.3). K-tiles for less than two fills of the ring leave nothing in flight to gain.
+bool mfma_gate_up_192(int M, int N, int K, int tile) {
+  return tile == 1 && (long)((M + 127) / 128) * ((N + 191) / 192) <= 256 && K > 512;
+}
+
 // Time that wgs workgroups of a tile shape take for a k-step each: in rounds of 256; a round that leaves CUs idle has k-steps
-// between the two costs of its tile; the narrow tiles run two workgroups per CU, so their last round overlaps the one before.
-static double rounds(int tile, long wgs) {
+// between the two costs of its tile. The narrow tiles run two workgroups per CU: their last round overlaps the one before, but
+// a CU with two takes twice as long as one with one, so a few more than 256 cost as much as a wide round (64 x 128: 0.66 us a
+// step at 264 workgroups, 0.79 at 352, 1.24 at 660, 1.98 at 1260; not where 32 rows fill half of the tile and weights are all
+// that streams: 1.0 at 296, HBM's rate, for 16 x 37888 x 3584).
+static double rounds(int tile, long wgs, int M) {
   const TileShape& ts = kTiles[tile];
   const long whole = tile < 3 || wgs <= 256 ? wgs / 256 : 0, rest = wgs - 256 * whole;
-  return whole * ts.full + (rest > 256 ? ts.full * rest / 256.0 : rest ? ts.lat + (ts.full - ts.lat) * rest / 256.0 : 0.0);
+  if (rest > 256) {
+    const double per_cu = rest / 256.0, two = 2.0 * ts.lat + 0.34 * (per_cu - 1.0);
+    return tile == 3 && M > 32 && two > ts.full * per_cu ? two : ts.full * per_cu;
+  }
+  return whole * ts.full + (rest ? ts.lat + (ts.full - ts.lat) * rest / 256.0 : 0.0);
 }
 
 // Products of more than a round of 256 x 256 tiles: the columns (in tiles, *n_tiles) that fill whole rounds, and the width of
@@ -611,13 +637,13 @@ static int rest_plan(int M, int N, int K, bool wide_only, int* n_tiles, double* 
   const int m_tiles = (M + 255) / 256, all = (N + 255) / 256;
   const long whole = (long)m_tiles * all / 256;
   *n_tiles = all;
-  *cost = rounds(0, (long)m_tiles * all);
+  *cost = rounds(0, (long)m_tiles * all, M);
   const int nb = (int)(256 * whole / m_tiles);
   if (nb == 0 || nb >= all) return 0;
   int width = 0;
   for (int tile = 1; tile <= (wide_only ? 1 : 2); ++tile) {
     const int bn = kTiles[tile].bn;
-    const double c = whole * kTiles[0].full + rounds(tile, (long)((M + 127) / 128) * ((N - 256 * nb + bn - 1) / bn)) + 3.0 * 64 / K;
+    const double c = whole * kTiles[0].full + rounds(tile, (long)((M + 127) / 128) * ((N - 256 * nb + bn - 1) / bn), M) + 3.0 * 64 / K;
     if (c < *cost) { *cost = c; *n_tiles = nb; width = bn; }
   }
   return width;
@@ -628,10 +654,9 @@ int mfma_gemm_rest(int M, int N, int K, bool wide_only, int* n_tiles) {
 }
 
 // Tile shape and K-split for an M x N x K product whose consumer can sum up to max_split partial products: the pair
-// with the least estimated time. The
-// weights cannot arrive faster than HBM delivers them, and about half of that time does not overlap with a short walk
-// through K. A launch costs about 3 us beside that, and every extra partial one more M x N float write here and one
-// more read in the consumer. The estimate is within 15 % of the measured times for 8..2048 rows of the projections with
+// with the least estimated time. The weights cannot arrive faster than HBM delivers them, and about half of that time does
+// not overlap with a short walk through K. A launch costs about 3 us beside that, and every extra partial one more M x N float
+// write here and one more read in the consumer. The estimate is within 15 % of the measured times for 8..2048 rows of the projections with
 // K = 1024..18944, except that it misses up to 20 % of the narrow tiles' cost when they run in many rounds, where the
 // wide ones are ahead anyway.
 void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* tile_out, int* split_out) {
@@ -643,7 +668,7 @@ void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* til
     const TileShape& ts = kTiles[tile];
     const long tiles = (long)((M + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn);
     for (int sp = 1; sp <= max_split && sp <= MFMA_MAX_SPLIT && (sp == 1 || sp * 4 <= KT + 3); ++sp) {
-      double step = rounds(tile, tiles * sp);
+      double step = rounds(tile, tiles * sp, M);
       int n_tiles;
       if (tile == 0 && sp == 1) rest_plan(M, N, K, wide_only, &n_tiles, &step);
       const double walk = step * ((KT + sp - 1) / sp) + 0.45 * stream;

@@ -44,3 +44,11 @@ def gemm_rest(M, N, K, wide_only=False):
     f.restype, f.argtypes = C.c_int, [C.c_int] * 3 + [C.c_bool, C.POINTER(C.c_int)]
     n = C.c_int()
     return f(M, N, K, wide_only, n), n.value
+
+
+def gate_up_kernel(M, F, K):
+    """Tile that the bf16 gate/up product gets: one of TILES, or the shape that only this product has."""
+    tile = gemm_kernel(M, 2 * F, K)[0]
+    f = library()._Z16mfma_gate_up_192iiii
+    f.restype, f.argtypes = C.c_bool, [C.c_int] * 4
+    return "128x192" if f(M, 2 * F, K, TILES.index(tile)) else tile

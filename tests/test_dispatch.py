@@ -4,7 +4,7 @@ import time
 
 import pytest
 
-from host_rules import decode_runs, gemm_kernel, gemm_rest
+from host_rules import decode_runs, gate_up_kernel, gemm_kernel, gemm_rest
 import test_gpu_kernels as kernels
 
 
@@ -71,3 +71,16 @@ def test_rest_products_have_the_rest_they_name(width, epilogue, M, N, K):
 def test_no_rest_where_the_rounds_are_full_or_half_full():
     for M, N, K in ((1024, 16384, 1536), (2048, 37888, 3584), (2048, 152064, 3584), (256, 17920, 1536), (2100, 7400, 64)):
         assert gemm_rest(M, N, K) == (0, -(-N // 256)), (M, N, K)
+
+
+@pytest.mark.parametrize("M,F,K", kernels.GATE_UP_192)
+def test_gate_up_192_products_have_that_tile(M, F, K):
+    assert gate_up_kernel(M, F, K) == "128x192"
+
+
+def test_other_gate_up_products_keep_their_tile():
+    for kernel, M, F, K in kernels.GATE_UP_SHAPES:
+        assert kernel.startswith(gate_up_kernel(M, F, K)), (kernel, M, F, K)
+    for _, epilogue, M, N, K in kernels.REST_PRODUCTS:
+        if epilogue == "gate_up":
+            assert gate_up_kernel(M, N // 2, K) == "256x256"

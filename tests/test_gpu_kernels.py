@@ -373,3 +373,12 @@ def test_products_with_a_rest(ctx, width, epilogue, M, N, K):
     else:
         hd = int(epilogue[3:])
         test_qkv_projection_with_rotary_embedding(ctx, "bf16", N // hd - 4, 2, hd, K, 1, 4, M // 4, [77])
+
+
+# 128 x 192 tiles, which gate and up alone have, from the shortest K they take on, ragged in rows and columns
+GATE_UP_192 = [(100, 16448, 576), (201, 8288, 640), (384, 5536, 704), (1100, 1888, 832), (256, 8960, 1536)]
+
+
+@pytest.mark.parametrize("M,F,K", GATE_UP_192)
+def test_gate_up_192(ctx, M, F, K):
+    test_gate_up_bf16(ctx, "128x192/4", M, F, K)
