@@ -417,8 +417,9 @@ __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, 
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const float x1 = acc[i][0][4 * g + e], x2 = acc[i][1][4 * g + e];
-              y1[e] = (__bf16)(x1 * c4[e] - x2 * s4[e]);
-              y2[e] = (__bf16)(x2 * c4[e] + x1 * s4[e]);
+              // spelled out, so that every tile shape rounds the same product
+              y1[e] = (__bf16)fmaf(x1, c4[e], -(x2 * s4[e]));
+              y2[e] = (__bf16)fmaf(x1, s4[e], x2 * c4[e]);
             }
             *(bf16x4*)(dst + i0) = y1;
             *(bf16x4*)(dst + HALF + i0) = y2;
