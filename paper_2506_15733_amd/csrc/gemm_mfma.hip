@@ -122,8 +122,8 @@ __device__ __forceinline__ bool tile_of(int block, int m_tiles, int n_tiles, int
 static int tile_grid(int total) { return 8 * (32 * (total / 256) + (total % 256 + 7) / 8); }
 
 // The BM x BN tile of the product at (m0, n0), K slice kslice.
-// HD128 (ME_QKV_ROPE only): head_dim 128 instead of 64. part: ME_LMHEAD, the tile's entry in a row of part_max.
-template <int BM, int BN, int NWM, int S, int EPI, bool HD128>
+// HD128 (ME_QKV_ROPE only): head_dim 128 instead of 64. MIXED: the launch has tiles of two shapes. part: ME_LMHEAD, the tile's entry in a row of part_max.
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128, bool MIXED>
 __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
   constexpr int NWN = BN / 64;
   // Rotary pairs are columns (i, i + hd/2) of a head. With head_dim 64 a wavefront's 64 columns are one head and
@@ -417,9 +417,10 @@ __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, 
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               const float x1 = acc[i][0][4 * g + e], x2 = acc[i][1][4 * g + e];
-              // spelled out, so that every tile shape rounds the same product
+              // spelled out, so that all tiles of a launch, and a launch whatever stands around it, round the same of
+              // the two products
               y1[e] = (__bf16)fmaf(x1, c4[e], -(x2 * s4[e]));
-              y2[e] = (__bf16)fmaf(x1, s4[e], x2 * c4[e]);
+              y2[e] = BM == 256 && !MIXED ? (__bf16)fmaf(x2, c4[e], x1 * s4[e]) : (__bf16)fmaf(x1, s4[e], x2 * c4[e]);
             }
             *(bf16x4*)(dst + i0) = y1;
             *(bf16x4*)(dst + HALF + i0) = y2;
@@ -523,13 +524,13 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
     const int block = (int)blockIdx.x - a.rest_block;
     if (block >= 0) {
       if (!tile_of(block, a.rest_m_tiles, a.rest_n_tiles, 1, at)) return;
-      tile_product<128, REST, REST == 256 ? 2 : 4, REST == 256 ? 3 : 5, EPI, HD128>(a, at.m * 128, a.n_tiles * BN + at.n * REST, 0,
+      tile_product<128, REST, REST == 256 ? 2 : 4, REST == 256 ? 3 : 5, EPI, HD128, true>(a, at.m * 128, a.n_tiles * BN + at.n * REST, 0,
                                                                                    a.n_tiles + at.n, smem);
       return;
     }
   }
   if (!tile_of(blockIdx.x, a.m_tiles, a.n_tiles, a.ksplit, at)) return;
-  tile_product<BM, BN, NWM, S, EPI, HD128>(a, at.m * BM, at.n * BN, at.kslice, at.n, smem);
+  tile_product<BM, BN, NWM, S, EPI, HD128, REST != 0>(a, at.m * BM, at.n * BN, at.kslice, at.n, smem);
 }
 
 template <int BM, int BN, int NWM, int S, int EPI, bool HD128, int REST = 0>
@@ -609,21 +610,23 @@ static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
 // more CUs, each with 120 KB of operands in flight instead of 96, which is what bounds such a product while its weights come
 // from HBM (256 x 1024 x 8192 in 128 x 256 tiles: 101 us, 96 without the product). us before / so: 256 x 17920 x 1536 29.1 /
 // 26.1, 200 rows 27.4 / 24.6, 100 x 37888 x 3584 64.6 / 56.7, 512 x 9728 x 896 17.9 / 17.2; in two rounds it is behind (321 x
-// 17920 x 1536: 27.7 / 44.3). K-tiles for less than two fills of the ring leave nothing in flight to gain.
+// 17920 x 1536: 27.7 / 44.3). K-tiles for less than two fills of the ring leave nothing in flight to gain. Up to 128 rows, where
+// the weights are read once, also in place of 64 x 128 tiles that put two workgroups on some CUs (48 x 37888 x 3584: 64.1 / 52.4).
 bool mfma_gate_up_192(int M, int N, int K, int tile) {
-  return tile == 1 && (long)((M + 127) / 128) * ((N + 191) / 192) <= 256 && K > 512;
+  const bool two_narrow = tile == 3 && M > 32 && M <= 128 && (long)((M + 63) / 64) * ((N + 127) / 128) > 256;
+  return (tile == 1 || two_narrow) && (long)((M + 127) / 128) * ((N + 191) / 192) <= 256 && K > 512;
 }
 
 // Time that wgs workgroups of a tile shape take for a k-step each: in rounds of 256; a round that leaves CUs idle has k-steps
 // between the two costs of its tile. The narrow tiles run two workgroups per CU: their last round overlaps the one before, but
-// a CU with two takes twice as long as one with one, so a few more than 256 cost as much as a wide round (64 x 128: 0.66 us a
-// step at 264 workgroups, 0.79 at 352, 1.24 at 660, 1.98 at 1260; not where 32 rows fill half of the tile and weights are all
-// that streams: 1.0 at 296, HBM's rate, for 16 x 37888 x 3584).
+// a few more than 256 cost what 512 do, twice one workgroup on a CU (64 x 128: 0.66 us a step at 264 workgroups, 0.79 at 352,
+// 0.71 at 484, 1.24 at 660, 1.98 at 1260; not where 32 rows fill half of the tile and weights are all that streams: 1.0 at
+// 296, HBM's rate, for 16 x 37888 x 3584).
 static double rounds(int tile, long wgs, int M) {
   const TileShape& ts = kTiles[tile];
   const long whole = tile < 3 || wgs <= 256 ? wgs / 256 : 0, rest = wgs - 256 * whole;
   if (rest > 256) {
-    const double per_cu = rest / 256.0, two = 2.0 * ts.lat + 0.34 * (per_cu - 1.0);
+    const double per_cu = rest / 256.0, two = rest <= 512 ? 2.2 * ts.lat : 2.0 * ts.lat + 0.34 * (per_cu - 1.0);
     return tile == 3 && M > 32 && two > ts.full * per_cu ? two : ts.full * per_cu;
   }
   return whole * ts.full + (rest ? ts.lat + (ts.full - ts.lat) * rest / 256.0 : 0.0);
@@ -634,6 +637,9 @@ static double rounds(int tile, long wgs, int M) {
 // k-step over all rounds. A last round of few tiles leaves most CUs idle for as long as a full one (us without a rest / with):
 // 1024 x 17920 x 1536, 280 tiles, 80 / 66; 2048 rows, 560 tiles, 127 / 110; 256 x 151936 x 1536, 594 tiles, 173 / 162;
 // 4493 x 37888 x 3584, 2664 tiles, 978 / 961. About 3 us go to the epilogue and the first loads of the rest.
+// The 128-column tiles are for a rest of an eighth of a round at most: they occupy the CUs for half as long again as the 256-column
+// ones, which other streams miss (step of 2184 rows of 7B models, 62 ms, a rest of 52 tiles: 0.9 % longer than without a rest so,
+// 0.3 % with the wide ones).
 static int rest_plan(int M, int N, int K, bool wide_only, int* n_tiles, double* cost) {
   const int m_tiles = (M + 255) / 256, all = (N + 255) / 256;
   const long whole = (long)m_tiles * all / 256;
@@ -642,7 +648,8 @@ static int rest_plan(int M, int N, int K, bool wide_only, int* n_tiles, double* 
   const int nb = (int)(256 * whole / m_tiles);
   if (nb == 0 || nb >= all) return 0;
   int width = 0;
-  for (int tile = 1; tile <= (wide_only ? 1 : 2); ++tile) {
+  const bool narrow = !wide_only && (long)m_tiles * (all - nb) <= 32;
+  for (int tile = 1; tile <= (narrow ? 2 : 1); ++tile) {
     const int bn = kTiles[tile].bn;
     const double c = whole * kTiles[0].full + rounds(tile, (long)((M + 127) / 128) * ((N - 256 * nb + bn - 1) / bn), M) + 3.0 * 64 / K;
     if (c < *cost) { *cost = c; *n_tiles = nb; width = bn; }

@@ -358,7 +358,7 @@ def test_qkv_projection_with_rotary_embedding(ctx, dtype, Hq, Hkv, hd, d_model, 
 # rows, columns and the K-tiles of either ring. test_dispatch.py checks that each product has that rest.
 REST_PRODUCTS = [(128, "linear", 1100, 14533, 448), (256, "linear", 1023, 20548, 512), (128, "linear", 255, 65605, 512),
                  (128, "gate_up", 1023, 16448, 448), (256, "gate_up", 1100, 16704, 768), (256, "lmhead", 1100, 14533, 448),
-                 (256, "lmhead", 255, 66000, 512), (128, "qkv128", 520, 206 * 128, 448), (128, "qkv64", 520, 412 * 64, 448),
+                 (256, "lmhead", 255, 66000, 512), (128, "qkv128", 1100, 114 * 128, 448), (128, "qkv64", 1100, 228 * 64, 448),
                  (256, "qkv128", 520, 222 * 128, 768), (256, "qkv64", 520, 444 * 64, 768)]
 
 
@@ -376,7 +376,7 @@ def test_products_with_a_rest(ctx, width, epilogue, M, N, K):
 
 
 # 128 x 192 tiles, which gate and up alone have, from the shortest K they take on, ragged in rows and columns
-GATE_UP_192 = [(100, 16448, 576), (201, 8288, 640), (384, 5536, 704), (1100, 1888, 832), (256, 8960, 1536)]
+GATE_UP_192 = [(33, 16448, 576), (100, 16448, 576), (201, 8288, 640), (384, 5536, 704), (1100, 1888, 832), (256, 8960, 1536)]
 
 
 @pytest.mark.parametrize("M,F,K", GATE_UP_192)
