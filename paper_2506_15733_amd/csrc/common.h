@@ -61,6 +61,21 @@ struct BatchGeom {
   int max_pages, page_tokens;
 };
 
+// Row m of the rotary table, pair i: cos and sin of pos * base^(-2i/hd), evaluated in double so that long contexts lose
+// nothing.
+__device__ __forceinline__ void rope_row(float* __restrict__ cs, int m, int i, int pos, int half, int hd, double base) {
+  double ang = (double)pos * pow(base, -2.0 * (double)i / (double)hd);
+  double sn, cn;
+  sincos(ang, &sn, &cn);
+  cs[(size_t)m * hd + i] = (float)cn;
+  cs[(size_t)m * hd + half + i] = (float)sn;
+}
+// four values of a row of the embedding, aligned, can be read and stored at once
+template <typename T>
+bool embed_quads(const T* E, const float* x, int d) {
+  return d % 4 == 0 && ((uintptr_t)E & (4 * sizeof(T) - 1)) == 0 && ((uintptr_t)x & 15) == 0;
+}
+
 struct ModelDims {
   int d, Hq, Hkv, hd, F, V;
   float eps, rope_base;
@@ -106,10 +121,13 @@ void launch_scatter_last_rows(const float* xs, float* x, int C, int L, int d, hi
 // block_out[c] = sum_t tok_logp[c][t] in index order, accumulated in double
 void launch_block_sum(const float* tok_logp, float* block_out, int L, int C, hipStream_t s);
 // Ancestral sampling of one token per row from softmax(logits[row, :limit]) by inverse CDF in id order from the
-// uniform u[row*L + t]; writes the id to cand[row*L + t] and its log-probability to tok_logp[row*L + t].
+// uniform u[row*L + t]; writes the id to cand[row*L + t] and its log-probability to tok_logp[row*L + t], and leaves what
+// launch_embed_rope would leave for the launch g of one position per block (g.t0 = t) with these tokens: x and cs.
 // scratch: sample_scratch_bytes(rows) bytes, 8-byte aligned.
+template <typename T>
 void launch_sample_tokens(const float* logits, int rows, int V, int limit, const double* u, int32_t* cand,
-                          float* tok_logp, int L, int t, void* scratch, int* status, hipStream_t s);
+                          float* tok_logp, int L, void* scratch, int* status, const T* E, float* x, int d, float* cs,
+                          const BatchGeom& g, int hd, float base, hipStream_t s);
 size_t sample_scratch_bytes(int rows);
 
 enum GemmEpilogue { EPI_STORE_F32 = 0, EPI_RESIDUAL_ADD = 1 };

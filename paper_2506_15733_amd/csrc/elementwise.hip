@@ -3,16 +3,7 @@
 #include "common.h"
 
 // ---------------------------------------------------------------- embedding and rotary angles
-// cos/sin of pos * base^(-2i/hd), pos = context length + t, evaluated in double so that long
-// contexts lose nothing; one table per call, shared by all layers and heads.
-__device__ __forceinline__ void rope_row(float* __restrict__ cs, int m, int i, int pos, int half, int hd, double base) {
-  double ang = (double)pos * pow(base, -2.0 * (double)i / (double)hd);
-  double sn, cn;
-  sincos(ang, &sn, &cn);
-  cs[(size_t)m * hd + i] = (float)cn;
-  cs[(size_t)m * hd + half + i] = (float)sn;
-}
-
+// Angles are those of pos = context length + t; one table per call, shared by all layers and heads.
 // One block per row: its embedding and its row of the table, which nothing but the row's position enters, so that a
 // pass (and every position of a generated block) starts with one launch instead of two.
 template <typename T, bool QUADS>
@@ -40,8 +31,7 @@ __global__ void __launch_bounds__(256) embed_rope_kernel(const int32_t* __restri
 template <typename T>
 void launch_embed_rope(const int32_t* tok, int tok_stride, int rows, const T* E, float* x, int d, int V, int* status,
                        float* cs, const BatchGeom& g, int hd, float base, hipStream_t s) {
-  const bool quads = d % 4 == 0 && ((uintptr_t)E & (4 * sizeof(T) - 1)) == 0 && ((uintptr_t)x & 15) == 0;
-  if (quads)
+  if (embed_quads(E, x, d))
     embed_rope_kernel<T, true><<<g.M, 256, 0, s>>>(tok, tok_stride, rows, E, x, d, V, status, cs, g.n * g.L, g.L, hd,
                                                    (double)base, g.lens, g.b0, g.len_override, g.t0);
   else

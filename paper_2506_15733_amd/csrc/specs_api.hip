@@ -559,7 +559,8 @@ static BatchGeom stretch_geom(const specs_prefix* p, const Stretch& st, int rows
 }
 
 // The trunk over g.M rows: every row attends to its beam's cached prefix and causally to the earlier
-// positions of its own block. Row m embeds tokens[m * tok_stride]. Leaves the final residual stream in x and the
+// positions of its own block. Row m embeds tokens[m * tok_stride]
+// (null: x and ws.cs hold the embedded rows and their angles already). Leaves the final residual stream in x and the
 // per-layer block keys/values in ws.kblk / ws.vblk (laid out for blocks of g.Lk tokens; a launch with g.L = 1 and
 // g.t0 = t adds position t of every block). stretches (prefill): the rows are those of these prompts, which only the
 // embedding, the attention and the pages tell apart; everything else sees one block of g.M rows. Keys and values are
@@ -589,7 +590,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
                                     md.V, ws.status, ws.cs + (size_t)st.row * md.hd, stretch_geom(p, st, span(i), g.vs),
                                     md.hd, md.rope_base, s));
     }
-  } else {
+  } else if (tokens) {
     PROFILED(ctx, SPECS_K_OTHER, s,
              launch_embed_rope<T>(tokens, tok_stride, g.M, (const T*)m->w.embed, x, md.d, md.V, ws.status, ws.cs, g, md.hd,
                                   md.rope_base, s));
@@ -818,8 +819,9 @@ static int generate_impl(specs_ctx* ctx, const specs_model* m, const specs_prefi
                gemm_store_split<T>((const T*)ws.a, (const T*)m->w.head, ws.logits, 1, g.M, d.vocab, d.d_model, s));
     }
     PROFILED(ctx, SPECS_K_OTHER, s,
-             launch_sample_tokens(ws.logits, g.M, d.vocab, limit, u, cand, tl, L, t, ws.sample, ws.status, s));
-    run_trunk<T>(ctx, m, p, ws, g, ws.xs, cand + t, L, max_ctx, nullptr, R, C, s);
+             launch_sample_tokens<T>(ws.logits, g.M, d.vocab, limit, u, cand, tl, L, ws.sample, ws.status,
+                                     (const T*)m->w.embed, ws.xs, d.d_model, ws.cs, g, d.head_dim, d.rope_base, s));
+    run_trunk<T>(ctx, m, p, ws, g, ws.xs, nullptr, 0, max_ctx, nullptr, R, C, s);
   }
   launch_scatter_last_rows(ws.xs, ws.x, (int)C, L, d.d_model, s);
   launch_block_sum(tl, out, L, (int)C, s);

@@ -269,6 +269,26 @@ def test_permitted_ids_at_the_edges_of_the_sampling_kernels(limit):
     step.close()
 
 
+@pytest.mark.parametrize("limit", [262144, 262145])
+def test_permitted_ids_at_the_edge_of_the_registers_of_a_thread(limit):
+    """Eight ids a thread stay in registers, more are read twice. An id owns at most about 1e-5 of the uniform's range, logits
+    within the stated 1e-5 move the running sum by a factor of 1 +- 2e-5: together the 3e-5 allowed."""
+    from paper_2506_15733_amd import synthetic
+    wl = small_workload("f32", B=1, n=4, L=2, V=262200, seed=18)
+    step = synthetic.ScoringStep(wl)
+    step.prefill()
+    u = W.rng.uniform_f64(5, "gen/u9", wl.n * wl.L).reshape(1, wl.n, wl.L)
+    u[0, 0, 0], u[0, 1, 0] = 0.0, 1.0 - 2.0 ** -53
+    cand, logp, tok = gpu_generate(step, "draft", u, vocab_limit=limit)
+    assert cand.max() < limit and cand[0, 0, 0] == 0 and cand[0, 1, 0] == limit - 1
+    hw = HostWeights(wl.draft, wl.seed)
+    cache = oracle.prefill(wl.draft, hw, wl.prefix_tokens())[0]
+    p_max = np.zeros((wl.n, wl.L))
+    o_tokens, o_tok, o_blk, _, o_bounds = oracle.generate_blocks(wl.draft, hw, cache, wl.n, wl.L, u[0], vocab_limit=limit, p_max=p_max)
+    assert compare_generation(cand[0], tok[0], logp[0], o_tokens, o_tok, o_blk, o_bounds, u[0], 1e-5, 3e-5, p_max) > 0.7
+    step.close()
+
+
 def test_uniforms_just_below_one_draw_the_last_permitted_id():
     """4097 permitted ids fill 125 of the sampling kernel's 128 chunks, so the total and the running sum of the last
     chunk in use are grouped differently, and with u = 1 - 2^-53 no chunk exceeds u times the total in about one row of
