@@ -705,3 +705,44 @@ def test_float_projections_with_their_norm_and_epilogue(d_model, hq, hkv, hd, ff
     B.specs_commit_block(dm.ctx, dm.model, pf.handle, [0, n - 1])
     check_pages([np.concatenate([t, ids[b, (0, n - 1)[b]]]) for b, t in enumerate(traces)])
     step.close()
+
+
+@pytest.mark.parametrize("dtype,page,hd,L", [("f32", 16, 16, 23), ("f32", 16, 16, 1), ("f32", 4, 8, 16), ("f32", 5, 16, 7),
+                                             ("f32", 1, 16, 3), ("f32", 16, 10, 17), ("bf16", 16, 64, 16),
+                                             ("bf16", 16, 64, 24), ("bf16", 16, 64, 37), ("bf16", 8, 8, 9)])
+def test_commit_puts_blocks_at_any_place_of_a_page(dtype, page, hd, L):
+    """Pieces of 16 bytes where the tokens of a page form whole ones, elements elsewhere: traces that end at a page's end, one
+    token before and behind it, at half a page, and inside the first. Misplaced values are off by their own size; bf16 ones that
+    another product shape rounded differently by less than 2 % of the largest."""
+    from paper_2506_15733_amd import synthetic, binding as B
+    mk = lambda role, head: ModelDesc(role, 2, 3 * hd + (-3 * hd) % 4, 3, 1, hd, 32, 97, dtype, head)
+    wl = Workload("commit", mk("target", "lm"), mk("draft", "lm"), mk("prm", "prm"), B=5, n=2, L=L, prefix_len=0,
+                  lens_range=(33, 40), betas=(1.0,), token_dist="uniform", page_tokens=page, seed=71, u_seed=72)
+    desc, hw = wl.target, HostWeights(wl.target, wl.seed)
+    lens = [32, 31, 33, 40, 7]
+    prefixes = [np.asarray(t)[:n] if n <= len(t) else np.resize(np.asarray(t), n) for t, n in zip(wl.prefix_tokens(), lens)]
+    need = [(n + L + page - 1) // page for n in lens]
+    table = np.full((5, max(need)), -1, np.int32)
+    for b, o in enumerate(np.concatenate([[0], np.cumsum(need)[:-1]])):
+        table[b, :need[b]] = sum(need) - 1 - np.arange(o, o + need[b])
+    stream = torch.cuda.current_stream()
+    dm = synthetic.DeviceModel(desc, "cuda:0", stream, max(5 * 2 * L, 64), 10, wl.seed)
+    pf = synthetic.DevicePrefix(dm, np.asarray(lens, np.int32), table, sum(need), page)
+    B.specs_prefill(dm.ctx, dm.model, pf.handle, torch.from_numpy(np.concatenate(prefixes).astype(np.int32)).to("cuda:0"))
+    cand = wl.candidates()
+    out, tok = torch.zeros((5, 2), device="cuda:0"), torch.zeros((5, 2, L), device="cuda:0")
+    B.specs_score_blocks(dm.ctx, dm.model, pf.handle, torch.from_numpy(cand).to("cuda:0"), out, tok)
+    chosen = [b % 2 for b in range(5)]
+    B.specs_commit_block(dm.ctx, dm.model, pf.handle, chosen)
+    torch.cuda.synchronize()
+    assert B.specs_ctx_status(dm.ctx) == 0
+    pool = pf.kv_pool.double().cpu().numpy()
+    for b, want in enumerate(oracle.prefill(desc, hw, [np.concatenate([t, cand[b, chosen[b]]]) for b, t in enumerate(prefixes)])):
+        pages = table[b, :need[b]]
+        for l in range(2):
+            k = pool[l, 0, pages].reshape(-1, 1, page, hd).transpose(0, 2, 1, 3).reshape(-1, 1, hd)[:want.length]
+            v = pool[l, 1, pages].reshape(-1, 1, hd, page).transpose(0, 3, 1, 2).reshape(-1, 1, hd)[:want.length]
+            for got, exp in ((k, want.K[l]), (v, want.V[l])):
+                assert np.abs(got - exp).max() < (1e-5 if dtype == "f32" else 2e-2) * max(1.0 if dtype == "f32" else 0.0, np.abs(exp).max()), (b, l)
+    pf.close()
+    dm.close()
