@@ -1,27 +1,22 @@
 // bf16 MFMA GEMM for gfx950: C[M,N] = A[M,K] * W[N,K]^T, float accumulation, K % 64 == 0.
 //
-// Block tile 256 x 256 x 64 (smaller ones for smaller products, see the ring further down), 512 threads = 8 wavefronts
-// laid out 2 (M) x 4 (N); every wavefront owns a 128 x 64 patch as 4 x 2 accumulators of
-// v_mfma_f32_32x32x16_bf16. Operand tiles go global -> LDS directly (16 bytes per lane,
-// no register staging) into a ring of five 32 KiB slots: two being multiplied, three in flight.
-// Wavefronts issue in order and the vector-memory queue is short, so the eight loads a wavefront
-// contributes per k-step are dealt over the k-step's four MFMA groups, one load between MFMAs,
-// instead of one burst; the k-loop is unrolled by the ring length so that slot addresses are
-// constants. LDS rows are 128 bytes (64 bf16); the 16-byte chunk c of row r is stored at
-// chunk position c ^ ((r >> 1) & 7) so that the 32 rows a fragment read touches spread over all
-// banks. Workgroup ids are dealt round-robin to the 8 XCDs by the hardware; the id -> tile map
+// Block tiles of 256 or 128 rows x 256 columns, where two rows of wavefronts take turns at the matrix cores and at moving
+// operands, or narrower ones with a ring of whole K-tiles for smaller products. All multiply with v_mfma_f32_16x16x32_bf16.
+// Operand tiles go global -> LDS directly (16 bytes per lane, no register staging). LDS rows are 128 bytes (64 bf16); the
+// 16-byte chunk c of row r is stored at chunk position c ^ ((r >> 1) & 7) so that the 16 rows a fragment read touches
+// spread over all banks. Workgroup ids are dealt round-robin to the 8 XCDs by the hardware; the id -> tile map
 // below keeps the M-tiles of one N-tile on one XCD, so a weight tile is fetched from HBM once
 // and re-used out of that XCD's L2 by workgroups that walk through K in step.
 //
 // Epilogues: plain float store; residual add into the float stream; SwiGLU (gate/up columns
 // interleaved in groups of 32 so that a lane holds gate and up of the same unit) with bf16
-// output; vocabulary head: per-row (max, sum exp) over the tile's 256 columns plus the logit of
-// the row's target token, so that logits never reach memory.
+// output; QKV projection: rotary embedding, conversion and the layouts of attention; vocabulary head: per-row (max, sum exp)
+// over the tile's 256 columns plus the logit of the row's target token, so that logits never reach memory.
 #include "common.h"
 #include <type_traits>
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 #define LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 #define GLB_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
@@ -86,6 +81,15 @@ __device__ __forceinline__ float half_wave_sum(float v) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+// the same of lane l and of lane l ^ 16 (v_permlane16_swap: odd rows of 16 lanes against even ones)
+__device__ __forceinline__ float quarter_wave_max(float v) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float quarter_wave_sum(float v) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 
 // Workgroup -> (K slice, m_tile, n_tile): ids congruent mod 8 share an XCD. The tile list goes through bands of 32 N-tiles,
 // in a band through blocks of 8 M-tiles, in a block through sub-bands of 4 N-tiles, so that 32 consecutive entries are
@@ -121,287 +125,86 @@ __device__ __forceinline__ bool tile_of(int block, int m_tiles, int n_tiles, int
 }
 static int tile_grid(int total) { return 8 * (32 * (total / 256) + (total % 256 + 7) / 8); }
 
-// The BM x BN tile of the product at (m0, n0), K slice kslice.
-// HD128 (ME_QKV_ROPE only): head_dim 128 instead of 64. part: ME_LMHEAD, the tile's entry in a row of part_max.
-template <int BM, int BN, int NWM, int S, int EPI, bool HD128>
-__device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
-  constexpr int NWN = BN / 64;
-  // Rotary pairs are columns (i, i + hd/2) of a head. With head_dim 64 a wavefront's 64 columns are one head and
-  // its two accumulator columns the two halves. With head_dim 128 a head spans two wavefronts, so the W tile is
-  // loaded with rows 32..63 and 64..95 of every 128 exchanged: wavefront (head, wq) then holds columns
-  // wq*32 .. +31 of the first half in accumulator column 0 and the same columns of the second half in column 1.
-  constexpr bool SWAP = EPI == ME_QKV_ROPE && HD128;
-  constexpr int NW = NWM * NWN;                       // wavefronts: NWM along M x NWN along N
-  constexpr int WM = BM / NWM, TM = WM / 32, WN = BN / NWN, TN = WN / 32;
-  // All epilogues multiply W-fragment x A-fragment, i.e. the transposed 32x32 product: a lane then holds runs of
-  // four consecutive COLUMNS of one row of C. The storing epilogues write them as one 16-byte (8-byte bf16) piece
-  // (four times fewer store instructions than with single elements of four rows), and the vocabulary head reduces
-  // its rows inside the lane instead of across lanes.
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int wm = wave / NWN, wn = wave % NWN;
-  const int lrow = lane & 31, lhalf = lane >> 5;
-
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  // K-tiles [kt0, kt0 + KT) of this workgroup's K slice
-  const int kt0 = (int)((long)kslice * (a.K / 64) / a.ksplit);
-  const int KT = (int)((long)(kslice + 1) * (a.K / 64) / a.ksplit) - kt0;
-  auto mma = [&](const bf16x8 (&af)[TM], const bf16x8 (&bfr)[TN]) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
-  };
-  constexpr int LA = (BM / 8 + NW - 1) / NW, LB = (BN / 8 + NW - 1) / NW;   // direct-to-LDS loads per thread per operand tile
-  constexpr int NLD = LA + LB;
-  auto share_size = [](int sh) { int c = 0; for (int j = 0; j < NLD; ++j) c += (j * 4 / NLD == sh); return c; };
-  constexpr int S0 = share_size(0), S1 = share_size(1), S2 = share_size(2), S3 = share_size(3);
-#define SGB __builtin_amdgcn_sched_group_barrier
-#define PIPE_GROUP_ORDER(NLOADS)                                                                                   \
-  SGB(0x008, 2, 0);                                                                                                \
-  SGB(0x100, TM + TN, 0);                                                                                          \
-  if (NLOADS == 1) { SGB(0x008, 3, 0); SGB(0x010, 1, 0); SGB(0x008, TM * TN - 5, 0); }                             \
-  else if (NLOADS == 2) { SGB(0x008, 1, 0); SGB(0x010, 1, 0); SGB(0x008, 3, 0); SGB(0x010, 1, 0); SGB(0x008, TM * TN - 6, 0); } \
-  else SGB(0x008, TM * TN - 2, 0);                                                                                 \
-  __builtin_amdgcn_sched_barrier(0)
-
-  if constexpr (BM == 256) {
-  // LDS ring of five slots; a slot holds one operand tile (A: BM x 64, W: 256 x 64). K-tile t uses slot 2t for
-  // W and slot 2t+1 for A (mod 5), so besides the two slots being multiplied three are in flight: the weights,
-  // which stream from HBM, are requested about two K-tiles ahead, the activations about one.
-  constexpr int SLOT = 256 * 128;
-  // phase = K-tile index mod 5; the k-loop is unrolled five times so that every slot address is a constant
-  auto wslot = [&](int ph) { return smem + ((2 * ph) % 5) * SLOT; };
-  auto aslot = [&](int ph) { return smem + ((2 * ph + 1) % 5) * SLOT; };
-  auto read_frags = [&](int ph, int ks, bf16x8 (&af)[TM], bf16x8 (&bfr)[TN]) {
-    const char* As = aslot(ph);
-    const char* Bs = wslot(ph);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) af[i] = lds_frag(As, wm * WM + i * 32 + lrow, ks * 2 + lhalf);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bfr[j] = lds_frag(Bs, wn * WN + j * 32 + lrow, ks * 2 + lhalf);
-  };
-  auto issue_w = [&](int t) {                           // prologue only: t < 5 is its own phase
-    const int src = t < KT ? t : KT - 1;
-#pragma unroll
-    for (int i = 0; i < LB; ++i) load_span_async<NW, BN / 8, SWAP>(a.W, n0, a.N, a.K, (kt0 + src) * 64, wslot(t), i, wave);
-  };
-  auto issue_a = [&](int t) {
-    const int src = t < KT ? t : KT - 1;
-#pragma unroll
-    for (int i = 0; i < LA; ++i) load_span_async<NW, BM / 8>(a.A, m0, a.M, a.K, (kt0 + src) * 64, aslot(t), i, wave);
-  };
-  static_assert(LB == 4 && (S0 == 2) && S1 <= 2 && S2 <= 2 && S3 <= 2, "the waits below are written for these counts");
-  // share SH of the loads of A-tile ta (phase pa) and W-tile tw (phase pw)
-  auto issue_share = [&](int ta, int pa, int tw, int pw, auto share) {
-    constexpr int SH = decltype(share)::value;
-    const int sa = ta < KT ? ta : KT - 1, sw = tw < KT ? tw : KT - 1;   // past the end: redundant loads into free slots
-#pragma unroll
-    for (int j = 0; j < NLD; ++j) {
-      if (j * 4 / NLD != SH) continue;
-      if (j < LA) load_span_async<NW, BM / 8>(a.A, m0, a.M, a.K, (kt0 + sa) * 64, aslot(pa), j, wave);
-      else load_span_async<NW, BN / 8, SWAP>(a.W, n0, a.N, a.K, (kt0 + sw) * 64, wslot(pw), j - LA, wave);
-    }
-  };
-  issue_w(0); issue_a(0); issue_w(1);
-  issue_share(1, 1, 2, 2, std::integral_constant<int, 0>{});
-  asm volatile("s_waitcnt vmcnt(6)\n\ts_barrier" ::: "memory");
-  bf16x8 a0[TM], b0[TN], a1[TM], b1[TN];
-  read_frags(0, 0, a0, b0);
-  auto step = [&](auto phase, int kt) {
-    constexpr int P = decltype(phase)::value;
-    constexpr int P1 = (P + 1) % 5, P2 = (P + 2) % 5, P3 = (P + 3) % 5;
-    read_frags(P, 1, a1, b1);
-    issue_share(kt + 1, P1, kt + 2, P2, std::integral_constant<int, 1>{});
-    mma(a0, b0);
-    PIPE_GROUP_ORDER(S1);
-    read_frags(P, 2, a0, b0);
-    issue_share(kt + 1, P1, kt + 2, P2, std::integral_constant<int, 2>{});
-    mma(a1, b1);
-    PIPE_GROUP_ORDER(S2);
-    read_frags(P, 3, a1, b1);
-    issue_share(kt + 1, P1, kt + 2, P2, std::integral_constant<int, 3>{});
-    mma(a0, b0);
-    PIPE_GROUP_ORDER(S3);
-    asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    issue_share(kt + 2, P2, kt + 3, P3, std::integral_constant<int, 0>{});
-    read_frags(P1, 0, a0, b0);                         // after the last K-tile: a read of a free slot, never used
-    mma(a1, b1);
-    PIPE_GROUP_ORDER(S0);
-  };
-  for (int kt = 0;;) {
-    step(std::integral_constant<int, 0>{}, kt); if (++kt >= KT) break;
-    step(std::integral_constant<int, 1>{}, kt); if (++kt >= KT) break;
-    step(std::integral_constant<int, 2>{}, kt); if (++kt >= KT) break;
-    step(std::integral_constant<int, 3>{}, kt); if (++kt >= KT) break;
-    step(std::integral_constant<int, 4>{}, kt); if (++kt >= KT) break;
-  }
-  } else {
-    // Small tiles (few rows, or few tiles for 256 CUs): the k-step is bound by the latency of the operand loads, not
-    // by the matrix pipe, so the ring holds S whole K-tiles and S-1 of them are in flight, activations as far ahead
-    // as weights. (With the five-slot ring above the activations are requested one K-tile ahead only: 1.1 - 1.75 us a
-    // k-step at 128 rows x 256 columns, most of it waiting.)
-    constexpr int STG = (BM + BN) * 128;
-    auto read_frags = [&](const char* st, int ks, bf16x8 (&af)[TM], bf16x8 (&bfr)[TN]) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i) af[i] = lds_frag(st, wm * WM + i * 32 + lrow, ks * 2 + lhalf);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) bfr[j] = lds_frag(st + BM * 128, wn * WN + j * 32 + lrow, ks * 2 + lhalf);
-    };
-    auto issue_share = [&](int t, char* st, auto share) {   // share SH of 4 of the loads of K-tile t (4: all of them)
-      constexpr int SH = decltype(share)::value;
-#pragma unroll
-      for (int j = 0; j < NLD; ++j) {
-        if (SH < 4 && j * 4 / NLD != SH) continue;
-        if (j < LA) load_span_async<NW, BM / 8>(a.A, m0, a.M, a.K, (kt0 + t) * 64, st, j, wave);
-        else load_span_async<NW, BN / 8, SWAP>(a.W, n0, a.N, a.K, (kt0 + t) * 64, st + BM * 128, j - LA, wave);
-      }
-    };
-    // own loads of all but the newest `ahead` K-tiles have landed and own fragment reads are done, then everybody's
-    auto wait_ahead = [&](int ahead) {
-      static_assert(S <= 6 && (S - 2) * NLD < 63, "the counts below");
-      if (ahead >= 4) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(4 * NLD) : "memory");
-      else if (ahead == 3) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(3 * NLD) : "memory");
-      else if (ahead == 2) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(2 * NLD) : "memory");
-      else if (ahead == 1) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NLD) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    };
-#define RING_GROUP_ORDER(NLOADS)                                                                     \
-  SGB(0x100, TM + TN, 0);                                                                            \
-  SGB(0x008, 1, 0);                                                                                  \
-  if (NLOADS) { SGB(0x010, NLOADS, 0); }                                                             \
-  SGB(0x008, TM * TN - 1, 0);                                                                        \
-  __builtin_amdgcn_sched_barrier(0)
-#define ALL_LOADS std::integral_constant<int, 4>{}
-#pragma unroll
-    for (int t = 0; t < S - 1; ++t)
-      if (t < KT) issue_share(t, smem + t * STG, ALL_LOADS);
-#undef ALL_LOADS
-    wait_ahead(KT - 1 < S - 2 ? KT - 1 : S - 2);
-    bf16x8 a0[TM], b0[TN], a1[TM], b1[TN];
-    const char* cur = smem;                              // slot of K-tile kt; the tile S-1 further on goes to the slot
-    char* free_slot = smem + (S - 1) * STG;              // that K-tile kt-1 was read from before the last barrier
-    read_frags(cur, 0, a0, b0);
-    auto step = [&](int kt, auto load) {
-      constexpr bool LOAD = decltype(load)::value;
-      const char* nxt = cur + STG == smem + S * STG ? smem : cur + STG;
-      if (LOAD) issue_share(kt + S - 1, free_slot, std::integral_constant<int, 0>{});
-      read_frags(cur, 1, a1, b1);
-      if (LOAD) issue_share(kt + S - 1, free_slot, std::integral_constant<int, 1>{});
-      mma(a0, b0);
-      RING_GROUP_ORDER((LOAD ? S0 + S1 : 0));
-      read_frags(cur, 2, a0, b0);
-      if (LOAD) issue_share(kt + S - 1, free_slot, std::integral_constant<int, 2>{});
-      mma(a1, b1);
-      RING_GROUP_ORDER((LOAD ? S2 : 0));
-      read_frags(cur, 3, a1, b1);
-      if (LOAD) issue_share(kt + S - 1, free_slot, std::integral_constant<int, 3>{});
-      mma(a0, b0);
-      RING_GROUP_ORDER((LOAD ? S3 : 0));
-      if (LOAD) wait_ahead(S - 2);
-      else wait_ahead(KT - 2 - kt);
-      if (LOAD || kt + 1 < KT) read_frags(nxt, 0, a0, b0);
-      mma(a1, b1);
-      RING_GROUP_ORDER(0);
-      free_slot = (char*)cur;
-      cur = nxt;
-    };
-    int kt = 0;
-    for (; kt + S - 1 < KT; ++kt) step(kt, std::true_type{});
-    for (; kt < KT; ++kt) step(kt, std::false_type{});
-  }
-#undef RING_GROUP_ORDER
-#undef PIPE_GROUP_ORDER
-#undef SGB
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-
-  // accumulator element r of a lane: row lrow, column 8*(r/4) + 4*lhalf + r%4 of the 32x32 tile
-  if (EPI == ME_STORE || EPI == ME_RESIDUAL) {
+// ---- epilogues ----
+// An accumulator [i][j] of a wavefront is a 16x16 tile of the TRANSPOSED product (the W fragment is the first MFMA operand):
+// lane l holds columns 4 (l / 16) .. + 3 of row l % 16. The storing epilogues write them as one 16-byte (8-byte bf16) piece,
+// and the vocabulary head reduces most of a row inside the lane. m, n: first row and column of the wavefront's part.
+// part: ME_LMHEAD, the tile's entry in a row of part_max.
+template <int BM, int BN, int NWM, int EPI, bool HD128, int TM>
+__device__ __forceinline__ void epilogue(const GemmArgs& a, floatx4 (&acc)[TM][4], int m0, int n0, int wm, int wn, int kslice, int part,
+                                         char* smem) {
+  constexpr int NWN = BN / 64, NW = NWM * NWN, TN = 4;
+  const int lane = threadIdx.x & 63, r16 = lane & 15, quad = lane >> 4;
+  const int m = m0 + wm * 16 * TM, n = n0 + wn * 64;
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  // one decision for the workgroup: a tile inside the matrix stores without per-piece bounds checks
+  const bool inside = m0 + BM <= a.M && n0 + BN <= a.N;
+  if constexpr (EPI == ME_STORE || EPI == ME_RESIDUAL) {
     float* __restrict__ Cs = a.C + (size_t)kslice * a.M * a.N;
-    // PIECES: 16 bytes at a time, aligned and wholly inside a row or outside. One decision for the workgroup: a tile inside
-    // the matrix stores without bounds checks. (Where a check per piece chooses between 16 bytes and elements, the compiler
-    // splits the pieces to share a tail: 256 x 131072 x 1536 152 us instead of 134.)
+    // PIECES: 16 bytes at a time, aligned and wholly inside a row or outside. (Where a check per piece chooses between 16 bytes
+    // and elements, the compiler splits the pieces to share a tail: 256 x 131072 x 1536 152 us instead of 134.)
     auto emit = [&](auto pieces, auto checked) {
       constexpr bool PIECES = decltype(pieces)::value, CHECK = decltype(checked)::value;
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const int row = m0 + wm * WM + i * 32 + lrow;
+        const int row = m + i * 16 + r16;
         if (CHECK && row >= a.M) continue;
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < TN; ++j) {
+          const int col = n + j * 16 + 4 * quad;
+          float* dst = Cs + (size_t)row * a.N + col;
+          if constexpr (PIECES) {
+            if (CHECK && col >= a.N) continue;
+            floatx4 v = acc[i][j];
+            if (EPI == ME_RESIDUAL) v += *(const floatx4*)dst;
+            *(floatx4*)dst = v;
+          } else {
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int col = n0 + wn * WN + j * 32 + 8 * g + 4 * lhalf;
-            float* dst = Cs + (size_t)row * a.N + col;
-            if constexpr (PIECES) {
-              if (CHECK && col >= a.N) continue;
-              float4 v = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-              if (EPI == ME_RESIDUAL) {
-                float4 o = *(const float4*)dst;
-                v.x += o.x; v.y += o.y; v.z += o.z; v.w += o.w;
+            for (int e = 0; e < 4; ++e)
+              if (col + e < a.N) {
+                if (EPI == ME_RESIDUAL) dst[e] += acc[i][j][e];
+                else dst[e] = acc[i][j][e];
               }
-              *(float4*)dst = v;
-            } else {
-#pragma unroll
-              for (int e = 0; e < 4; ++e)
-                if (col + e < a.N) {
-                  if (EPI == ME_RESIDUAL) dst[e] += acc[i][j][4 * g + e];
-                  else dst[e] = acc[i][j][4 * g + e];
-                }
-            }
           }
+        }
       }
     };
     if ((a.N & 3) != 0 || ((uintptr_t)a.C & 15) != 0) emit(std::false_type{}, std::true_type{});
-    else if (m0 + BM <= a.M && n0 + BN <= a.N) emit(std::true_type{}, std::false_type{});
+    else if (inside) emit(std::true_type{}, std::false_type{});
     else emit(std::true_type{}, std::true_type{});
-  } else if (EPI == ME_SWIGLU) {
+  } else if constexpr (EPI == ME_SWIGLU) {
     const int F = a.N >> 1;                            // a multiple of 32: whole 4-unit pieces
-    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-    // one decision for the workgroup: a tile inside the matrix stores without per-piece bounds checks
-    const bool inside = m0 + BM <= a.M && n0 + BN <= a.N;
     auto emit = [&](auto checked) {
       constexpr bool CHECK = decltype(checked)::value;
 #pragma unroll
-      for (int jp = 0; jp < TN / 2; ++jp) {            // accumulator pair (2jp, 2jp+1) = gate, up of 32 units
+      for (int i = 0; i < TM; ++i) {
+        const int row = m + i * 16 + r16;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const int row = m0 + wm * WM + i * 32 + lrow;
+        for (int j = 0; j < TN / 2; ++j) {             // columns 0..31 of the part are gates, 32..63 the same units' ups
+          const int unit = (n >> 1) + j * 16 + 4 * quad;
+          bf16x4 o;
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int unit = ((n0 + wn * WN + jp * 64) >> 1) + 8 * g + 4 * lhalf;
-            bf16x4 o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              float gt = acc[i][2 * jp][4 * g + e], u = acc[i][2 * jp + 1][4 * g + e];
-              // v_rcp_f32 (1 ulp) instead of an IEEE division: the quotient is rounded to bf16 right away, and the
-              // division's scale/fix-up sequence alone was ten instructions per value
-              o[e] = (__bf16)(gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * u);
-            }
-            if (!CHECK || (row < a.M && unit < F)) *(bf16x4*)(a.act + (size_t)row * F + unit) = o;
+          for (int e = 0; e < 4; ++e) {
+            const float gt = acc[i][j][e], u = acc[i][j + TN / 2][e];
+            // v_rcp_f32 (1 ulp) instead of an IEEE division: the quotient is rounded to bf16 right away, and the
+            // division's scale/fix-up sequence alone was ten instructions per value
+            o[e] = (__bf16)(gt * __builtin_amdgcn_rcpf(1.0f + __expf(-gt)) * u);
           }
+          if (!CHECK || (row < a.M && unit < F)) *(bf16x4*)(a.act + (size_t)row * F + unit) = o;
         }
       }
     };
     if (inside) emit(std::false_type{});
     else emit(std::true_type{});
-  } else if (EPI == ME_QKV_ROPE) {
-    static_assert(EPI != ME_QKV_ROPE || TN == 2, "one rotary half per accumulator column");
-    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  } else if constexpr (EPI == ME_QKV_ROPE) {
+    // columns 0..31 of the part: 32 pairs' first elements, 32..63 their second ones
     constexpr int HDIM = HD128 ? 128 : 64, HALF = HDIM / 2;
     const int head = HD128 ? (n0 >> 7) + (wn >> 1) : (n0 >> 6) + wn;
-    const int i_base = (HD128 ? (wn & 1) * 32 : 0) + 4 * lhalf;          // + 8 g + e: index of the pair inside the head
+    const int i_base = (HD128 ? (wn & 1) * 32 : 0) + 4 * quad;           // + 16 j + e: index of the pair inside the head
     if (head < a.Hq + 2 * a.Hkv) {
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
-        const int row = m0 + wm * WM + i * 32 + lrow;
+        const int row = m + i * 16 + r16;
         const int cand = row / a.Lrows, t = row - cand * a.Lrows;
         if (head < a.Hq + a.Hkv) {
           if (row >= a.M) continue;
@@ -409,14 +212,14 @@ __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, 
           bf16_t* dst = head < a.Hq ? a.q + ((size_t)row * a.Hq + head) * HDIM
                                     : a.kblk + ((size_t)row * a.Hkv + (head - a.Hq)) * HDIM;
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const int i0 = i_base + 8 * g;
+          for (int j = 0; j < 2; ++j) {
+            const int i0 = i_base + 16 * j;
             const float4 cn = *(const float4*)(cs + i0), sn = *(const float4*)(cs + HALF + i0);
             const float c4[4] = {cn.x, cn.y, cn.z, cn.w}, s4[4] = {sn.x, sn.y, sn.z, sn.w};
             bf16x4 y1, y2;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              const float2 y = rotate_pair(acc[i][0][4 * g + e], acc[i][1][4 * g + e], c4[e], s4[e]);
+              const float2 y = rotate_pair(acc[i][j][e], acc[i][2 + j][e], c4[e], s4[e]);
               y1[e] = (__bf16)y.x;
               y2[e] = (__bf16)y.y;
             }
@@ -424,23 +227,23 @@ __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, 
             *(bf16x4*)(dst + HALF + i0) = y2;
           }
         } else {
-          // values: not rotated, stored transposed; the 32 lanes of a half-wave write 32 consecutive positions
+          // values: not rotated, stored transposed; 16 lanes write 16 consecutive positions
           bf16_t* head_v = a.vT + (size_t)(head - a.Hq - a.Hkv) * HDIM * a.Lp;
           const size_t cand_v = (size_t)a.Hkv * HDIM * a.Lp;
           if (row < a.M) {
             bf16_t* dst = head_v + cand * cand_v + t;
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
+            for (int j = 0; j < 2; ++j)
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
-                const int d = i_base + 8 * g + e;
-                dst[(size_t)d * a.Lp] = (__bf16)acc[i][0][4 * g + e];
-                dst[(size_t)(HALF + d) * a.Lp] = (__bf16)acc[i][1][4 * g + e];
+                const int d = i_base + 16 * j + e;
+                dst[(size_t)d * a.Lp] = (__bf16)acc[i][j][e];
+                dst[(size_t)(HALF + d) * a.Lp] = (__bf16)acc[i][2 + j][e];
               }
           }
           // The positions that pad a candidate's block to whole 16s: the wavefront that holds its last row clears them, a
-          // lane per column (the two lanes of that row on their own took 32 stores a position).
-          unsigned ends = (unsigned)__ballot(row < a.M && t == a.Lrows - 1 && a.Lp > a.Lrows);
+          // lane per column (the lanes of that row on their own took 32 stores a position).
+          unsigned ends = (unsigned)(__ballot(row < a.M && t == a.Lrows - 1 && a.Lp > a.Lrows) & 0xffff);
           while (ends) {
             const int of = __builtin_amdgcn_readlane(cand, __builtin_ctz(ends));
             ends &= ends - 1;
@@ -455,41 +258,40 @@ __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, 
     __syncthreads();                                   // every wavefront is done with the operand tiles
     float* red_max = (float*)smem;                     // [BM][NWN]
     float* red_sum = red_max + BM * NWN;
-    // A lane owns row lrow of each of its TM row tiles and, of the wavefront's WN columns, the 16 * TN with
-    // (column / 4) % 2 == lhalf: maximum and sum of exponentials run over the lane's own registers, one exchange
-    // joins the two half-waves, and the row's target column is looked for among the same registers.
+    // A lane owns, of row r16 of each of its TM row tiles, the 16 columns with (column / 4) % 4 == quad: maximum and sum of
+    // exponentials run over the lane's own registers, two exchanges join the four lanes of a row, and the row's target column
+    // is looked for among the same registers.
     const bool ragged = n0 + BN > a.N;                 // only the last N-tile has columns beyond the matrix
-    const int cbase = n0 + wn * WN + 4 * lhalf;        // column of element (j, r): cbase + 32 j + 8 (r / 4) + r % 4
+    const int cbase = n + 4 * quad;                    // column of element (j, e): cbase + 16 j + e
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const int lr = wm * WM + i * 32 + lrow, row = m0 + lr;
+      const int lr = wm * 16 * TM + i * 16 + r16, row = m0 + lr;
       const int target = row < a.M ? a.tok[row] : -1;
       float mx = -INFINITY;
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          if (ragged && cbase + 32 * j + 8 * (r >> 2) + (r & 3) >= a.N) acc[i][j][r] = -INFINITY;
-          mx = fmaxf(mx, acc[i][j][r]);
+        for (int e = 0; e < 4; ++e) {
+          if (ragged && cbase + 16 * j + e >= a.N) acc[i][j][e] = -INFINITY;
+          mx = fmaxf(mx, acc[i][j][e]);
         }
-      mx = half_wave_max(mx);
-      // the target's offset among this lane's columns; element (j, r) sits at 32 j + 8 (r / 4) + r % 4
-      const int d = target - cbase;
+      mx = half_wave_max(quarter_wave_max(mx));
+      const int d = target - cbase;                    // the target's offset among this lane's columns
       float sm = 0.f, zt = 0.f;
       bool hit = false;
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float v = acc[i][j][r];
+        for (int e = 0; e < 4; ++e) {
+          const float v = acc[i][j][e];
           sm += mx == -INFINITY ? 0.f : __expf(v - mx);
-          const bool here = d == 32 * j + 8 * (r >> 2) + (r & 3);
+          const bool here = d == 16 * j + e;
           zt = here ? v : zt;
           hit |= here;
         }
-      sm = half_wave_sum(sm);
+      sm = half_wave_sum(quarter_wave_sum(sm));
       if (hit) a.zt[row] = zt;
-      if (lhalf == 0) {
+      if (quad == 0) {
         red_max[lr * NWN + wn] = mx;
         red_sum[lr * NWN + wn] = sm;
       }
@@ -510,6 +312,318 @@ __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, 
       }
     }
   }
+}
+
+// Rotary pairs are columns (i, i + hd/2) of a head. With head_dim 64 a wavefront's 64 columns are one head, the first 32 of
+// them one half of its pairs. With head_dim 128 a head spans two wavefronts, so the W tile is loaded with rows 32..63 and
+// 64..95 of every 128 exchanged: wavefront (head, wq) then holds columns wq*32 .. +31 of the first half in its first 32
+// columns and the same columns of the second half in the others.
+__device__ __forceinline__ constexpr int swap56(int row) { return (row & ~0x60) | ((row & 0x20) << 1) | ((row & 0x40) >> 1); }
+
+// K-tiles [kt0, kt0 + KT) of K slice kslice
+__device__ __forceinline__ void slice_tiles(const GemmArgs& a, int kslice, int& kt0, int& KT) {
+  kt0 = (int)((long)kslice * (a.K / 64) / a.ksplit);
+  KT = (int)((long)(kslice + 1) * (a.K / 64) / a.ksplit) - kt0;
+}
+
+// Barriers of a workgroup, in which no instruction moves across. LANDED_AND_MEET: own LDS reads are done before it (their
+// place may be overwritten after it), and own loads but the newest n have landed. The compiler is told of the wait, as it
+// would otherwise wait for these reads, and all later ones with them, where they are used.
+#define MEET()                            \
+  __builtin_amdgcn_sched_barrier(0);      \
+  asm volatile("s_barrier" ::: "memory"); \
+  __builtin_amdgcn_sched_barrier(0)
+#define LANDED_AND_MEET(n)                                          \
+  asm volatile("" ::: "memory");                                    \
+  __builtin_amdgcn_sched_barrier(0);                                \
+  __builtin_amdgcn_s_waitcnt(((n) & 15) | ((n) >> 4) << 14 | 0x70); \
+  MEET()
+
+// The BM x 256 tile (BM 256 or 128) of the product at (m0, n0), K slice kslice, by eight wavefronts 2 (M) x 4 (N).
+//
+// The two rows of wavefronts, one wavefront of each on every SIMD, run half a phase apart: while one multiplies (16 MFMAs, 64
+// rows x 32 columns x 64 deep of its part), the other reads the fragments of its next phase from LDS and requests operands,
+// and a barrier changes the roles. Reads, address arithmetic and the wait for a place in the memory queue then stand beside
+// the other wavefront's MFMAs instead of in front of the own ones. (One loop for all wavefronts with loads and reads dealt
+// between the MFMAs and a barrier per K-tile, us: 16384 x 37888 x 3584 3360, 8192 x 8192 x 8192 798, 2048 x 37888 x 3584
+// 473, so: 2920, 695, 399, i.e. 1.52, 1.58 and 1.39 PFLOP/s. With 32x32x16 MFMAs: 3183, 764, 423: they move twice as much
+// of the accumulators per flop, and the clock of a power-limited part shows it. A phase of 32 MFMAs, 64 x 64: 2962, 703, 400.)
+//
+// Every phase reads one piece of an operand tile and frees its place in the LDS ring a phase later, so the ring is filled
+// piece by piece, as far ahead as it goes: BM = 256: 16 KiB halves in the order A0 W1 A1 W0', one per phase (half 0, 1 of A: rows 0..63, 64..127 of
+// each row of wavefronts, half 0, 1 of W: columns 0..31, 32..63 of each wavefront; ' the next K-tile's), ten of them in
+// 160 KiB, i.e. nearly two and a half K-tiles. BM = 128: A | W1 W0' in two phases, three K-tiles in 144 KiB.
+// Operands are requested through buffer descriptors whose size ends with the matrix: rows beyond it, and K-tiles beyond the
+// slice (size 0), are zeros that cost no traffic.
+template <int BM, int EPI, bool HD128>
+__device__ __forceinline__ void wide_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
+  static_assert(BM == 256 || BM == 128, "two halves of A, or one");
+  constexpr bool SWAP = EPI == ME_QKV_ROPE && HD128;
+  constexpr int NH = BM / 128, TM = 4 * NH, U = 8192;    // U: what one load of every wavefront fills
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wm = wave >> 2, wn = wave & 3, r16 = lane & 15, quad = lane >> 4;
+  int kt0, KT;
+  slice_tiles(a, kslice, kt0, KT);
+
+  floatx4 acc[TM][4];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+  // Offsets of the 16 bytes that this lane requests. A half is 128 LDS rows in 16 spans of 8; a wavefront fills spans `wave`
+  // and 8 + wave. All of a row is in the vector offset, which the bounds check covers; the scalar offset advances along K.
+  const bf16_t *Ab = a.A + (size_t)m0 * a.K + kt0 * 64, *Wb = a.W + (size_t)n0 * a.K + kt0 * 64;
+  const unsigned row_bytes = (unsigned)a.K * 2u;
+  const unsigned a_size = (unsigned)min(a.M - m0, BM) * row_bytes - kt0 * 128, w_size = (unsigned)min(a.N - n0, 256) * row_bytes - kt0 * 128;
+  unsigned aoff[NH][2], woff[2][2];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    const int r = (p * 8 + wave) * 8 + (lane >> 3);
+    const unsigned chunk = ((lane & 7) ^ ((r >> 1) & 7)) * 16;
+#pragma unroll
+    for (int h = 0; h < NH; ++h) aoff[h][p] = (unsigned)((r >> 6) * 64 * NH + h * 64 + (r & 63)) * row_bytes + chunk;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int c = (r >> 5) * 64 + h * 32 + (r & 31);
+      woff[h][p] = (unsigned)(SWAP ? swap56(c) : c) * row_bytes + chunk;
+    }
+  }
+  // Unit p of half h of A (W) of K-tile t, to unit `slot` of the ring
+  auto load_a = [&](int h, int p, int slot, int t) {
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)Ab, 0, t < KT ? a_size : 0u, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(smem + slot * U + wave * 1024), 16, aoff[h][p], t * 128, 0, 0);
+  };
+  auto load_w = [&](int h, int p, int slot, int t) {
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)Wb, 0, t < KT ? w_size : 0u, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(smem + slot * U + wave * 1024), 16, woff[h][p], t * 128, 0, 0);
+  };
+
+  // A fragment is 16 rows x 32 of K: lane l has row l % 16, chunk l / 16 (of 4; chunks 4..7 are the second 32). The rows of a
+  // lane's fragments differ by multiples of 16, so they share their swizzle.
+  const int sw = (r16 >> 1) & 7, c0 = (quad ^ sw) << 4, c1 = c0 ^ 64;
+  const int abase = (wm * 64 + r16) * 128, bbase = (wn * 32 + r16) * 128;
+  bf16x8 af[4][2], b0[2][2], b1[2][2];
+  auto read_a = [&](int slot) {
+    const char* p = smem + slot * U + abase;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      af[i][0] = *(const bf16x8*)(p + i * 2048 + c0);
+      af[i][1] = *(const bf16x8*)(p + i * 2048 + c1);
+    }
+  };
+  auto read_w = [&](int slot, bf16x8 (&b)[2][2]) {
+    const char* p = smem + slot * U + bbase;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      b[j][0] = *(const bf16x8*)(p + j * 2048 + c0);
+      b[j][1] = *(const bf16x8*)(p + j * 2048 + c1);
+    }
+  };
+  auto mma = [&](int hm, int hn, const bf16x8 (&b)[2][2]) {
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[hm * 4 + i][hn * 2 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j][kk], af[i][kk], acc[hm * 4 + i][hn * 2 + j], 0, 0, 0);
+  };
+  if constexpr (BM == 256) {
+    // Position s of the stream of halves: s = 0 is W0 of K-tile 0; of K-tile t A0 is 4t + 1, W1 4t + 2, A1 4t + 3 and the next
+    // one's W0 4t + 4. Phase s reads half s. Its first part requests half s + 9, in the place of half s - 1, which
+    // the later row of wavefronts has read in the first part of phase s - 1; eight halves are newer than the next one read.
+    auto load_half = [&](int s, int t) {                 // s modulo 20, t the K-tile that the half belongs to
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        if (s & 1) load_a((s & 3) >> 1, p, s % 10 * 2 + p, t);
+        else load_w((s & 3) >> 1, p, s % 10 * 2 + p, t);
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < 9; ++s) load_half(s, s >> 2);
+    LANDED_AND_MEET(14);                                         // s = 0 and 1
+    load_half(9, 2);
+    read_w(0, b0);
+    LANDED_AND_MEET(16);
+    if (wm == 1) { MEET(); }
+    auto step = [&](auto phase, int t) {
+      constexpr int S = decltype(phase)::value * 4;      // 4t modulo 20
+      read_a((S + 1) % 10 * 2);
+      load_half(S + 10, t + 2);
+      LANDED_AND_MEET(16);
+      mma(0, 0, b0);
+      MEET();
+      read_w((S + 2) % 10 * 2, b1);
+      load_half(S + 11, t + 2);
+      LANDED_AND_MEET(16);
+      mma(0, 1, b1);
+      MEET();
+      read_a((S + 3) % 10 * 2);
+      load_half(S + 12, t + 3);
+      LANDED_AND_MEET(16);
+      mma(1, 0, b0);
+      MEET();
+      read_w((S + 4) % 10 * 2, b0);                      // after the last K-tile: zeros, never used
+      load_half(S + 13, t + 3);
+      LANDED_AND_MEET(16);
+      mma(1, 1, b1);
+      MEET();
+    };
+    for (int t = 0;;) {
+      step(std::integral_constant<int, 0>{}, t); if (++t >= KT) break;
+      step(std::integral_constant<int, 1>{}, t); if (++t >= KT) break;
+      step(std::integral_constant<int, 2>{}, t); if (++t >= KT) break;
+      step(std::integral_constant<int, 3>{}, t); if (++t >= KT) break;
+      step(std::integral_constant<int, 4>{}, t); if (++t >= KT) break;
+    }
+  } else {
+    // Position s of the stream of units: 0 and 1 are W0 of K-tile 0; of K-tile t A is 6t + 2, 3, W1 6t + 4, 5 and the next
+    // one's W0 6t + 6, 7. The first phase of a K-tile reads A and requests 6t + 16 .. 18, the second W1 and W0' and requests
+    // 6t + 19 .. 21, each into places read a phase before at the latest.
+    auto load_unit = [&](int s, int t) {                 // s modulo 18, t: s belongs to K-tile t (6t + 2 <= s < 6t + 8)
+      const int r = (s + 4) % 6;
+      if (r < 2) load_a(0, r, s % 18, t);
+      else if (r < 4) load_w(1, r - 2, s % 18, t);
+      else load_w(0, r - 4, s % 18, t + 1);
+    };
+#pragma unroll
+    for (int s = 0; s < 16; ++s) load_unit(s, (s + 4) / 6 - 1);
+    LANDED_AND_MEET(12);                                         // W0 and A of K-tile 0
+    read_w(0, b0);
+    LANDED_AND_MEET(12);
+    if (wm == 1) { MEET(); }
+    auto step = [&](auto phase, int t) {
+      constexpr int S = decltype(phase)::value * 6;      // 6t modulo 18
+      read_a(S + 2);
+      load_unit(S + 16, t + 2); load_unit(S + 17, t + 2); load_unit(S + 18, t + 2);
+      LANDED_AND_MEET(11);
+      mma(0, 0, b0);
+      MEET();
+      read_w(S + 4, b1);
+      read_w((S + 6) % 18, b0);                          // after the last K-tile: zeros, never used
+      load_unit(S + 19, t + 2); load_unit(S + 20, t + 3); load_unit(S + 21, t + 3);
+      LANDED_AND_MEET(12);
+      mma(0, 1, b1);
+      MEET();
+    };
+    for (int t = 0;;) {
+      step(std::integral_constant<int, 0>{}, t); if (++t >= KT) break;
+      step(std::integral_constant<int, 1>{}, t); if (++t >= KT) break;
+      step(std::integral_constant<int, 2>{}, t); if (++t >= KT) break;
+    }
+  }
+  if (wm == 0) { MEET(); }                               // both rows of wavefronts have met the same barriers
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  epilogue<BM, 256, 2, EPI, HD128>(a, acc, m0, n0, wm, wn, kslice, part, smem);
+}
+
+// The BM x BN tile of the product at (m0, n0), K slice kslice, for products of few rows or few tiles: the k-step is bound by
+// the latency of the operand loads, not by the matrix pipe, so the ring holds S whole K-tiles and S-1 of them are in flight.
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128>
+__device__ __forceinline__ void ring_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
+  constexpr bool SWAP = EPI == ME_QKV_ROPE && HD128;
+  constexpr int NWN = BN / 64, NW = NWM * NWN;        // wavefronts: NWM along M x NWN along N, 64 columns each
+  constexpr int WM = BM / NWM, TM = WM / 16, TN = 4;
+  constexpr int LA = (BM / 8 + NW - 1) / NW, LB = (BN / 8 + NW - 1) / NW, NLD = LA + LB;   // loads per thread and operand tile
+  constexpr int STG = (BM + BN) * 128;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int wm = wave / NWN, wn = wave % NWN;
+  const int r16 = lane & 15, quad = lane >> 4;
+  int kt0, KT;
+  slice_tiles(a, kslice, kt0, KT);
+
+  floatx4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto mma = [&](const bf16x8 (&af)[TM], const bf16x8 (&bfr)[TN]) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
+  };
+  auto read_frags = [&](const char* st, int kk, bf16x8 (&af)[TM], bf16x8 (&bfr)[TN]) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) af[i] = lds_frag(st, wm * WM + i * 16 + r16, kk * 4 + quad);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) bfr[j] = lds_frag(st + BM * 128, wn * 64 + j * 16 + r16, kk * 4 + quad);
+  };
+  // loads [lo, hi) of K-tile t
+  auto issue = [&](int t, char* st, auto lo, auto hi) {
+#pragma unroll
+    for (int j = decltype(lo)::value; j < decltype(hi)::value; ++j) {
+      if (j < LA) load_span_async<NW, BM / 8>(a.A, m0, a.M, a.K, (kt0 + t) * 64, st, j, wave);
+      else load_span_async<NW, BN / 8, SWAP>(a.W, n0, a.N, a.K, (kt0 + t) * 64, st + BM * 128, j - LA, wave);
+    }
+  };
+  constexpr std::integral_constant<int, 0> FIRST{};
+  constexpr std::integral_constant<int, NLD / 2> MID{};
+  constexpr std::integral_constant<int, NLD> LAST{};
+  // own loads of all but the newest `ahead` K-tiles have landed and own fragment reads are done, then everybody's
+  auto wait_ahead = [&](int ahead) {
+    static_assert(S <= 6 && 4 * NLD < 63, "the counts below");
+    if (ahead >= 4) { LANDED_AND_MEET(4 * NLD); }
+    else if (ahead == 3) { LANDED_AND_MEET(3 * NLD); }
+    else if (ahead == 2) { LANDED_AND_MEET(2 * NLD); }
+    else if (ahead == 1) { LANDED_AND_MEET(NLD); }
+    else { LANDED_AND_MEET(0); }
+  };
+#define SGB __builtin_amdgcn_sched_group_barrier
+  // fragment reads, then MFMAs with a load after each of the first
+  auto order = [&](auto loads) {
+    constexpr int N = decltype(loads)::value;
+    SGB(0x100, TM + TN, 0);
+#pragma unroll
+    for (int i = 0; i < N && i < TM * TN; ++i) {
+      SGB(0x008, 1, 0);
+      SGB(0x010, 1, 0);
+    }
+    SGB(0x008, TM * TN, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int t = 0; t < S - 1; ++t)
+    if (t < KT) issue(t, smem + t * STG, FIRST, LAST);
+  wait_ahead(KT - 1 < S - 2 ? KT - 1 : S - 2);
+  bf16x8 a0[TM], b0[TN], a1[TM], b1[TN];
+  if (S - 1 < KT) issue(S - 1, smem + (S - 1) * STG, FIRST, MID);
+  char* cur = smem;                                    // slot of K-tile kt, and of kt + S once kt has been read
+  char* last = smem + (S - 1) * STG;                   // slot of K-tile kt - 1, and of kt - 1 + S
+  read_frags(cur, 0, a0, b0);
+  // A K-tile's slot is free once all have read its second half, a barrier and half of its MFMAs before the next K-tile
+  // begins: the first loads of K-tile kt + S follow there, the others a half later.
+  auto step = [&](int kt, auto rest_of, auto first_of) {
+    constexpr bool REST = decltype(rest_of)::value, NEXT = decltype(first_of)::value;   // loads of kt + S - 1, kt + S
+    char* nxt = cur + STG == smem + S * STG ? smem : cur + STG;
+    read_frags(cur, 1, a1, b1);
+    if (REST) issue(kt + S - 1, last, MID, LAST);
+    mma(a0, b0);
+    order(std::integral_constant<int, REST ? NLD - NLD / 2 : 0>{});
+    if (REST) wait_ahead(S - 2);
+    else wait_ahead(KT - 2 - kt);
+    if (REST || kt + 1 < KT) read_frags(nxt, 0, a0, b0);
+    if (NEXT) issue(kt + S, cur, FIRST, MID);
+    mma(a1, b1);
+    order(std::integral_constant<int, NEXT ? NLD / 2 : 0>{});
+    last = cur;
+    cur = nxt;
+  };
+  int kt = 0;
+  for (; kt + S < KT; ++kt) step(kt, std::true_type{}, std::true_type{});
+  if (kt + S == KT) step(kt++, std::true_type{}, std::false_type{});
+  for (; kt < KT; ++kt) step(kt, std::false_type{}, std::false_type{});
+#undef SGB
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  epilogue<BM, BN, NWM, EPI, HD128>(a, acc, m0, n0, wm, wn, kslice, part, smem);
+}
+
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128>
+__device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
+  if constexpr (BN == 256) wide_product<BM, EPI, HD128>(a, m0, n0, kslice, part, smem);
+  else ring_product<BM, BN, NWM, S, EPI, HD128>(a, m0, n0, kslice, part, smem);
 }
 
 // REST: the tiles cover the first columns only, in whole rounds of the 256 CUs; what is left, too little for another round,
@@ -533,7 +647,7 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
 
 template <int BM, int BN, int NWM, int S, int EPI, bool HD128, int REST = 0>
 static void launch_variant(const GemmArgs& a, hipStream_t s) {
-  constexpr int smem = BM == 256 ? 5 * 256 * 128 : S * (BM + BN) * 128;
+  constexpr int smem = BM == 256 ? 5 * 256 * 128 : S * (BM + BN) * 128;   // the rest's tiles take no more
   static bool configured = false;
   if (!configured) {
     (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128, REST>,
@@ -566,10 +680,14 @@ int mfma_gemm_ring(int tile, int M, int N, int K, int ksplit) {
   return tile == 3 && wgs <= 256 && K / 64 > 11 * ksplit ? 6 : ring[tile];
 }
 
+// The wide tiles request operands in 16-byte pieces through descriptors of at most 256 rows, whose offsets have 32 bits.
+static bool wide_operands(const GemmArgs& a) { return (((uintptr_t)a.A | (uintptr_t)a.W) & 15) == 0 && a.K <= 1 << 22; }
+
 int mfma_gemm_rest(int M, int N, int K, bool wide_only, int* n_tiles);
 bool mfma_gate_up_192(int M, int N, int K, int tile);
 template <int EPI, bool HD128 = false>
 static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
+  if (tile < 2 && !wide_operands(a)) tile = 2;           // the head, which has no narrower tiles, does not come here then
   if constexpr (EPI == ME_SWIGLU)
     if (mfma_gate_up_192(a.M, a.N, a.K, tile)) {
       a.m_tiles = (a.M + 127) / 128;
@@ -596,10 +714,11 @@ static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
   }
   else if (tile == 1) launch_variant<128, 256, 2, 3, EPI, HD128>(a, s);
   else if constexpr (EPI != ME_LMHEAD) {
-    // four wavefronts along M: two per SIMD cover each other's LDS reads (69 -> 64 us at 256 x 1536 x 8960)
+    // four wavefronts along M: two per SIMD cover each other's LDS reads (us, two along M / four: 1024 x 2048 x 1536 in 64 x 128
+    // tiles 13.9 / 12.2, 1024 x 1536 x 1536 13.6 / 11.2, 256 x 2048 x 1024 9.8 / 8.3)
     if (tile == 2) launch_variant<128, 128, 4, 5, EPI, HD128>(a, s);
-    else if (mfma_gemm_ring(tile, a.M, a.N, a.K, a.ksplit) == 6) launch_variant<64, 128, 2, 6, EPI, HD128>(a, s);
-    else if (tile == 3) launch_variant<64, 128, 2, 3, EPI, HD128>(a, s);
+    else if (mfma_gemm_ring(tile, a.M, a.N, a.K, a.ksplit) == 6) launch_variant<64, 128, 4, 6, EPI, HD128>(a, s);
+    else if (tile == 3) launch_variant<64, 128, 4, 3, EPI, HD128>(a, s);
     else launch_variant<32, 128, 1, 4, EPI, HD128>(a, s);
   }
 }
@@ -725,6 +844,7 @@ bool launch_gemm_mfma(int epi, const bf16_t* A, const bf16_t* W, int M, int N, i
   GemmArgs a = {};
   a.A = A; a.W = W; a.M = M; a.N = N; a.K = K; a.C = C; a.act = act; a.tok = tok;
   a.part_max = part_max; a.part_sum = part_sum; a.zt = zt; a.ksplit = ksplit;
+  if (epi == ME_LMHEAD && !wide_operands(a)) return false;
   int split = 1;
   if (tile < 0) mfma_gemm_plan(M, N, K, 1, epi == ME_LMHEAD, &tile, &split);
   switch (epi) {

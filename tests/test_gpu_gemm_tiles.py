@@ -1,0 +1,81 @@
+"""Every tile shape of the bf16 product family, launched by its index on whole-number operands: the sums are exact in float,
+so each element has to be equal, whatever the tile, the K-tiles against the length of its LDS ring, the K slices and the
+remainders of the last tiles. Only the plan's choice of a tile is left to the other tests."""
+import ctypes as C
+
+import pytest
+import torch
+
+from host_rules import library
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+WIDE, TILES = (0, 1), (0, 1, 2, 3, 4)
+STORE, RESIDUAL, SWIGLU, HEAD = 0, 1, 2, 3
+
+
+def launch(epilogue, A, Wt, M, N, K, out=None, act=None, tok=None, pm=None, ps=None, zt=None, split=1, tile=-1):
+    f = library()._Z16launch_gemm_mfmaiPKDF16bS0_iiiPfPDF16bPKiS1_S1_S1_iiP12ihipStream_t
+    p = C.c_void_p
+    f.restype, f.argtypes = C.c_bool, [C.c_int, p, p] + [C.c_int] * 3 + [p] * 6 + [C.c_int] * 2 + [p]
+    ptr = lambda t: None if t is None else t.data_ptr()
+    return f(epilogue, A.data_ptr(), Wt.data_ptr(), M, N, K, ptr(out), ptr(act), ptr(tok), ptr(pm), ptr(ps), ptr(zt), split, tile,
+             torch.cuda.current_stream().cuda_stream)
+
+
+def whole(shape, seed, top=3):
+    g = torch.Generator().manual_seed(seed)
+    return torch.randint(-top, top + 1, shape, generator=g).to(torch.bfloat16).to(DEV)
+
+
+# K-tiles: fewer than any ring holds, one more than a turn of the unrolled loops (5 and 3 K-tiles), several turns
+@pytest.mark.parametrize("k_tiles", [1, 2, 3, 4, 5, 6, 7, 11])
+@pytest.mark.parametrize("tile", TILES)
+def test_store_and_residual_are_exact(tile, k_tiles):
+    K = 64 * k_tiles
+    for M, N in ((300, 520), (1, 64), (257, 259)):       # remainders of rows and columns; a row length of no whole 16 bytes
+        if tile == 4 and M > 32:
+            M = 31                                       # the tile for up to 32 rows
+        A, Wt = whole((M, K), 1), whole((N, K), 2)
+        want = A.float() @ Wt.float().t()                # exact: sums of at most 704 products of at most 9
+        for split in (1, 2, 3):
+            if split > k_tiles:
+                break
+            out = torch.full((split, M, N), float("nan"), device=DEV)
+            assert launch(STORE, A, Wt, M, N, K, out, split=split, tile=tile)
+            assert torch.equal(out.sum(0), want), (M, N, split)
+        assert launch(RESIDUAL, A, Wt, M, N, K, out := want.clone(), tile=tile)
+        assert torch.equal(out, 2 * want), (M, N)
+
+
+@pytest.mark.parametrize("k_tiles", [1, 4, 6])
+@pytest.mark.parametrize("tile", WIDE)
+def test_vocabulary_head_finds_targets_and_maxima(tile, k_tiles):
+    M, N, K = 261, 1000, 64 * k_tiles
+    A, Wt = whole((M, K), 3), whole((N, K), 4)
+    z = A.float() @ Wt.float().t()
+    tok = torch.randint(0, N, (M,), generator=torch.Generator().manual_seed(5), dtype=torch.int32).to(DEV)
+    tiles = -(-N // 256)
+    pm, ps = torch.full((2, M, tiles), float("nan"), device=DEV)
+    zt = torch.full((M,), float("nan"), device=DEV)
+    assert launch(HEAD, A, Wt, M, N, K, tok=tok, pm=pm, ps=ps, zt=zt, tile=tile)
+    assert torch.equal(zt, z.gather(1, tok.long()[:, None])[:, 0])
+    pad = torch.nn.functional.pad(z, (0, tiles * 256 - N), value=float("-inf")).view(M, tiles, 256)
+    assert torch.equal(pm, pad.max(2).values)
+    want = (pad.double() - pm.double()[:, :, None]).exp().sum(2)
+    # 256 positive terms with 2 ulp each of v_exp_f32, on arguments rounded to float by __expf's product with log2(e)
+    assert torch.allclose(ps.double(), want, rtol=256 * 2.0 ** -24, atol=0)
+
+
+@pytest.mark.parametrize("tile", TILES)
+def test_gate_up_columns_meet_their_partners(tile):
+    """Gate g and up u of every unit whole numbers: the product is bf16(silu(g) u) up to the rounding of silu."""
+    M, F, K = 30 if tile == 4 else 290, 480, 128
+    A, Wt = whole((M, K), 6, 1), whole((2 * F, K), 7, 1)
+    z = (A.double() @ Wt.double().t()).view(M, F // 32, 2, 32)
+    act = torch.full((M, F), float("nan"), dtype=torch.bfloat16, device=DEV)
+    assert launch(SWIGLU, A, Wt, M, 2 * F, K, act=act, tile=tile)
+    want = (torch.nn.functional.silu(z[:, :, 0]) * z[:, :, 1]).reshape(M, F)
+    # half a unit in the last of 8 significant bits is 2^-8 at most; __expf rounds an argument of at most 64 times log2(e) to
+    # float, half a unit in the last place of 2^6, and its result, sum, reciprocal and products take a unit each
+    assert torch.all((act.double() - want).abs() <= want.abs() * (2.0 ** -8 + 2.0 ** -17 + 8 * 2.0 ** -23) + 1e-30)
