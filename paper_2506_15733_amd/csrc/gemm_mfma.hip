@@ -519,8 +519,11 @@ __device__ __forceinline__ void wide_product(const GemmArgs& a, int m0, int n0, 
 }
 
 // The BM x BN tile of the product at (m0, n0), K slice kslice, for products of few rows or few tiles: the k-step is bound by
-// the latency of the operand loads, not by the matrix pipe, so the ring holds S whole K-tiles and S-1 of them are in flight.
-template <int BM, int BN, int NWM, int S, int EPI, bool HD128>
+// the latency of the operand loads and by what a wavefront issues per k-step, not by the matrix pipe. So the ring holds S whole
+// K-tiles, nearly all of them in flight, and a load is one vector instruction (us with the addresses computed per load, and
+// the last K-tiles in loops of their own / so: 256 x 2048 x 1024 8.3 / 7.2, 1024 x 1536 x 1536 13.0 / 11.0,
+// 256 x 1536 x 8960 in 5 slices 14.9 / 12.7, gate/up of 256 x 5632 x 1024 9.0 / 7.5).
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128, bool BUFFER>
 __device__ __forceinline__ void ring_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
   constexpr bool SWAP = EPI == ME_QKV_ROPE && HD128;
   constexpr int NWN = BN / 64, NW = NWM * NWN;        // wavefronts: NWM along M x NWN along N, 64 columns each
@@ -551,26 +554,41 @@ __device__ __forceinline__ void ring_product(const GemmArgs& a, int m0, int n0, 
 #pragma unroll
     for (int j = 0; j < TN; ++j) bfr[j] = lds_frag(st + BM * 128, wn * 64 + j * 16 + r16, kk * 4 + quad);
   };
+  // Load j of a K-tile fills 1 KiB of LDS (8 rows) per wavefront; where the wavefronts outnumber the last spans of an operand
+  // tile, some fetch the last one again. BUFFER: by descriptors that end with the matrix (and are empty behind the slice), so
+  // that a load is one vector instruction, with all of a row in the offset that the bounds check covers.
+  const unsigned row_bytes = (unsigned)a.K * 2u;
+  const unsigned a_size = (unsigned)min(a.M - m0, BM) * row_bytes - kt0 * 128, w_size = (unsigned)min(a.N - n0, BN) * row_bytes - kt0 * 128;
+  const bf16_t *Ab = a.A + (size_t)m0 * a.K + kt0 * 64, *Wb = a.W + (size_t)n0 * a.K + kt0 * 64;
+  int dst[NLD];
+  unsigned off[NLD];
+#pragma unroll
+  for (int j = 0; j < NLD; ++j) {
+    const int spans = j < LA ? BM / 8 : BN / 8, span = min((j < LA ? j : j - LA) * NW + wave, spans - 1);
+    const int row = span * 8 + (lane >> 3);
+    dst[j] = (j < LA ? 0 : BM * 128) + span * 1024;
+    off[j] = (unsigned)(SWAP && j >= LA ? swap56(row) : row) * row_bytes + ((lane & 7) ^ ((row >> 1) & 7)) * 16;
+  }
   // loads [lo, hi) of K-tile t
   auto issue = [&](int t, char* st, auto lo, auto hi) {
+    if constexpr (BUFFER) {
+      const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)Ab, 0, t < KT ? a_size : 0u, 0x00020000);
+      const auto rw = __builtin_amdgcn_make_buffer_rsrc((void*)Wb, 0, t < KT ? w_size : 0u, 0x00020000);
 #pragma unroll
-    for (int j = decltype(lo)::value; j < decltype(hi)::value; ++j) {
-      if (j < LA) load_span_async<NW, BM / 8>(a.A, m0, a.M, a.K, (kt0 + t) * 64, st, j, wave);
-      else load_span_async<NW, BN / 8, SWAP>(a.W, n0, a.N, a.K, (kt0 + t) * 64, st + BM * 128, j - LA, wave);
+      for (int j = decltype(lo)::value; j < decltype(hi)::value; ++j)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(j < LA ? ra : rw, LDS_PTR(st + dst[j]), 16, off[j], t * 128, 0, 0);
+    } else {
+      const int src = t < KT ? t : KT - 1;             // behind the slice: redundant loads
+#pragma unroll
+      for (int j = decltype(lo)::value; j < decltype(hi)::value; ++j) {
+        if (j < LA) load_span_async<NW, BM / 8>(a.A, m0, a.M, a.K, (kt0 + src) * 64, st, j, wave);
+        else load_span_async<NW, BN / 8, SWAP>(a.W, n0, a.N, a.K, (kt0 + src) * 64, st + BM * 128, j - LA, wave);
+      }
     }
   };
   constexpr std::integral_constant<int, 0> FIRST{};
   constexpr std::integral_constant<int, NLD / 2> MID{};
   constexpr std::integral_constant<int, NLD> LAST{};
-  // own loads of all but the newest `ahead` K-tiles have landed and own fragment reads are done, then everybody's
-  auto wait_ahead = [&](int ahead) {
-    static_assert(S <= 6 && 4 * NLD < 63, "the counts below");
-    if (ahead >= 4) { LANDED_AND_MEET(4 * NLD); }
-    else if (ahead == 3) { LANDED_AND_MEET(3 * NLD); }
-    else if (ahead == 2) { LANDED_AND_MEET(2 * NLD); }
-    else if (ahead == 1) { LANDED_AND_MEET(NLD); }
-    else { LANDED_AND_MEET(0); }
-  };
 #define SGB __builtin_amdgcn_sched_group_barrier
   // fragment reads, then MFMAs with a load after each of the first
   auto order = [&](auto loads) {
@@ -584,51 +602,46 @@ __device__ __forceinline__ void ring_product(const GemmArgs& a, int m0, int n0, 
     SGB(0x008, TM * TN, 0);
     __builtin_amdgcn_sched_barrier(0);
   };
+  // own loads of all but the newest S - 2 K-tiles have landed and own fragment reads are done, then everybody's
+  static_assert((S - 2) * NLD < 63, "the counter's range");
 #pragma unroll
-  for (int t = 0; t < S - 1; ++t)
-    if (t < KT) issue(t, smem + t * STG, FIRST, LAST);
-  wait_ahead(KT - 1 < S - 2 ? KT - 1 : S - 2);
+  for (int t = 0; t < S - 1; ++t) issue(t, smem + t * STG, FIRST, LAST);
+  LANDED_AND_MEET((S - 2) * NLD);
   bf16x8 a0[TM], b0[TN], a1[TM], b1[TN];
-  if (S - 1 < KT) issue(S - 1, smem + (S - 1) * STG, FIRST, MID);
+  issue(S - 1, smem + (S - 1) * STG, FIRST, MID);
   char* cur = smem;                                    // slot of K-tile kt, and of kt + S once kt has been read
   char* last = smem + (S - 1) * STG;                   // slot of K-tile kt - 1, and of kt - 1 + S
   read_frags(cur, 0, a0, b0);
   // A K-tile's slot is free once all have read its second half, a barrier and half of its MFMAs before the next K-tile
   // begins: the first loads of K-tile kt + S follow there, the others a half later.
-  auto step = [&](int kt, auto rest_of, auto first_of) {
-    constexpr bool REST = decltype(rest_of)::value, NEXT = decltype(first_of)::value;   // loads of kt + S - 1, kt + S
+  for (int kt = 0; kt < KT; ++kt) {
     char* nxt = cur + STG == smem + S * STG ? smem : cur + STG;
     read_frags(cur, 1, a1, b1);
-    if (REST) issue(kt + S - 1, last, MID, LAST);
+    issue(kt + S - 1, last, MID, LAST);
     mma(a0, b0);
-    order(std::integral_constant<int, REST ? NLD - NLD / 2 : 0>{});
-    if (REST) wait_ahead(S - 2);
-    else wait_ahead(KT - 2 - kt);
-    if (REST || kt + 1 < KT) read_frags(nxt, 0, a0, b0);
-    if (NEXT) issue(kt + S, cur, FIRST, MID);
+    order(std::integral_constant<int, NLD - NLD / 2>{});
+    LANDED_AND_MEET((S - 2) * NLD);
+    read_frags(nxt, 0, a0, b0);                        // after the last K-tile: not used
+    issue(kt + S, cur, FIRST, MID);
     mma(a1, b1);
-    order(std::integral_constant<int, NEXT ? NLD / 2 : 0>{});
+    order(std::integral_constant<int, NLD / 2>{});
     last = cur;
     cur = nxt;
-  };
-  int kt = 0;
-  for (; kt + S < KT; ++kt) step(kt, std::true_type{}, std::true_type{});
-  if (kt + S == KT) step(kt++, std::true_type{}, std::false_type{});
-  for (; kt < KT; ++kt) step(kt, std::false_type{}, std::false_type{});
+  }
 #undef SGB
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   epilogue<BM, BN, NWM, EPI, HD128>(a, acc, m0, n0, wm, wn, kslice, part, smem);
 }
 
-template <int BM, int BN, int NWM, int S, int EPI, bool HD128>
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128, bool BUFFER = true>
 __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
   if constexpr (BN == 256) wide_product<BM, EPI, HD128>(a, m0, n0, kslice, part, smem);
-  else ring_product<BM, BN, NWM, S, EPI, HD128>(a, m0, n0, kslice, part, smem);
+  else ring_product<BM, BN, NWM, S, EPI, HD128, BUFFER>(a, m0, n0, kslice, part, smem);
 }
 
 // REST: the tiles cover the first columns only, in whole rounds of the 256 CUs; what is left, too little for another round,
 // is cut into tiles of 128 rows and REST columns, which further workgroups of the same launch take as CUs come free.
-template <int BM, int BN, int NWM, int S, int EPI, bool HD128, int REST>
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128, int REST, bool BUFFER>
 __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   TileAt at;
@@ -642,20 +655,20 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
     }
   }
   if (!tile_of(blockIdx.x, a.m_tiles, a.n_tiles, a.ksplit, at)) return;
-  tile_product<BM, BN, NWM, S, EPI, HD128>(a, at.m * BM, at.n * BN, at.kslice, at.n, smem);
+  tile_product<BM, BN, NWM, S, EPI, HD128, BUFFER>(a, at.m * BM, at.n * BN, at.kslice, at.n, smem);
 }
 
-template <int BM, int BN, int NWM, int S, int EPI, bool HD128, int REST = 0>
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128, int REST = 0, bool BUFFER = true>
 static void launch_variant(const GemmArgs& a, hipStream_t s) {
   constexpr int smem = BM == 256 ? 5 * 256 * 128 : S * (BM + BN) * 128;   // the rest's tiles take no more
   static bool configured = false;
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128, REST>,
+    (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128, REST, BUFFER>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     configured = true;
   }
   const int grid = REST ? a.rest_block + tile_grid(a.rest_m_tiles * a.rest_n_tiles) : tile_grid(a.m_tiles * a.n_tiles * a.ksplit);
-  gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128, REST><<<grid, NWM * BN, smem, s>>>(a);
+  gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128, REST, BUFFER><<<grid, NWM * BN, smem, s>>>(a);
 }
 
 int mfma_lmhead_tiles(int V) { return (V + 255) / 256; }
@@ -680,14 +693,21 @@ int mfma_gemm_ring(int tile, int M, int N, int K, int ksplit) {
   return tile == 3 && wgs <= 256 && K / 64 > 11 * ksplit ? 6 : ring[tile];
 }
 
-// The wide tiles request operands in 16-byte pieces through descriptors of at most 256 rows, whose offsets have 32 bits.
-static bool wide_operands(const GemmArgs& a) { return (((uintptr_t)a.A | (uintptr_t)a.W) & 15) == 0 && a.K <= 1 << 22; }
+// Operands are requested in 16-byte pieces through descriptors of at most 256 rows, whose offsets have 32 bits. Any others go
+// to one kernel that takes plain addresses, and the vocabulary head of such to the plain kernels.
+static bool buffer_operands(const GemmArgs& a) { return (((uintptr_t)a.A | (uintptr_t)a.W) & 15) == 0 && a.K <= 1 << 22; }
 
 int mfma_gemm_rest(int M, int N, int K, bool wide_only, int* n_tiles);
 bool mfma_gate_up_192(int M, int N, int K, int tile);
 template <int EPI, bool HD128 = false>
 static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
-  if (tile < 2 && !wide_operands(a)) tile = 2;           // the head, which has no narrower tiles, does not come here then
+  if constexpr (EPI != ME_LMHEAD)
+    if (!buffer_operands(a)) {
+      a.m_tiles = (a.M + 127) / 128;
+      a.n_tiles = (a.N + 127) / 128;
+      launch_variant<128, 128, 4, 5, EPI, HD128, 0, false>(a, s);
+      return;
+    }
   if constexpr (EPI == ME_SWIGLU)
     if (mfma_gate_up_192(a.M, a.N, a.K, tile)) {
       a.m_tiles = (a.M + 127) / 128;
@@ -719,7 +739,7 @@ static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
     if (tile == 2) launch_variant<128, 128, 4, 5, EPI, HD128>(a, s);
     else if (mfma_gemm_ring(tile, a.M, a.N, a.K, a.ksplit) == 6) launch_variant<64, 128, 4, 6, EPI, HD128>(a, s);
     else if (tile == 3) launch_variant<64, 128, 4, 3, EPI, HD128>(a, s);
-    else launch_variant<32, 128, 1, 4, EPI, HD128>(a, s);
+    else launch_variant<32, 128, 2, 4, EPI, HD128>(a, s);
   }
 }
 
@@ -844,7 +864,7 @@ bool launch_gemm_mfma(int epi, const bf16_t* A, const bf16_t* W, int M, int N, i
   GemmArgs a = {};
   a.A = A; a.W = W; a.M = M; a.N = N; a.K = K; a.C = C; a.act = act; a.tok = tok;
   a.part_max = part_max; a.part_sum = part_sum; a.zt = zt; a.ksplit = ksplit;
-  if (epi == ME_LMHEAD && !wide_operands(a)) return false;
+  if (epi == ME_LMHEAD && !buffer_operands(a)) return false;
   int split = 1;
   if (tile < 0) mfma_gemm_plan(M, N, K, 1, epi == ME_LMHEAD, &tile, &split);
   switch (epi) {

@@ -28,8 +28,9 @@ def whole(shape, seed, top=3):
     return torch.randint(-top, top + 1, shape, generator=g).to(torch.bfloat16).to(DEV)
 
 
-# K-tiles: fewer than any ring holds, one more than a turn of the unrolled loops (5 and 3 K-tiles), several turns
-@pytest.mark.parametrize("k_tiles", [1, 2, 3, 4, 5, 6, 7, 11])
+# K-tiles: fewer than any ring holds, one more than a turn of the unrolled loops (5 and 3 K-tiles), several turns; beyond 11 the
+# 64 x 128 tile has its longer ring
+@pytest.mark.parametrize("k_tiles", [1, 2, 3, 4, 5, 6, 7, 11, 13])
 @pytest.mark.parametrize("tile", TILES)
 def test_store_and_residual_are_exact(tile, k_tiles):
     K = 64 * k_tiles
@@ -37,7 +38,7 @@ def test_store_and_residual_are_exact(tile, k_tiles):
         if tile == 4 and M > 32:
             M = 31                                       # the tile for up to 32 rows
         A, Wt = whole((M, K), 1), whole((N, K), 2)
-        want = A.float() @ Wt.float().t()                # exact: sums of at most 704 products of at most 9
+        want = A.float() @ Wt.float().t()                # exact: sums of at most 832 products of at most 9
         for split in (1, 2, 3):
             if split > k_tiles:
                 break
@@ -79,3 +80,23 @@ def test_gate_up_columns_meet_their_partners(tile):
     # half a unit in the last of 8 significant bits is 2^-8 at most; __expf rounds an argument of at most 64 times log2(e) to
     # float, half a unit in the last place of 2^6, and its result, sum, reciprocal and products take a unit each
     assert torch.all((act.double() - want).abs() <= want.abs() * (2.0 ** -8 + 2.0 ** -17 + 8 * 2.0 ** -23) + 1e-30)
+
+
+@pytest.mark.parametrize("epilogue", [STORE, SWIGLU, HEAD])
+def test_operands_off_the_16_byte_grid(epilogue):
+    """4 bytes beside it: the kernel that takes plain addresses, and for the head, which has none, the caller's plain kernel."""
+    M, N, K = 140, 192, 320
+    A = torch.zeros(M * K + 2, dtype=torch.bfloat16, device=DEV)[2:].view(M, K).copy_(whole((M, K), 8, 1))
+    Wt = torch.zeros(N * K + 2, dtype=torch.bfloat16, device=DEV)[2:].view(N, K).copy_(whole((N, K), 9, 1))
+    want = A.float() @ Wt.float().t()
+    if epilogue == HEAD:
+        assert not launch(HEAD, A, Wt, M, N, K)
+    elif epilogue == STORE:
+        for tile in (-1, *TILES[:4]):
+            assert launch(STORE, A, Wt, M, N, K, out := torch.full((M, N), float("nan"), device=DEV), tile=tile)
+            assert torch.equal(out, want), tile
+    else:
+        assert launch(SWIGLU, A, Wt, M, N, K, act=(act := torch.full((M, N // 2), float("nan"), dtype=torch.bfloat16, device=DEV)))
+        z = want.double().view(M, N // 64, 2, 32)
+        ref = (torch.nn.functional.silu(z[:, :, 0]) * z[:, :, 1]).reshape(M, N // 2)
+        assert torch.allclose(act.double(), ref, rtol=2.0 ** -8 + 2.0 ** -16, atol=1e-30)
