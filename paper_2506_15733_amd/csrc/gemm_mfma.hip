@@ -199,8 +199,8 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, floatx4 (&acc)[TM][4
   } else if constexpr (EPI == ME_QKV_ROPE) {
     // columns 0..31 of the part: 32 pairs' first elements, 32..63 their second ones
     constexpr int HDIM = HD128 ? 128 : 64, HALF = HDIM / 2;
-    const int head = HD128 ? (n0 >> 7) + (wn >> 1) : (n0 >> 6) + wn;
-    const int i_base = (HD128 ? (wn & 1) * 32 : 0) + 4 * quad;           // + 16 j + e: index of the pair inside the head
+    const int head = HD128 ? (n >> 7) : (n >> 6), wq = HD128 ? (n >> 6) & 1 : 0;
+    const int i_base = wq * 32 + 4 * quad;                               // + 16 j + e: index of the pair inside the head
     if (head < a.Hq + 2 * a.Hkv) {
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
@@ -247,7 +247,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, floatx4 (&acc)[TM][4
           while (ends) {
             const int of = __builtin_amdgcn_readlane(cand, __builtin_ctz(ends));
             ends &= ends - 1;
-            const int d = HD128 ? (wn & 1) * 32 + (lane & 31) + (lane >> 5) * HALF : lane;
+            const int d = HD128 ? wq * 32 + (lane & 31) + (lane >> 5) * HALF : lane;
             bf16_t* pad = head_v + of * cand_v + (size_t)d * a.Lp;
             for (int k = a.Lrows; k < a.Lp; ++k) pad[k] = (__bf16)0.f;
           }
@@ -317,7 +317,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, floatx4 (&acc)[TM][4
 // Rotary pairs are columns (i, i + hd/2) of a head. With head_dim 64 a wavefront's 64 columns are one head, the first 32 of
 // them one half of its pairs. With head_dim 128 a head spans two wavefronts, so the W tile is loaded with rows 32..63 and
 // 64..95 of every 128 exchanged: wavefront (head, wq) then holds columns wq*32 .. +31 of the first half in its first 32
-// columns and the same columns of the second half in the others.
+// columns and the same columns of the second half in the others. (A tile of 64 columns is loaded from its whole head's rows.)
 __device__ __forceinline__ constexpr int swap56(int row) { return (row & ~0x60) | ((row & 0x20) << 1) | ((row & 0x40) >> 1); }
 
 // K-tiles [kt0, kt0 + KT) of K slice kslice
@@ -525,6 +525,7 @@ __device__ __forceinline__ void wide_product(const GemmArgs& a, int m0, int n0, 
 // 256 x 1536 x 8960 in 5 slices 14.9 / 12.7, gate/up of 256 x 5632 x 1024 9.0 / 7.5).
 template <int BM, int BN, int NWM, int S, int EPI, bool HD128, bool BUFFER>
 __device__ __forceinline__ void ring_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
+  static_assert(BUFFER || BN % 128 == 0, "whole heads");
   constexpr bool SWAP = EPI == ME_QKV_ROPE && HD128;
   constexpr int NWN = BN / 64, NW = NWM * NWN;        // wavefronts: NWM along M x NWN along N, 64 columns each
   constexpr int WM = BM / NWM, TM = WM / 16, TN = 4;
@@ -558,16 +559,18 @@ __device__ __forceinline__ void ring_product(const GemmArgs& a, int m0, int n0, 
   // tile, some fetch the last one again. BUFFER: by descriptors that end with the matrix (and are empty behind the slice), so
   // that a load is one vector instruction, with all of a row in the offset that the bounds check covers.
   const unsigned row_bytes = (unsigned)a.K * 2u;
-  const unsigned a_size = (unsigned)min(a.M - m0, BM) * row_bytes - kt0 * 128, w_size = (unsigned)min(a.N - n0, BN) * row_bytes - kt0 * 128;
-  const bf16_t *Ab = a.A + (size_t)m0 * a.K + kt0 * 64, *Wb = a.W + (size_t)n0 * a.K + kt0 * 64;
+  constexpr bool HALF_HEAD = SWAP && BN == 64;
+  const int w0 = HALF_HEAD ? n0 & ~127 : n0, w_rows = HALF_HEAD ? 128 : BN;
+  const unsigned a_size = (unsigned)min(a.M - m0, BM) * row_bytes - kt0 * 128, w_size = (unsigned)min(a.N - w0, w_rows) * row_bytes - kt0 * 128;
+  const bf16_t *Ab = a.A + (size_t)m0 * a.K + kt0 * 64, *Wb = a.W + (size_t)w0 * a.K + kt0 * 64;
   int dst[NLD];
   unsigned off[NLD];
 #pragma unroll
   for (int j = 0; j < NLD; ++j) {
     const int spans = j < LA ? BM / 8 : BN / 8, span = min((j < LA ? j : j - LA) * NW + wave, spans - 1);
-    const int row = span * 8 + (lane >> 3);
+    const int row = span * 8 + (lane >> 3), w_row = HALF_HEAD ? swap56(n0 - w0 + row) : SWAP ? swap56(row) : row;
     dst[j] = (j < LA ? 0 : BM * 128) + span * 1024;
-    off[j] = (unsigned)(SWAP && j >= LA ? swap56(row) : row) * row_bytes + ((lane & 7) ^ ((row >> 1) & 7)) * 16;
+    off[j] = (unsigned)(j < LA ? row : w_row) * row_bytes + ((lane & 7) ^ ((row >> 1) & 7)) * 16;
   }
   // loads [lo, hi) of K-tile t
   auto issue = [&](int t, char* st, auto lo, auto hi) {
@@ -697,6 +700,9 @@ int mfma_gemm_ring(int tile, int M, int N, int K, int ksplit) {
 // to one kernel that takes plain addresses, and the vocabulary head of such to the plain kernels.
 static bool buffer_operands(const GemmArgs& a) { return (((uintptr_t)a.A | (uintptr_t)a.W) & 15) == 0 && a.K <= 1 << 22; }
 
+// Tiles that only mfma_gemm_tile gives, behind those of the plan.
+enum { TILE_64 = MFMA_TILES, TILE_32, ALL_TILES };
+
 int mfma_gemm_rest(int M, int N, int K, bool wide_only, int* n_tiles);
 bool mfma_gate_up_192(int M, int N, int K, int tile);
 template <int EPI, bool HD128 = false>
@@ -706,6 +712,14 @@ static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
       a.m_tiles = (a.M + 127) / 128;
       a.n_tiles = (a.N + 127) / 128;
       launch_variant<128, 128, 4, 5, EPI, HD128, 0, false>(a, s);
+      return;
+    }
+  if constexpr (EPI != ME_LMHEAD)
+    if (tile == TILE_64 || tile == TILE_32) {
+      a.m_tiles = tile == TILE_64 ? (a.M + 63) / 64 : (a.M + 31) / 32;
+      a.n_tiles = (a.N + 63) / 64;
+      if (tile == TILE_64) launch_variant<64, 64, 4, 4, EPI, HD128>(a, s);
+      else launch_variant<32, 64, 2, 6, EPI, HD128>(a, s);
       return;
     }
   if constexpr (EPI == ME_SWIGLU)
@@ -830,6 +844,21 @@ void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* til
   if (*split_out == 1 && rest_plan(M, N, K, wide_only, &n_tiles, &step)) consider(0, 1, step);
 }
 
+// The plan's tile and slices, or a finer tile where the plan says 64 x 128 and the product leaves CUs without a workgroup of
+// that: what such a launch takes is how long its few CUs pull weights from HBM, so more and smaller workgroups are ahead as long
+// as each has a CU to itself. us with cold weights, of 64 x 128, 64 x 64 and 32 x 64: 256 x 2048 x 1024 10.3, 7.7, 6.7;
+// 256 x 2048 x 1536 14.8, 10.3, 8.6; 256 x 1024 x 1024 in 4 slices 6.1, 4.9, 5.4 (512 workgroups of the last, in 2: 5.2). A few CUs
+// with two of the 64 x 64 ones do no harm (555 x 2048 x 1536, 288 of them: 14.3 / 12.4); where many have two, 64 x 128 is ahead
+// (256 x 5632 x 1024: 352, 11.2 / 12.3; 1024 x 2048 x 1536: 512, 14.6 / 16.1). The slices stay the plan's: all tiles add a slice's
+// products in the same order, so the finer ones leave the same bits.
+void mfma_gemm_tile(int M, int N, int K, int max_split, bool wide_only, int* tile_out, int* split_out) {
+  mfma_gemm_plan(M, N, K, max_split, wide_only, tile_out, split_out);
+  if (*tile_out != 3) return;
+  const long columns = (long)((N + 63) / 64) * *split_out;
+  if ((M + 31) / 32 * columns <= 256) *tile_out = TILE_32;
+  else if ((M + 63) / 64 * columns <= 288) *tile_out = TILE_64;
+}
+
 // QKV projection with the rotary embedding, the bf16 conversion and the per-candidate transposition of the values
 // in the epilogue: no float [M, (Hq+2Hkv)*hd] round trip through memory and no separate kernel. Row m is in-block
 // position m % g.L of candidate m / g.L. Returns false when the shape is not taken (head_dim other than 64/128,
@@ -845,7 +874,7 @@ bool launch_gemm_mfma_qkv_rope(const bf16_t* A, const bf16_t* W, const float* cs
   a.cs = cs; a.q = q; a.kblk = kblk; a.vT = vT;
   a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lrows = g.L; a.Lp = Lp;
   int split = 1;
-  if (tile < 0) mfma_gemm_plan(M, N, K, 1, false, &tile, &split);
+  if (tile < 0) mfma_gemm_tile(M, N, K, 1, false, &tile, &split);
   if (md.hd == 128) launch_tile<ME_QKV_ROPE, true>(a, tile, s);
   else launch_tile<ME_QKV_ROPE, false>(a, tile, s);
   return true;
@@ -860,13 +889,13 @@ bool launch_gemm_mfma(int epi, const bf16_t* A, const bf16_t* W, int M, int N, i
   if (K % 64 != 0 || M <= 0 || N <= 0) return false;
   if (epi == ME_SWIGLU && (N % 64 != 0 || ((uintptr_t)act & 7))) return false;
   if (ksplit < 1 || (ksplit > 1 && (epi != ME_STORE || ksplit > K / 64))) return false;
-  if (tile >= (epi == ME_LMHEAD ? 2 : MFMA_TILES)) return false;
+  if (tile >= (epi == ME_LMHEAD ? 2 : (int)ALL_TILES)) return false;
   GemmArgs a = {};
   a.A = A; a.W = W; a.M = M; a.N = N; a.K = K; a.C = C; a.act = act; a.tok = tok;
   a.part_max = part_max; a.part_sum = part_sum; a.zt = zt; a.ksplit = ksplit;
   if (epi == ME_LMHEAD && !buffer_operands(a)) return false;
   int split = 1;
-  if (tile < 0) mfma_gemm_plan(M, N, K, 1, epi == ME_LMHEAD, &tile, &split);
+  if (tile < 0) mfma_gemm_tile(M, N, K, 1, epi == ME_LMHEAD, &tile, &split);
   switch (epi) {
     case ME_STORE: launch_tile<ME_STORE>(a, tile, s); break;
     case ME_RESIDUAL: launch_tile<ME_RESIDUAL>(a, tile, s); break;

@@ -408,7 +408,7 @@ int gemm_residual_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* x, floa
   // Also with one slice the product goes to `part` and the normalisation kernel, which reads x anyway, adds it:
   // the GEMM's epilogue then only writes, instead of waiting for a read of x before every store.
   int tile = -1, split = 1;
-  if (K % 64 == 0 && max_split > 1) mfma_gemm_plan(M, N, K, max_split, false, &tile, &split);
+  if (K % 64 == 0 && max_split > 1) mfma_gemm_tile(M, N, K, max_split, false, &tile, &split);
   if (max_split >= 1 &&
       launch_gemm_mfma(MFMA_STORE, A, W, M, N, K, part, nullptr, nullptr, nullptr, nullptr, nullptr, split, tile, s)) {
     count_mfma(M);
@@ -428,7 +428,7 @@ template <>
 int gemm_store_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* C, int max_split, int M, int N, int K,
                              hipStream_t s) {
   int tile = -1, split = 1;
-  if (K % 64 == 0 && max_split > 1) mfma_gemm_plan(M, N, K, max_split, false, &tile, &split);
+  if (K % 64 == 0 && max_split > 1) mfma_gemm_tile(M, N, K, max_split, false, &tile, &split);
   if (launch_gemm_mfma(MFMA_STORE, A, W, M, N, K, C, nullptr, nullptr, nullptr, nullptr, nullptr, split, tile, s)) {
     count_mfma(M);
     return split;
@@ -1010,7 +1010,7 @@ extern "C" int specs_op_linear(specs_ctx* ctx, int32_t dtype, const void* A, con
     size_t per = (size_t)M * N * sizeof(float);
     size_t room = ctx->workspace_bytes > 256 ? (ctx->workspace_bytes - 256) / per : 0;
     int tile = -1, split = 1;
-    if (K % 64 == 0 && room > 1) mfma_gemm_plan(M, N, K, room > MFMA_MAX_SPLIT ? MFMA_MAX_SPLIT : (int)room, false, &tile, &split);
+    if (K % 64 == 0 && room > 1) mfma_gemm_tile(M, N, K, room > MFMA_MAX_SPLIT ? MFMA_MAX_SPLIT : (int)room, false, &tile, &split);
     float* part = (float*)(ctx->workspace + 256);
     if (split > 1 && launch_gemm_mfma(MFMA_STORE, (const bf16_t*)A, (const bf16_t*)W, M, N, K, part, nullptr, nullptr,
                                       nullptr, nullptr, nullptr, split, tile, ctx->stream)) {

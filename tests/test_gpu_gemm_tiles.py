@@ -6,11 +6,11 @@ import ctypes as C
 import pytest
 import torch
 
-from host_rules import library
+from host_rules import BatchGeom, ModelDims, library
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-WIDE, TILES = (0, 1), (0, 1, 2, 3, 4)
+WIDE, TILES = (0, 1), (0, 1, 2, 3, 4, 5, 6)      # those of the plan, 64 x 64, 32 x 64
 STORE, RESIDUAL, SWIGLU, HEAD = 0, 1, 2, 3
 
 
@@ -92,7 +92,7 @@ def test_operands_off_the_16_byte_grid(epilogue):
     if epilogue == HEAD:
         assert not launch(HEAD, A, Wt, M, N, K)
     elif epilogue == STORE:
-        for tile in (-1, *TILES[:4]):
+        for tile in (-1, *TILES):
             assert launch(STORE, A, Wt, M, N, K, out := torch.full((M, N), float("nan"), device=DEV), tile=tile)
             assert torch.equal(out, want), tile
     else:
@@ -100,3 +100,29 @@ def test_operands_off_the_16_byte_grid(epilogue):
         z = want.double().view(M, N // 64, 2, 32)
         ref = (torch.nn.functional.silu(z[:, :, 0]) * z[:, :, 1]).reshape(M, N // 2)
         assert torch.allclose(act.double(), ref, rtol=2.0 ** -8 + 2.0 ** -16, atol=1e-30)
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("tile", TILES)
+def test_queries_keys_and_values_land_where_they_belong(tile, hd):
+    """Rotations by multiples of a quarter turn: every output is a whole number that bf16 holds."""
+    Hq, Hkv, L, C_, K = 5, 2, 21, 1 if tile == 4 else 14, 64
+    M, Lp = C_ * L, 32
+    A, Wt = whole((M, K), 10, 1), whole(((Hq + 2 * Hkv) * hd, K), 11, 1)
+    turn = torch.randint(0, 4, (M, hd // 2), generator=torch.Generator().manual_seed(12)).to(DEV)
+    c, s = torch.tensor([1.0, 0, -1, 0], device=DEV)[turn], torch.tensor([0, 1.0, 0, -1], device=DEV)[turn]
+    cs = torch.cat([c, s], 1).contiguous()
+    new = lambda *shape: torch.full(shape, float("nan"), dtype=torch.bfloat16, device=DEV)
+    q, k, v = new(M, Hq, hd), new(M, Hkv, hd), new(C_, Hkv, hd, Lp)
+    f = library()._Z25launch_gemm_mfma_qkv_ropePKDF16bS0_PKfPDF16bS3_S3_RK9BatchGeomRK9ModelDimsiiP12ihipStream_t
+    p = C.c_void_p
+    f.restype, f.argtypes = C.c_bool, [p] * 6 + [C.POINTER(BatchGeom), C.POINTER(ModelDims), C.c_int, C.c_int, p]
+    g = BatchGeom(B=1, n=C_, L=L, M=M, Lk=L, vs=Lp)
+    md = ModelDims(d=K, Hq=Hq, Hkv=Hkv, hd=hd)
+    assert f(*(t.data_ptr() for t in (A, Wt, cs, q, k, v)), g, md, Lp, tile, torch.cuda.current_stream().cuda_stream)
+    y = (A.float() @ Wt.float().t()).view(M, Hq + 2 * Hkv, hd)
+    x1, x2 = y[:, :Hq + Hkv, :hd // 2], y[:, :Hq + Hkv, hd // 2:]
+    rot = torch.cat([x1 * c[:, None] - x2 * s[:, None], x2 * c[:, None] + x1 * s[:, None]], 2)
+    assert torch.equal(q.float(), rot[:, :Hq]) and torch.equal(k.float(), rot[:, Hq:])
+    vals = y[:, Hq + Hkv:].view(C_, L, Hkv, hd).permute(0, 2, 3, 1)
+    assert torch.equal(v.float(), torch.nn.functional.pad(vals, (0, Lp - L)))
