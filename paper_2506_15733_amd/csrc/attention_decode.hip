@@ -7,7 +7,7 @@
 
 bool launch_attention_mfma_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                                   const bf16_t* poolV, const BatchGeom& g, const ModelDims& md, int Lp, const DecodeRuns& runs,
-                                  float* part, size_t part_floats, bool with_block, hipStream_t s);
+                                  float* part, size_t part_floats, bool with_block, const WeightsAhead& ahead, hipStream_t s);
 bool decode_block_beside(const BatchGeom& g, const ModelDims& md, int Lp, const DecodeRuns& runs, size_t part_floats);
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -341,10 +341,10 @@ int decode_block_kernel(const BatchGeom& g, const ModelDims& md, int Lp, const D
 // Returns false when the shape is not taken (the caller then uses the plain kernel).
 bool launch_attention_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                              const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,
-                             const DecodeRuns& runs, float* part, size_t part_floats, hipStream_t s) {
+                             const DecodeRuns& runs, float* part, size_t part_floats, const WeightsAhead& ahead, hipStream_t s) {
   const int kernel = decode_block_kernel(g, md, Lp, runs, part_floats);
   const bool with_block = kernel == 0;
-  if (!launch_attention_mfma_decode(q, kb, vbT, poolK, poolV, g, md, Lp, runs, part, part_floats, with_block, s)) return false;
+  if (!launch_attention_mfma_decode(q, kb, vbT, poolK, poolV, g, md, Lp, runs, part, part_floats, with_block, ahead, s)) return false;
   const int n_splits = runs.count;
   const size_t rows_all = (size_t)g.B * md.Hkv * (n_splits + (with_block ? 1 : 0)) * g.n * (md.Hq / md.Hkv);
   MergeArgs a;

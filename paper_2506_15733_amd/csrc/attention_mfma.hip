@@ -28,6 +28,9 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 #define LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 #define GLB_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
+// Tables that no kernel writes while this one runs, read by scalar loads. (Left to itself the compiler takes vector loads where it
+// cannot rule out that the stores and loads to LDS before them change the table, and then waits for all of these.)
+typedef const __attribute__((address_space(4))) int32_t* table_t;
 
 struct AttnArgs {
   const bf16_t* q;      // [M][Hq][hd]
@@ -50,6 +53,7 @@ struct AttnArgs {
                         // single positions: [b*Hkv + kvh][part_splits][n*g rows][HD]
   float* part_m;        // [..][128] running maximum (log2 domain), -inf if the run was empty
   float* part_l;        // [..][128] sum of weights relative to that maximum
+  WeightsAhead ahead;   // touched by the workgroups with blockIdx.y > 0 (an id that costs no argument to know)
 };
 
 // The value of lane l and of lane l ^ 32 (v_permlane32_swap: the upper half of one copy trades places with the lower
@@ -171,6 +175,18 @@ __device__ __forceinline__ void block_part(const AttnArgs& a, int id, char* smem
   }
 }
 
+// The launches of a few hundred rows leave CUs and nearly all of HBM idle while their chain of softmaxes runs, and the projections
+// behind them wait for weights: what these CUs touch meanwhile comes out of the Infinity Cache afterwards.
+__device__ __forceinline__ void touch_weights(const WeightsAhead& a, char* smem) {
+  const uint32_t all = gridDim.x * (gridDim.y - 1) * 256, first = (gridDim.x * (blockIdx.y - 1) + blockIdx.x) * 256 + threadIdx.x;
+  char* dst = smem + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 256;
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+    for (uint32_t i = first; i < a.lines[r]; i += all)
+      __builtin_amdgcn_global_load_lds(GLB_PTR(a.at[r] + (size_t)i * 32), LDS_PTR(dst), 4, 0, 0);
+  __builtin_amdgcn_s_waitcnt(0x0f70);                  // vmcnt(0)
+}
+
 // MODE 0: whole blocks, as described above. MODE 1: one position per candidate; the stacked rows of a
 // (beam, kv head) are its n candidates x g query heads (row r = i*g + j), the workgroup covers only one run of
 // run_tiles prefix tiles and writes (O un-normalised, m, l) instead of the output; the candidate's own block keys
@@ -191,6 +207,10 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
   constexpr int BQ = 128 * QT;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
 
+  if (blockIdx.y != 0) {
+    touch_weights(a.ahead, smem);
+    return;
+  }
   // workgroup id -> logical index: each XCD (id % 8) takes a contiguous run of the (beam, kv head, candidate, tile)
   // list; single positions deal the (beam, kv head, run) list round, since beams of different lengths lie in a row, and
   // keep the query tiles of one entry together
@@ -230,13 +250,13 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
   // the wavefront index as a scalar: page ids, page bases and LDS destinations then live in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int lq = lane & 31, lh = lane >> 5;
-  const int P = G.len_override >= 0 ? G.len_override : G.lens[G.b0 + b];
+  const int P = G.len_override >= 0 ? G.len_override : ((table_t)G.lens)[G.b0 + b];
   const int L = G.L;
   const int cand_idx = b * G.n + cand;
   const size_t m_c0 = (size_t)cand_idx * L;                 // first row of this candidate
   const int rows_total = DEC ? G.n * g : L * g;
   const int r_wg0 = qt_idx * BQ;
-  const int32_t* ptab = G.page_table + (size_t)(G.b0 + b) * G.max_pages;
+  const table_t ptab = (table_t)G.page_table + (size_t)(G.b0 + b) * G.max_pages;
 
   // --- queries of this wavefront as B-operand fragments (column = query) ---
   int tq[QT];
@@ -513,7 +533,9 @@ static void launch_attn_variant(const AttnArgs& a, hipStream_t s) {
                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     configured = true;
   }
-  attention_mfma_kernel<HD, QT, MODE><<<dim3(a.wg_per_xcd * 8 + a.block_wgs), 256, smem, s>>>(a);
+  // beside workgroups that leave CUs without one only (32 beams x 8 candidates x 12 heads, 608: nothing gained)
+  const int own = a.wg_per_xcd * 8 + a.block_wgs, more = own > 256 ? 0 : (a.ahead.wgs + own - 1) / own;
+  attention_mfma_kernel<HD, QT, MODE><<<dim3(own, 1 + more), 256, smem, s>>>(a);
 }
 
 // Merge of the partial results of a MODE 2 launch: HD / 4 lanes per (row, query head), each 16 bytes of it, with all of the
@@ -567,9 +589,10 @@ __global__ void __launch_bounds__(256) attention_split_merge_kernel(const float*
 // part: scratch of part_floats floats for launches whose key tiles are split over several workgroups (may be null).
 bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                            const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,
-                           int max_ctx, float* part, size_t part_floats, hipStream_t s) {
+                           int max_ctx, float* part, size_t part_floats, const WeightsAhead& ahead, hipStream_t s) {
   if ((md.hd != 64 && md.hd != 128) || g.page_tokens != 16 || Lp % 16 != 0) return false;
   AttnArgs a;
+  a.ahead = ahead;
   a.q = q; a.kb = kb; a.vbT = vbT; a.poolK = poolK; a.poolV = poolV; a.out = out; a.g = g;
   a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lp = Lp;
   a.last_first = g.B == 1 && g.n == 1;
@@ -676,9 +699,10 @@ bool decode_block_beside(const BatchGeom& g, const ModelDims& md, int Lp, const 
 // (floats); returns false if the shape is not taken or the partials of the prefix would not fit.
 bool launch_attention_mfma_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                                   const bf16_t* poolV, const BatchGeom& g, const ModelDims& md, int Lp, const DecodeRuns& runs,
-                                  float* part, size_t part_floats, bool with_block, hipStream_t s) {
+                                  float* part, size_t part_floats, bool with_block, const WeightsAhead& ahead, hipStream_t s) {
   if ((md.hd != 64 && md.hd != 128) || g.page_tokens != 16 || g.L != 1 || runs.count < 1) return false;
   AttnArgs a;
+  a.ahead = ahead;
   a.last_first = 0;
   a.q = q; a.kb = kb; a.vbT = vbT; a.poolK = poolK; a.poolV = poolV; a.out = nullptr; a.g = g;
   a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lp = Lp;

@@ -158,13 +158,17 @@ bool launch_few_rows_logits(const float* x, const float* gain, const bf16_t* W, 
 // x[M, N] += A[M, K] W[N, K]^T
 bool launch_few_rows_residual(const bf16_t* A, const bf16_t* W, float* x, int M, int N, int K, hipStream_t s);
 
+// Weights that the launches behind an attention launch read: workgroups beside its own (at least wgs of them, 0: none) touch a
+// word of every 128-byte line.
+struct WeightsAhead { const uint32_t* at[3]; uint32_t lines[3]; int wgs; };
+
 template <typename T>
 void launch_attention_simple(const T* q, const T* kb, const T* vbT, const T* poolK, const T* poolV, T* out,
                              const BatchGeom& g, const ModelDims& md, int max_ctx, hipStream_t s);
 // part / part_floats: float scratch for launches that split the key tiles over workgroups (null: never split)
 bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                            const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,
-                           int max_ctx, float* part, size_t part_floats, hipStream_t s);
+                           int max_ctx, float* part, size_t part_floats, const WeightsAhead& ahead, hipStream_t s);
 
 // The same launches with the two-phase schedule (attention_pingpong.hip): 256 stacked rows of all candidates of a
 // (beam, kv head) per workgroup. False if the shape is not taken.
@@ -181,7 +185,7 @@ struct DecodeRuns { int tiles, count; };   // key tiles of a run, runs of the lo
 DecodeRuns plan_decode_runs(const BatchGeom& g, const ModelDims& md, const int32_t* lens_host, size_t part_floats);
 bool launch_attention_decode(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* poolK,
                              const bf16_t* poolV, bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp,
-                             const DecodeRuns& runs, float* part, size_t part_floats, hipStream_t s);
+                             const DecodeRuns& runs, float* part, size_t part_floats, const WeightsAhead& ahead, hipStream_t s);
 
 // Fused vocabulary head: per (row, 64-column tile) partial (max, sum exp) and the target-token logit.
 template <typename T>

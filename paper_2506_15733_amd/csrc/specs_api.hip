@@ -537,7 +537,32 @@ int lmhead_partials<bf16_t>(const bf16_t* A, const bf16_t* W, const int32_t* tok
 template <typename T>
 static void attention(const T* q, const T* kb, const T* vbT, const T* pK, const T* pV, T* out, const BatchGeom& g,
                       const ModelDims& md, int Lp, int max_ctx, const DecodeRuns& runs, float* scratch,
-                      size_t scratch_floats, hipStream_t s);
+                      size_t scratch_floats, const WeightsAhead& ahead, hipStream_t s);
+// What of a layer's weights to touch during the attention of `rows` rows: of the O projection, gate and up, and down, in this order,
+// as much as comes in beside such a launch (24 MB). Up to 256 rows, whose projections are bound by how soon and fast their weights
+// arrive (step of 256 rows of d = 1024 1.28 -> 1.26 ms, generation of 16 rows of d = 1536 95.2 -> 94.0; 1024 rows of d = 1536 10.19 ->
+// 10.24), not where a layer is so large that this is little of it (d = 3584: 117.5 -> 118.1), and not where a model that is
+// generating fits the Infinity Cache and is there from the position before (165 MB of d = 1024: 6.65 -> 6.75).
+template <typename T>
+static WeightsAhead weights_ahead(const specs_layer_weights&, const specs_model_desc&, int, bool) { return WeightsAhead{}; }
+template <>
+WeightsAhead weights_ahead<bf16_t>(const specs_layer_weights& L, const specs_model_desc& d, int rows, bool position) {
+  WeightsAhead a = {};
+  const size_t dm = d.d_model, qd = (size_t)d.n_q_heads * d.head_dim, kvd = (size_t)d.n_kv_heads * d.head_dim;
+  const size_t bytes[3] = {2 * qd * dm, 4 * dm * d.ffn, 2 * dm * d.ffn}, layer = bytes[0] + bytes[1] + bytes[2];
+  const size_t model = d.n_layers * (layer + 2 * dm * (qd + 2 * kvd)) + (d.head == SPECS_HEAD_LM ? 2 * dm * d.vocab : 0);
+  if (rows > 256 || layer > 128u << 20 || (position && model < 256u << 20)) return a;
+  const void* at[3] = {L.wo, L.wgu, L.wd};
+  size_t room = 24u << 20;
+  for (int i = 0; i < 3; ++i) {
+    const size_t some = bytes[i] < room ? bytes[i] : room, skip = -(uintptr_t)at[i] & 3;
+    a.at[i] = (const uint32_t*)((const char*)at[i] + skip);
+    a.lines[i] = some < 128 ? 0 : (uint32_t)((some - skip) / 128);
+    room -= some;
+  }
+  a.wgs = 128;
+  return a;
+}
 
 // A stretch of one beam's prompt in a prefill launch: tokens c0 .. c0 + rows - 1 of beam b, in rows `row` .. of the
 // launch. All but the last stretch occupy rows rounded up to stretch_unit, the surplus ones being copies of their last
@@ -638,7 +663,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
                launch_gather_last_rows<T>((const T*)ws.q, q1, qd, x, ws.xs, md.d, (int)C, g.L, s));
       PROFILED(ctx, SPECS_K_ATTENTION, s,
                attention<T>(q1, kb, vb, pK, pV, (T*)ws.attn, gl, md, Lp, max_ctx, runs, ws.gu,
-                            ws.gu_floats, s));
+                            ws.gu_floats, weights_ahead<T>(L, d, gl.M, false), s));
       int pl = 0;
       PROFILED(ctx, SPECS_K_OPROJ, s,
                pl = gemm_residual_split<T>((const T*)ws.attn, (const T*)L.wo, ws.xs, ws.gu, max_split_of(gl.M), gl.M, md.d, qd, s));
@@ -669,14 +694,14 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
         const BatchGeom ga = stretch_geom(p, st, span(i), g.vs);
         PROFILED(ctx, SPECS_K_ATTENTION, s,
                  attention<T>((const T*)ws.q + r * qd, kb + r * kvd, vb + r, pK, pV, (T*)ws.attn + r * qd, ga, md,
-                              round16(ga.L), st.c0, runs, ws.gu, ws.gu_floats, s));
+                              round16(ga.L), st.c0, runs, ws.gu, ws.gu_floats, WeightsAhead{}, s));
         launch_kv_commit<T>(kb + r * kvd, vb + r, pK, pV, stretch_geom(p, st, st.rows, g.vs), md, g.vs, nullptr, 1, 0, 0, 0,
                             s);
       }
     } else {
       PROFILED(ctx, SPECS_K_ATTENTION, s,
                attention<T>((const T*)ws.q, kb, vb, pK, pV, (T*)ws.attn, g, md, Lp, max_ctx, runs,
-                            ws.gu, ws.gu_floats, s));
+                            ws.gu, ws.gu_floats, weights_ahead<T>(L, d, g.M, g.L < g.Lk), s));
     }
     int parts = 0;
     PROFILED(ctx, SPECS_K_OPROJ, s,
@@ -1068,14 +1093,14 @@ extern "C" int specs_op_lmhead_logprob(specs_ctx* ctx, int32_t dtype, const void
 template <typename T>
 static void attention(const T* q, const T* kb, const T* vbT, const T* pK, const T* pV, T* out, const BatchGeom& g,
                       const ModelDims& md, int Lp, int max_ctx, const DecodeRuns& runs, float* scratch,
-                      size_t scratch_floats, hipStream_t s) {
+                      size_t scratch_floats, const WeightsAhead&, hipStream_t s) {
   count_path(SPECS_PATH_ATTN_PLAIN);
   launch_attention_simple<T>(q, kb, vbT, pK, pV, out, g, md, max_ctx, s);
 }
 template <>
 void attention<bf16_t>(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, const bf16_t* pK, const bf16_t* pV,
                        bf16_t* out, const BatchGeom& g, const ModelDims& md, int Lp, int max_ctx,
-                       const DecodeRuns& runs, float* scratch, size_t scratch_floats, hipStream_t s) {
+                       const DecodeRuns& runs, float* scratch, size_t scratch_floats, const WeightsAhead& ahead, hipStream_t s) {
   bool whole_blocks = g.t0 == 0 && g.Lk == g.L;
   // Launches with at least ~160 workgroups of 256 stacked rows take the two-phase kernel (measured 3-8 % faster
   // at the 7B shapes); smaller ones the one-phase kernel, which cuts long key lists over several workgroups.
@@ -1085,12 +1110,12 @@ void attention<bf16_t>(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT, con
       count_path(SPECS_PATH_ATTN_MFMA);
       return;
     }
-    if (launch_attention_mfma(q, kb, vbT, pK, pV, out, g, md, Lp, max_ctx, scratch, scratch_floats, s)) {
+    if (launch_attention_mfma(q, kb, vbT, pK, pV, out, g, md, Lp, max_ctx, scratch, scratch_floats, ahead, s)) {
       count_path(SPECS_PATH_ATTN_MFMA);
       return;
     }
   } else if (g.L == 1 && scratch &&
-             launch_attention_decode(q, kb, vbT, pK, pV, out, g, md, Lp, runs, scratch, scratch_floats, s)) {
+             launch_attention_decode(q, kb, vbT, pK, pV, out, g, md, Lp, runs, scratch, scratch_floats, ahead, s)) {
     count_path(SPECS_PATH_ATTN_MFMA);
     return;
   }
@@ -1115,11 +1140,11 @@ extern "C" int specs_op_attention(specs_ctx* ctx, const specs_model* m, const sp
   if (d.dtype == SPECS_BF16) {
     launch_transpose_v<bf16_t>((const bf16_t*)vb, (bf16_t*)vT, cands, md.Hkv, md.hd, L, Lp, ctx->stream);
     attention<bf16_t>((const bf16_t*)q, (const bf16_t*)kb, (const bf16_t*)vT, pool_ptr<bf16_t>(p, d, layer, 0),
-                      pool_ptr<bf16_t>(p, d, layer, 1), (bf16_t*)out, g, md, Lp, max_ctx, DecodeRuns{}, nullptr, 0, ctx->stream);
+                      pool_ptr<bf16_t>(p, d, layer, 1), (bf16_t*)out, g, md, Lp, max_ctx, DecodeRuns{}, nullptr, 0, WeightsAhead{}, ctx->stream);
   } else {
     launch_transpose_v<float>((const float*)vb, (float*)vT, cands, md.Hkv, md.hd, L, Lp, ctx->stream);
     attention<float>((const float*)q, (const float*)kb, (const float*)vT, pool_ptr<float>(p, d, layer, 0),
-                     pool_ptr<float>(p, d, layer, 1), (float*)out, g, md, Lp, max_ctx, DecodeRuns{}, nullptr, 0, ctx->stream);
+                     pool_ptr<float>(p, d, layer, 1), (float*)out, g, md, Lp, max_ctx, DecodeRuns{}, nullptr, 0, WeightsAhead{}, ctx->stream);
   }
   HIP_TRY(hipGetLastError());
   ctx->last_model = nullptr;
