@@ -39,13 +39,13 @@ struct GemmArgs {
   int part_tiles;        // ME_LMHEAD: entries of a row in part_max and part_sum
   // ME_QKV_ROPE: the product is the QKV projection [M, (Hq + 2 Hkv) * hd]; the epilogue rotates the q and k heads
   // (pairs (i, i + hd/2), angles from the table cs[M][hd] = cos | sin) and writes bf16 q [M][Hq][hd], block keys
-  // kblk[M][Hkv][hd] and block values transposed per candidate vT[cand][Hkv][hd][Lp], where row m is in-block position
-  // t = m % Lrows of candidate m / Lrows.
+  // kblk[cand][Lk][Hkv][hd] and block values transposed per candidate vT[cand][Hkv][hd][Lp], where row m is in-block position
+  // t0 + m % Lrows of candidate m / Lrows.
   const float* cs;
   bf16_t* q;
   bf16_t* kblk;
   bf16_t* vT;
-  int Hq, Hkv, Lrows, Lp;
+  int Hq, Hkv, Lrows, Lk, Lp, t0;
 };
 
 // One direct-to-LDS load instruction: the workgroup's NW wavefronts write NW consecutive 1 KiB spans
@@ -205,12 +205,12 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, floatx4 (&acc)[TM][4
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const int row = m + i * 16 + r16;
-        const int cand = row / a.Lrows, t = row - cand * a.Lrows;
+        const int cand = row / a.Lrows, t = a.t0 + row - cand * a.Lrows;
         if (head < a.Hq + a.Hkv) {
           if (row >= a.M) continue;
           const float* cs = a.cs + (size_t)row * HDIM;
           bf16_t* dst = head < a.Hq ? a.q + ((size_t)row * a.Hq + head) * HDIM
-                                    : a.kblk + ((size_t)row * a.Hkv + (head - a.Hq)) * HDIM;
+                                    : a.kblk + (((size_t)cand * a.Lk + t) * a.Hkv + (head - a.Hq)) * HDIM;
 #pragma unroll
           for (int j = 0; j < 2; ++j) {
             const int i0 = i_base + 16 * j;
@@ -243,13 +243,13 @@ __device__ __forceinline__ void epilogue(const GemmArgs& a, floatx4 (&acc)[TM][4
           }
           // The positions that pad a candidate's block to whole 16s: the wavefront that holds its last row clears them, a
           // lane per column (the lanes of that row on their own took 32 stores a position).
-          unsigned ends = (unsigned)(__ballot(row < a.M && t == a.Lrows - 1 && a.Lp > a.Lrows) & 0xffff);
+          unsigned ends = (unsigned)(__ballot(row < a.M && t == a.Lk - 1 && a.Lp > a.Lk) & 0xffff);
           while (ends) {
             const int of = __builtin_amdgcn_readlane(cand, __builtin_ctz(ends));
             ends &= ends - 1;
             const int d = HD128 ? wq * 32 + (lane & 31) + (lane >> 5) * HALF : lane;
             bf16_t* pad = head_v + of * cand_v + (size_t)d * a.Lp;
-            for (int k = a.Lrows; k < a.Lp; ++k) pad[k] = (__bf16)0.f;
+            for (int k = a.Lk; k < a.Lp; ++k) pad[k] = (__bf16)0.f;
           }
         }
       }
@@ -861,23 +861,35 @@ void mfma_gemm_tile(int M, int N, int K, int max_split, bool wide_only, int* til
 
 // QKV projection with the rotary embedding, the bf16 conversion and the per-candidate transposition of the values
 // in the epilogue: no float [M, (Hq+2Hkv)*hd] round trip through memory and no separate kernel. Row m is in-block
-// position m % g.L of candidate m / g.L. Returns false when the shape is not taken (head_dim other than 64/128,
-// K % 64 != 0, misaligned buffers, launches of one position of longer blocks); the caller then runs the projection and
+// position g.t0 + m % g.L of candidate m / g.L. Returns false when the shape is not taken (head_dim other than 64/128,
+// K % 64 != 0, misaligned buffers, parts of blocks other than single positions); the caller then runs the projection and
 // the rotary kernel separately.
 bool launch_gemm_mfma_qkv_rope(const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q, bf16_t* kblk, bf16_t* vT,
                                const BatchGeom& g, const ModelDims& md, int Lp, int tile, hipStream_t s) {
   const int M = g.M, N = (md.Hq + 2 * md.Hkv) * md.hd, K = md.d;
-  if (K % 64 != 0 || M <= 0 || (md.hd != 64 && md.hd != 128) || g.t0 != 0 || g.Lk != g.L) return false;
+  if (K % 64 != 0 || M <= 0 || (md.hd != 64 && md.hd != 128) || (g.L != 1 && (g.t0 != 0 || g.Lk != g.L))) return false;
   if (((uintptr_t)cs & 15) || ((uintptr_t)q & 7) || ((uintptr_t)kblk & 7)) return false;
   GemmArgs a = {};
   a.A = A; a.W = W; a.M = M; a.N = N; a.K = K; a.ksplit = 1;
   a.cs = cs; a.q = q; a.kblk = kblk; a.vT = vT;
-  a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lrows = g.L; a.Lp = Lp;
+  a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lrows = g.L; a.Lk = g.Lk; a.Lp = Lp; a.t0 = g.t0;
   int split = 1;
   if (tile < 0) mfma_gemm_tile(M, N, K, 1, false, &tile, &split);
   if (md.hd == 128) launch_tile<ME_QKV_ROPE, true>(a, tile, s);
   else launch_tile<ME_QKV_ROPE, false>(a, tile, s);
   return true;
+}
+
+// Whether single positions of more rows than the kernels for few rows take have their rotary embedding in the epilogue. The
+// projection can then not be cut into slices of K (up to max_split), so where the plan wants some, only if the whole walk is short or
+// every CU's share of it small. Against slices and the rotary kernel's 6 us (us, cold weights): 256 x 2048 x 1536 8.2 + 6.2 / 8.8;
+// 48 x 4608 x 3584 11 + 6 / 15, but 128 rows 12.4 + 6 / 20.
+bool qkv_rope_position(int M, int N, int K, int max_split) {
+  int tile, split;
+  mfma_gemm_tile(M, N, K, max_split, false, &tile, &split);
+  if (split == 1 || K <= 2048) return true;
+  mfma_gemm_tile(M, N, K, 1, false, &tile, &split);
+  return tile == TILE_32;
 }
 
 // Returns false when the shape is not one this kernel takes (the caller then uses the SIMT kernel).

@@ -437,21 +437,20 @@ int gemm_store_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* C, int max
   return 1;
 }
 
-// Rotary embedding, conversion and value transposition inside the projection's epilogue: bf16 launches of whole blocks.
-// (One position per block writes a column of the transposed values, a cache line per element, which the two or three
-// workgroups of the value heads alone are slow at: those launches leave it to the rotary kernel, or to the kernel for few
-// rows, whose tiles are narrow.)
+// Rotary embedding, conversion and value transposition inside the projection's epilogue: bf16 launches of whole blocks, and
+// of one position per block where the projection does not gain more from slices of K (max_split at most). Blocks that have no
+// more than one token, which no workload scores or generates, keep the rotary kernel.
 template <typename T>
-static bool qkv_rope_fused(const T*, const T*, const float*, T*, T*, T*, const BatchGeom&, const ModelDims&, int,
+static bool qkv_rope_fused(const T*, const T*, const float*, T*, T*, T*, const BatchGeom&, const ModelDims&, int, int,
                            hipStream_t) {
   return false;
 }
 template <>
 bool qkv_rope_fused<bf16_t>(const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q, bf16_t* kb, bf16_t* vT,
-                            const BatchGeom& g, const ModelDims& md, int Lp, hipStream_t s) {
-  if (g.L == 1 ? !launch_few_rows_qkv_rope(nullptr, nullptr, A, W, cs, q, kb, vT, g, md, Lp, s)
-               : !launch_gemm_mfma_qkv_rope(A, W, cs, q, kb, vT, g, md, Lp, -1, s))
-    return false;
+                            const BatchGeom& g, const ModelDims& md, int Lp, int max_split, hipStream_t s) {
+  const bool few = g.L == 1 && launch_few_rows_qkv_rope(nullptr, nullptr, A, W, cs, q, kb, vT, g, md, Lp, s);
+  if (!few && g.L == 1 && (g.M <= 32 || g.Lk == 1 || !qkv_rope_position(g.M, (md.Hq + 2 * md.Hkv) * md.hd, md.d, max_split))) return false;
+  if (!few && !launch_gemm_mfma_qkv_rope(A, W, cs, q, kb, vT, g, md, Lp, -1, s)) return false;
   count_mfma(g.M);
   return true;
 }
@@ -627,6 +626,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
     return (int)(room < MFMA_MAX_SPLIT ? room : MFMA_MAX_SPLIT);
   };
   const int max_split = max_split_of(g.M);
+  const int qkv_split = (int)(R / g.M < MFMA_MAX_SPLIT ? R / g.M : MFMA_MAX_SPLIT);   // ws.qkv has room for R / g.M slices of QKV
   DecodeRuns runs = {};
   if (d.dtype == SPECS_BF16 && !stretches && (g.L == 1 || last_token_only))
     runs = plan_decode_runs(g, md, p->lens.data(), ws.gu_floats);
@@ -647,11 +647,11 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
       PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(x, L.g_attn, (T*)ws.a, g.M, md.d, md.eps, s));
     if (!fused_rope)
       PROFILED_IF(ctx, SPECS_K_QKV, s, fused_rope,
-                  qkv_rope_fused<T>((const T*)ws.a, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, s));
+                  qkv_rope_fused<T>((const T*)ws.a, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, qkv_split, s));
     if (!fused_rope) {
-      int qkv_parts = 1;                                 // ws.qkv has room for R / g.M slices of the projection
+      int qkv_parts = 1;
       PROFILED(ctx, SPECS_K_QKV, s,
-               qkv_parts = gemm_store_split<T>((const T*)ws.a, (const T*)L.wqkv, ws.qkv, (int)(R / g.M < MFMA_MAX_SPLIT ? R / g.M : MFMA_MAX_SPLIT),
+               qkv_parts = gemm_store_split<T>((const T*)ws.a, (const T*)L.wqkv, ws.qkv, qkv_split,
                                                g.M, qd + 2 * kvd, md.d, s));
       PROFILED(ctx, SPECS_K_OTHER, s, launch_rope_split<T>(ws.qkv, qkv_parts, ws.cs, (T*)ws.q, kb, vb, g, Lp, md, s));
     }
@@ -1169,11 +1169,11 @@ extern "C" int specs_op_qkv_rope(specs_ctx* ctx, const specs_model* m, const spe
   HIP_TRY(hipSetDevice(ctx->device));
   launch_rope_table(cs, g, md.hd, md.rope_base, s);
   if (d.dtype == SPECS_BF16) {
+    const size_t room = (ctx->workspace_bytes - 256 - cs_bytes) / ((size_t)g.M * width * sizeof(float));
+    const int max_split = (int)(room < MFMA_MAX_SPLIT ? room : MFMA_MAX_SPLIT);
     if (!qkv_rope_fused<bf16_t>((const bf16_t*)A, (const bf16_t*)Wqkv, cs, (bf16_t*)q, (bf16_t*)kblk, (bf16_t*)vT, g, md, Lp,
-                                s)) {
-      const size_t room = (ctx->workspace_bytes - 256 - cs_bytes) / ((size_t)g.M * width * sizeof(float));
-      int parts = gemm_store_split<bf16_t>((const bf16_t*)A, (const bf16_t*)Wqkv, qkv,
-                                           (int)(room < MFMA_MAX_SPLIT ? room : MFMA_MAX_SPLIT), g.M, (int)width, md.d, s);
+                                max_split, s)) {
+      int parts = gemm_store_split<bf16_t>((const bf16_t*)A, (const bf16_t*)Wqkv, qkv, max_split, g.M, (int)width, md.d, s);
       launch_rope_split<bf16_t>(qkv, parts, cs, (bf16_t*)q, (bf16_t*)kblk, (bf16_t*)vT, g, Lp, md, s);
     }
   } else {

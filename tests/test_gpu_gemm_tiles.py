@@ -102,27 +102,35 @@ def test_operands_off_the_16_byte_grid(epilogue):
         assert torch.allclose(act.double(), ref, rtol=2.0 ** -8 + 2.0 ** -16, atol=1e-30)
 
 
+@pytest.mark.parametrize("position", [None, 0, 9, 20])   # whole blocks of 21 tokens, or one token of each
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("tile", TILES)
-def test_queries_keys_and_values_land_where_they_belong(tile, hd):
+def test_queries_keys_and_values_land_where_they_belong(tile, hd, position):
     """Rotations by multiples of a quarter turn: every output is a whole number that bf16 holds."""
-    Hq, Hkv, L, C_, K = 5, 2, 21, 1 if tile == 4 else 14, 64
-    M, Lp = C_ * L, 32
+    Hq, Hkv, Lk, C_, K, Lp = 5, 2, 21, 1 if tile == 4 else 14 if position is None else 70, 64, 32
+    L = Lk if position is None else 1
+    M = C_ * L
     A, Wt = whole((M, K), 10, 1), whole(((Hq + 2 * Hkv) * hd, K), 11, 1)
     turn = torch.randint(0, 4, (M, hd // 2), generator=torch.Generator().manual_seed(12)).to(DEV)
     c, s = torch.tensor([1.0, 0, -1, 0], device=DEV)[turn], torch.tensor([0, 1.0, 0, -1], device=DEV)[turn]
     cs = torch.cat([c, s], 1).contiguous()
     new = lambda *shape: torch.full(shape, float("nan"), dtype=torch.bfloat16, device=DEV)
-    q, k, v = new(M, Hq, hd), new(M, Hkv, hd), new(C_, Hkv, hd, Lp)
+    q, k, v = new(M, Hq, hd), new(C_, Lk, Hkv, hd), new(C_, Hkv, hd, Lp)
     f = library()._Z25launch_gemm_mfma_qkv_ropePKDF16bS0_PKfPDF16bS3_S3_RK9BatchGeomRK9ModelDimsiiP12ihipStream_t
     p = C.c_void_p
     f.restype, f.argtypes = C.c_bool, [p] * 6 + [C.POINTER(BatchGeom), C.POINTER(ModelDims), C.c_int, C.c_int, p]
-    g = BatchGeom(B=1, n=C_, L=L, M=M, Lk=L, vs=Lp)
+    g = BatchGeom(B=1, n=C_, L=L, M=M, t0=position or 0, Lk=Lk, vs=Lp)
     md = ModelDims(d=K, Hq=Hq, Hkv=Hkv, hd=hd)
     assert f(*(t.data_ptr() for t in (A, Wt, cs, q, k, v)), g, md, Lp, tile, torch.cuda.current_stream().cuda_stream)
     y = (A.float() @ Wt.float().t()).view(M, Hq + 2 * Hkv, hd)
     x1, x2 = y[:, :Hq + Hkv, :hd // 2], y[:, :Hq + Hkv, hd // 2:]
     rot = torch.cat([x1 * c[:, None] - x2 * s[:, None], x2 * c[:, None] + x1 * s[:, None]], 2)
-    assert torch.equal(q.float(), rot[:, :Hq]) and torch.equal(k.float(), rot[:, Hq:])
-    vals = y[:, Hq + Hkv:].view(C_, L, Hkv, hd).permute(0, 2, 3, 1)
-    assert torch.equal(v.float(), torch.nn.functional.pad(vals, (0, Lp - L)))
+    assert torch.equal(q.float(), rot[:, :Hq])
+    at = slice(0, Lk) if position is None else slice(position, position + 1)
+    want_k, want_v = torch.full_like(k, float("nan")).float(), torch.full_like(v, float("nan")).float()
+    want_k[:, at] = rot[:, Hq:].view(C_, L, Hkv, hd)
+    want_v[..., at] = y[:, Hq + Hkv:].view(C_, L, Hkv, hd).permute(0, 2, 3, 1)
+    if at.stop == Lk:                                    # with the last token, what pads a row of values
+        want_v[..., Lk:] = 0
+    for got, want in ((k, want_k), (v, want_v)):         # nothing else is written
+        assert torch.equal(torch.nan_to_num(got.float(), nan=1e9), torch.nan_to_num(want, nan=1e9))
