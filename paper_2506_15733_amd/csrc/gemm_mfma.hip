@@ -339,7 +339,7 @@ __device__ __forceinline__ void slice_tiles(const GemmArgs& a, int kslice, int& 
   __builtin_amdgcn_s_waitcnt(((n) & 15) | ((n) >> 4) << 14 | 0x70); \
   MEET()
 
-// The BM x 256 tile (BM 256 or 128) of the product at (m0, n0), K slice kslice, by eight wavefronts 2 (M) x 4 (N).
+// The BM x 256 tile (BM 256, 192 or 128) of the product at (m0, n0), K slice kslice, by eight wavefronts 2 (M) x 4 (N).
 //
 // The two rows of wavefronts, one wavefront of each on every SIMD, run half a phase apart: while one multiplies (16 MFMAs, 64
 // rows x 32 columns x 64 deep of its part), the other reads the fragments of its next phase from LDS and requests operands,
@@ -357,9 +357,9 @@ __device__ __forceinline__ void slice_tiles(const GemmArgs& a, int kslice, int& 
 // slice (size 0), are zeros that cost no traffic.
 template <int BM, int EPI, bool HD128>
 __device__ __forceinline__ void wide_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
-  static_assert(BM == 256 || BM == 128, "two halves of A, or one");
+  static_assert(BM == 256 || BM == 192 || BM == 128, "two halves of A, or one");
   constexpr bool SWAP = EPI == ME_QKV_ROPE && HD128;
-  constexpr int NH = BM / 128, TM = 4 * NH, U = 8192;    // U: what one load of every wavefront fills
+  constexpr int NH = BM == 128 ? 1 : 2, TMH = BM / NH / 32, TM = TMH * NH, U = 8192;    // U: what one load of every wavefront fills
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int wm = wave >> 2, wn = wave & 3, r16 = lane & 15, quad = lane >> 4;
   int kt0, KT;
@@ -382,7 +382,10 @@ __device__ __forceinline__ void wide_product(const GemmArgs& a, int m0, int n0, 
     const int r = (p * 8 + wave) * 8 + (lane >> 3);
     const unsigned chunk = ((lane & 7) ^ ((r >> 1) & 7)) * 16;
 #pragma unroll
-    for (int h = 0; h < NH; ++h) aoff[h][p] = (unsigned)((r >> 6) * 64 * NH + h * 64 + (r & 63)) * row_bytes + chunk;
+    for (int h = 0; h < NH; ++h) {                       // rows beyond the half (BM = 192: 96 of 128) are zeros
+      const int wr = r / (16 * TMH), row = wr * 16 * TM + h * 16 * TMH + r - wr * 16 * TMH;
+      aoff[h][p] = wr < 2 ? (unsigned)row * row_bytes + chunk : 0x7fffffffu;
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int c = (r >> 5) * 64 + h * 32 + (r & 31);
@@ -402,12 +405,12 @@ __device__ __forceinline__ void wide_product(const GemmArgs& a, int m0, int n0, 
   // A fragment is 16 rows x 32 of K: lane l has row l % 16, chunk l / 16 (of 4; chunks 4..7 are the second 32). The rows of a
   // lane's fragments differ by multiples of 16, so they share their swizzle.
   const int sw = (r16 >> 1) & 7, c0 = (quad ^ sw) << 4, c1 = c0 ^ 64;
-  const int abase = (wm * 64 + r16) * 128, bbase = (wn * 32 + r16) * 128;
-  bf16x8 af[4][2], b0[2][2], b1[2][2];
+  const int abase = (wm * 16 * TMH + r16) * 128, bbase = (wn * 32 + r16) * 128;
+  bf16x8 af[TMH][2], b0[2][2], b1[2][2];
   auto read_a = [&](int slot) {
     const char* p = smem + slot * U + abase;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < TMH; ++i) {
       af[i][0] = *(const bf16x8*)(p + i * 2048 + c0);
       af[i][1] = *(const bf16x8*)(p + i * 2048 + c1);
     }
@@ -424,12 +427,12 @@ __device__ __forceinline__ void wide_product(const GemmArgs& a, int m0, int n0, 
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < TMH; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          acc[hm * 4 + i][hn * 2 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j][kk], af[i][kk], acc[hm * 4 + i][hn * 2 + j], 0, 0, 0);
+          acc[hm * TMH + i][hn * 2 + j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[j][kk], af[i][kk], acc[hm * TMH + i][hn * 2 + j], 0, 0, 0);
   };
-  if constexpr (BM == 256) {
+  if constexpr (NH == 2) {
     // Position s of the stream of halves: s = 0 is W0 of K-tile 0; of K-tile t A0 is 4t + 1, W1 4t + 2, A1 4t + 3 and the next
     // one's W0 4t + 4. Phase s reads half s. Its first part requests half s + 9, in the place of half s - 1, which
     // the later row of wavefronts has read in the first part of phase s - 1; eight halves are newer than the next one read.
@@ -663,7 +666,7 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
 
 template <int BM, int BN, int NWM, int S, int EPI, bool HD128, int REST = 0, bool BUFFER = true>
 static void launch_variant(const GemmArgs& a, hipStream_t s) {
-  constexpr int smem = BM == 256 ? 5 * 256 * 128 : S * (BM + BN) * 128;   // the rest's tiles take no more
+  constexpr int smem = BN == 256 && BM > 128 ? 5 * 256 * 128 : S * (BM + BN) * 128;   // the rest's tiles take no more
   static bool configured = false;
   if (!configured) {
     (void)hipFuncSetAttribute((const void*)gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128, REST, BUFFER>,
@@ -701,7 +704,7 @@ int mfma_gemm_ring(int tile, int M, int N, int K, int ksplit) {
 static bool buffer_operands(const GemmArgs& a) { return (((uintptr_t)a.A | (uintptr_t)a.W) & 15) == 0 && a.K <= 1 << 22; }
 
 // Tiles that only mfma_gemm_tile gives, behind those of the plan.
-enum { TILE_64 = MFMA_TILES, TILE_32, ALL_TILES };
+enum { TILE_64 = MFMA_TILES, TILE_32, TILE_192, ALL_TILES };
 
 int mfma_gemm_rest(int M, int N, int K, bool wide_only, int* n_tiles);
 bool mfma_gate_up_192(int M, int N, int K, int tile);
@@ -722,6 +725,13 @@ static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
       else launch_variant<32, 64, 2, 6, EPI, HD128>(a, s);
       return;
     }
+  a.part_tiles = mfma_lmhead_tiles(a.N);
+  if (tile == TILE_192) {
+    a.m_tiles = (a.M + 191) / 192;
+    a.n_tiles = (a.N + 255) / 256;
+    launch_variant<192, 256, 2, 5, EPI, HD128>(a, s);
+    return;
+  }
   if constexpr (EPI == ME_SWIGLU)
     if (mfma_gate_up_192(a.M, a.N, a.K, tile)) {
       a.m_tiles = (a.M + 127) / 128;
@@ -731,7 +741,6 @@ static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
     }
   a.m_tiles = (a.M + kTiles[tile].bm - 1) / kTiles[tile].bm;
   a.n_tiles = (a.N + kTiles[tile].bn - 1) / kTiles[tile].bn;
-  a.part_tiles = mfma_lmhead_tiles(a.N);
   if (tile == 0) {
     const int rest = EPI == ME_RESIDUAL || a.ksplit > 1 ? 0 : mfma_gemm_rest(a.M, a.N, a.K, EPI == ME_LMHEAD, &a.n_tiles);
     if (rest) {
@@ -844,19 +853,31 @@ void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* til
   if (*split_out == 1 && rest_plan(M, N, K, wide_only, &n_tiles, &step)) consider(0, 1, step);
 }
 
-// The plan's tile and slices, or a finer tile where the plan says 64 x 128 and the product leaves CUs without a workgroup of
-// that: what such a launch takes is how long its few CUs pull weights from HBM, so more and smaller workgroups are ahead as long
-// as each has a CU to itself. us with cold weights, of 64 x 128, 64 x 64 and 32 x 64: 256 x 2048 x 1024 10.3, 7.7, 6.7;
-// 256 x 2048 x 1536 14.8, 10.3, 8.6; 256 x 1024 x 1024 in 4 slices 6.1, 4.9, 5.4 (512 workgroups of the last, in 2: 5.2). A few CUs
-// with two of the 64 x 64 ones do no harm (555 x 2048 x 1536, 288 of them: 14.3 / 12.4); where many have two, 64 x 128 is ahead
-// (256 x 5632 x 1024: 352, 11.2 / 12.3; 1024 x 2048 x 1536: 512, 14.6 / 16.1). The slices stay the plan's: all tiles add a slice's
-// products in the same order, so the finer ones leave the same bits.
+// The plan's tile and slices, or a tile that it does not know with the same slices: all tiles add a slice's products in the same
+// order, so these leave the same bits.
+// 192 x 256 for 256 x 256 where the rounds they take are shorter: fewer rows that only pad, or a single round with more CUs in it
+// (us: 1600 x 4608 x 3584 64.2 / 54.9, 1100 rows 64.1 / 53.8, 1100 x 3584 x 18944 in 3 slices 130 / 119, gate/up of 555 x 9728 x 896
+// 21.9 / 18.3, head of 555 x 151936 x 1536 270 / 250; but 1600 x 17920 x 1536, 490 / 630 tiles, 76.6 / 96.5, 1300 x 37888 x 3584
+// 283 / 313, and 1100 x 17920 x 1536, where a rest makes up for the padding, 62.7 / 64.8). A k-step takes 0.85 of the larger tile's.
+// Finer ones where the plan says 64 x 128 and the product leaves CUs without a workgroup of that: what such a launch takes is how
+// long its few CUs pull weights from HBM, so more and smaller workgroups are ahead as long as each has a CU to itself. us with cold
+// weights, of 64 x 128, 64 x 64 and 32 x 64: 256 x 2048 x 1024 10.3, 7.7, 6.7; 256 x 2048 x 1536 14.8, 10.3, 8.6; 256 x 1024 x 1024 in 4
+// slices 6.1, 4.9, 5.4 (512 workgroups of the last, in 2: 5.2). A few CUs with two of the 64 x 64 ones do no harm (555 x 2048 x
+// 1536, 288 of them: 14.3 / 12.4); where many have two, 64 x 128 is ahead (256 x 5632 x 1024: 352, 11.2 / 12.3;
+// 1024 x 2048 x 1536: 512, 14.6 / 16.1).
 void mfma_gemm_tile(int M, int N, int K, int max_split, bool wide_only, int* tile_out, int* split_out) {
   mfma_gemm_plan(M, N, K, max_split, wide_only, tile_out, split_out);
-  if (*tile_out != 3) return;
-  const long columns = (long)((N + 63) / 64) * *split_out;
-  if ((M + 31) / 32 * columns <= 256) *tile_out = TILE_32;
-  else if ((M + 63) / 64 * columns <= 288) *tile_out = TILE_64;
+  if (*tile_out == 0) {
+    const long columns = (long)((N + 255) / 256) * *split_out;
+    int n_tiles;
+    double large = rounds(0, (M + 255) / 256 * columns, M), with_rest;
+    if (*split_out == 1 && rest_plan(M, N, K, wide_only, &n_tiles, &with_rest)) large = with_rest;
+    if (0.85 * rounds(0, (M + 191) / 192 * columns, M) < 0.97 * large) *tile_out = TILE_192;
+  } else if (*tile_out == 3) {
+    const long columns = (long)((N + 63) / 64) * *split_out;
+    if ((M + 31) / 32 * columns <= 256) *tile_out = TILE_32;
+    else if ((M + 63) / 64 * columns <= 288) *tile_out = TILE_64;
+  }
 }
 
 // QKV projection with the rotary embedding, the bf16 conversion and the per-candidate transposition of the values
@@ -901,7 +922,7 @@ bool launch_gemm_mfma(int epi, const bf16_t* A, const bf16_t* W, int M, int N, i
   if (K % 64 != 0 || M <= 0 || N <= 0) return false;
   if (epi == ME_SWIGLU && (N % 64 != 0 || ((uintptr_t)act & 7))) return false;
   if (ksplit < 1 || (ksplit > 1 && (epi != ME_STORE || ksplit > K / 64))) return false;
-  if (tile >= (epi == ME_LMHEAD ? 2 : (int)ALL_TILES)) return false;
+  if (tile >= ALL_TILES || (epi == ME_LMHEAD && tile >= 2 && tile != TILE_192)) return false;
   GemmArgs a = {};
   a.A = A; a.W = W; a.M = M; a.N = N; a.K = K; a.C = C; a.act = act; a.tok = tok;
   a.part_max = part_max; a.part_sum = part_sum; a.zt = zt; a.ksplit = ksplit;
