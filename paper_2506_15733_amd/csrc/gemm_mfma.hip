@@ -855,28 +855,29 @@ void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* til
 
 // The plan's tile and slices, or a tile that it does not know with the same slices: all tiles add a slice's products in the same
 // order, so these leave the same bits.
-// 192 x 256 for 256 x 256 where the rounds they take are shorter: fewer rows that only pad, or a single round with more CUs in it
-// (us: 1600 x 4608 x 3584 64.2 / 54.9, 1100 rows 64.1 / 53.8, 1100 x 3584 x 18944 in 3 slices 130 / 119, gate/up of 555 x 9728 x 896
-// 21.9 / 18.3, head of 555 x 151936 x 1536 270 / 250; but 1600 x 17920 x 1536, 490 / 630 tiles, 76.6 / 96.5, 1300 x 37888 x 3584
-// 283 / 313, and 1100 x 17920 x 1536, where a rest makes up for the padding, 62.7 / 64.8). A k-step takes 0.85 of the larger tile's.
+// 192 x 256 for 256 x 256 and 128 x 256 where the rounds they take are shorter: fewer rows that only pad, or a single round with more
+// CUs in it (us: 1600 x 4608 x 3584 64.2 / 54.9, 1100 rows 64.1 / 53.8, 1100 x 3584 x 18944 in 3 slices 130 / 119, gate/up of
+// 555 x 9728 x 896 21.9 / 18.3 and of 555 x 37888 x 3584 154 / 134, head of 555 x 151936 x 1536 270 / 250; but 1600 x 17920 x 1536,
+// 490 / 630 tiles, 76.6 / 96.5, 1300 x 37888 x 3584 283 / 313, and 1100 x 17920 x 1536, where a rest makes up for the padding,
+// 62.7 / 64.8). A k-step takes 0.85 of the larger tile's.
 // Finer ones where the plan says 64 x 128 and the product leaves CUs without a workgroup of that: what such a launch takes is how
 // long its few CUs pull weights from HBM, so more and smaller workgroups are ahead as long as each has a CU to itself. us with cold
 // weights, of 64 x 128, 64 x 64 and 32 x 64: 256 x 2048 x 1024 10.3, 7.7, 6.7; 256 x 2048 x 1536 14.8, 10.3, 8.6; 256 x 1024 x 1024 in 4
-// slices 6.1, 4.9, 5.4 (512 workgroups of the last, in 2: 5.2). A few CUs with two of the 64 x 64 ones do no harm (555 x 2048 x
-// 1536, 288 of them: 14.3 / 12.4); where many have two, 64 x 128 is ahead (256 x 5632 x 1024: 352, 11.2 / 12.3;
-// 1024 x 2048 x 1536: 512, 14.6 / 16.1).
+// slices 6.1, 4.9, 5.4 (512 workgroups of the last, in 2: 5.2). A few CUs with two of the 64 x 64 ones do no harm while the weights are
+// few (555 x 2048 x 1536, 288 of them: 14.3 / 12.4; but 256 x 4608 x 3584, 288: 28.1 / 32.4, gate/up of 64 x 17920 x 1536, 280: 18.3 /
+// 20.1); where many have two, 64 x 128 is ahead (256 x 5632 x 1024: 352, 11.2 / 12.3; 1024 x 2048 x 1536: 512, 14.6 / 16.1).
 void mfma_gemm_tile(int M, int N, int K, int max_split, bool wide_only, int* tile_out, int* split_out) {
   mfma_gemm_plan(M, N, K, max_split, wide_only, tile_out, split_out);
-  if (*tile_out == 0) {
+  if (*tile_out <= 1) {
     const long columns = (long)((N + 255) / 256) * *split_out;
     int n_tiles;
-    double large = rounds(0, (M + 255) / 256 * columns, M), with_rest;
-    if (*split_out == 1 && rest_plan(M, N, K, wide_only, &n_tiles, &with_rest)) large = with_rest;
+    double large = rounds(*tile_out, (M + kTiles[*tile_out].bm - 1) / kTiles[*tile_out].bm * columns, M), with_rest;
+    if (*tile_out == 0 && *split_out == 1 && rest_plan(M, N, K, wide_only, &n_tiles, &with_rest)) large = with_rest;
     if (0.85 * rounds(0, (M + 191) / 192 * columns, M) < 0.97 * large) *tile_out = TILE_192;
   } else if (*tile_out == 3) {
     const long columns = (long)((N + 63) / 64) * *split_out;
     if ((M + 31) / 32 * columns <= 256) *tile_out = TILE_32;
-    else if ((M + 63) / 64 * columns <= 288) *tile_out = TILE_64;
+    else if ((M + 63) / 64 * columns <= ((long)N * K <= 4 << 20 ? 288 : 256)) *tile_out = TILE_64;
   }
 }
 
