@@ -2,7 +2,7 @@
 //
 // Work decomposition. For one beam b, candidate i and kv head, the g = Hq/Hkv query heads of the
 // L block tokens are stacked into L*g rows (row r = t*g + j: token t, query head kvh*g + j) that
-// all read the same keys. A workgroup (4 wavefronts) owns 32*QT*4 of those rows and walks over
+// all read the same keys. A workgroup (4 wavefronts) owns 32*QT*4 of those rows, or 16*4 (Rows16), and walks over
 // the keys in tiles of 64: first the beam's cached prefix (4 pages per tile), then the
 // candidate's own block (causal). The n candidates of a beam run as neighbouring workgroups on the
 // same XCD, so the prefix pages are fetched from HBM once and re-read from L2.
@@ -31,6 +31,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // Tables that no kernel writes while this one runs, read by scalar loads. (Left to itself the compiler takes vector loads where it
 // cannot rule out that the stores and loads to LDS before them change the table, and then waits for all of these.)
 typedef const __attribute__((address_space(4))) int32_t* table_t;
+constexpr float RESCALE_LOG2 = 8.f;             // how far weights may outgrow the reference exponent of their row (see the kernel)
 
 struct AttnArgs {
   const bf16_t* q;      // [M][Hq][hd]
@@ -67,10 +68,126 @@ __device__ __forceinline__ float half_wave_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-template <int HD>
+// Where a key row keeps its 16-byte chunks, so that the rows of a fragment read (16 consecutive lanes) spread over all banks:
+// 16 rows in a row, in some order, for 32 query rows a wavefront; rows 8 i + (0..3) or 8 i + (4..7), i = 0..3, for 16.
+template <int HD, int ROWS>
 __device__ __forceinline__ int k_swizzle(int row, int chunk) {
+  if (ROWS == 16) return HD == 128 ? (chunk ^ ((row & 3) | ((row >> 1) & 12))) : (chunk ^ (((row >> 1) & 1) | ((row >> 2) & 6)));
   return HD == 128 ? (chunk ^ (row & 15)) : (chunk ^ ((row >> 1) & 7));
 }
+
+// Sixteen query rows of a wavefront, one per lane of each quarter wavefront: launches whose stacked rows do not fill wavefronts
+// of 32. A tile takes such a wavefront half the exponentials and half the matrix time, and four of them cover 64 rows that
+// would leave half of the workgroup's SIMDs to padding. Bound by the chain of one tile (LDS, scores, maximum, exponentials,
+// values). (8 candidates x 32 tokens x 16 heads of 64 dims, 8 kv heads, 512 keys: 10.4 us with wavefronts of 32 rows, 9.1 so;
+// single positions of 32 beams x 8 candidates x 12 heads of 128 dims, 2 kv heads, 1024 to 8192 keys: 47.4 and 43.0.)
+// Quarter q holds keys 8 q .. 8 q + 7 of each 32: two score products, whose A-rows 4 q + e are keys 8 q + e and 8 q + 4 + e. The
+// results are those of wavefronts of 32 rows to the bit: the same products in the same order of K, and the weights are added
+// in the order in which a lane there holds them, keys 8 h + 16 i + (0..7) for i = 0..3 on one chain, h = 0 and 1.
+template <int HD>
+struct Rows16 {
+  typedef float floatx4 __attribute__((ext_vector_type(4)));
+  bf16x8 qf[HD / 32];                           // dims 32 ks + 8 q .. + 7
+  floatx4 o[HD / 16];                           // dims 16 dt + 4 q + e
+  float m, l;                                   // l: in the upper half of the wavefront
+
+  __device__ __forceinline__ void clear() {
+    m = -INFINITY;
+    l = 0.f;
+#pragma unroll
+    for (int dt = 0; dt < HD / 16; ++dt) o[dt] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  static __device__ __forceinline__ float from_lower(float v) {
+    return __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false)[0]);
+  }
+  static __device__ __forceinline__ float from_upper(float v) {
+    return __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false)[1]);
+  }
+  // the value of lane l in the other quarter of its half: lane l ^ 16
+  static __device__ __forceinline__ float quarter_max(float v) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  __device__ __forceinline__ float sum() const {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(l), __float_as_uint(l), false, false);
+    return from_upper(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+  }
+
+  // one tile of 64 keys; keys from `limit` on are masked if need_mask
+  __device__ __forceinline__ void tile(const char* Ks, const char* Vs, bool need_mask, int key_base, int limit, float scale_log2e) {
+    const int lane = threadIdx.x & 63, col = lane & 15, quad = lane >> 4;
+    bf16x8 kf[4][HD / 32], vf[2][HD / 16];
+#pragma unroll
+    for (int ks = 0; ks < HD / 32; ++ks)
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const int row = 32 * (p >> 1) + 8 * (col >> 2) + 4 * (p & 1) + (col & 3);
+        kf[p][ks] = *(const bf16x8*)(Ks + row * HD * 2 + (k_swizzle<HD, 16>(row, ks * 4 + quad) << 4));
+      }
+    // the values are on their way while the scores become weights
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int dt = 0; dt < HD / 16; ++dt)
+        vf[hf][dt] = *(const bf16x8*)(Vs + (hf * 2 + (quad >> 1)) * HD * 32 + (dt * 16 + col) * 32 + (((quad & 1) ^ (col >> 3)) << 4));
+    floatx4 s[4];                               // [2 half tile + which four of the eight keys]
+#pragma unroll
+    for (int p = 0; p < 4; ++p) s[p] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < HD / 32; ++ks)
+#pragma unroll
+      for (int p = 0; p < 4; ++p) s[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[p][ks], qf[ks], s[p], 0, 0, 0);
+    if (need_mask) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          s[p][e] = key_base + 32 * (p >> 1) + 8 * quad + 4 * (p & 1) + e < limit ? s[p][e] : -INFINITY;
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, s[p][e]);
+    mx = half_wave_max(quarter_max(mx));
+    const float m_tile = mx * scale_log2e;      // the reference exponent as for 32 rows, below
+    const bool move = m_tile > m + RESCALE_LOG2;
+    if (__any(move)) {
+      const float m_new = move ? ceilf(m_tile) : m;
+      const float alpha = move ? __builtin_amdgcn_exp2f(m - m_new) : 1.f;
+      l *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < HD / 16; ++dt) o[dt] *= alpha;
+      m = m_new;
+    }
+    const float m_use = m == -INFINITY ? 0.f : m;
+    float p8[2][8];
+    bf16x8 pf[2];
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        p8[hf][e] = __builtin_amdgcn_exp2f(fmaf(s[2 * hf + (e >> 2)][e & 3], scale_log2e, -m_use));
+        pf[hf][e] = (bf16_t)p8[hf][e];
+      }
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int dt = 0; dt < HD / 16; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[hf][dt], pf[hf], o[dt], 0, 0, 0);
+    // quarters 0 and 2 (1 and 3) in turn: what the other half adds meanwhile is dropped
+    float sum = 0.f;
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      if (hf) sum = from_upper(sum);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sum += p8[hf][e];
+      sum = from_lower(sum);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sum += p8[hf][e];
+    }
+    l += sum;
+  }
+};
 
 // MODE 1's block keys: one workgroup of four wavefronts per (candidate, kv head, 16 of its query heads), which share the
 // block keys 0..t and values. The chain of short dependent phases on a few KB, bound by latency, is as long as that of a
@@ -194,8 +311,10 @@ __device__ __forceinline__ void touch_weights(const WeightsAhead& a, char* smem)
 // no long workgroups that the others wait for. MODE 2: whole blocks, but the tile list (prefix tiles, then block tiles) is cut
 // into n_splits runs handled by different workgroups, for launches that would otherwise leave most CUs idle; a
 // merge kernel combines the partial results.
-template <int HD, int QT, int MODE>
+// ROWS: query rows of a wavefront and query tile, 32 or (QT 1, MODE 0 and 1) 16.
+template <int HD, int QT, int MODE, int ROWS>
 __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(AttnArgs a) {
+  static_assert(ROWS == 32 || (ROWS == 16 && QT == 1), "16 rows");
   constexpr bool DEC = MODE == 1, SPLIT = MODE != 0;
   constexpr int KROW = HD * 2;              // bytes per key row
   constexpr int KCH = HD / 8;               // 16-byte chunks per key row
@@ -204,7 +323,7 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
   constexpr int STAGE = K_BYTES + V_BYTES;
   constexpr int NI = HD / 32;               // direct-to-LDS instructions per wave per operand; also d-tiles
   constexpr int KS = HD / 16;               // MFMA K-steps of the S^T product
-  constexpr int BQ = 128 * QT;
+  constexpr int BQ = 4 * ROWS * QT;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
 
   if (blockIdx.y != 0) {
@@ -249,7 +368,7 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
 
   // the wavefront index as a scalar: page ids, page bases and LDS destinations then live in scalar registers
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int lq = lane & 31, lh = lane >> 5;
+  const int lq = lane & (ROWS - 1), lh = lane / ROWS;
   const int P = G.len_override >= 0 ? G.len_override : ((table_t)G.lens)[G.b0 + b];
   const int L = G.L;
   const int cand_idx = b * G.n + cand;
@@ -261,18 +380,25 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
   // --- queries of this wavefront as B-operand fragments (column = query) ---
   int tq[QT];
   bf16x8 qf[QT][KS];
+  Rows16<HD> r16;
 #pragma unroll
   for (int u = 0; u < QT; ++u) {
-    int r = r_wg0 + (wave * QT + u) * 32 + lq;
+    int r = r_wg0 + (wave * QT + u) * ROWS + lq;
     int rc = r < rows_total ? r : rows_total - 1;
     int t = rc / g, j = rc - t * g;                 // DEC: t is the candidate index within the beam
     tq[u] = t;
     const size_t qrow = DEC ? (size_t)b * G.n + t : m_c0 + t;
     const bf16_t* src = a.q + (qrow * a.Hq + (size_t)kvh * g + j) * HD;
+    if constexpr (ROWS == 16) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) qf[u][ks] = *(const bf16x8*)(src + ks * 16 + lh * 8);
+      for (int ks = 0; ks < HD / 32; ++ks) r16.qf[ks] = *(const bf16x8*)(src + ks * 32 + lh * 8);
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) qf[u][ks] = *(const bf16x8*)(src + ks * 16 + lh * 8);
+    }
   }
 
+  r16.clear();
   floatx16 o[QT][NI];
   float m_run[QT], l_run[QT];
 #pragma unroll
@@ -319,7 +445,7 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
       for (int i = 0; i < NI; ++i) {
         int qi = i * 64 + lane;
         int row = qi / KCH, slot = qi % KCH;
-        int chunk = k_swizzle<HD>(wave * 16 + row, slot);
+        int chunk = k_swizzle<HD, ROWS>(wave * 16 + row, slot);
         __builtin_amdgcn_global_load_lds(GLB_PTR(ksrc + (unsigned)(row * HD + chunk * 8)), LDS_PTR(kdst + i * 1024), 16, 0,
                                          0);
       }
@@ -335,7 +461,7 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
       for (int i = 0; i < NI; ++i) {
         int qi = i * 64 + lane;
         int row = qi / KCH, slot = qi % KCH;
-        int chunk = k_swizzle<HD>(wave * 16 + row, slot);
+        int chunk = k_swizzle<HD, ROWS>(wave * 16 + row, slot);
         int key = key0 + row;
         key = key < L ? key : L - 1;
         const bf16_t* src = a.kb + ((m_c0 + key) * a.Hkv + kvh) * HD + chunk * 8;
@@ -369,11 +495,15 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
       stage_tile(tile + 1, page_next, smem + ((it + 1) & 1) * STAGE);
       page_next = page_of(tile + 2);                   // lands while this tile is being multiplied
     }
-    if (DEC && r_wg0 + wave * QT * 32 >= rows_total) continue;   // no rows of its own: this wavefront only stages
+    if ((DEC || ROWS == 16) && r_wg0 + wave * QT * ROWS >= rows_total) continue;   // no rows of its own: this wavefront only stages
     const char* Ks = smem + (it & 1) * STAGE;
     const char* Vs = Ks + K_BYTES;
     const bool is_block = tile >= n_ptiles;
     const int key_base = is_block ? (tile - n_ptiles) * 64 : tile * 64;
+    if constexpr (ROWS == 16) {
+      r16.tile(Ks, Vs, is_block || key_base + 64 > P, key_base, is_block ? tq[0] + 1 : P, a.scale_log2e);
+      continue;
+    }
 
     // S^T for the two 32-key halves
     floatx16 s[QT][2];
@@ -388,7 +518,7 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
     constexpr int KPF = 2;
     auto read_kf = [&](int ks, int hf) {
       int row = hf * 32 + pi_row;
-      return *(const bf16x8*)(Ks + row * KROW + (k_swizzle<HD>(row, ks * 2 + lh) << 4));
+      return *(const bf16x8*)(Ks + row * KROW + (k_swizzle<HD, ROWS>(row, ks * 2 + lh) << 4));
     };
     bf16x8 kf[KPF + 1][2];
 #pragma unroll
@@ -439,7 +569,6 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
       // follows the row maximum lazily: the accumulators are rescaled only when the maximum has grown by more than
       // 2^RESCALE_LOG2 past the reference, so weights reach at most that factor (exact in float; O/l at the end
       // does not depend on the reference) and the 64 multiplications per lane become rare.
-      constexpr float RESCALE_LOG2 = 8.f;
       const float m_tile = mx * a.scale_log2e;
       const bool move = m_tile > m_run[u] + RESCALE_LOG2;   // also the first visible key: -inf + 8 = -inf
       if (__any(move)) {
@@ -491,15 +620,21 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
   // normalise and store: lane = query column, accumulator value r of d-tile dt is d = dt*32 + 8*(r/4) + 4*lh + r%4
 #pragma unroll
   for (int u = 0; u < QT; ++u) {
-    int r = r_wg0 + (wave * QT + u) * 32 + lq;
-    float l = half_wave_sum(l_run[u]);
+    int r = r_wg0 + (wave * QT + u) * ROWS + lq;
+    if (ROWS == 16) m_run[u] = r16.m;
+    float l = ROWS == 16 ? r16.sum() : half_wave_sum(l_run[u]);
     if (SPLIT) {
-      if (DEC && r >= rows_total) continue;
+      if ((DEC || ROWS == 16) && r >= rows_total) continue;
       const size_t group = DEC ? (size_t)b * a.Hkv + kvh : ((size_t)b * a.Hkv + kvh) * G.n + cand;
       const size_t prow = DEC ? (group * a.part_splits + split) * rows_total + r
-                              : ((group * a.q_tiles + qt_idx) * a.n_splits + split) * BQ + (wave * QT + u) * 32 + lq;
+                              : ((group * a.q_tiles + qt_idx) * a.n_splits + split) * 128 + (wave * QT + u) * ROWS + lq;
       if (lh == 0) { a.part_m[prow] = m_run[u]; a.part_l[prow] = l; }
       float* dst = a.part_o + prow * HD;
+      if constexpr (ROWS == 16) {
+#pragma unroll
+        for (int dt = 0; dt < HD / 16; ++dt) *(typename Rows16<HD>::floatx4*)(dst + 16 * dt + 4 * lh) = r16.o[dt];
+        continue;
+      }
 #pragma unroll
       for (int dt = 0; dt < NI; ++dt)
 #pragma unroll
@@ -511,6 +646,13 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
       int t = r / g, j = r - t * g;
       float inv = 1.0f / l;
       bf16_t* dst = a.out + ((m_c0 + t) * a.Hq + (size_t)kvh * g + j) * HD;
+      if constexpr (ROWS == 16) {
+#pragma unroll
+        for (int dt = 0; dt < HD / 16; ++dt)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dst[16 * dt + 4 * lh + e] = (bf16_t)(r16.o[dt][e] * inv);
+        continue;
+      }
 #pragma unroll
       for (int dt = 0; dt < NI; ++dt)
 #pragma unroll
@@ -523,19 +665,19 @@ __global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(At
   }
 }
 
-template <int HD, int QT, int MODE = 0>
+template <int HD, int QT, int MODE = 0, int ROWS = 32>
 static void launch_attn_variant(const AttnArgs& a, hipStream_t s) {
   constexpr int smem = 2 * (64 * HD * 2 + 4 * HD * 32);
   static_assert(smem >= BLOCK_LDS, "MODE 1's block keys");
   static bool configured = false;
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)attention_mfma_kernel<HD, QT, MODE>,
+    (void)hipFuncSetAttribute((const void*)attention_mfma_kernel<HD, QT, MODE, ROWS>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     configured = true;
   }
   // beside workgroups that leave CUs without one only (32 beams x 8 candidates x 12 heads, 608: nothing gained)
   const int own = a.wg_per_xcd * 8 + a.block_wgs, more = own > 256 ? 0 : (a.ahead.wgs + own - 1) / own;
-  attention_mfma_kernel<HD, QT, MODE><<<dim3(own, 1 + more), 256, smem, s>>>(a);
+  attention_mfma_kernel<HD, QT, MODE, ROWS><<<dim3(own, 1 + more), 256, smem, s>>>(a);
 }
 
 // Merge of the partial results of a MODE 2 launch: HD / 4 lanes per (row, query head), each 16 bytes of it, with all of the
@@ -623,7 +765,11 @@ bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT,
     a.part_o = part; a.part_m = part + rows_all * md.hd; a.part_l = a.part_m + rows_all;
     a.total_wg *= splits;
     a.wg_per_xcd = (a.total_wg + 7) / 8;
-    if (md.hd == 128) launch_attn_variant<128, 1, 2>(a, s); else launch_attn_variant<64, 1, 2>(a, s);
+    if (rows <= 64) {                                        // 64 rows, 1024 keys: 12.7 us with 32 a wavefront, 11.3 so; 4096: 21.9 and 19.2
+      if (md.hd == 128) launch_attn_variant<128, 1, 2, 16>(a, s); else launch_attn_variant<64, 1, 2, 16>(a, s);
+    } else {
+      if (md.hd == 128) launch_attn_variant<128, 1, 2>(a, s); else launch_attn_variant<64, 1, 2>(a, s);
+    }
     const int groups = g.B * md.Hkv * g.n;                   // fewer than 384
     if (md.hd == 128)
       attention_split_merge_kernel<128><<<dim3((rows + 7) / 8, groups), 256, 0, s>>>(
@@ -631,6 +777,18 @@ bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT,
     else
       attention_split_merge_kernel<64><<<dim3((rows + 15) / 16, groups), 256, 0, s>>>(
           a.part_o, a.part_m, a.part_l, out, g.n, g.L, md.Hq, md.Hkv, a.q_tiles, splits);
+    return true;
+  }
+  // At most 64 rows, or so few that each workgroup of 64 has a CU to itself: 16 rows a wavefront (64 rows, 2048 workgroups:
+  // 61.0 us with 32, 43.7 so; 128, 192 and 224 rows, 256 workgroups of 64 or fewer: 11.2, 15.2, 15.9 and 9.5, 12.0, 12.9; 384,
+  // 512 and 768 workgroups: 11.7, 12.0, 25.9 and 12.7, 12.8, 27.3, since the rows of a wavefront share its reads of the keys).
+  const int t64 = (rows + 63) / 64;
+  const long wgs64 = (long)g.B * md.Hkv * g.n * t64;
+  if (t64 == 1 || wgs64 <= 256) {
+    a.q_tiles = t64;
+    a.total_wg = (int)wgs64;
+    a.wg_per_xcd = (a.total_wg + 7) / 8;
+    if (md.hd == 128) launch_attn_variant<128, 1, 0, 16>(a, s); else launch_attn_variant<64, 1, 0, 16>(a, s);
     return true;
   }
   a.wg_per_xcd = (a.total_wg + 7) / 8;
@@ -722,7 +880,17 @@ bool launch_attention_mfma_decode(const bf16_t* q, const bf16_t* kb, const bf16_
   a.part_m = part + rows_all * md.hd;
   a.part_l = a.part_m + rows_all;
   a.block_wgs = with_block ? decode_block_wgs(g, md) : 0;
-  if (md.hd == 128) launch_attn_variant<128, 1, 1>(a, s);
-  else launch_attn_variant<64, 1, 1>(a, s);
+  // 16 rows a wavefront where workgroups of 64 rows are no more than those of 128, or all resident at once all the same. The runs
+  // and so the results stay. (48 rows of 32 beams: 47.4 us with 32, 43.0 so; 96 rows, 2 kv heads, 4096 keys: 12.9 and 11.7; 112
+  // rows, 4 kv heads: 15.3 and 14.4.)
+  const int t64 = (rows + 63) / 64;
+  if (t64 == 1 || (long)entries * t64 + a.block_wgs <= 512) {
+    a.q_tiles = t64;
+    a.total_wg = entries * t64;
+    a.wg_per_xcd = (entries + 7) / 8 * t64;
+    if (md.hd == 128) launch_attn_variant<128, 1, 1, 16>(a, s); else launch_attn_variant<64, 1, 1, 16>(a, s);
+  } else {
+    if (md.hd == 128) launch_attn_variant<128, 1, 1>(a, s); else launch_attn_variant<64, 1, 1>(a, s);
+  }
   return true;
 }
