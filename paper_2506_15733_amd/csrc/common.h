@@ -211,8 +211,9 @@ bool launch_gemm_mfma(int epi, const bf16_t* A, const bf16_t* W, int M, int N, i
 bool launch_gemm_mfma_qkv_rope(const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q, bf16_t* kblk, bf16_t* vT,
                                const BatchGeom& g, const ModelDims& md, int Lp, int tile, hipStream_t s);
 bool qkv_rope_position(int M, int N, int K, int max_split);
-// tile shape (wide_only: of 256 columns) and number of K slices for a product whose consumer sums up to max_split partial products
-void mfma_gemm_tile(int M, int N, int K, int max_split, bool wide_only, int* tile_out, int* split_out);
+// tile shape (wide_only: of 256 columns; beside: for a launch that others run beside) and number of K slices for a product whose
+// consumer sums up to max_split partial products
+void mfma_gemm_tile(int M, int N, int K, int max_split, bool wide_only, bool beside, int* tile_out, int* split_out);
 // x[M,d] (+)= sum of `parts` partial products P[parts][M,d]; init != 0 overwrites x instead of adding to it.
 // With gain != nullptr also out = RMSNorm(x) * gain (the operand of the next projection).
 template <typename T>

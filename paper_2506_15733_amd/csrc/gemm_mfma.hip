@@ -704,7 +704,7 @@ int mfma_gemm_ring(int tile, int M, int N, int K, int ksplit) {
 static bool buffer_operands(const GemmArgs& a) { return (((uintptr_t)a.A | (uintptr_t)a.W) & 15) == 0 && a.K <= 1 << 22; }
 
 // Tiles that only mfma_gemm_tile gives, behind those of the plan.
-enum { TILE_64 = MFMA_TILES, TILE_32, TILE_192, ALL_TILES };
+enum { TILE_64 = MFMA_TILES, TILE_32, TILE_192, TILE_SHORT /* 64 x 128, three K-tiles */, ALL_TILES };
 
 int mfma_gemm_rest(int M, int N, int K, bool wide_only, int* n_tiles);
 bool mfma_gate_up_192(int M, int N, int K, int tile);
@@ -723,6 +723,13 @@ static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
       a.n_tiles = (a.N + 63) / 64;
       if (tile == TILE_64) launch_variant<64, 64, 4, 4, EPI, HD128>(a, s);
       else launch_variant<32, 64, 2, 6, EPI, HD128>(a, s);
+      return;
+    }
+  if constexpr (EPI != ME_LMHEAD)
+    if (tile == TILE_SHORT) {
+      a.m_tiles = (a.M + 63) / 64;
+      a.n_tiles = (a.N + 127) / 128;
+      launch_variant<64, 128, 4, 3, EPI, HD128>(a, s);
       return;
     }
   a.part_tiles = mfma_lmhead_tiles(a.N);
@@ -856,17 +863,22 @@ void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* til
 // The plan's tile and slices, or a tile that it does not know with the same slices: all tiles add a slice's products in the same
 // order, so these leave the same bits.
 // 192 x 256 for 256 x 256 and 128 x 256 where the rounds they take are shorter: fewer rows that only pad, or a single round with more
-// CUs in it (us: 1600 x 4608 x 3584 64.2 / 54.9, 1100 rows 64.1 / 53.8, 1100 x 3584 x 18944 in 3 slices 130 / 119, gate/up of
-// 555 x 9728 x 896 21.9 / 18.3 and of 555 x 37888 x 3584 154 / 134, head of 555 x 151936 x 1536 270 / 250; but 1600 x 17920 x 1536,
-// 490 / 630 tiles, 76.6 / 96.5, 1300 x 37888 x 3584 283 / 313, and 1100 x 17920 x 1536, where a rest makes up for the padding,
-// 62.7 / 64.8). A k-step takes 0.85 of the larger tile's.
+// CUs in it (us, 256 x 256 / 192 x 256: 1100 x 3584 x 18944 in 3 slices 130 / 119, 1600 rows in 2 186 / 165, gate/up of 1100 x 9728 x
+// 896 24.4 / 22.1, head of 555 x 151936 x 1536 270 / 250; but 1600 x 17920 x 1536, 490 / 630 tiles, 78 / 94, 1600 x 37888 x 3584 330 /
+// 373, and 1100 x 17920 x 1536, where a rest makes up for the padding, 62.7 / 64.8; against 128 x 256: gate/up of 555 x 37888 x 3584
+// 154 / 135, but 1600 x 4608 x 3584 51.8 / 58.5, 1100 rows 52.7 / 62.9). A k-step takes 0.85 of the larger tile's.
 // Finer ones where the plan says 64 x 128 and the product leaves CUs without a workgroup of that: what such a launch takes is how
 // long its few CUs pull weights from HBM, so more and smaller workgroups are ahead as long as each has a CU to itself. us with cold
 // weights, of 64 x 128, 64 x 64 and 32 x 64: 256 x 2048 x 1024 10.3, 7.7, 6.7; 256 x 2048 x 1536 14.8, 10.3, 8.6; 256 x 1024 x 1024 in 4
 // slices 6.1, 4.9, 5.4 (512 workgroups of the last, in 2: 5.2). A few CUs with two of the 64 x 64 ones do no harm while the weights are
 // few (555 x 2048 x 1536, 288 of them: 14.3 / 12.4; but 256 x 4608 x 3584, 288: 28.1 / 32.4, gate/up of 64 x 17920 x 1536, 280: 18.3 /
 // 20.1); where many have two, 64 x 128 is ahead (256 x 5632 x 1024: 352, 11.2 / 12.3; 1024 x 2048 x 1536: 512, 14.6 / 16.1).
-void mfma_gemm_tile(int M, int N, int K, int max_split, bool wide_only, int* tile_out, int* split_out) {
+// beside: the launch will probably run beside those of other models (the models of a step score their blocks at the same time). The
+// longer ring of the 64 x 128 tiles takes a CU's LDS to itself, so of two such launches, of 129 to 256 workgroups each, one waits for
+// CUs of the other. The short one leaves room for a second workgroup; alone it costs 4 to 7 % of a launch up to 24
+// K-tiles, and 7 to 10 % beyond (us, 256 x 5632 x 1024 7.9 / 8.5, 1024 x 2048 x 1536 12.2 / 12.7, 256 x 1536 x 8960 in 5 slices 12.4 /
+// 13.3, 256 x 4608 x 3584 18.6 / 20.7). A step of three models of 4 and 16 layers of d = 1024 1260 us with the long ring, 1210 so.
+void mfma_gemm_tile(int M, int N, int K, int max_split, bool wide_only, bool beside, int* tile_out, int* split_out) {
   mfma_gemm_plan(M, N, K, max_split, wide_only, tile_out, split_out);
   if (*tile_out <= 1) {
     const long columns = (long)((N + 255) / 256) * *split_out;
@@ -878,6 +890,7 @@ void mfma_gemm_tile(int M, int N, int K, int max_split, bool wide_only, int* til
     const long columns = (long)((N + 63) / 64) * *split_out;
     if ((M + 31) / 32 * columns <= 256) *tile_out = TILE_32;
     else if ((M + 63) / 64 * columns <= ((long)N * K <= 4 << 20 ? 288 : 256)) *tile_out = TILE_64;
+    else if (beside && mfma_gemm_ring(3, M, N, K, *split_out) == 6 && K / 64 <= 24 * *split_out) *tile_out = TILE_SHORT;
   }
 }
 
@@ -896,7 +909,7 @@ bool launch_gemm_mfma_qkv_rope(const bf16_t* A, const bf16_t* W, const float* cs
   a.cs = cs; a.q = q; a.kblk = kblk; a.vT = vT;
   a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lrows = g.L; a.Lk = g.Lk; a.Lp = Lp; a.t0 = g.t0;
   int split = 1;
-  if (tile < 0) mfma_gemm_tile(M, N, K, 1, false, &tile, &split);
+  if (tile < 0) mfma_gemm_tile(M, N, K, 1, false, g.L > 1 && g.B * g.n > 1, &tile, &split);
   if (md.hd == 128) launch_tile<ME_QKV_ROPE, true>(a, tile, s);
   else launch_tile<ME_QKV_ROPE, false>(a, tile, s);
   return true;
@@ -908,9 +921,9 @@ bool launch_gemm_mfma_qkv_rope(const bf16_t* A, const bf16_t* W, const float* cs
 // 48 x 4608 x 3584 11 + 6 / 15, but 128 rows 12.4 + 6 / 20.
 bool qkv_rope_position(int M, int N, int K, int max_split) {
   int tile, split;
-  mfma_gemm_tile(M, N, K, max_split, false, &tile, &split);
+  mfma_gemm_tile(M, N, K, max_split, false, false, &tile, &split);
   if (split == 1 || K <= 2048) return true;
-  mfma_gemm_tile(M, N, K, 1, false, &tile, &split);
+  mfma_gemm_tile(M, N, K, 1, false, false, &tile, &split);
   return tile == TILE_32;
 }
 
@@ -929,7 +942,7 @@ bool launch_gemm_mfma(int epi, const bf16_t* A, const bf16_t* W, int M, int N, i
   a.part_max = part_max; a.part_sum = part_sum; a.zt = zt; a.ksplit = ksplit;
   if (epi == ME_LMHEAD && !buffer_operands(a)) return false;
   int split = 1;
-  if (tile < 0) mfma_gemm_tile(M, N, K, 1, epi == ME_LMHEAD, &tile, &split);
+  if (tile < 0) mfma_gemm_tile(M, N, K, 1, epi == ME_LMHEAD, false, &tile, &split);
   switch (epi) {
     case ME_STORE: launch_tile<ME_STORE>(a, tile, s); break;
     case ME_RESIDUAL: launch_tile<ME_RESIDUAL>(a, tile, s); break;

@@ -393,13 +393,13 @@ void gemm<bf16_t>(const bf16_t* A, const bf16_t* W, float* C, int M, int N, int 
 // better, writes the partial products to `part` (room for max_split of them) and returns their number;
 // the caller's next normalisation kernel sums them into x. Returns 0 when the product was added to x directly.
 template <typename T>
-static int gemm_residual_split(const T* A, const T* W, float* x, float* part, int max_split, int M, int N, int K,
+static int gemm_residual_split(const T* A, const T* W, float* x, float* part, int max_split, bool beside, int M, int N, int K,
                                hipStream_t s) {
   gemm<T>(A, W, x, M, N, K, EPI_RESIDUAL_ADD, s);
   return 0;
 }
 template <>
-int gemm_residual_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* x, float* part, int max_split, int M, int N,
+int gemm_residual_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* x, float* part, int max_split, bool beside, int M, int N,
                                 int K, hipStream_t s) {
   if (launch_few_rows_residual(A, W, x, M, N, K, s)) {
     count_mfma(M);
@@ -408,7 +408,7 @@ int gemm_residual_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* x, floa
   // Also with one slice the product goes to `part` and the normalisation kernel, which reads x anyway, adds it:
   // the GEMM's epilogue then only writes, instead of waiting for a read of x before every store.
   int tile = -1, split = 1;
-  if (K % 64 == 0 && max_split > 1) mfma_gemm_tile(M, N, K, max_split, false, &tile, &split);
+  if (K % 64 == 0 && max_split > 1) mfma_gemm_tile(M, N, K, max_split, false, beside, &tile, &split);
   if (max_split >= 1 &&
       launch_gemm_mfma(MFMA_STORE, A, W, M, N, K, part, nullptr, nullptr, nullptr, nullptr, nullptr, split, tile, s)) {
     count_mfma(M);
@@ -428,7 +428,7 @@ template <>
 int gemm_store_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* C, int max_split, int M, int N, int K,
                              hipStream_t s) {
   int tile = -1, split = 1;
-  if (K % 64 == 0 && max_split > 1) mfma_gemm_tile(M, N, K, max_split, false, &tile, &split);
+  if (K % 64 == 0 && max_split > 1) mfma_gemm_tile(M, N, K, max_split, false, false, &tile, &split);
   if (launch_gemm_mfma(MFMA_STORE, A, W, M, N, K, C, nullptr, nullptr, nullptr, nullptr, nullptr, split, tile, s)) {
     count_mfma(M);
     return split;
@@ -493,14 +493,16 @@ static bool norm_logits(const float* x, const float* gain, const bf16_t* W, floa
 
 // act[M,F] = silu(A Wg^T) * (A Wu^T) with Wgu interleaved by 32 rows
 template <typename T>
-static void gate_up(const T* A, const T* Wgu, float* gu, T* act, int M, int F, int K, hipStream_t s) {
+static void gate_up(const T* A, const T* Wgu, float* gu, T* act, int M, int F, int K, bool beside, hipStream_t s) {
   count_path(SPECS_PATH_GEMM_PLAIN);
   launch_gemm_simple<T>(A, Wgu, gu, M, 2 * F, K, EPI_STORE_F32, s);
   launch_silu_mul<T>(gu, act, M, F, s);
 }
 template <>
-void gate_up<bf16_t>(const bf16_t* A, const bf16_t* Wgu, float* gu, bf16_t* act, int M, int F, int K, hipStream_t s) {
-  if (launch_gemm_mfma(MFMA_SWIGLU, A, Wgu, M, 2 * F, K, nullptr, act, nullptr, nullptr, nullptr, nullptr, 1, -1, s)) {
+void gate_up<bf16_t>(const bf16_t* A, const bf16_t* Wgu, float* gu, bf16_t* act, int M, int F, int K, bool beside, hipStream_t s) {
+  int tile = -1, split = 1;
+  if (K % 64 == 0) mfma_gemm_tile(M, 2 * F, K, 1, false, beside, &tile, &split);
+  if (launch_gemm_mfma(MFMA_SWIGLU, A, Wgu, M, 2 * F, K, nullptr, act, nullptr, nullptr, nullptr, nullptr, 1, tile, s)) {
     count_mfma(M);
     return;
   }
@@ -626,6 +628,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
     return (int)(room < MFMA_MAX_SPLIT ? room : MFMA_MAX_SPLIT);
   };
   const int max_split = max_split_of(g.M);
+  const bool beside = g.L > 1 && g.B * g.n > 1;          // blocks of several candidates, which several models score at the same time
   const int qkv_split = (int)(R / g.M < MFMA_MAX_SPLIT ? R / g.M : MFMA_MAX_SPLIT);   // ws.qkv has room for R / g.M slices of QKV
   DecodeRuns runs = {};
   if (d.dtype == SPECS_BF16 && !stretches && (g.L == 1 || last_token_only))
@@ -666,7 +669,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
                             ws.gu_floats, weights_ahead<T>(L, d, gl.M, false), s));
       int pl = 0;
       PROFILED(ctx, SPECS_K_OPROJ, s,
-               pl = gemm_residual_split<T>((const T*)ws.attn, (const T*)L.wo, ws.xs, ws.gu, max_split_of(gl.M), gl.M, md.d, qd, s));
+               pl = gemm_residual_split<T>((const T*)ws.attn, (const T*)L.wo, ws.xs, ws.gu, max_split_of(gl.M), false, gl.M, md.d, qd, s));
       if (pl)
         PROFILED(ctx, SPECS_K_OTHER, s,
                  launch_add_partials_rmsnorm<T>(ws.xs, ws.gu, pl, 0, L.g_ffn, (T*)ws.a, gl.M, md.d, md.eps, s));
@@ -678,9 +681,9 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
         PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(ws.xs, L.g_ffn, (T*)ws.a, gl.M, md.d, md.eps, s));
       if (!fused_ffn)
         PROFILED(ctx, SPECS_K_GATE_UP, s,
-                 gate_up<T>((const T*)ws.a, (const T*)L.wgu, ws.gu, (T*)ws.act, gl.M, md.F, md.d, s));
+                 gate_up<T>((const T*)ws.a, (const T*)L.wgu, ws.gu, (T*)ws.act, gl.M, md.F, md.d, false, s));
       PROFILED(ctx, SPECS_K_DOWN, s,
-               pl = gemm_residual_split<T>((const T*)ws.act, (const T*)L.wd, ws.xs, ws.gu, max_split_of(gl.M), gl.M, md.d, md.F, s));
+               pl = gemm_residual_split<T>((const T*)ws.act, (const T*)L.wd, ws.xs, ws.gu, max_split_of(gl.M), false, gl.M, md.d, md.F, s));
       if (pl)
         PROFILED(ctx, SPECS_K_OTHER, s,
                  launch_add_partials_rmsnorm<T>(ws.xs, ws.gu, pl, 0, nullptr, (T*)ws.a, gl.M, md.d, md.eps, s));
@@ -705,7 +708,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
     }
     int parts = 0;
     PROFILED(ctx, SPECS_K_OPROJ, s,
-             parts = gemm_residual_split<T>((const T*)ws.attn, (const T*)L.wo, x, ws.gu, max_split, g.M, md.d, qd, s));
+             parts = gemm_residual_split<T>((const T*)ws.attn, (const T*)L.wo, x, ws.gu, max_split, beside, g.M, md.d, qd, s));
     if (parts)
       PROFILED(ctx, SPECS_K_OTHER, s,
                launch_add_partials_rmsnorm<T>(x, ws.gu, parts, 0, L.g_ffn, (T*)ws.a, g.M, md.d, md.eps, s));
@@ -717,9 +720,9 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
       PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(x, L.g_ffn, (T*)ws.a, g.M, md.d, md.eps, s));
     if (!fused_ffn)
       PROFILED(ctx, SPECS_K_GATE_UP, s,
-               gate_up<T>((const T*)ws.a, (const T*)L.wgu, ws.gu, (T*)ws.act, g.M, md.F, md.d, s));
+               gate_up<T>((const T*)ws.a, (const T*)L.wgu, ws.gu, (T*)ws.act, g.M, md.F, md.d, beside, s));
     PROFILED(ctx, SPECS_K_DOWN, s,
-             parts = gemm_residual_split<T>((const T*)ws.act, (const T*)L.wd, x, ws.gu, max_split, g.M, md.d, md.F, s));
+             parts = gemm_residual_split<T>((const T*)ws.act, (const T*)L.wd, x, ws.gu, max_split, beside, g.M, md.d, md.F, s));
     normed = false;
     if (parts) {
       // the sum of the partials is folded into the next layer's first normalisation (none after the last layer)
@@ -1035,7 +1038,7 @@ extern "C" int specs_op_linear(specs_ctx* ctx, int32_t dtype, const void* A, con
     size_t per = (size_t)M * N * sizeof(float);
     size_t room = ctx->workspace_bytes > 256 ? (ctx->workspace_bytes - 256) / per : 0;
     int tile = -1, split = 1;
-    if (K % 64 == 0 && room > 1) mfma_gemm_tile(M, N, K, room > MFMA_MAX_SPLIT ? MFMA_MAX_SPLIT : (int)room, false, &tile, &split);
+    if (K % 64 == 0 && room > 1) mfma_gemm_tile(M, N, K, room > MFMA_MAX_SPLIT ? MFMA_MAX_SPLIT : (int)room, false, false, &tile, &split);
     float* part = (float*)(ctx->workspace + 256);
     if (split > 1 && launch_gemm_mfma(MFMA_STORE, (const bf16_t*)A, (const bf16_t*)W, M, N, K, part, nullptr, nullptr,
                                       nullptr, nullptr, nullptr, split, tile, ctx->stream)) {
@@ -1060,8 +1063,8 @@ extern "C" int specs_op_gate_up(specs_ctx* ctx, int32_t dtype, const void* A, co
   if (need > ctx->workspace_bytes) return SPECS_EWORKSPACE;
   float* gu = (float*)(ctx->workspace + 256);
   HIP_TRY(hipSetDevice(ctx->device));
-  if (dtype == SPECS_BF16) gate_up<bf16_t>((const bf16_t*)A, (const bf16_t*)Wgu, gu, (bf16_t*)act, M, F, K, ctx->stream);
-  else gate_up<float>((const float*)A, (const float*)Wgu, gu, (float*)act, M, F, K, ctx->stream);
+  if (dtype == SPECS_BF16) gate_up<bf16_t>((const bf16_t*)A, (const bf16_t*)Wgu, gu, (bf16_t*)act, M, F, K, false, ctx->stream);
+  else gate_up<float>((const float*)A, (const float*)Wgu, gu, (float*)act, M, F, K, false, ctx->stream);
   HIP_TRY(hipGetLastError());
   ctx->last_model = nullptr;
   return SPECS_OK;

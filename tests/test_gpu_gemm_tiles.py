@@ -10,7 +10,7 @@ from host_rules import BatchGeom, ModelDims, library
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
-WIDE, TILES = (0, 1, 7), (0, 1, 2, 3, 4, 5, 6, 7)      # those of the plan, 64 x 64, 32 x 64, 192 x 256
+WIDE, TILES = (0, 1, 7), (0, 1, 2, 3, 4, 5, 6, 7, 8)   # those of the plan, 64 x 64, 32 x 64, 192 x 256, 64 x 128 with 3 K-tiles
 STORE, RESIDUAL, SWIGLU, HEAD = 0, 1, 2, 3
 
 
