@@ -861,7 +861,8 @@ bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT,
   // alone as runs and their merge (192 workgroups of 64, 12 heads of 128 dims, 2048 keys: 25.2 + 7.3 us / 30.1), but a step of three
   // models has the CUs and the memory that runs and their partial results take (1024 rows of d = 1536 10.15 -> 9.83 ms, 555 rows
   // 7.00 -> 6.75; 120, 240 and 180 such workgroups, lists of 18, 18 and at most 48 tiles: 2.6, 2.3 and 3.3 % shorter). With longer lists the
-  // few CUs are what counts (140 workgroups, 65 tiles 0.5 % shorter; 120, 95 tiles 1.3 % longer, 192, 126 tiles 4.1).
+  // few CUs are what counts (140 workgroups, 65 tiles 0.5 % shorter; 120, 95 tiles 1.3 % longer, 192, 126 tiles 4.1); shorter ones have
+  // no runs to save (64 workgroups, 9 tiles: a step of small models 1205 us, 1217 with two groups).
   if (!a.last_first && list_tiles >= 16 && list_tiles <= 48 && wgs64 >= 120 && wgs64 <= 256) {
     a.q_tiles = t64;
     a.total_wg = (int)wgs64;
