@@ -2,7 +2,7 @@
 //
 // Work decomposition. For one beam b, candidate i and kv head, the g = Hq/Hkv query heads of the
 // L block tokens are stacked into L*g rows (row r = t*g + j: token t, query head kvh*g + j) that
-// all read the same keys. A workgroup (4 wavefronts) owns 32*QT*4 of those rows, or 16*4 (Rows16, also 8 wavefronts), and walks over
+// all read the same keys. A workgroup (4 wavefronts) owns 32*QT*4 of those rows, or 16*4 (Rows16), and walks over
 // the keys in tiles of 64: first the beam's cached prefix (4 pages per tile), then the
 // candidate's own block (causal). The n candidates of a beam run as neighbouring workgroups on the
 // same XCD, so the prefix pages are fetched from HBM once and re-read from L2.
@@ -31,13 +31,6 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // Tables that no kernel writes while this one runs, read by scalar loads. (Left to itself the compiler takes vector loads where it
 // cannot rule out that the stores and loads to LDS before them change the table, and then waits for all of these.)
 typedef const __attribute__((address_space(4))) int32_t* table_t;
-// Barrier of a workgroup, in which no instruction moves across
-#define MEET()                              \
-  do {                                      \
-    __builtin_amdgcn_sched_barrier(0);      \
-    asm volatile("s_barrier" ::: "memory"); \
-    __builtin_amdgcn_sched_barrier(0);      \
-  } while (0)
 constexpr float RESCALE_LOG2 = 8.f;             // how far weights may outgrow the reference exponent of their row (see the kernel)
 
 struct AttnArgs {
@@ -96,10 +89,7 @@ struct Rows16 {
   typedef float floatx4 __attribute__((ext_vector_type(4)));
   bf16x8 qf[HD / 32];                           // dims 32 ks + 8 q .. + 7
   floatx4 o[HD / 16];                           // dims 16 dt + 4 q + e
-  float m, l;                                   // l: in the upper half of the wavefront, or in parts (weights)
-  bf16x8 kf[4][HD / 32], vf[2][HD / 16];        // keys, values, scores [2 half tile + which four of the eight keys], weights
-  floatx4 s[4];
-  bf16x8 pf[2];
+  float m, l;                                   // l: in the upper half of the wavefront
 
   __device__ __forceinline__ void clear() {
     m = -INFINITY;
@@ -118,17 +108,15 @@ struct Rows16 {
     auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
   }
-  __device__ __forceinline__ float lane_sum() const {
-    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(l), __float_as_uint(l), false, false);
-    return half_wave_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
-  }
   __device__ __forceinline__ float sum() const {
     auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(l), __float_as_uint(l), false, false);
     return from_upper(__uint_as_float(r[0]) + __uint_as_float(r[1]));
   }
 
-  __device__ __forceinline__ void read_keys(const char* Ks) {
+  // one tile of 64 keys; keys from `limit` on are masked if need_mask
+  __device__ __forceinline__ void tile(const char* Ks, const char* Vs, bool need_mask, int key_base, int limit, float scale_log2e) {
     const int lane = threadIdx.x & 63, col = lane & 15, quad = lane >> 4;
+    bf16x8 kf[4][HD / 32], vf[2][HD / 16];
 #pragma unroll
     for (int ks = 0; ks < HD / 32; ++ks)
 #pragma unroll
@@ -136,33 +124,19 @@ struct Rows16 {
         const int row = 32 * (p >> 1) + 8 * (col >> 2) + 4 * (p & 1) + (col & 3);
         kf[p][ks] = *(const bf16x8*)(Ks + row * HD * 2 + (k_swizzle<HD, 16>(row, ks * 4 + quad) << 4));
       }
-  }
-  __device__ __forceinline__ void read_values(const char* Vs) {
-    const int lane = threadIdx.x & 63, col = lane & 15, quad = lane >> 4;
+    // the values are on their way while the scores become weights
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
       for (int dt = 0; dt < HD / 16; ++dt)
         vf[hf][dt] = *(const bf16x8*)(Vs + (hf * 2 + (quad >> 1)) * HD * 32 + (dt * 16 + col) * 32 + (((quad & 1) ^ (col >> 3)) << 4));
-  }
-  __device__ __forceinline__ void scores() {
+    floatx4 s[4];                               // [2 half tile + which four of the eight keys]
 #pragma unroll
     for (int p = 0; p < 4; ++p) s[p] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < HD / 32; ++ks)
 #pragma unroll
       for (int p = 0; p < 4; ++p) s[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[p][ks], qf[ks], s[p], 0, 0, 0);
-  }
-  __device__ __forceinline__ void values() {
-#pragma unroll
-    for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-      for (int dt = 0; dt < HD / 16; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[hf][dt], pf[hf], o[dt], 0, 0, 0);
-  }
-  // Scores of 64 keys to weights; keys from `limit` on are masked if need_mask. LANE_SUMS: l is each lane's own part of the sum.
-  template <bool LANE_SUMS, typename F>
-  __device__ __forceinline__ void weights(bool need_mask, int key_base, int limit, float scale_log2e, F then) {
-    const int quad = (threadIdx.x & 63) >> 4;
     if (need_mask) {
 #pragma unroll
       for (int p = 0; p < 4; ++p)
@@ -188,6 +162,7 @@ struct Rows16 {
     }
     const float m_use = m == -INFINITY ? 0.f : m;
     float p8[2][8];
+    bf16x8 pf[2];
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
@@ -195,16 +170,10 @@ struct Rows16 {
         p8[hf][e] = __builtin_amdgcn_exp2f(fmaf(s[2 * hf + (e >> 2)][e & 3], scale_log2e, -m_use));
         pf[hf][e] = (bf16_t)p8[hf][e];
       }
-    then();
-    if (LANE_SUMS) {
-      float sum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int hf = 0; hf < 2; ++hf)
+    for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) sum[e & 3] += p8[hf][e];
-      l += (sum[0] + sum[1]) + (sum[2] + sum[3]);
-      return;
-    }
+      for (int dt = 0; dt < HD / 16; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[hf][dt], pf[hf], o[dt], 0, 0, 0);
     // quarters 0 and 2 (1 and 3) in turn: what the other half adds meanwhile is dropped
     float sum = 0.f;
 #pragma unroll
@@ -217,13 +186,6 @@ struct Rows16 {
       for (int e = 0; e < 8; ++e) sum += p8[hf][e];
     }
     l += sum;
-  }
-  // one tile of 64 keys; the values are on their way while the scores become weights
-  __device__ __forceinline__ void tile(const char* Ks, const char* Vs, bool need_mask, int key_base, int limit, float scale_log2e) {
-    read_keys(Ks);
-    read_values(Vs);
-    scores();
-    weights<false>(need_mask, key_base, limit, scale_log2e, [&] { values(); });
   }
 };
 
@@ -333,8 +295,7 @@ __device__ __forceinline__ void block_part(const AttnArgs& a, int id, char* smem
 // The launches of a few hundred rows leave CUs and nearly all of HBM idle while their chain of softmaxes runs, and the projections
 // behind them wait for weights: what these CUs touch meanwhile comes out of the Infinity Cache afterwards.
 __device__ __forceinline__ void touch_weights(const WeightsAhead& a, char* smem) {
-  const uint32_t wgs = gridDim.x * (gridDim.y - 1), first = (gridDim.x * (blockIdx.y - 1) + blockIdx.x) * blockDim.x + threadIdx.x;
-  const uint32_t all = wgs * blockDim.x;
+  const uint32_t all = gridDim.x * (gridDim.y - 1) * 256, first = (gridDim.x * (blockIdx.y - 1) + blockIdx.x) * 256 + threadIdx.x;
   char* dst = smem + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 256;
 #pragma unroll
   for (int r = 0; r < 3; ++r)
@@ -350,12 +311,10 @@ __device__ __forceinline__ void touch_weights(const WeightsAhead& a, char* smem)
 // no long workgroups that the others wait for. MODE 2: whole blocks, but the tile list (prefix tiles, then block tiles) is cut
 // into n_splits runs handled by different workgroups, for launches that would otherwise leave most CUs idle; a
 // merge kernel combines the partial results.
-// ROWS: query rows of a wavefront and query tile, 32 or (QT 1) 16. GROUPS: of four wavefronts, which take the tiles of the list in
-// turns (two: MODE 0, 16 rows).
-template <int HD, int QT, int MODE, int ROWS, int GROUPS>
-__global__ void __launch_bounds__(256 * GROUPS, QT == 1 ? 2 : 1) attention_mfma_kernel(AttnArgs a) {
+// ROWS: query rows of a wavefront and query tile, 32 or (QT 1, MODE 0 and 1) 16.
+template <int HD, int QT, int MODE, int ROWS>
+__global__ void __launch_bounds__(256, QT == 1 ? 2 : 1) attention_mfma_kernel(AttnArgs a) {
   static_assert(ROWS == 32 || (ROWS == 16 && QT == 1), "16 rows");
-  static_assert(GROUPS == 1 || (MODE == 0 && ROWS == 16), "groups");
   constexpr bool DEC = MODE == 1, SPLIT = MODE != 0;
   constexpr int KROW = HD * 2;              // bytes per key row
   constexpr int KCH = HD / 8;               // 16-byte chunks per key row
@@ -408,7 +367,7 @@ __global__ void __launch_bounds__(256 * GROUPS, QT == 1 ? 2 : 1) attention_mfma_
   }
 
   // the wavefront index as a scalar: page ids, page bases and LDS destinations then live in scalar registers
-  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wave = wave_all & 3, group = wave_all >> 2, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int lq = lane & (ROWS - 1), lh = lane / ROWS;
   const int P = G.len_override >= 0 ? G.len_override : ((table_t)G.lens)[G.b0 + b];
   const int L = G.L;
@@ -521,65 +480,23 @@ __global__ void __launch_bounds__(256 * GROUPS, QT == 1 ? 2 : 1) attention_mfma_
   };
 
   int page_next = 0;
-  char* const ring = smem + group * 2 * STAGE;
-  if (group < n_tiles) {
-    stage_tile(tile_lo + group, page_of(tile_lo + group), ring);
-    page_next = page_of(tile_lo + group + GROUPS);
-  }
-  if constexpr (GROUPS == 2) {
-    // The groups run half a tile apart: while one reads fragments and multiplies (the values of its last tile, the scores of this
-    // one), the other has its softmax, and a barrier changes the roles. Bound by the way of the tiles from L2: two of a group are
-    // on it. (192 workgroups, 2048 keys, us: 33.2 in step, one tile on its way; 36.5 half a tile apart, one; 30.1 two. The value product
-    // in the softmax half: 31.5; values read there, too: 37.4.)
-    if (group + GROUPS < n_tiles) {
-      stage_tile(tile_lo + group + GROUPS, page_next, ring + STAGE);
-      page_next = page_of(tile_lo + group + 2 * GROUPS);
-    }
-    __builtin_amdgcn_s_waitcnt(0x0f70);                // vmcnt(0), which the compiler is told of: the queries are there
-    const bool has_rows = r_wg0 + wave * ROWS < rows_total;
-    if (group == 1) MEET();
-    for (int it = 0; it * GROUPS < n_tiles; ++it) {
-      const int of = it * GROUPS + group, tile = tile_lo + of;
-      char* buf = ring + (it & 1) * STAGE;
-      // own loads of this tile have landed, those of the group's next (2 NI) may be on their way
-      if (of + GROUPS < n_tiles) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * NI) : "memory");
-      else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      MEET();
-      const bool busy = has_rows && of < n_tiles;
-      if (busy) {
-        r16.read_keys(buf);
-        if (it > 0) r16.values();
-        r16.read_values(buf + K_BYTES);
-        r16.scores();
-      }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-      MEET();
-      if (of + 2 * GROUPS < n_tiles) {                 // in place of the tile, whose fragments all have
-        stage_tile(tile + 2 * GROUPS, page_next, buf);
-        page_next = page_of(tile + 3 * GROUPS);        // lands while tiles are being multiplied
-      }
-      if (busy) {
-        const bool is_block = tile >= n_ptiles;
-        const int key_base = is_block ? (tile - n_ptiles) * 64 : tile * 64;
-        r16.template weights<true>(is_block || key_base + 64 > P, key_base, is_block ? tq[0] + 1 : P, a.scale_log2e, [] {});
-      }
-    }
-    if (has_rows && group < n_tiles) r16.values();
-    if (group == 0) MEET();
+  if (n_tiles > 0) {
+    stage_tile(tile_lo, page_of(tile_lo), smem);
+    page_next = page_of(tile_lo + 1);
   }
   // pi(i): A-row i of the S^T product carries key pi(i) of the 32-key half tile
   const int pi_row = (lq & 16) | ((lq & 4) << 1) | ((lq & 8) >> 1) | (lq & 3);
 
-  if constexpr (GROUPS == 1) for (int it = 0; it < n_tiles; ++it) {
+  for (int it = 0; it < n_tiles; ++it) {
     const int tile = tile_lo + it;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (it + 1 < n_tiles) {
-      stage_tile(tile + 1, page_next, ring + ((it + 1) & 1) * STAGE);
+      stage_tile(tile + 1, page_next, smem + ((it + 1) & 1) * STAGE);
       page_next = page_of(tile + 2);                   // lands while this tile is being multiplied
     }
     if ((DEC || ROWS == 16) && r_wg0 + wave * QT * ROWS >= rows_total) continue;   // no rows of its own: this wavefront only stages
-    const char* Ks = ring + (it & 1) * STAGE;
+    const char* Ks = smem + (it & 1) * STAGE;
     const char* Vs = Ks + K_BYTES;
     const bool is_block = tile >= n_ptiles;
     const int key_base = is_block ? (tile - n_ptiles) * 64 : tile * 64;
@@ -700,33 +617,12 @@ __global__ void __launch_bounds__(256 * GROUPS, QT == 1 ? 2 : 1) attention_mfma_
     }
   }
 
-  if constexpr (GROUPS == 2) {
-    // the second group's part goes through LDS to the first
-    typename Rows16<HD>::floatx4* part = (typename Rows16<HD>::floatx4*)smem + threadIdx.x % 256;
-    float* stat = (float*)(smem + HD / 16 * 256 * 16) + threadIdx.x % 256;
-    __syncthreads();                                   // every wavefront is done with the tiles
-    if (group == 1) {
-#pragma unroll
-      for (int dt = 0; dt < HD / 16; ++dt) part[dt * 256] = r16.o[dt];
-      stat[0] = r16.m;
-      stat[256] = r16.l;
-    }
-    __syncthreads();
-    if (group == 1) return;
-    const float m1 = stat[0], m = fmaxf(r16.m, m1);
-    const float w0 = __builtin_amdgcn_exp2f(r16.m - m), w1 = __builtin_amdgcn_exp2f(m1 - m);   // the first group sees a key
-    r16.m = m;
-    r16.l = fmaf(r16.l, w0, stat[256] * w1);
-#pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt) r16.o[dt] = r16.o[dt] * w0 + part[dt * 256] * w1;
-  }
-
   // normalise and store: lane = query column, accumulator value r of d-tile dt is d = dt*32 + 8*(r/4) + 4*lh + r%4
 #pragma unroll
   for (int u = 0; u < QT; ++u) {
     int r = r_wg0 + (wave * QT + u) * ROWS + lq;
     if (ROWS == 16) m_run[u] = r16.m;
-    float l = GROUPS == 2 ? r16.lane_sum() : ROWS == 16 ? r16.sum() : half_wave_sum(l_run[u]);
+    float l = ROWS == 16 ? r16.sum() : half_wave_sum(l_run[u]);
     if (SPLIT) {
       if ((DEC || ROWS == 16) && r >= rows_total) continue;
       const size_t group = DEC ? (size_t)b * a.Hkv + kvh : ((size_t)b * a.Hkv + kvh) * G.n + cand;
@@ -769,19 +665,19 @@ __global__ void __launch_bounds__(256 * GROUPS, QT == 1 ? 2 : 1) attention_mfma_
   }
 }
 
-template <int HD, int QT, int MODE = 0, int ROWS = 32, int GROUPS = 1>
+template <int HD, int QT, int MODE = 0, int ROWS = 32>
 static void launch_attn_variant(const AttnArgs& a, hipStream_t s) {
-  constexpr int smem = 2 * GROUPS * (64 * HD * 2 + 4 * HD * 32);
+  constexpr int smem = 2 * (64 * HD * 2 + 4 * HD * 32);
   static_assert(smem >= BLOCK_LDS, "MODE 1's block keys");
   static bool configured = false;
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)attention_mfma_kernel<HD, QT, MODE, ROWS, GROUPS>,
+    (void)hipFuncSetAttribute((const void*)attention_mfma_kernel<HD, QT, MODE, ROWS>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     configured = true;
   }
   // beside workgroups that leave CUs without one only (32 beams x 8 candidates x 12 heads, 608: nothing gained)
   const int own = a.wg_per_xcd * 8 + a.block_wgs, more = own > 256 ? 0 : (a.ahead.wgs + own - 1) / own;
-  attention_mfma_kernel<HD, QT, MODE, ROWS, GROUPS><<<dim3(own, 1 + more), 256 * GROUPS, smem, s>>>(a);
+  attention_mfma_kernel<HD, QT, MODE, ROWS><<<dim3(own, 1 + more), 256, smem, s>>>(a);
 }
 
 // Merge of the partial results of a MODE 2 launch: HD / 4 lanes per (row, query head), each 16 bytes of it, with all of the
@@ -855,21 +751,6 @@ bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT,
   // eight runs.
   int list_tiles = (max_ctx + 63) / 64 + (g.L + 63) / 64;
   int splits = 1;
-  const int t64 = (rows + 63) / 64;
-  const long wgs64 = (long)g.B * md.Hkv * g.n * t64;
-  // In between, two groups of a workgroup's wavefronts take the list in turns, 64 rows a workgroup, and add up in LDS: as long
-  // alone as runs and their merge (192 workgroups of 64, 12 heads of 128 dims, 2048 keys: 25.2 + 7.3 us / 30.1), but a step of three
-  // models has the CUs and the memory that runs and their partial results take (1024 rows of d = 1536 10.15 -> 9.83 ms, 555 rows
-  // 7.00 -> 6.75; 120, 240 and 180 such workgroups, lists of 18, 18 and at most 48 tiles: 2.6, 2.3 and 3.3 % shorter). With longer lists the
-  // few CUs are what counts (140 workgroups, 65 tiles 0.5 % shorter; 120, 95 tiles 1.3 % longer, 192, 126 tiles 4.1); shorter ones have
-  // no runs to save (64 workgroups, 9 tiles: a step of small models 1205 us, 1217 with two groups).
-  if (!a.last_first && list_tiles >= 16 && list_tiles <= 48 && wgs64 >= 120 && wgs64 <= 256) {
-    a.q_tiles = t64;
-    a.total_wg = (int)wgs64;
-    a.wg_per_xcd = (a.total_wg + 7) / 8;
-    if (md.hd == 128) launch_attn_variant<128, 1, 0, 16, 2>(a, s); else launch_attn_variant<64, 1, 0, 16, 2>(a, s);
-    return true;
-  }
   if (!big && part && a.total_wg < 384 && list_tiles >= 16 && ((uintptr_t)out & 7) == 0) {   // short lists: a second kernel costs more than it saves
     splits = 512 / a.total_wg;
     splits = splits > 8 ? 8 : splits;
@@ -901,6 +782,8 @@ bool launch_attention_mfma(const bf16_t* q, const bf16_t* kb, const bf16_t* vbT,
   // At most 64 rows, or so few that each workgroup of 64 has a CU to itself: 16 rows a wavefront (64 rows, 2048 workgroups:
   // 61.0 us with 32, 43.7 so; 128, 192 and 224 rows, 256 workgroups of 64 or fewer: 11.2, 15.2, 15.9 and 9.5, 12.0, 12.9; 384,
   // 512 and 768 workgroups: 11.7, 12.0, 25.9 and 12.7, 12.8, 27.3, since the rows of a wavefront share its reads of the keys).
+  const int t64 = (rows + 63) / 64;
+  const long wgs64 = (long)g.B * md.Hkv * g.n * t64;
   if (t64 == 1 || wgs64 <= 256) {
     a.q_tiles = t64;
     a.total_wg = (int)wgs64;

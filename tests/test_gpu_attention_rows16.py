@@ -23,13 +23,8 @@ pytestmark = pytest.mark.gpu
     (6, 2, 128, 2, 2, 33, [1, 333]),          # 99
     (4, 1, 64, 1, 3, 70, [100]),              # 280, blocks of two key tiles
     (2, 2, 64, 1, 129, 65, [70]),             # 65 rows, 516 workgroups of 64: wavefronts of 32 rows
-    (2, 2, 128, 1, 2, 32, [1500]),            # 64 rows, 25 key tiles
-    (3, 1, 64, 2, 2, 7, [2000, 1025]),
-    (3, 1, 64, 1, 120, 5, [960]),             # two groups of wavefronts: 16 key tiles in turns, 120 workgroups
-    (2, 2, 128, 1, 30, 70, [1025]),           # 19 tiles, two of them the block's
-    (6, 1, 128, 2, 20, 33, [1, 2900]),        # 2 and 47 tiles
-    (1, 1, 64, 2, 128, 1, [100, 3008]),       # 3 and 48 tiles, 256 workgroups of one row
-    (4, 2, 64, 1, 60, 32, [3009])])           # 49 tiles: one group
+    (2, 2, 128, 1, 2, 32, [1500]),            # 64 rows, a key list in runs
+    (3, 1, 64, 2, 2, 7, [2000, 1025])])
 def test_stacked_rows_around_a_wavefront_and_a_workgroup(ctx, Hq, Hkv, hd, Bn, n, L, lens):   # noqa: F811
     """Averages of unit normals rounded to bf16: half a unit in the last place of values below 4 is 2^-7, and as much again
     for the weights' rounding where a row sees few keys."""
@@ -40,10 +35,9 @@ def test_stacked_rows_around_a_wavefront_and_a_workgroup(ctx, Hq, Hkv, hd, Bn, n
 
 @pytest.mark.parametrize("n,hq,hkv,hd,lens", [
     (1, 1, 1, 64, (63, 64)), (5, 6, 2, 64, (200, 201)), (4, 4, 1, 64, (64, 65)), (8, 4, 2, 128, (700, 701)),
-    (13, 5, 1, 64, (130, 131)), (16, 6, 1, 128, (1024, 1025)), (40, 8, 4, 64, (90, 91)),
-    (3, 3, 1, 128, (4100, 4101)), (3, 2, 1, 64, (6280, 6281))])          # runs of 3 and of 4 key tiles, the last of 2 and of 3
+    (13, 5, 1, 64, (130, 131)), (16, 6, 1, 128, (1024, 1025)), (40, 8, 4, 64, (90, 91))])
 def test_generated_positions_equal_scoring(n, hq, hkv, hd, lens):
-    """Single positions of 1, 15, 16, 16, 65, 96, 80, 9 and 6 stacked rows: log-likelihoods of the drawn tokens against block scoring,
+    """Single positions of 1, 15, 16, 16, 65, 96 and 80 stacked rows: log-likelihoods of the drawn tokens against block scoring,
     within the stated tolerance between the two (2e-2 a token)."""
     from paper_2506_15733_amd import synthetic
     d = hq * hd
