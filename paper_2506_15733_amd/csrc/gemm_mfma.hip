@@ -354,10 +354,10 @@ __device__ __forceinline__ void slice_tiles(const GemmArgs& a, int kslice, int& 
 // each row of wavefronts, half 0, 1 of W: columns 0..31, 32..63 of each wavefront; ' the next K-tile's), ten of them in
 // 160 KiB, i.e. nearly two and a half K-tiles. BM = 128: A | W1 W0' in two phases, three K-tiles in 144 KiB.
 // Operands are requested through buffer descriptors whose size ends with the matrix: rows beyond it, and K-tiles beyond the
-// slice (size 0), are zeros that cost no traffic.
-template <int BM, int EPI, bool HD128>
+// slice (size 0), are zeros that cost no traffic. Without BUFFER by plain addresses, the last row and K-tile again in their place.
+template <int BM, int EPI, bool HD128, bool BUFFER>
 __device__ __forceinline__ void wide_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
-  static_assert(BM == 256 || BM == 192 || BM == 128, "two halves of A, or one");
+  static_assert(BM == 256 || (BM == 192 && BUFFER) || BM == 128, "two halves of A, or one");
   constexpr bool SWAP = EPI == ME_QKV_ROPE && HD128;
   constexpr int NH = BM == 128 ? 1 : 2, TMH = BM / NH / 32, TM = TMH * NH, U = 8192;    // U: what one load of every wavefront fills
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -377,6 +377,7 @@ __device__ __forceinline__ void wide_product(const GemmArgs& a, int m0, int n0, 
   const unsigned row_bytes = (unsigned)a.K * 2u;
   const unsigned a_size = (unsigned)min(a.M - m0, BM) * row_bytes - kt0 * 128, w_size = (unsigned)min(a.N - n0, 256) * row_bytes - kt0 * 128;
   unsigned aoff[NH][2], woff[2][2];
+  const bf16_t *aptr[NH][2], *wptr[2][2];                // without BUFFER, in place of the offsets
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
     const int r = (p * 8 + wave) * 8 + (lane >> 3);
@@ -385,21 +386,31 @@ __device__ __forceinline__ void wide_product(const GemmArgs& a, int m0, int n0, 
     for (int h = 0; h < NH; ++h) {                       // rows beyond the half (BM = 192: 96 of 128) are zeros
       const int wr = r / (16 * TMH), row = wr * 16 * TM + h * 16 * TMH + r - wr * 16 * TMH;
       aoff[h][p] = wr < 2 ? (unsigned)row * row_bytes + chunk : 0x7fffffffu;
+      aptr[h][p] = Ab + (size_t)min(row, a.M - 1 - m0) * a.K + chunk / 2;
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int c = (r >> 5) * 64 + h * 32 + (r & 31);
-      woff[h][p] = (unsigned)(SWAP ? swap56(c) : c) * row_bytes + chunk;
+      const int c = (r >> 5) * 64 + h * 32 + (r & 31), row = SWAP ? swap56(c) : c;
+      woff[h][p] = (unsigned)row * row_bytes + chunk;
+      wptr[h][p] = Wb + (size_t)min(row, a.N - 1 - n0) * a.K + chunk / 2;
     }
   }
   // Unit p of half h of A (W) of K-tile t, to unit `slot` of the ring
   auto load_a = [&](int h, int p, int slot, int t) {
-    const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)Ab, 0, t < KT ? a_size : 0u, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(smem + slot * U + wave * 1024), 16, aoff[h][p], t * 128, 0, 0);
+    if constexpr (BUFFER) {
+      const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)Ab, 0, t < KT ? a_size : 0u, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(smem + slot * U + wave * 1024), 16, aoff[h][p], t * 128, 0, 0);
+    } else {
+      __builtin_amdgcn_global_load_lds(GLB_PTR(aptr[h][p] + min(t, KT - 1) * 64), LDS_PTR(smem + slot * U + wave * 1024), 16, 0, 0);
+    }
   };
   auto load_w = [&](int h, int p, int slot, int t) {
-    const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)Wb, 0, t < KT ? w_size : 0u, 0x00020000);
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(smem + slot * U + wave * 1024), 16, woff[h][p], t * 128, 0, 0);
+    if constexpr (BUFFER) {
+      const auto rs = __builtin_amdgcn_make_buffer_rsrc((void*)Wb, 0, t < KT ? w_size : 0u, 0x00020000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(smem + slot * U + wave * 1024), 16, woff[h][p], t * 128, 0, 0);
+    } else {
+      __builtin_amdgcn_global_load_lds(GLB_PTR(wptr[h][p] + min(t, KT - 1) * 64), LDS_PTR(smem + slot * U + wave * 1024), 16, 0, 0);
+    }
   };
 
   // A fragment is 16 rows x 32 of K: lane l has row l % 16, chunk l / 16 (of 4; chunks 4..7 are the second 32). The rows of a
@@ -528,7 +539,7 @@ __device__ __forceinline__ void wide_product(const GemmArgs& a, int m0, int n0, 
 // 256 x 1536 x 8960 in 5 slices 14.9 / 12.7, gate/up of 256 x 5632 x 1024 9.0 / 7.5).
 template <int BM, int BN, int NWM, int S, int EPI, bool HD128, bool BUFFER>
 __device__ __forceinline__ void ring_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
-  static_assert(BUFFER || BN % 128 == 0, "whole heads");
+  static_assert(BUFFER || BN > 64, "whole heads");
   constexpr bool SWAP = EPI == ME_QKV_ROPE && HD128;
   constexpr int NWN = BN / 64, NW = NWM * NWN;        // wavefronts: NWM along M x NWN along N, 64 columns each
   constexpr int WM = BM / NWM, TM = WM / 16, TN = 4;
@@ -639,9 +650,9 @@ __device__ __forceinline__ void ring_product(const GemmArgs& a, int m0, int n0, 
   epilogue<BM, BN, NWM, EPI, HD128>(a, acc, m0, n0, wm, wn, kslice, part, smem);
 }
 
-template <int BM, int BN, int NWM, int S, int EPI, bool HD128, bool BUFFER = true>
+template <int BM, int BN, int NWM, int S, int EPI, bool HD128, bool BUFFER>
 __device__ __forceinline__ void tile_product(const GemmArgs& a, int m0, int n0, int kslice, int part, char* smem) {
-  if constexpr (BN == 256) wide_product<BM, EPI, HD128>(a, m0, n0, kslice, part, smem);
+  if constexpr (BN == 256) wide_product<BM, EPI, HD128, BUFFER>(a, m0, n0, kslice, part, smem);
   else ring_product<BM, BN, NWM, S, EPI, HD128, BUFFER>(a, m0, n0, kslice, part, smem);
 }
 
@@ -655,8 +666,8 @@ __global__ void __launch_bounds__(NWM * BN) gemm_mfma_kernel(GemmArgs a) {
     const int block = (int)blockIdx.x - a.rest_block;
     if (block >= 0) {
       if (!tile_of(block, a.rest_m_tiles, a.rest_n_tiles, 1, at)) return;
-      tile_product<128, REST, REST == 256 ? 2 : 4, REST == 256 ? 3 : 5, EPI, HD128>(a, at.m * 128, a.n_tiles * BN + at.n * REST, 0,
-                                                                             a.n_tiles + at.n, smem);
+      tile_product<128, REST, REST == 256 ? 2 : 4, REST == 256 ? 3 : 5, EPI, HD128, BUFFER>(a, at.m * 128, a.n_tiles * BN + at.n * REST,
+                                                                                            0, a.n_tiles + at.n, smem);
       return;
     }
   }
@@ -699,8 +710,9 @@ int mfma_gemm_ring(int tile, int M, int N, int K, int ksplit) {
   return tile == 3 && wgs <= 256 && K / 64 > 11 * ksplit ? 6 : ring[tile];
 }
 
-// Operands are requested in 16-byte pieces through descriptors of at most 256 rows, whose offsets have 32 bits. Any others go
-// to one kernel that takes plain addresses, and the vocabulary head of such to the plain kernels.
+// Operands are requested in 16-byte pieces through descriptors of at most 256 rows, whose offsets have 32 bits. Any others get
+// the plan's tile by plain addresses (us, weights 4 bytes beside the grid / on it: head of 2048 x 152064 x 3584 1729 / 1559, gate/up of
+// 2048 x 37888 x 3584 446 / 402, 256 x 1536 x 8960 20.2 / 17.1; all in 128 x 128 tiles 713 for the second and 23.7 for the third).
 static bool buffer_operands(const GemmArgs& a) { return (((uintptr_t)a.A | (uintptr_t)a.W) & 15) == 0 && a.K <= 1 << 22; }
 
 // Tiles that only mfma_gemm_tile gives, behind those of the plan.
@@ -708,42 +720,40 @@ enum { TILE_64 = MFMA_TILES, TILE_32, TILE_192, TILE_SHORT /* 64 x 128, three K-
 
 int mfma_gemm_rest(int M, int N, int K, bool wide_only, int* n_tiles);
 bool mfma_gate_up_192(int M, int N, int K, int tile);
-template <int EPI, bool HD128 = false>
-static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
-  if constexpr (EPI != ME_LMHEAD)
-    if (!buffer_operands(a)) {
-      a.m_tiles = (a.M + 127) / 128;
-      a.n_tiles = (a.N + 127) / 128;
-      launch_variant<128, 128, 4, 5, EPI, HD128, 0, false>(a, s);
+template <int EPI, bool HD128, bool BUFFER>
+static void launch_tile_of(GemmArgs& a, int tile, hipStream_t s) {
+  a.part_tiles = mfma_lmhead_tiles(a.N);
+  if constexpr (BUFFER) {
+    if constexpr (EPI != ME_LMHEAD)
+      if (tile == TILE_64 || tile == TILE_32) {
+        a.m_tiles = tile == TILE_64 ? (a.M + 63) / 64 : (a.M + 31) / 32;
+        a.n_tiles = (a.N + 63) / 64;
+        if (tile == TILE_64) launch_variant<64, 64, 4, 4, EPI, HD128>(a, s);
+        else launch_variant<32, 64, 2, 6, EPI, HD128>(a, s);
+        return;
+      }
+    if (tile == TILE_192) {
+      a.m_tiles = (a.M + 191) / 192;
+      a.n_tiles = (a.N + 255) / 256;
+      launch_variant<192, 256, 2, 5, EPI, HD128>(a, s);
       return;
     }
-  if constexpr (EPI != ME_LMHEAD)
-    if (tile == TILE_64 || tile == TILE_32) {
-      a.m_tiles = tile == TILE_64 ? (a.M + 63) / 64 : (a.M + 31) / 32;
-      a.n_tiles = (a.N + 63) / 64;
-      if (tile == TILE_64) launch_variant<64, 64, 4, 4, EPI, HD128>(a, s);
-      else launch_variant<32, 64, 2, 6, EPI, HD128>(a, s);
-      return;
-    }
+  } else {
+    if (tile == TILE_64 || tile == TILE_32) tile = 3;
+    if (tile == TILE_192) tile = 0;
+  }
   if constexpr (EPI != ME_LMHEAD)
     if (tile == TILE_SHORT) {
       a.m_tiles = (a.M + 63) / 64;
       a.n_tiles = (a.N + 127) / 128;
-      launch_variant<64, 128, 4, 3, EPI, HD128>(a, s);
+      launch_variant<64, 128, 4, 3, EPI, HD128, 0, BUFFER>(a, s);
       return;
     }
-  a.part_tiles = mfma_lmhead_tiles(a.N);
-  if (tile == TILE_192) {
-    a.m_tiles = (a.M + 191) / 192;
-    a.n_tiles = (a.N + 255) / 256;
-    launch_variant<192, 256, 2, 5, EPI, HD128>(a, s);
-    return;
-  }
   if constexpr (EPI == ME_SWIGLU)
     if (mfma_gate_up_192(a.M, a.N, a.K, tile)) {
       a.m_tiles = (a.M + 127) / 128;
       a.n_tiles = (a.N + 191) / 192;
-      launch_variant<128, 192, 2, 4, EPI, HD128>(a, s);
+      launch_variant<128, 192, 2, 4, EPI, HD128, 0, BUFFER>(a, s);
       return;
     }
   a.m_tiles = (a.M + kTiles[tile].bm - 1) / kTiles[tile].bm;
@@ -756,21 +766,26 @@ static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
       a.rest_n_tiles = (a.N - 256 * a.n_tiles + rest - 1) / rest;
     }
     if constexpr (EPI != ME_RESIDUAL) {
-      if (rest == 256) launch_variant<256, 256, 2, 5, EPI, HD128, 256>(a, s);
+      if (rest == 256) launch_variant<256, 256, 2, 5, EPI, HD128, 256, BUFFER>(a, s);
       if constexpr (EPI != ME_LMHEAD)
-        if (rest == 128) launch_variant<256, 256, 2, 5, EPI, HD128, 128>(a, s);
+        if (rest == 128) launch_variant<256, 256, 2, 5, EPI, HD128, 128, BUFFER>(a, s);
     }
-    if (!rest) launch_variant<256, 256, 2, 5, EPI, HD128>(a, s);
+    if (!rest) launch_variant<256, 256, 2, 5, EPI, HD128, 0, BUFFER>(a, s);
   }
-  else if (tile == 1) launch_variant<128, 256, 2, 3, EPI, HD128>(a, s);
+  else if (tile == 1) launch_variant<128, 256, 2, 3, EPI, HD128, 0, BUFFER>(a, s);
   else if constexpr (EPI != ME_LMHEAD) {
     // four wavefronts along M: two per SIMD cover each other's LDS reads (us, two along M / four: 1024 x 2048 x 1536 in 64 x 128
     // tiles 13.9 / 12.2, 1024 x 1536 x 1536 13.6 / 11.2, 256 x 2048 x 1024 9.8 / 8.3)
-    if (tile == 2) launch_variant<128, 128, 4, 5, EPI, HD128>(a, s);
-    else if (mfma_gemm_ring(tile, a.M, a.N, a.K, a.ksplit) == 6) launch_variant<64, 128, 4, 6, EPI, HD128>(a, s);
-    else if (tile == 3) launch_variant<64, 128, 4, 3, EPI, HD128>(a, s);
-    else launch_variant<32, 128, 2, 4, EPI, HD128>(a, s);
+    if (tile == 2) launch_variant<128, 128, 4, 5, EPI, HD128, 0, BUFFER>(a, s);
+    else if (mfma_gemm_ring(tile, a.M, a.N, a.K, a.ksplit) == 6) launch_variant<64, 128, 4, 6, EPI, HD128, 0, BUFFER>(a, s);
+    else if (tile == 3) launch_variant<64, 128, 4, 3, EPI, HD128, 0, BUFFER>(a, s);
+    else launch_variant<32, 128, 2, 4, EPI, HD128, 0, BUFFER>(a, s);
   }
+}
+template <int EPI, bool HD128 = false>
+static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
+  if (buffer_operands(a)) launch_tile_of<EPI, HD128, true>(a, tile, s);
+  else launch_tile_of<EPI, HD128, false>(a, tile, s);
 }
 
 // Gate and up in 128 x 192 tiles where the plan says 128 x 256 and a single round does: a few hundred rows then occupy a third
@@ -940,7 +955,6 @@ bool launch_gemm_mfma(int epi, const bf16_t* A, const bf16_t* W, int M, int N, i
   GemmArgs a = {};
   a.A = A; a.W = W; a.M = M; a.N = N; a.K = K; a.C = C; a.act = act; a.tok = tok;
   a.part_max = part_max; a.part_sum = part_sum; a.zt = zt; a.ksplit = ksplit;
-  if (epi == ME_LMHEAD && !buffer_operands(a)) return false;
   int split = 1;
   if (tile < 0) mfma_gemm_tile(M, N, K, 1, epi == ME_LMHEAD, false, &tile, &split);
   switch (epi) {

@@ -54,7 +54,11 @@ def test_store_and_residual_are_exact(tile, k_tiles):
 def test_vocabulary_head_finds_targets_and_maxima(tile, k_tiles):
     M, N, K = 261, 1000, 64 * k_tiles
     A, Wt = whole((M, K), 3), whole((N, K), 4)
-    z = A.float() @ Wt.float().t()
+    check_head(A, Wt, A.float() @ Wt.float().t(), tile)
+
+
+def check_head(A, Wt, z, tile):
+    (M, K), N = A.shape, len(Wt)
     tok = torch.randint(0, N, (M,), generator=torch.Generator().manual_seed(5), dtype=torch.int32).to(DEV)
     tiles = -(-N // 256)
     pm, ps = torch.full((2, M, tiles), float("nan"), device=DEV)
@@ -82,35 +86,49 @@ def test_gate_up_columns_meet_their_partners(tile):
     assert torch.all((act.double() - want).abs() <= want.abs() * (2.0 ** -8 + 2.0 ** -17 + 8 * 2.0 ** -23) + 1e-30)
 
 
-@pytest.mark.parametrize("epilogue", [STORE, SWIGLU, HEAD])
-def test_operands_off_the_16_byte_grid(epilogue):
-    """4 bytes beside it: the kernel that takes plain addresses, and for the head, which has none, the caller's plain kernel."""
-    M, N, K = 140, 192, 320
-    A = torch.zeros(M * K + 2, dtype=torch.bfloat16, device=DEV)[2:].view(M, K).copy_(whole((M, K), 8, 1))
-    Wt = torch.zeros(N * K + 2, dtype=torch.bfloat16, device=DEV)[2:].view(N, K).copy_(whole((N, K), 9, 1))
-    want = A.float() @ Wt.float().t()
-    if epilogue == HEAD:
-        assert not launch(HEAD, A, Wt, M, N, K)
-    elif epilogue == STORE:
-        for tile in (-1, *TILES):
-            assert launch(STORE, A, Wt, M, N, K, out := torch.full((M, N), float("nan"), device=DEV), tile=tile)
-            assert torch.equal(out, want), tile
-    else:
-        assert launch(SWIGLU, A, Wt, M, N, K, act=(act := torch.full((M, N // 2), float("nan"), dtype=torch.bfloat16, device=DEV)))
-        z = want.double().view(M, N // 64, 2, 32)
-        ref = (torch.nn.functional.silu(z[:, :, 0]) * z[:, :, 1]).reshape(M, N // 2)
-        assert torch.allclose(act.double(), ref, rtol=2.0 ** -8 + 2.0 ** -16, atol=1e-30)
+def off_the_grid(x):
+    """The same values 4 bytes beside the 16-byte grid."""
+    return torch.zeros(x.numel() + 2, dtype=x.dtype, device=DEV)[2:].view(x.shape).copy_(x)
 
 
+@pytest.mark.parametrize("k_tiles", [1, 5, 7])
+@pytest.mark.parametrize("epilogue", [STORE, RESIDUAL, SWIGLU, HEAD])
+def test_operands_off_the_16_byte_grid(epilogue, k_tiles):
+    """The kernels that take plain addresses."""
+    M, N, K = 300, 576, 64 * k_tiles
+    A, Wt = off_the_grid(whole((M, K), 8, 1)), off_the_grid(whole((N, K), 9, 1))
+    z = A.float() @ Wt.float().t()
+    for tile in (-1, *(WIDE if epilogue == HEAD else TILES)):
+        if epilogue == STORE:
+            for split in (1, 2)[:k_tiles]:
+                out = torch.full((split, M, N), float("nan"), device=DEV)
+                assert launch(STORE, A, Wt, M, N, K, out, split=split, tile=tile)
+                assert torch.equal(out.sum(0), z), (tile, split)
+        elif epilogue == RESIDUAL:
+            assert launch(RESIDUAL, A, Wt, M, N, K, out := z.clone(), tile=tile)
+            assert torch.equal(out, 2 * z), tile
+        elif epilogue == SWIGLU:
+            act = torch.full((M, N // 2), float("nan"), dtype=torch.bfloat16, device=DEV)
+            assert launch(SWIGLU, A, Wt, M, N, K, act=act, tile=tile)
+            y = z.double().view(M, N // 64, 2, 32)
+            ref = (torch.nn.functional.silu(y[:, :, 0]) * y[:, :, 1]).reshape(M, N // 2)
+            assert torch.allclose(act.double(), ref, rtol=2.0 ** -8 + 2.0 ** -16, atol=1e-30), tile
+        else:
+            check_head(A, Wt, z, tile)
+
+
+@pytest.mark.parametrize("on_grid", [True, False])
 @pytest.mark.parametrize("position", [None, 0, 9, 20])   # whole blocks of 21 tokens, or one token of each
 @pytest.mark.parametrize("hd", [64, 128])
 @pytest.mark.parametrize("tile", TILES)
-def test_queries_keys_and_values_land_where_they_belong(tile, hd, position):
+def test_queries_keys_and_values_land_where_they_belong(tile, hd, position, on_grid):
     """Rotations by multiples of a quarter turn: every output is a whole number that bf16 holds."""
     Hq, Hkv, Lk, C_, K, Lp = 5, 2, 21, 1 if tile == 4 else 14 if position is None else 70, 64, 32
     L = Lk if position is None else 1
     M = C_ * L
     A, Wt = whole((M, K), 10, 1), whole(((Hq + 2 * Hkv) * hd, K), 11, 1)
+    if not on_grid:
+        A, Wt = off_the_grid(A), off_the_grid(Wt)
     turn = torch.randint(0, 4, (M, hd // 2), generator=torch.Generator().manual_seed(12)).to(DEV)
     c, s = torch.tensor([1.0, 0, -1, 0], device=DEV)[turn], torch.tensor([0, 1.0, 0, -1], device=DEV)[turn]
     cs = torch.cat([c, s], 1).contiguous()
