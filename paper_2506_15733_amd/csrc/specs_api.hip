@@ -541,9 +541,15 @@ static void attention(const T* q, const T* kb, const T* vbT, const T* pK, const 
                       size_t scratch_floats, const WeightsAhead& ahead, hipStream_t s);
 // What of a layer's weights to touch during the attention of `rows` rows: of the O projection, gate and up, and down, in this order,
 // as much as comes in beside such a launch (24 MB). Up to 256 rows, whose projections are bound by how soon and fast their weights
-// arrive (step of 256 rows of d = 1024 1.28 -> 1.26 ms, generation of 16 rows of d = 1536 95.2 -> 94.0; 1024 rows of d = 1536 10.19 ->
-// 10.24), not where a layer is so large that this is little of it (d = 3584: 117.5 -> 118.1), and not where a model that is
-// generating fits the Infinity Cache and is there from the position before (165 MB of d = 1024: 6.65 -> 6.75).
+// arrive: passes that score 16 to 256 rows, prefixes of 24 to 4096 tokens, take 0.90 to 0.98 of the time at 16 layers of d = 1024,
+// 0.94 to 1.00 at 24 of d = 896 and 0.96 to 1.01 at 28 of d = 1536, where runs differ by 0.8 % (1024 rows of d = 1536, a step of three models: 10.19 -> 10.24 ms).
+// Not where a layer is so large that this is little of it (d = 3584: 117.5 -> 118.1), nor where the whole model fits the Infinity
+// Cache and is there from the pass before (154 MB of d = 1024: 16 rows 139.8 -> 143.4 us, 256 rows 202.3 -> 201.9). While generating
+// not where it is nearly a whole layer either, whose products are bound by their latency then (27 MB of d = 896: 2 rows 6.71 -> 6.85
+// ms, 16 rows 7.25 -> 7.40, 32 rows 8.32 -> 8.51; 83 MB of d = 1536: 10.52 -> 10.35, 11.38 -> 11.05, 12.49 -> 12.27).
+bool weights_touched(int rows, size_t layer, size_t model, bool position) {
+  return rows <= 256 && layer <= 128u << 20 && model >= 256u << 20 && (!position || layer >= 64u << 20);
+}
 template <typename T>
 static WeightsAhead weights_ahead(const specs_layer_weights&, const specs_model_desc&, int, bool) { return WeightsAhead{}; }
 template <>
@@ -552,7 +558,7 @@ WeightsAhead weights_ahead<bf16_t>(const specs_layer_weights& L, const specs_mod
   const size_t dm = d.d_model, qd = (size_t)d.n_q_heads * d.head_dim, kvd = (size_t)d.n_kv_heads * d.head_dim;
   const size_t bytes[3] = {2 * qd * dm, 4 * dm * d.ffn, 2 * dm * d.ffn}, layer = bytes[0] + bytes[1] + bytes[2];
   const size_t model = d.n_layers * (layer + 2 * dm * (qd + 2 * kvd)) + (d.head == SPECS_HEAD_LM ? 2 * dm * d.vocab : 0);
-  if (rows > 256 || layer > 128u << 20 || (position && model < 256u << 20)) return a;
+  if (!weights_touched(rows, layer, model, position)) return a;
   const void* at[3] = {L.wo, L.wgu, L.wd};
   size_t room = 24u << 20;
   for (int i = 0; i < 3; ++i) {
