@@ -294,7 +294,7 @@ def main():
         with torch.cuda.stream(step.role_streams[r]):
             e0.record()
             for _ in range(3):
-                step.score(r)
+                step.score(r, alone=True)
             e1.record()
         torch.cuda.synchronize()
         role_ms[r] = e0.elapsed_time(e1) / 3
@@ -306,7 +306,7 @@ def main():
     dm = step.models["target"]
     B.specs_ctx_profile(dm.ctx, True)
     for _ in range(3):
-        step.score("target")
+        step.score("target", alone=True)
     prof = B.specs_ctx_profile_read(dm.ctx)
     B.specs_ctx_profile(dm.ctx, False)
     kernel_us = {k: (1e3 * ms / n if n else 0.0) for k, (ms, n) in prof.items()}

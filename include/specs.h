@@ -100,6 +100,12 @@ int specs_ctx_destroy(specs_ctx* ctx);
  * error since the last call of this function) in *device_status and clears it. */
 int specs_ctx_status(specs_ctx* ctx, int* device_status);
 
+/* Says whether the scoring passes of this context usually run at the same time as work of other contexts on the same GPU
+ * (the models of a step, each with a stream of its own). Off at first. Their kernels then leave each other room, which makes
+ * the passes together shorter and one on its own a little longer; the results are the same to the bit.
+ * specs_score_target_and_reward knows by itself when its two contexts have different streams. */
+int specs_ctx_concurrent(specs_ctx* ctx, int enable);
+
 /* Per-kernel timing (HIP events on the context's stream around every launch of the scoring pass, grouped
  * by kernel class). specs_ctx_profile(ctx, 1) clears the records and switches recording on for the calls
  * that follow; specs_ctx_profile_read synchronises the stream and returns, per class, the summed duration

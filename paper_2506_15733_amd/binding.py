@@ -16,7 +16,7 @@ EXPORTED_SYMBOLS = [
     "specs_commit_block", "specs_subsample", "specs_strerror", "specs_generate_blocks",
     "specs_op_linear", "specs_op_gate_up", "specs_op_lmhead_logprob", "specs_op_attention",
     "specs_ctx_profile", "specs_ctx_profile_read", "specs_score_blocks_static", "specs_score_target_and_reward", "specs_op_qkv_rope",
-    "specs_commit_block_dev", "specs_select_and_switch", "specs_path_counts",
+    "specs_commit_block_dev", "specs_select_and_switch", "specs_path_counts", "specs_ctx_concurrent",
 ]
 PATH_CLASSES = ("gemm_mfma", "gemm_skinny", "gemm_plain", "attn_mfma", "attn_plain")
 KERNEL_CLASSES = ("qkv", "attention", "oproj", "gate_up", "down", "lmhead", "other")
@@ -76,6 +76,7 @@ def load_library():
     lib.specs_select_and_switch.argtypes = [vp, vp, vp, vp, vp, i32, i32, C.c_float, C.c_float, vp, vp, vp, vp]
     lib.specs_path_counts.argtypes = [C.POINTER(i32), C.c_int]
     lib.specs_subsample.argtypes = [vp, vp, vp, vp, vp, i32, i32, C.POINTER(C.c_float), i32, vp, vp, vp]
+    lib.specs_ctx_concurrent.argtypes = [vp, C.c_int]
     lib.specs_ctx_profile.argtypes = [vp, C.c_int]
     lib.specs_ctx_profile_read.argtypes = [vp, C.POINTER(C.c_float), C.POINTER(i32)]
     lib.specs_op_linear.argtypes = [vp, i32, vp, vp, i32, i32, i32, vp, i32]
@@ -138,6 +139,10 @@ def specs_ctx_status(ctx):
     v = C.c_int(0)
     _check(load_library().specs_ctx_status(ctx, C.byref(v)), "specs_ctx_status")
     return v.value
+
+
+def specs_ctx_concurrent(ctx, enable):
+    _check(load_library().specs_ctx_concurrent(ctx, 1 if enable else 0), "specs_ctx_concurrent")
 
 
 def specs_ctx_profile(ctx, enable):

@@ -888,11 +888,12 @@ void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* til
 // slices 6.1, 4.9, 5.4 (512 workgroups of the last, in 2: 5.2). A few CUs with two of the 64 x 64 ones do no harm while the weights are
 // few (555 x 2048 x 1536, 288 of them: 14.3 / 12.4; but 256 x 4608 x 3584, 288: 28.1 / 32.4, gate/up of 64 x 17920 x 1536, 280: 18.3 /
 // 20.1); where many have two, 64 x 128 is ahead (256 x 5632 x 1024: 352, 11.2 / 12.3; 1024 x 2048 x 1536: 512, 14.6 / 16.1).
-// beside: the launch will probably run beside those of other models (the models of a step score their blocks at the same time). The
+// beside: the caller said that other launches run beside this one (the models of a step score their blocks at the same time). The
 // longer ring of the 64 x 128 tiles takes a CU's LDS to itself, so of two such launches, of 129 to 256 workgroups each, one waits for
 // CUs of the other. The short one leaves room for a second workgroup; alone it costs 4 to 7 % of a launch up to 24
 // K-tiles, and 7 to 10 % beyond (us, 256 x 5632 x 1024 7.9 / 8.5, 1024 x 2048 x 1536 12.2 / 12.7, 256 x 1536 x 8960 in 5 slices 12.4 /
-// 13.3, 256 x 4608 x 3584 18.6 / 20.7). A step of three models of 4 and 16 layers of d = 1024 1260 us with the long ring, 1210 so.
+// 13.3, 256 x 4608 x 3584 18.6 / 20.7). A step of three models of 4 and 16 layers of d = 1024 1260 us with the long ring, 1210 so;
+// one of them alone 795 us with the long ring, 805 so.
 void mfma_gemm_tile(int M, int N, int K, int max_split, bool wide_only, bool beside, int* tile_out, int* split_out) {
   mfma_gemm_plan(M, N, K, max_split, wide_only, tile_out, split_out);
   if (*tile_out <= 1) {
@@ -924,7 +925,7 @@ bool launch_gemm_mfma_qkv_rope(const bf16_t* A, const bf16_t* W, const float* cs
   a.cs = cs; a.q = q; a.kblk = kblk; a.vT = vT;
   a.Hq = md.Hq; a.Hkv = md.Hkv; a.Lrows = g.L; a.Lk = g.Lk; a.Lp = Lp; a.t0 = g.t0;
   int split = 1;
-  if (tile < 0) mfma_gemm_tile(M, N, K, 1, false, g.L > 1 && g.B * g.n > 1, &tile, &split);
+  if (tile < 0) mfma_gemm_tile(M, N, K, 1, false, false, &tile, &split);
   if (md.hd == 128) launch_tile<ME_QKV_ROPE, true>(a, tile, s);
   else launch_tile<ME_QKV_ROPE, false>(a, tile, s);
   return true;

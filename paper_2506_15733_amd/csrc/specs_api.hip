@@ -189,6 +189,7 @@ struct specs_ctx {
   const specs_model* last_model;
   const specs_prefix* last_prefix;
   int last_n, last_L;
+  bool concurrent;           // specs_ctx_concurrent
 };
 
 static bool desc_ok(const specs_model_desc& d) {
@@ -222,6 +223,7 @@ extern "C" int specs_ctx_create(int device, void* hip_stream, void* workspace, s
   c->last_model = nullptr;
   c->last_prefix = nullptr;
   c->last_n = c->last_L = 0;
+  c->concurrent = false;
   hipError_t e = hipMemsetAsync(workspace, 0, 256, c->stream);   // the status word
   if (e != hipSuccess) { delete c; return SPECS_EHIP; }
   *out = c;
@@ -232,6 +234,12 @@ extern "C" int specs_ctx_destroy(specs_ctx* ctx) {
   if (ctx)
     for (hipEvent_t e : ctx->prof.pool) (void)hipEventDestroy(e);
   delete ctx;
+  return SPECS_OK;
+}
+
+extern "C" int specs_ctx_concurrent(specs_ctx* ctx, int enable) {
+  if (!ctx) return SPECS_EINVAL;
+  ctx->concurrent = enable != 0;
   return SPECS_OK;
 }
 
@@ -441,16 +449,19 @@ int gemm_store_split<bf16_t>(const bf16_t* A, const bf16_t* W, float* C, int max
 // of one position per block where the projection does not gain more from slices of K (max_split at most). Blocks that have no
 // more than one token, which no workload scores or generates, keep the rotary kernel.
 template <typename T>
-static bool qkv_rope_fused(const T*, const T*, const float*, T*, T*, T*, const BatchGeom&, const ModelDims&, int, int,
+static bool qkv_rope_fused(const T*, const T*, const float*, T*, T*, T*, const BatchGeom&, const ModelDims&, int, int, bool,
                            hipStream_t) {
   return false;
 }
 template <>
 bool qkv_rope_fused<bf16_t>(const bf16_t* A, const bf16_t* W, const float* cs, bf16_t* q, bf16_t* kb, bf16_t* vT,
-                            const BatchGeom& g, const ModelDims& md, int Lp, int max_split, hipStream_t s) {
+                            const BatchGeom& g, const ModelDims& md, int Lp, int max_split, bool beside, hipStream_t s) {
   const bool few = g.L == 1 && launch_few_rows_qkv_rope(nullptr, nullptr, A, W, cs, q, kb, vT, g, md, Lp, s);
-  if (!few && g.L == 1 && (g.M <= 32 || g.Lk == 1 || !qkv_rope_position(g.M, (md.Hq + 2 * md.Hkv) * md.hd, md.d, max_split))) return false;
-  if (!few && !launch_gemm_mfma_qkv_rope(A, W, cs, q, kb, vT, g, md, Lp, -1, s)) return false;
+  const int N = (md.Hq + 2 * md.Hkv) * md.hd;
+  if (!few && g.L == 1 && (g.M <= 32 || g.Lk == 1 || !qkv_rope_position(g.M, N, md.d, max_split))) return false;
+  int tile = -1, split = 1;
+  if (!few && md.d % 64 == 0) mfma_gemm_tile(g.M, N, md.d, 1, false, beside, &tile, &split);
+  if (!few && !launch_gemm_mfma_qkv_rope(A, W, cs, q, kb, vT, g, md, Lp, tile, s)) return false;
   count_mfma(g.M);
   return true;
 }
@@ -544,21 +555,22 @@ static void attention(const T* q, const T* kb, const T* vbT, const T* pK, const 
 // arrive: passes that score 16 to 256 rows, prefixes of 24 to 4096 tokens, take 0.90 to 0.98 of the time at 16 layers of d = 1024,
 // 0.94 to 1.00 at 24 of d = 896 and 0.96 to 1.01 at 28 of d = 1536, where runs differ by 0.8 % (1024 rows of d = 1536, a step of three models: 10.19 -> 10.24 ms).
 // Not where a layer is so large that this is little of it (d = 3584: 117.5 -> 118.1), nor where the whole model fits the Infinity
-// Cache and is there from the pass before (154 MB of d = 1024: 16 rows 139.8 -> 143.4 us, 256 rows 202.3 -> 201.9). While generating
+// Cache and is there from the pass before (154 MB of d = 1024: 16 rows 139.8 -> 143.4 us, 256 rows 202.3 -> 201.9; but beside two
+// models of 424 and 360 MB, whose weights take its place, a step 1199 -> 1192). While generating
 // not where it is nearly a whole layer either, whose products are bound by their latency then (27 MB of d = 896: 2 rows 6.71 -> 6.85
 // ms, 16 rows 7.25 -> 7.40, 32 rows 8.32 -> 8.51; 83 MB of d = 1536: 10.52 -> 10.35, 11.38 -> 11.05, 12.49 -> 12.27).
-bool weights_touched(int rows, size_t layer, size_t model, bool position) {
-  return rows <= 256 && layer <= 128u << 20 && model >= 256u << 20 && (!position || layer >= 64u << 20);
+bool weights_touched(int rows, size_t layer, size_t model, bool position, bool beside) {
+  return rows <= 256 && layer <= 128u << 20 && (beside || model >= 256u << 20) && (!position || layer >= 64u << 20);
 }
 template <typename T>
-static WeightsAhead weights_ahead(const specs_layer_weights&, const specs_model_desc&, int, bool) { return WeightsAhead{}; }
+static WeightsAhead weights_ahead(const specs_layer_weights&, const specs_model_desc&, int, bool, bool) { return WeightsAhead{}; }
 template <>
-WeightsAhead weights_ahead<bf16_t>(const specs_layer_weights& L, const specs_model_desc& d, int rows, bool position) {
+WeightsAhead weights_ahead<bf16_t>(const specs_layer_weights& L, const specs_model_desc& d, int rows, bool position, bool beside) {
   WeightsAhead a = {};
   const size_t dm = d.d_model, qd = (size_t)d.n_q_heads * d.head_dim, kvd = (size_t)d.n_kv_heads * d.head_dim;
   const size_t bytes[3] = {2 * qd * dm, 4 * dm * d.ffn, 2 * dm * d.ffn}, layer = bytes[0] + bytes[1] + bytes[2];
   const size_t model = d.n_layers * (layer + 2 * dm * (qd + 2 * kvd)) + (d.head == SPECS_HEAD_LM ? 2 * dm * d.vocab : 0);
-  if (!weights_touched(rows, layer, model, position)) return a;
+  if (!weights_touched(rows, layer, model, position, beside)) return a;
   const void* at[3] = {L.wo, L.wgu, L.wd};
   size_t room = 24u << 20;
   for (int i = 0; i < 3; ++i) {
@@ -590,6 +602,9 @@ static BatchGeom stretch_geom(const specs_prefix* p, const Stretch& st, int rows
   return g;
 }
 
+// Whether a pass leaves room for launches beside its own: blocks of several candidates, where the caller says that there are some.
+bool launches_beside(bool concurrent, const BatchGeom& g) { return concurrent && g.L > 1 && g.B * g.n > 1; }
+
 // The trunk over g.M rows: every row attends to its beam's cached prefix and causally to the earlier
 // positions of its own block. Row m embeds tokens[m] (null: x and
 // ws.cs hold the embedded rows and their angles already). Leaves the final residual stream in x and the
@@ -597,14 +612,14 @@ static BatchGeom stretch_geom(const specs_prefix* p, const Stretch& st, int rows
 // g.t0 = t adds position t of every block). stretches (prefill): the rows are those of these prompts, which only the
 // embedding, the attention and the pages tell apart; everything else sees one block of g.M rows. Keys and values are
 // also written into the prefix pages.
-// last_token_only (whole-block launches): the caller reads x only at the last token of every block (the PRM head),
+// concurrent: what specs_ctx_concurrent says. last_token_only (whole-block launches): the caller reads x only at the last token of every block (the PRM head),
 // so after the last layer's keys and values exist for all rows, its attention output, O projection and
 // feed-forward run for that one row per block; the other rows of x are left as the last layer found them.
 template <typename T>
 static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* p, const Workspace& ws,
                       const BatchGeom& g, float* x, const int32_t* tokens, int max_ctx,
                       const Stretches* stretches, int64_t R, int64_t C, hipStream_t s,
-                      bool last_token_only = false) {
+                      bool last_token_only = false, bool concurrent = false) {
   const specs_model_desc& d = m->desc;
   ModelDims md = dims_of(d);
   const int Lp = round16(g.Lk);
@@ -634,7 +649,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
     return (int)(room < MFMA_MAX_SPLIT ? room : MFMA_MAX_SPLIT);
   };
   const int max_split = max_split_of(g.M);
-  const bool beside = g.L > 1 && g.B * g.n > 1;          // blocks of several candidates, which several models score at the same time
+  const bool beside = launches_beside(concurrent, g);
   const int qkv_split = (int)(R / g.M < MFMA_MAX_SPLIT ? R / g.M : MFMA_MAX_SPLIT);   // ws.qkv has room for R / g.M slices of QKV
   DecodeRuns runs = {};
   if (d.dtype == SPECS_BF16 && !stretches && (g.L == 1 || last_token_only))
@@ -656,7 +671,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
       PROFILED(ctx, SPECS_K_OTHER, s, launch_rmsnorm<T>(x, L.g_attn, (T*)ws.a, g.M, md.d, md.eps, s));
     if (!fused_rope)
       PROFILED_IF(ctx, SPECS_K_QKV, s, fused_rope,
-                  qkv_rope_fused<T>((const T*)ws.a, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, qkv_split, s));
+                  qkv_rope_fused<T>((const T*)ws.a, (const T*)L.wqkv, ws.cs, (T*)ws.q, kb, vb, g, md, Lp, qkv_split, beside, s));
     if (!fused_rope) {
       int qkv_parts = 1;
       PROFILED(ctx, SPECS_K_QKV, s,
@@ -672,7 +687,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
                launch_gather_last_rows<T>((const T*)ws.q, q1, qd, x, ws.xs, md.d, (int)C, g.L, s));
       PROFILED(ctx, SPECS_K_ATTENTION, s,
                attention<T>(q1, kb, vb, pK, pV, (T*)ws.attn, gl, md, Lp, max_ctx, runs, ws.gu,
-                            ws.gu_floats, weights_ahead<T>(L, d, gl.M, false), s));
+                            ws.gu_floats, weights_ahead<T>(L, d, gl.M, false, beside), s));
       int pl = 0;
       PROFILED(ctx, SPECS_K_OPROJ, s,
                pl = gemm_residual_split<T>((const T*)ws.attn, (const T*)L.wo, ws.xs, ws.gu, max_split_of(gl.M), false, gl.M, md.d, qd, s));
@@ -710,7 +725,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
     } else {
       PROFILED(ctx, SPECS_K_ATTENTION, s,
                attention<T>((const T*)ws.q, kb, vb, pK, pV, (T*)ws.attn, g, md, Lp, max_ctx, runs,
-                            ws.gu, ws.gu_floats, weights_ahead<T>(L, d, g.M, g.L < g.Lk), s));
+                            ws.gu, ws.gu_floats, weights_ahead<T>(L, d, g.M, g.L < g.Lk, beside), s));
     }
     int parts = 0;
     PROFILED(ctx, SPECS_K_OPROJ, s,
@@ -744,7 +759,7 @@ static void run_trunk(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
 // The status word is the context's in both cases.
 template <typename T>
 static int score_impl(specs_ctx* ctx, const specs_model* m, const specs_prefix* p, const int32_t* cand, int n, int L,
-                      float* out, float* tok_logp, char* base, size_t bytes) {
+                      float* out, float* tok_logp, char* base, size_t bytes, bool concurrent) {
   const specs_model_desc& d = m->desc;
   int64_t R = (int64_t)p->B * n * L;
   int64_t C = (int64_t)p->B * n;
@@ -755,7 +770,7 @@ static int score_impl(specs_ctx* ctx, const specs_model* m, const specs_prefix* 
   int max_ctx = 0;
   for (int b = 0; b < p->B; ++b) max_ctx = p->lens[b] > max_ctx ? p->lens[b] : max_ctx;
   hipStream_t s = ctx->stream;
-  run_trunk<T>(ctx, m, p, ws, g, ws.x, cand, max_ctx, nullptr, R, C, s, d.head == SPECS_HEAD_PRM);
+  run_trunk<T>(ctx, m, p, ws, g, ws.x, cand, max_ctx, nullptr, R, C, s, d.head == SPECS_HEAD_PRM, concurrent);
   if (d.head == SPECS_HEAD_LM) {
     int tiles = 0;
     PROFILED(ctx, SPECS_K_OTHER, s,
@@ -790,13 +805,18 @@ static int score_args_ok(specs_ctx* ctx, const specs_model* m, const specs_prefi
   return SPECS_OK;
 }
 
+static int score_blocks(specs_ctx* ctx, const specs_model* m, const specs_prefix* p, const int32_t* cand, int n, int L, float* out,
+                        float* tok_logp, bool concurrent) {
+  HIP_TRY(hipSetDevice(ctx->device));
+  return m->desc.dtype == SPECS_BF16
+             ? score_impl<bf16_t>(ctx, m, p, cand, n, L, out, tok_logp, ctx->workspace, ctx->workspace_bytes, concurrent)
+             : score_impl<float>(ctx, m, p, cand, n, L, out, tok_logp, ctx->workspace, ctx->workspace_bytes, concurrent);
+}
+
 extern "C" int specs_score_blocks(specs_ctx* ctx, const specs_model* m, const specs_prefix* p, const int32_t* cand,
                                   int32_t n, int32_t L, float* out, float* tok_logp) {
   if (int rc = score_args_ok(ctx, m, p, cand, n, L, out, tok_logp)) return rc;
-  HIP_TRY(hipSetDevice(ctx->device));
-  return m->desc.dtype == SPECS_BF16
-             ? score_impl<bf16_t>(ctx, m, p, cand, n, L, out, tok_logp, ctx->workspace, ctx->workspace_bytes)
-             : score_impl<float>(ctx, m, p, cand, n, L, out, tok_logp, ctx->workspace, ctx->workspace_bytes);
+  return score_blocks(ctx, m, p, cand, n, L, out, tok_logp, ctx->concurrent);
 }
 
 extern "C" int specs_score_target_and_reward(specs_ctx* ctx_target, const specs_model* target,
@@ -807,8 +827,9 @@ extern "C" int specs_score_target_and_reward(specs_ctx* ctx_target, const specs_
   if (!p_target || !p_prm || p_target->B != p_prm->B) return SPECS_EINVAL;
   if (int rc = score_args_ok(ctx_target, target, p_target, cand, n, L, logp_target, tok_logp_target)) return rc;
   if (int rc = score_args_ok(ctx_prm, prm, p_prm, cand, n, L, reward, nullptr)) return rc;
-  if (int rc = specs_score_blocks(ctx_target, target, p_target, cand, n, L, logp_target, tok_logp_target)) return rc;
-  return specs_score_blocks(ctx_prm, prm, p_prm, cand, n, L, reward, nullptr);
+  const bool two = ctx_target->stream != ctx_prm->stream;
+  if (int rc = score_blocks(ctx_target, target, p_target, cand, n, L, logp_target, tok_logp_target, two || ctx_target->concurrent)) return rc;
+  return score_blocks(ctx_prm, prm, p_prm, cand, n, L, reward, nullptr, two || ctx_prm->concurrent);
 }
 
 extern "C" int specs_score_blocks_static(specs_ctx* ctx, const specs_model* m, const specs_prefix* p,
@@ -819,8 +840,8 @@ extern "C" int specs_score_blocks_static(specs_ctx* ctx, const specs_model* m, c
   HIP_TRY(hipSetDevice(ctx->device));
   char* base = g_static_scratch[ctx->device];        // the device address, never the array's name
   return m->desc.dtype == SPECS_BF16
-             ? score_impl<bf16_t>(ctx, m, p, cand, n, L, out, tok_logp, base, SPECS_STATIC_SCRATCH_BYTES)
-             : score_impl<float>(ctx, m, p, cand, n, L, out, tok_logp, base, SPECS_STATIC_SCRATCH_BYTES);
+             ? score_impl<bf16_t>(ctx, m, p, cand, n, L, out, tok_logp, base, SPECS_STATIC_SCRATCH_BYTES, ctx->concurrent)
+             : score_impl<float>(ctx, m, p, cand, n, L, out, tok_logp, base, SPECS_STATIC_SCRATCH_BYTES, ctx->concurrent);
 }
 
 // Alg. 1, Step I: n blocks of L tokens per beam, one position at a time. Step t: next-token logits from the
@@ -1181,7 +1202,7 @@ extern "C" int specs_op_qkv_rope(specs_ctx* ctx, const specs_model* m, const spe
     const size_t room = (ctx->workspace_bytes - 256 - cs_bytes) / ((size_t)g.M * width * sizeof(float));
     const int max_split = (int)(room < MFMA_MAX_SPLIT ? room : MFMA_MAX_SPLIT);
     if (!qkv_rope_fused<bf16_t>((const bf16_t*)A, (const bf16_t*)Wqkv, cs, (bf16_t*)q, (bf16_t*)kblk, (bf16_t*)vT, g, md, Lp,
-                                max_split, s)) {
+                                max_split, false, s)) {
       int parts = gemm_store_split<bf16_t>((const bf16_t*)A, (const bf16_t*)Wqkv, qkv, max_split, g.M, (int)width, md.d, s);
       launch_rope_split<bf16_t>(qkv, parts, cs, (bf16_t*)q, (bf16_t*)kblk, (bf16_t*)vT, g, Lp, md, s);
     }

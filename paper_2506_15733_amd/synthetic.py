@@ -20,7 +20,8 @@ def pack_gate_up(wg, wu):
 
 
 class DeviceModel:
-    """Weights of one model in device memory + its ABI handles (context with own workspace, model)."""
+    """Weights of one model in device memory + its ABI handles (context with own workspace, model). A stream other than the
+    current one says that the model works beside others."""
 
     def __init__(self, desc, device, stream, max_rows, max_blocks, seed=0):
         self.desc, self.device = desc, device
@@ -45,6 +46,7 @@ class DeviceModel:
         stream.wait_stream(torch.cuda.current_stream())
         self.workspace.record_stream(stream)
         self.ctx = B.specs_ctx_create(torch.device(device).index or 0, stream.cuda_stream, self.workspace)
+        B.specs_ctx_concurrent(self.ctx, stream != torch.cuda.current_stream())
         self.model = B.specs_model_create(self.ctx, self.cdesc, self.embed, self.head, self.g_final, self.layers)
 
     def close(self):
@@ -121,8 +123,10 @@ class ScoringStep:
             B.specs_prefill(self.models[r].ctx, self.models[r].model, self.prefixes[r].handle, self.prefix_tokens)
         self._join()
 
-    def score(self, role, cand=None, out=None, tok=None):
+    def score(self, role, cand=None, out=None, tok=None, alone=False):
+        """alone: nothing else runs meanwhile, although every role has a stream of its own."""
         dm = self.models[role]
+        B.specs_ctx_concurrent(dm.ctx, self.concurrent and not alone)
         B.specs_score_blocks(dm.ctx, dm.model, self.prefixes[role].handle, self.cand if cand is None else cand,
                              self.out[role] if out is None else out,
                              (self.tok.get(role) if tok is None else tok))
@@ -189,7 +193,7 @@ def run_specs_loop(step: ScoringStep, blocks, tau, beta_index=0, start_with_targ
         u = torch.from_numpy(u_all[h].copy()).to(dev)
         step._fork()
         for r in (("prm",) if fast else step.ROLES):
-            step.score(r)
+            step.score(r, alone=fast)
         step._join()
         lt, ld = (zeros, zeros) if fast else (step.out["target"], step.out["draft"])
         B.specs_select_and_switch(step.sel_ctx, lt, ld, step.out["prm"], beta, tau, u, gen, idx, None, step.max_reward)
@@ -264,7 +268,7 @@ def run_specs_generation_loop(step: ScoringStep, H, tau, beta_index=0, start_wit
             step.cand = torch.where(gen.bool()[:, None, None], gen_cand["draft"], gen_cand["target"]).contiguous()
         step._fork()
         if gens == ["target"]:
-            step.score("prm")
+            step.score("prm", alone=True)
         elif gens == ["draft"]:
             step.score("target")
             step.score("prm")
@@ -291,7 +295,7 @@ def run_specs_generation_loop(step: ScoringStep, H, tau, beta_index=0, start_wit
             if gens == ["draft"]:
                 commit("target", idx)                   # the target scored all n candidates
             else:                                       # the draft saw none of them: run it over the chosen block
-                step.score(other, cand=picked, out=out1[other], tok=tok1[other])
+                step.score(other, cand=picked, out=out1[other], tok=tok1[other], alone=True)
                 commit(other, zero_idx)
         else:
             for r in step.ROLES:

@@ -52,6 +52,7 @@ def test_null_arguments_are_rejected_without_touching_a_gpu(lib):
     assert lib.specs_score_blocks(None, None, None, None, 1, 1, None, None) == 1
     assert lib.specs_subsample(None, None, None, None, None, 1, 1, None, 1, None, None, None) == 1
     assert lib.specs_prefill(None, None, None, None) == 1
+    assert lib.specs_ctx_concurrent(None, 1) == 1
     assert lib.specs_ctx_destroy(None) == 0
 
 

@@ -7,15 +7,15 @@ import workload as W
 from host_rules import library
 
 
-def touched(config, role, rows, position):
+def touched(config, role, rows, position, beside=False):
     """For a layer of this model: the O, gate/up and down weights; the model: all layers and the vocabulary head."""
     d = W.get_config(config).models()[role]
     qd, kvd = d.n_q_heads * d.head_dim, d.n_kv_heads * d.head_dim
     layer = 2 * qd * d.d_model + 6 * d.d_model * d.ffn
     model = d.n_layers * (layer + 2 * d.d_model * (qd + 2 * kvd)) + (2 * d.d_model * d.vocab if d.head == "lm" else 0)
-    f = library()._Z15weights_touchedimmb
-    f.restype, f.argtypes = C.c_bool, [C.c_int, C.c_size_t, C.c_size_t, C.c_bool]
-    return f(rows, layer, model, position)
+    f = library()._Z15weights_touchedimmbb
+    f.restype, f.argtypes = C.c_bool, [C.c_int, C.c_size_t, C.c_size_t, C.c_bool, C.c_bool]
+    return f(rows, layer, model, position, beside)
 
 
 def test_models_and_rows():
@@ -23,7 +23,8 @@ def test_models_and_rows():
         for config, role in (("c2_small", "target"), ("c2_small", "prm"), ("c3_1p5b", "target"), ("c3_1p5b", "draft")):
             assert touched(config, role, rows, False)
         assert touched("c4_7b", "draft", rows, True)
-        assert not touched("c2_small", "draft", rows, False)        # fits the Infinity Cache
+        assert not touched("c2_small", "draft", rows, False)        # fits the Infinity Cache, unless others are beside it
+        assert touched("c2_small", "draft", rows, False, True)
         assert not touched("c2_small", "draft", rows, True) and not touched("c2_small", "target", rows, True)
         assert not touched("c3_1p5b", "draft", rows, True)          # 27 MB a layer
         assert not touched("c4_7b", "target", rows, False) and not touched("c4_7b", "target", rows, True)

@@ -4,7 +4,7 @@ import random
 
 import pytest
 
-from host_rules import library
+from host_rules import BatchGeom, library
 
 PLAN = ("256x256", "128x256", "128x128", "64x128", "32x128", "64x64", "32x64", "192x256", "64x128 short")
 
@@ -63,6 +63,13 @@ def test_tiles_of_measured_products(tile, max_split, M, N, K):
     ("64x64", 1, 40, 16384, 1024)])                  # few enough for the finer tiles
 def test_rings_of_launches_beside_others(tile, max_split, M, N, K):
     assert launched(M, N, K, max_split, beside=True)[0] == tile
+
+
+def test_only_the_caller_says_that_others_run_beside():
+    f = library()._Z15launches_besidebRK9BatchGeom
+    f.restype, f.argtypes = C.c_bool, [C.c_bool, C.POINTER(BatchGeom)]
+    assert f(True, BatchGeom(B=1, n=8, L=32)) and not f(False, BatchGeom(B=1, n=8, L=32))
+    assert not f(True, BatchGeom(B=1, n=1, L=2048)) and not f(True, BatchGeom(B=4, n=8, L=1))
 
 
 def test_rotary_embedding_of_single_positions():
