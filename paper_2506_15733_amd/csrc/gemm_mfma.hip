@@ -126,8 +126,10 @@ void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* til
 // long its few CUs pull weights from HBM, so more and smaller workgroups are ahead as long as each has a CU to itself. us with cold
 // weights, of 64 x 128, 64 x 64 and 32 x 64: 256 x 2048 x 1024 10.3, 7.7, 6.7; 256 x 2048 x 1536 14.8, 10.3, 8.6; 256 x 1024 x 1024 in 4
 // slices 6.1, 4.9, 5.4 (512 workgroups of the last, in 2: 5.2). A few CUs with two of the 64 x 64 ones do no harm while the weights are
-// few (555 x 2048 x 1536, 288 of them: 14.3 / 12.4; but 256 x 4608 x 3584, 288: 28.1 / 32.4, gate/up of 64 x 17920 x 1536, 280: 18.3 /
-// 20.1); where many have two, 64 x 128 is ahead (256 x 5632 x 1024: 352, 11.2 / 12.3; 1024 x 2048 x 1536: 512, 14.6 / 16.1).
+// few, up to 3.1 M of them (264 to 288 workgroups: 513, 555 and 576 x 2048 x 1536 12.5, 14.4, 14.7 / 12.0, 12.4, 12.5; 650, 704 and 768 x
+// 1536 x 1536 13.0, 14.5, 14.5 / 12.4, 12.6, 12.8; 900, 960 and 1024 x 1152 x 896 9.1, 9.8, 9.8 / 8.8, 8.9, 8.9; 1100 and 1152 x 1024 x
+// 1024 9.6, 10.2 / 9.1, 9.2; from 3.7 M on they do: 320 x 3584 x 1024 10.9 / 11.3, 256 x 4608 x 896 10.4 / 11.3, 256 x 4608 x 3584 28.1 /
+// 32.4, gate/up of 64 x 17920 x 1536 18.3 / 20.1); where many have two, 64 x 128 is ahead (256 x 5632 x 1024: 352, 11.2 / 12.3; 1024 x 2048 x 1536: 512, 14.6 / 16.1).
 // beside: the caller said that other launches run beside this one (the models of a step score their blocks at the same time). The
 // longer ring of the 64 x 128 tiles takes a CU's LDS to itself, so of two such launches, of 129 to 256 workgroups each, one waits for
 // CUs of the other. The short one leaves room for a second workgroup; alone it costs 4 to 7 % of a launch up to 24
@@ -145,7 +147,7 @@ void mfma_gemm_tile(int M, int N, int K, int max_split, bool wide_only, bool bes
   } else if (*tile_out == 3) {
     const long columns = (long)((N + 63) / 64) * *split_out;
     if ((M + 31) / 32 * columns <= 256) *tile_out = TILE_32;
-    else if ((M + 63) / 64 * columns <= ((long)N * K <= 4 << 20 ? 288 : 256)) *tile_out = TILE_64;
+    else if ((M + 63) / 64 * columns <= ((long)N * K <= 13 << 18 ? 288 : 256)) *tile_out = TILE_64;
     else if (beside && mfma_gemm_ring(3, M, N, K, *split_out) == 6 && K / 64 <= 24 * *split_out) *tile_out = TILE_SHORT;
   }
 }

@@ -50,7 +50,9 @@ def test_slices_are_always_those_of_the_plan():
     ("32x64", 1, 256, 2048, 1024), ("32x64", 1, 256, 2048, 1536),
     ("64x64", 16, 256, 1024, 1024),                  # 4 slices: 256 workgroups of 64 x 64
     ("64x64", 1, 555, 2048, 1536),                   # 288 workgroups, few weights
+    ("64x64", 1, 650, 1536, 1536), ("64x64", 1, 768, 1536, 1536), ("64x64", 1, 900, 1152, 896), ("64x64", 1, 1152, 1024, 1024),
     ("64x128", 1, 256, 4608, 3584),                  # 288, and many
+    ("64x128", 1, 320, 3584, 1024), ("64x128", 1, 256, 4608, 896),
     ("64x128", 1, 256, 5632, 1024), ("64x128", 1, 1024, 2048, 1536)])
 def test_tiles_of_measured_products(tile, max_split, M, N, K):
     assert launched(M, N, K, max_split)[0] == tile
