@@ -1,12 +1,13 @@
 """Attention launches whose wavefronts take 16 query rows, and the launches of 32 beside them, against the oracle: numbers of
-stacked rows around a wavefront and a workgroup, prefixes around a key tile, and key lists that are cut."""
+stacked rows around a wavefront and a workgroup, prefixes around a key tile, and long key lists that one workgroup walks
+(those that are cut: test_gpu_attention_runs)."""
 import numpy as np
 import pytest
 import torch
 
 import workload as W
 from workload.configs import ModelDesc, Workload
-from test_gpu_kernels import attention_case, ctx   # noqa: F401  (the fixture)
+from test_gpu_attention_runs import Operands
 from test_gpu_generate import gpu_generate
 
 pytestmark = pytest.mark.gpu
@@ -25,12 +26,12 @@ pytestmark = pytest.mark.gpu
     (2, 2, 64, 1, 129, 65, [70]),             # 65 rows, 516 workgroups of 64: wavefronts of 32 rows
     (2, 2, 128, 1, 2, 32, [1500]),            # 64 rows, a key list in runs
     (3, 1, 64, 2, 2, 7, [2000, 1025])])
-def test_stacked_rows_around_a_wavefront_and_a_workgroup(ctx, Hq, Hkv, hd, Bn, n, L, lens):   # noqa: F811
-    """Averages of unit normals rounded to bf16: half a unit in the last place of values below 4 is 2^-7, and as much again
-    for the weights' rounding where a row sees few keys."""
-    d = ModelDesc("target", 1, Hq * hd, Hq, Hkv, hd, 64, 64, "bf16", "lm")
-    sample = None if Bn * n <= 8 else [0, Bn * n // 2, Bn * n - 1]
-    assert attention_case(ctx, d, Bn, n, L, lens, 16, sample) <= 2.0 ** -6
+def test_stacked_rows_around_a_wavefront_and_a_workgroup(Hq, Hkv, hd, Bn, n, L, lens):
+    """Without scratch, so that no list is cut; the ends of the lists and tiles are many times the rest, so a lost key shows."""
+    x = Operands(Hq, Hkv, hd, Bn, n, L, lens)
+    out, used = x.launch()
+    some = [divmod(c, n) for c in (range(Bn * n) if Bn * n <= 8 else (0, Bn * n // 2, Bn * n - 1))]
+    assert not used and x.beyond_the_bound(out, some) <= 1
 
 
 @pytest.mark.parametrize("n,hq,hkv,hd,lens", [

@@ -1,5 +1,5 @@
-"""Sampling with every number of ids per thread that the two kernels are compiled for: 128 chunks of 256 threads, so up to
-32768 permitted ids one id per thread, up to 65536 two, and so on."""
+"""Sampling with one to seven ids per thread, each a kernel of its own: 128 chunks of 256 threads, so up to 32768 permitted ids one
+id per thread, up to 65536 two, and so on. (Eight, and the kernel for more: test_gpu_generate.)"""
 import numpy as np
 import pytest
 
@@ -11,11 +11,13 @@ from test_gpu_generate import compare_generation, gpu_generate, small_workload
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("limit", [32768, 32769, 65537, 98305, 131072, 163841, 229376])
-def test_draws_match_the_oracle_at_the_edges_of_the_runs(limit):
+@pytest.mark.parametrize("limit,ids", [(32768, 1), (32769, 2), (65536, 2), (65537, 3), (98304, 3), (98305, 4), (131072, 4), (131073, 5),
+                                       (163840, 5), (163841, 6), (196608, 6), (196609, 7), (229376, 7)])
+def test_draws_match_the_oracle_at_the_edges_of_the_runs(limit, ids):
     """Logits within 1e-5 move the oracle's running sum by a factor of 1 +- 2e-5; a draw may lie one id beside the oracle's
     within that distance, so the mass of one id, the oracle's largest, is added."""
     from paper_2506_15733_amd import synthetic
+    assert ids == -(-(-(-limit // 128)) // 256)
     wl = small_workload("f32", B=1, n=4, L=2, V=limit + 40, seed=18)
     step = synthetic.ScoringStep(wl)
     step.prefill()
