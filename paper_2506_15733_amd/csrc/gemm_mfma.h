@@ -689,13 +689,15 @@ static void launch_variant(const GemmArgs& a, hipStream_t s) {
   gemm_mfma_kernel<BM, BN, NWM, S, EPI, HD128, REST, BUFFER><<<grid, NWM * BN, smem, s>>>(a);
 }
 
-// The tile shapes, and what one 64-deep k-step of a workgroup costs (us) when a few CUs are busy and when all 256 are.
-// The two wide ones are for products that fill the chip, where operand traffic counts (2048 x 37888 x 3584: 457, 539,
-// 670, 834 us in this order); the narrow ones put four to eight times as many workgroups on a short product and have
-// more of its loads in flight (256 x 2048 x 1536: 33.7, 21.4, 15.2, 11.8 us). The last is for up to 32 rows (the
-// positions of a generated block), where all that counts is how fast the weights stream: with K in slices, 16 x 1536 x
-// 8960 takes 7.8 us and 16 x 3584 x 18944 25.3, HBM's rate, where a kernel that loaded weights to registers and walked
-// K wavefront by wavefront took 10.9 and 31.2.
+// The tile shapes of the plan, and what one 64-deep k-step of a workgroup costs when a few CUs are busy and when all 256 are. The two
+// wide ones are for products that fill the chip, where operand traffic counts (2048 x 37888 x 3584 to float: 469, 539, 635, 715 us in
+// this order); the narrow ones put four to eight times as many workgroups on a short product and have more of its loads in flight
+// (256 x 2048 x 1536: 32.1, 20.6, 12.4, 8.8 us). The last is for up to 32 rows (the positions of a generated block), where
+// all that counts is how fast the weights stream: with K in slices and cold weights, 16 x 1536 x 8960 takes 7.9 us and 16 x 3584 x
+// 18944 25.3, HBM's rate, where a kernel that loaded weights to registers and walked K wavefront by wavefront took 10.9 and 31.2.
+// The costs (us) were those of earlier loops and weigh the tiles against each other: the present ones take 0.90 and 1.25, 0.56
+// and 0.73, 0.31 and 0.42, 0.20 and 0.28 (192 x 256: 0.74 and 1.01, 64 x 64: 0.21 and 0.22, 32 x 64: 0.17 and 0.17). The slices of K,
+// and with them the order of a product's sums, hang on this table.
 struct TileShape { int bm, bn; double lat, full; };
 static const TileShape kTiles[MFMA_TILES] = {{256, 256, 1.15, 1.7}, {128, 256, 0.68, 1.04}, {128, 128, 0.46, 0.65}, {64, 128, 0.33, 0.41}, {32, 128, 0.30, 0.36}};
 

@@ -6,7 +6,7 @@ int mfma_lmhead_tiles(int V) { return (V + 255) / 256; }
 
 // K-tiles in the LDS ring of the kernel that takes a product. 64 x 128: six, in one workgroup per CU, where few
 // workgroups walk a long K; else half of that and two workgroups per CU, which fill it sooner and leave no nearly empty
-// last round (16 x 37888 x 3584, 296 workgroups: 62.2 -> 58.8 us).
+// last round (16 x 37888 x 3584, 296 workgroups: 62.2 -> 60.3 us).
 int mfma_gemm_ring(int tile, int M, int N, int K, int ksplit) {
   const TileShape& ts = kTiles[tile];
   const long wgs = (long)((M + ts.bm - 1) / ts.bm) * ((N + ts.bn - 1) / ts.bn) * ksplit;
@@ -30,10 +30,10 @@ static void launch_tile(GemmArgs& a, int tile, hipStream_t s) {
 
 // Gate and up in 128 x 192 tiles where the plan says 128 x 256 and a single round does: a few hundred rows then occupy a third
 // more CUs, each with 120 KB of operands in flight instead of 96, which is what bounds such a product while its weights come
-// from HBM (256 x 1024 x 8192 in 128 x 256 tiles: 101 us, 96 without the product). us before / so: 256 x 17920 x 1536 29.1 /
-// 26.1, 200 rows 27.4 / 24.6, 100 x 37888 x 3584 64.6 / 56.7, 512 x 9728 x 896 17.9 / 17.2; in two rounds it is behind (321 x
-// 17920 x 1536: 27.7 / 44.3). K-tiles for less than two fills of the ring leave nothing in flight to gain. Up to 128 rows, where
-// the weights are read once, also in place of 64 x 128 tiles that put two workgroups on some CUs (48 x 37888 x 3584: 64.1 / 52.4).
+// from HBM. us with cold weights, in 128 x 256 tiles / so: 256 x 17920 x 1536 30.0 / 26.0, 200 rows 27.7 / 23.8, 100 x 37888 x 3584
+// 64.9 / 55.4, 512 x 9728 x 896 17.8 / 15.4; in two rounds it is behind (321 x 17920 x 1536, with the loops of then: 27.7 / 44.3).
+// K-tiles for less than two fills of the ring leave nothing in flight to gain. Up to 128 rows, where the weights are read once,
+// also in place of 64 x 128 tiles that put two workgroups on some CUs (48 x 37888 x 3584: 66.3 / 50.4).
 bool mfma_gate_up_192(int M, int N, int K, int tile) {
   const bool two_narrow = tile == 3 && M > 32 && M <= 128 && (long)((M + 63) / 64) * ((N + 127) / 128) > 256;
   return (tile == 1 || two_narrow) && (long)((M + 127) / 128) * ((N + 191) / 192) <= 256 && K > 512;
@@ -41,8 +41,8 @@ bool mfma_gate_up_192(int M, int N, int K, int tile) {
 
 // Time that wgs workgroups of a tile shape take for a k-step each: in rounds of 256; a round that leaves CUs idle has k-steps
 // between the two costs of its tile. The narrow tiles run two workgroups per CU: their last round overlaps the one before, but
-// a few more than 256 cost what 512 do, twice one workgroup on a CU (64 x 128: 0.66 us a step at 264 workgroups, 0.79 at 352,
-// 0.71 at 484, 1.24 at 660, 1.98 at 1260; not where 32 rows fill half of the tile and weights are all that streams: 1.0 at
+// a few more than 256 cost what 512 do, twice one workgroup on a CU (64 x 128: 0.28 us a step at 256 workgroups, 0.52 at 264 and
+// 352, 0.56 at 484, 0.82 at 660, 1.45 at 1260; not where 32 rows fill half of the tile and weights are all that streams: 0.96 at
 // 296, HBM's rate, for 16 x 37888 x 3584).
 static double rounds(int tile, long wgs, int M) {
   const TileShape& ts = kTiles[tile];
@@ -57,12 +57,12 @@ static double rounds(int tile, long wgs, int M) {
 // Products of more than a round of 256 x 256 tiles: the columns (in tiles, *n_tiles) that fill whole rounds, and the width of
 // the 128-row tiles that the rest is cut into, 0 where another round of the large ones takes no longer. *cost: time of a
 // k-step over all rounds. A last round of few tiles leaves most CUs idle for as long as a full one (us without a rest / with):
-// 1024 x 17920 x 1536, 280 tiles, 80 / 66; 2048 rows, 560 tiles, 127 / 110; 256 x 151936 x 1536, 594 tiles, 173 / 162;
-// 4493 x 37888 x 3584, 2664 tiles, 978 / 961. About 3 us go to the epilogue and the first loads of the rest.
+// gate/up of 1024 x 17920 x 1536, 280 tiles, 66 / 50; 2048 rows, 560 tiles, 107 / 96; of 4493 x 37888 x 3584, 2664 tiles, 862 / 847;
+// head of 256 x 151936 x 1536, 594 tiles, 138 / 130. About 3 us go to the epilogue and the first loads of the rest.
 // The 128-column tiles are for a rest of an eighth of a round at most: they occupy the CUs for half as long again as the 256-column
-// ones, which other streams miss (step of 2184 rows of 7B models, 62 ms, a rest of 52 tiles: 0.9 % longer than without a rest so,
+// ones, which other streams miss (with the loops of then: step of 2184 rows of 7B models, 62 ms, a rest of 52 tiles: 0.9 % longer than without a rest so,
 // 0.3 % with the wide ones). For the same reason none from three whole rounds on where half a round or more is left: alone,
-// such a rest gains 2 to 5 % of a launch (16384 x 4608 x 3584 485 / 470 us, 3584 columns 372 / 348), but less than half of the CUs
+// such a rest gains 2 to 5 % of a launch (also then: 16384 x 4608 x 3584 485 / 470 us, 3584 columns 372 / 348), but less than half of the CUs
 // would have idled, and a step of 16384 rows on three streams is shorter without (492.3 / 494.5 ms).
 static int rest_plan(int M, int N, int K, bool wide_only, int* n_tiles, double* cost) {
   const int m_tiles = (M + 255) / 256, all = (N + 255) / 256;
@@ -88,11 +88,11 @@ int mfma_gemm_rest(int M, int N, int K, bool wide_only, int* n_tiles) {
 // Tile shape and K-split for an M x N x K product whose consumer can sum up to max_split partial products: the pair
 // with the least estimated time. The weights cannot arrive faster than HBM delivers them, and about half of that time does
 // not overlap with a short walk through K. A launch costs about 3 us beside that, and every extra partial one more M x N float
-// write here and one more read in the consumer. The estimate is within 15 % of the measured times for 8..2048 rows of the projections with
-// K = 1024..18944, except that it misses up to 20 % of the narrow tiles' cost when they run in many rounds, where the
-// wide ones are ahead anyway.
+// write here and one more read in the consumer. Of 64 products without slices (the projections of
+// K = 896 to 18944, 34 to 3490 rows, cold weights) 58 get the fastest of the tiles with what mfma_gemm_tile makes of it, the others lose 0.3
+// to 10 %.
 // A rest competes with the other unsliced tiles only: slices fill their rounds as well as a rest does (product and the
-// addition behind it, us with slices / with a rest: 16384 x 3584 x 18944 1874 / 1870, 4700 rows 653 / 654, 16384 x 1536 x 8960
+// addition behind it, us with slices / with a rest, with the loops of then: 16384 x 3584 x 18944 1874 / 1870, 4700 rows 653 / 654, 16384 x 1536 x 8960
 // 447 / 439), and the order of a product's sums then does not hang on how its last round is cut.
 void mfma_gemm_plan(int M, int N, int K, int max_split, bool wide_only, int* tile_out, int* split_out) {
   const int KT = K / 64, shapes = wide_only ? 2 : M <= 32 ? MFMA_TILES : MFMA_TILES - 1;
