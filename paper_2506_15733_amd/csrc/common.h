@@ -201,7 +201,7 @@ void launch_subsample(const float* lt, const float* lg, const float* r, const ui
                       const float* beta_dev, int nb, const double* u, int32_t* idx, float* max_reward,
                       uint8_t* gen_is_draft, float tau, int* status, hipStream_t s);
 
-// bf16 MFMA GEMM family (gemm_mfma.hip). Returns false if the shape is not supported.
+// bf16 MFMA GEMM family (gemm_mfma.h). Returns false if the shape is not supported.
 enum { MFMA_STORE = 0, MFMA_RESIDUAL = 1, MFMA_SWIGLU = 2, MFMA_LMHEAD = 3 };
 enum { MFMA_TILES = 5, MFMA_MAX_SPLIT = 16 };   // tile shapes of the family (an index is what mfma_gemm_plan gives)
 // ksplit > 1 (MFMA_STORE only): C is [ksplit][M][N], one partial product per K slice; tile < 0: chosen by the launch.
